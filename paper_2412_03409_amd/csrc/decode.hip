@@ -2,23 +2,22 @@
 // interacts with the cached KV vectors of every layer).  ONE kernel per step (two for bf16 caches whose
 // KV heads serve several query heads: a planning kernel and decode_gqa_kernel, further down):
 //
-//  decode_attn_kernel   a workgroup of a few wavefronts owns one (sequence, layer, kv head) -- or a
-//                       sub-group of G of its query heads -- and its wavefronts take the segment's
-//                       64-token chunks round-robin.  A wavefront issues all K and V loads of a chunk up
-//                       front (16 B per lane, whole rows, fully coalesced), then does
-//                       the dot products, a block softmax and the weighted V sum in registers for every
-//                       query head of the group, so each cached byte is read from HBM once per group.
+//  decode_attn_kernel   a unit is one (sequence, layer, kv head), or a sub-group of G of its query heads.  One to
+//                       eight wavefronts work on a unit (see the launcher) and take its row blocks round-robin.  A
+//                       wavefront issues all K and V loads of a block up front (16 B per lane, whole rows, fully
+//                       coalesced), then does the dot products, a block softmax and the weighted V sum in registers
+//                       for every query head of the group, so each cached byte is read from HBM once per group.
 //                       The wavefronts' (max, sum, weighted V) are merged through LDS and the output is
 //                       written directly: no partial results ever go to HBM.
 //
 // Append: the new token's k/v are taken from k_new/v_new in place of the slot they are written to, so
 // no wavefront reads a slot that is written in the same launch.
 //
-// lens is advanced inside the same launch without a second kernel: every workgroup reads the old
-// length of its segment when it starts, and announces that it has finished by adding 1 to the
-// bits above kLenBits of lens[b,l].  The workgroup that finds all others of the segment already
+// lens is advanced inside the same launch without a second kernel: every wavefront reads the old
+// length of its segment when it starts, and every unit, once its wavefronts have, adds 1 to the
+// bits above kLenBits of lens[b,l].  The unit that finds all others of the segment already
 // counted stores the new plain length, which also clears the count.  Between launches lens holds plain
-// lengths (< 2^20).
+// lengths (< 2^20).  The ranking of the segments goes by capacity, which no launch changes.
 #include "pkv_common.hpp"
 
 namespace pkv {
@@ -47,7 +46,12 @@ struct DecodeParams {
     // work list of the grouped-query kernel (see decode_plan_kernel)
     int G, n_seg, S0, pieces_cap, record_word, partial_word;
     int* plan;
+    // ranked launches of decode_attn_kernel (n_seg above): segments per group, and how many of the longest ones get
+    // four and two wavefronts per unit
+    int gsz, n4, n2;
 };
+
+constexpr int kRankRegs = 8;      // capacities per lane of a ranked launch: groups of up to 512 segments
 
 // Virtual row numbering of a segment under pruning: rows [0, perm) are the permanent slots, rows
 // perm + j are ring slot j (the last d+1 slots of the segment).  r_new is the row of the token stored
@@ -79,59 +83,53 @@ __device__ __forceinline__ void unpack16(const uint4& r, float* f) {
     }
 }
 
-// One sub-block of SB = NI * (64/LPR) rows starting at row r0 of the segment, for the G query heads of
-// the group: online-softmax update of (mrun, srun, o).  LPR lanes cover one row with 16 bytes each.
-// TAIL = false: every row is an occupied cache slot.  TAIL = true: rows >= len are masked, and the row
-// len_old, if it is being appended (app), comes from k_new/v_new and is written to its slot (writer).
-template <bool BF16, int LPR, int G, int NI, bool TAIL, bool EV = false>
-__device__ __forceinline__ void attend_block(const unsigned char* __restrict__ kseg,
-                                             const unsigned char* __restrict__ vseg, int r0, int len,
-                                             int len_old, bool app, bool writer, const RingMap& ring,
-                                             const unsigned char* __restrict__ knew,
-                                             const unsigned char* __restrict__ vnew, unsigned char* kw,
-                                             unsigned char* vw, int row_bytes, int sub, int rg,
-                                             const float (&qf)[G][BF16 ? 8 : 4], float (&o)[G][BF16 ? 8 : 4],
-                                             float (&mrun)[G], float (&srun)[G]) {
-    constexpr int EPL = BF16 ? 8 : 4;
+// Rows r0 .. r0 + BR - 1 of one block (BR = NI * 64/LPR; LPR lanes cover a row with 16 bytes each) into registers.
+// Blocks of occupied cache slots only take the plain path.  In the guarded one the row being appended comes from
+// k_new / v_new, under pruning ring rows map to the ring slots, and rows that do not take part (past the end, or
+// pruned in this step) are read from the block's first slot and ignored by attend_block: every load is issued
+// without a branch.
+template <int LPR, int NI, bool EV>
+__device__ __forceinline__ void load_block(uint4 (&kr)[NI], uint4 (&vr)[NI], int r0, int len, int len_old, bool app,
+                                           const RingMap& ring, const unsigned char* kseg, const unsigned char* vseg,
+                                           const unsigned char* knew, const unsigned char* vnew, int row_bytes,
+                                           int sub, int rg) {
     constexpr int RPI = kWave / LPR;
-    uint4 kr[NI], vr[NI];
     const uint32_t lane_off = (uint32_t)(r0 + rg) * (uint32_t)row_bytes + (uint32_t)sub * 16u;
+    if (r0 + NI * RPI <= len_old) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const uint32_t o_i = lane_off + (uint32_t)(i * RPI) * (uint32_t)row_bytes;
-        if constexpr (!TAIL) {
+        for (int i = 0; i < NI; ++i) {
+            const uint32_t o_i = lane_off + (uint32_t)(i * RPI) * (uint32_t)row_bytes;
             kr[i] = load_stream16(kseg + o_i);
             vr[i] = load_stream16(vseg + o_i);
-        } else {
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
             const int r = r0 + i * RPI + rg;
-            kr[i] = make_uint4(0, 0, 0, 0); vr[i] = make_uint4(0, 0, 0, 0);
-            if constexpr (!EV) {
-                if (r < len) {
-                    const bool isnew = app && r == len_old;
-                    kr[i] = load_stream16(isnew ? knew + sub * 16 : kseg + o_i);
-                    vr[i] = load_stream16(isnew ? vnew + sub * 16 : vseg + o_i);
-                    if (isnew && writer) {
-                        *(uint4*)(kw + o_i) = kr[i];
-                        *(uint4*)(vw + o_i) = vr[i];
-                    }
-                }
-            } else {
-                if (r < len && r != ring.r_mask) {
-                    const uint32_t o_s = o_i + (r >= len_old ? (uint32_t)ring.shift * (uint32_t)row_bytes : 0u);
-                    const bool isnew = r == ring.r_new;
-                    kr[i] = load_stream16(isnew ? knew + sub * 16 : kseg + o_s);
-                    vr[i] = load_stream16(isnew ? vnew + sub * 16 : vseg + o_s);
-                    if (isnew && writer) {
-                        *(uint4*)(kw + o_s) = kr[i];
-                        *(uint4*)(vw + o_s) = vr[i];
-                    }
-                }
+            int slot = r;
+            bool valid = r < len, isnew = app && r == len_old;
+            if constexpr (EV) {
+                valid = valid && r != ring.r_mask;
+                isnew = valid && r == ring.r_new;
+                slot = r >= len_old ? r + ring.shift : r;
             }
+            slot = valid ? slot : (EV && r0 >= len_old ? r0 + ring.shift : r0);
+            const uint32_t o_i = (uint32_t)slot * (uint32_t)row_bytes + (uint32_t)sub * 16u;
+            kr[i] = load_stream16(isnew ? knew + sub * 16 : kseg + o_i);
+            vr[i] = load_stream16(isnew ? vnew + sub * 16 : vseg + o_i);
         }
     }
-    float s[G][NI], mx[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) mx[g] = -INFINITY;
+}
+
+// Online-softmax update of (mrun, srun, o) with one block for the G query heads of the group.
+template <bool BF16, int LPR, int G, int NI, bool EV>
+__device__ __forceinline__ void attend_block(const uint4 (&kr)[NI], uint4 (&vr)[NI], int r0, int len, int len_old,
+                                             const RingMap& ring, int rg, const float (&qf)[G][BF16 ? 8 : 4],
+                                             float (&o)[G][BF16 ? 8 : 4], float (&mrun)[G], float (&srun)[G]) {
+    constexpr int EPL = BF16 ? 8 : 4;
+    constexpr int RPI = kWave / LPR;
+    const bool full = r0 + NI * RPI <= len_old;
+    float s[G][NI];
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
         float kf[EPL];
@@ -141,27 +139,43 @@ __device__ __forceinline__ void attend_block(const unsigned char* __restrict__ k
             float d = 0.f;
 #pragma unroll
             for (int x = 0; x < EPL; ++x) d = fmaf(qf[g][x], kf[x], d);
-#pragma unroll
-            for (int sh = 1; sh < LPR; sh <<= 1) d += __shfl_xor(d, sh, kWave);
-            if constexpr (TAIL) {
-                const int r = r0 + i * RPI + rg;
-                d = (r < len && (!EV || r != ring.r_mask)) ? d : -INFINITY;
-            }
             s[g][i] = d;
-            mx[g] = fmaxf(mx[g], d);
+        }
+    }
+#pragma unroll
+    for (int sh = 1; sh < LPR; sh <<= 1)
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int g = 0; g < G; ++g) s[g][i] += __shfl_xor(s[g][i], sh, kWave);
+    if (!full) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int r = r0 + i * RPI + rg;
+            const bool valid = r < len && (!EV || r != ring.r_mask);
+#pragma unroll
+            for (int g = 0; g < G; ++g) s[g][i] = valid ? s[g][i] : -INFINITY;
+            vr[i].x = valid ? vr[i].x : 0; vr[i].y = valid ? vr[i].y : 0;   // 0 * (what is there) could be NaN
+            vr[i].z = valid ? vr[i].z : 0; vr[i].w = valid ? vr[i].w : 0;
         }
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
+        float mx = s[g][0];
 #pragma unroll
-        for (int sh = LPR; sh < kWave; sh <<= 1) mx[g] = fmaxf(mx[g], __shfl_xor(mx[g], sh, kWave));
-        // the caller guarantees r0 < len: some row is valid, so mx is finite
-        const float mnew = fmaxf(mrun[g], mx[g]);
-        const float corr = __builtin_amdgcn_exp2f(mrun[g] - mnew);  // 0 on the first block
+        for (int i = 1; i < NI; ++i) mx = fmaxf(mx, s[g][i]);
+#pragma unroll
+        for (int sh = LPR; sh < kWave; sh <<= 1) mx = fmaxf(mx, __shfl_xor(mx, sh, kWave));
+        // r0 < len: some row is valid and mx finite, unless the only one is the row pruned in this step
+        const float mnew = fmaxf(mrun[g], mx);
+        const float mref = EV && mnew == -INFINITY ? 0.f : mnew;
+        const float corr = __builtin_amdgcn_exp2f(mrun[g] - mref);  // 0 on the first block
         mrun[g] = mnew;
         srun[g] *= corr;
 #pragma unroll
         for (int x = 0; x < EPL; ++x) o[g][x] *= corr;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) s[g][i] = __builtin_amdgcn_exp2f(s[g][i] - mref);
     }
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -169,35 +183,91 @@ __device__ __forceinline__ void attend_block(const unsigned char* __restrict__ k
         unpack16<BF16>(vr[i], vf);
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const float pr = __builtin_amdgcn_exp2f(s[g][i] - mrun[g]);
-            srun[g] += pr;   // per row group; the groups are merged at the end
+            srun[g] += s[g][i];   // per row group; the groups are merged at the end
 #pragma unroll
-            for (int x = 0; x < EPL; ++x) o[g][x] = fmaf(pr, vf[x], o[g][x]);
+            for (int x = 0; x < EPL; ++x) o[g][x] = fmaf(s[g][i], vf[x], o[g][x]);
         }
     }
 }
 
-// W wavefronts per workgroup; OCC = wavefronts per SIMD the register allocation must allow.
-template <bool BF16, int LPR, int G, int NI, int W, int OCC, bool EV = false>
+// The segment of rank `r` when the n segments are ordered by capacity, largest first (equal ones by index): found
+// by every wavefront for itself, with a radix selection on ballots.  n <= 64 * PER.
+template <int PER>
+__device__ __forceinline__ int ranked_segment(const int32_t* __restrict__ caps, int n, int nl, int L, int l0, int first, int r, int lane) {
+    int c[PER];
+    int any = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int i = u * kWave + lane;
+        c[u] = -1;
+        if (i < n) { const int j = first + i; c[u] = caps[nl == L ? j : (j / nl) * L + l0 + j % nl] & kLenMask; }
+        any |= c[u] < 0 ? 0 : c[u];
+    }
+    int prefix = 0, left = r;               // the value found so far (high bits), rank among those that share it
+    for (int bit = kLenBits - 1; bit >= 0; --bit) {
+        if (__builtin_amdgcn_ballot_w64((any >> bit) & 1) == 0) continue;
+        const int want = prefix | (1 << bit);
+        int cnt = 0;
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            cnt += __builtin_popcountll(__builtin_amdgcn_ballot_w64(c[u] >= 0 && (c[u] >> bit) == (want >> bit)));
+        if (left < cnt) prefix = want; else left -= cnt;
+    }
+    int found = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(c[u] == prefix);
+        const int cnt = __builtin_popcountll(m);
+        if (left >= 0 && left < cnt) {
+            unsigned long long x = m;
+            for (int k = 0; k < left; ++k) x &= x - 1;
+            found = u * kWave + __builtin_ctzll(x);
+        }
+        left -= cnt;
+    }
+    return found;
+}
+
+// W wavefronts per workgroup; OCC = wavefronts per SIMD the register allocation must allow.  RANK = 0: all W work on
+// one unit.  RANK > 0: units of the longest segments first, with W, W/2 or W/4 wavefronts per unit (see the launcher).
+template <bool BF16, int LPR, int G, int NI, int W, int OCC, bool EV, int RANK>
 __global__ void __launch_bounds__(W * kWave, OCC)
 decode_attn_kernel(DecodeParams p) {
     constexpr int EPL = BF16 ? 8 : 4;            // elements per lane (16 bytes)
     constexpr int RPI = kWave / LPR;             // rows per wavefront-wide load instruction
-    constexpr int SB = NI * RPI;                 // rows per sub-block
-    constexpr int NSB = kDecodeChunk / SB;       // sub-blocks per chunk
+    constexpr int BR = NI * RPI;                 // rows per block
     constexpr int ESZ = BF16 ? 2 : 4;
     constexpr int DMAX = 128;
-    static_assert(kDecodeChunk % SB == 0 && NSB >= 1, "chunk must be a whole number of sub-blocks");
     __shared__ float s_part[W][G][DMAX + 2];
 
-    const int HU = p.H / G;                      // workgroups (head groups) per segment
-    const int hu = blockIdx.x % HU, i_seg = blockIdx.x / HU;
+    const int HU = p.H / G;                      // units per segment
+    const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    int UW = W, hu, i_seg;
+    if constexpr (RANK > 0) {
+        // groups of p.gsz segments; in each the p.n4 longest get four wavefronts per unit, the next p.n2 two and
+        // the others one
+        static_assert(W == 4, "a workgroup holds one, two or four units");
+        const int w2 = (HU + 1) / 2, w1 = (HU + 3) / 4;
+        const int bpg = p.n4 * HU + p.n2 * w2 + (p.gsz - p.n4 - p.n2) * w1;
+        const int grp = blockIdx.x / bpg;
+        int j = blockIdx.x - grp * bpg;
+        const int first = grp * p.gsz, n = min(p.gsz, p.n_seg - first);
+        int r;
+        if (j < p.n4 * HU) { r = j / HU; hu = j - r * HU; }
+        else if ((j -= p.n4 * HU) < p.n2 * w2) { r = j / w2; hu = 2 * (j - r * w2) + wv / 2; r += p.n4; UW = 2; }
+        else { j -= p.n2 * w2; r = j / w1; hu = 4 * (j - r * w1) + wv; r += p.n4 + p.n2; UW = 1; }
+        if (r >= n) return;
+        i_seg = first + ranked_segment<RANK>(p.caps, n, p.nl, p.L, p.l0, first, r, lane);
+    } else {
+        hu = blockIdx.x % HU; i_seg = blockIdx.x / HU;
+    }
+    const bool live = hu < HU;
+    const int uw = wv & (UW - 1);
     const int b = i_seg / p.nl, l = p.l0 + i_seg % p.nl, sl = b * p.L + l;
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
     const int sub = lane % LPR, rg = lane / LPR;
     const int row_bytes = p.D * ESZ;
 
-    const int len_old = __hip_atomic_load(p.lens + sl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kLenMask;
+    const int len_old = __builtin_amdgcn_readfirstlane(__hip_atomic_load(p.lens + sl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) & kLenMask;
     const int cap = p.caps[sl];
     const int64_t off = p.seg_off[sl];
     // plain step: append at slot len_old.  Pruning step: len_old counts the permanent entries, the new
@@ -223,11 +293,13 @@ decode_attn_kernel(DecodeParams p) {
         len = app ? len_old + (p.t < p.d + 1 ? p.t : p.d + 1) : 0;
         len_next = len_old + (grad ? 1 : 0);
     }
-    const int nch = (len + kDecodeChunk - 1) / kDecodeChunk;
+    const int nb = live ? (len + BR - 1) / BR : 0;
     const int kvh = (hu * G) / p.grp;
-    const bool writer = app && ((hu * G) % p.grp == 0);
+    const bool writer = app && live && ((hu * G) % p.grp == 0);
     const int64_t segbase = (off * p.Hkv + (int64_t)kvh * cap) * row_bytes;
     const int64_t newrow = ((int64_t)sl * p.Hkv + kvh) * row_bytes;
+    unsigned char* kseg = p.kc + segbase;
+    unsigned char* vseg = p.vc + segbase;
 
     float o[G][EPL], mrun[G], srun[G];
 #pragma unroll
@@ -236,8 +308,7 @@ decode_attn_kernel(DecodeParams p) {
 #pragma unroll
         for (int x = 0; x < EPL; ++x) o[g][x] = 0.f;
     }
-
-    if (wv < nch) {
+    if (uw < nb) {
         float qf[G][EPL];
         const float qs = p.scale[l] * 1.4426950408889634f;
 #pragma unroll
@@ -247,27 +318,32 @@ decode_attn_kernel(DecodeParams p) {
 #pragma unroll
             for (int x = 0; x < EPL; ++x) qf[g][x] *= qs;
         }
-        const unsigned char* kseg = p.kc + segbase;
-        const unsigned char* vseg = p.vc + segbase;
-        for (int c = wv; c < nch; c += W) {
-            const bool full = (c + 1) * kDecodeChunk <= len_old;   // no masked row, no appended row
-#pragma unroll
-            for (int sb = 0; sb < NSB; ++sb) {
-                const int r0 = c * kDecodeChunk + sb * SB;
-                if (full) {
-                    attend_block<BF16, LPR, G, NI, false>(kseg, vseg, r0, len, len_old, app, writer, ring, nullptr,
-                                                          nullptr, nullptr, nullptr, row_bytes, sub, rg, qf, o,
-                                                          mrun, srun);
-                } else if (r0 < len) {
-                    if constexpr (EV) {   // a sub-block whose only occupied row is the pruned one has no work
-                        const int hi = len < r0 + SB ? len : r0 + SB;
-                        if (hi - r0 == 1 && ring.r_mask == r0) continue;
-                    }
-                    attend_block<BF16, LPR, G, NI, true, EV>(kseg, vseg, r0, len, len_old, app, writer, ring,
-                                                             p.k_new + newrow, p.v_new + newrow, p.kc + segbase,
-                                                             p.vc + segbase, row_bytes, sub, rg, qf, o, mrun, srun);
-                }
-            }
+        auto load = [&](uint4 (&kr)[NI], uint4 (&vr)[NI], int blk) {
+            load_block<LPR, NI, EV>(kr, vr, blk * BR, len, len_old, app, ring, kseg, vseg, p.k_new + newrow,
+                                    p.v_new + newrow, row_bytes, sub, rg);
+        };
+        auto attend = [&](const uint4 (&kr)[NI], uint4 (&vr)[NI], int blk) {
+            attend_block<BF16, LPR, G, NI, EV>(kr, vr, blk * BR, len, len_old, ring, rg, qf, o, mrun, srun);
+        };
+        uint4 k0[NI], v0[NI];
+        // the appended row goes to its slot; attention takes it from k_new / v_new
+        const bool put = writer && uw == 0 && rg == 0;
+        uint4 nk = make_uint4(0, 0, 0, 0), nv = nk;
+        if (put) {
+            nk = *(const uint4*)(p.k_new + newrow + sub * 16);
+            nv = *(const uint4*)(p.v_new + newrow + sub * 16);
+        }
+        load(k0, v0, uw);
+        if (put) {
+            const size_t slot = EV ? (size_t)(ring0 + (p.t - 1) % (p.d + 1)) : (size_t)len_old;
+            *(uint4*)(kseg + slot * row_bytes + sub * 16) = nk;
+            *(uint4*)(vseg + slot * row_bytes + sub * 16) = nv;
+        }
+        for (int blk = uw;;) {
+            attend(k0, v0, blk);
+            blk += UW;
+            if (blk >= nb) break;
+            load(k0, v0, blk);
         }
         // merge the RPI row groups of the wavefront (they share mrun)
 #pragma unroll
@@ -283,13 +359,13 @@ decode_attn_kernel(DecodeParams p) {
     if constexpr (EV) {
         // the surviving token moves from its ring slot to the next permanent slot.  Attention above read it
         // from the ring slot; nobody reads the permanent slot in this launch.
-        if (grad && writer && wv == 0 && rg == 0) {
-            const unsigned char* src_k = p.kc + segbase + (size_t)(ring0 + cs) * row_bytes + sub * 16;
-            const unsigned char* src_v = p.vc + segbase + (size_t)(ring0 + cs) * row_bytes + sub * 16;
-            *(uint4*)(p.kc + segbase + (size_t)len_old * row_bytes + sub * 16) = *(const uint4*)src_k;
-            *(uint4*)(p.vc + segbase + (size_t)len_old * row_bytes + sub * 16) = *(const uint4*)src_v;
+        if (grad && writer && uw == 0 && rg == 0) {
+            const unsigned char* src_k = kseg + (size_t)(ring0 + cs) * row_bytes + sub * 16;
+            const unsigned char* src_v = vseg + (size_t)(ring0 + cs) * row_bytes + sub * 16;
+            *(uint4*)(kseg + (size_t)len_old * row_bytes + sub * 16) = *(const uint4*)src_k;
+            *(uint4*)(vseg + (size_t)len_old * row_bytes + sub * 16) = *(const uint4*)src_v;
         }
-        if (p.kept_pos && app && hu == 0 && threadIdx.x == 0) {
+        if (p.kept_pos && app && hu == 0 && uw == 0 && lane == 0) {
             int32_t* kp = p.kept_pos + off;
             kp[ring0 + (p.t - 1) % (p.d + 1)] = p.N + p.t - 1;
             if (decide) {
@@ -298,41 +374,63 @@ decode_attn_kernel(DecodeParams p) {
             }
         }
     }
-    if (rg == 0) {
+    // Count the unit in once every wavefront of it has read lens (UW > 1: behind the barrier below); the round
+    // trip of the atomic passes while the output is written.
+    const bool counter = live && uw == 0 && lane == 0;
+    int counted = 0;
+    if (UW == 1) {
+        if (counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
+        if (live && rg == 0) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            float* dst = s_part[wv][g];
+            for (int g = 0; g < G; ++g) {
+                const size_t oi = ((size_t)sl * p.H + hu * G + g) * p.D + sub * EPL;
+                float r[EPL];
 #pragma unroll
-            for (int x = 0; x < EPL; ++x) dst[sub * EPL + x] = o[g][x];
-            if (sub == 0) { dst[DMAX] = mrun[g]; dst[DMAX + 1] = srun[g]; }
-        }
-    }
-    __syncthreads();
-    // merge the wavefronts: thread (g, d)
-    for (int i = threadIdx.x; i < G * p.D; i += blockDim.x) {
-        const int g = i / p.D, d = i % p.D;
-        float M = -INFINITY;
+                for (int x = 0; x < EPL; ++x) r[x] = srun[g] > 0.f ? o[g][x] / srun[g] : 0.f;   // an empty segment gives zeros
+                if constexpr (BF16) {
+                    uint32_t w[4];
 #pragma unroll
-        for (int w = 0; w < W; ++w) M = fmaxf(M, s_part[w][g][DMAX]);
-        float num = 0.f, den = 0.f;
-        if (M > -INFINITY) {
-#pragma unroll
-            for (int w = 0; w < W; ++w) {
-                const float wgt = __builtin_amdgcn_exp2f(s_part[w][g][DMAX] - M);
-                num = fmaf(wgt, s_part[w][g][d], num);
-                den = fmaf(wgt, s_part[w][g][DMAX + 1], den);
+                    for (int x = 0; x < 4; ++x) w[x] = (uint32_t)f32_to_bf16(r[2 * x]) | ((uint32_t)f32_to_bf16(r[2 * x + 1]) << 16);
+                    *(uint4*)((bf16_t*)p.out + oi) = make_uint4(w[0], w[1], w[2], w[3]);
+                } else {
+                    *(float4*)((float*)p.out + oi) = make_float4(r[0], r[1], r[2], r[3]);
+                }
             }
         }
-        const float r = den > 0.f ? num / den : 0.f;   // an empty segment gives zeros
-        const size_t oi = ((size_t)sl * p.H + hu * G + g) * p.D + d;
-        if constexpr (BF16) ((bf16_t*)p.out)[oi] = f32_to_bf16(r); else ((float*)p.out)[oi] = r;
+    } else {
+        if (rg == 0) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                float* dst = s_part[wv][g];
+#pragma unroll
+                for (int x = 0; x < EPL; ++x) dst[sub * EPL + x] = o[g][x];
+                if (sub == 0) { dst[DMAX] = mrun[g]; dst[DMAX + 1] = srun[g]; }
+            }
+        }
+        __syncthreads();
+        if (counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
+        // merge the wavefronts of a unit: thread (g, d)
+        const int w0 = wv & ~(UW - 1);
+        for (int i = uw * kWave + lane; live && i < G * p.D; i += UW * kWave) {
+            const int g = i / p.D, d = i % p.D;
+            float M = -INFINITY;
+            for (int w = 0; w < UW; ++w) M = fmaxf(M, s_part[w0 + w][g][DMAX]);
+            float num = 0.f, den = 0.f;
+            if (M > -INFINITY) {
+                for (int w = 0; w < UW; ++w) {
+                    const float wgt = __builtin_amdgcn_exp2f(s_part[w0 + w][g][DMAX] - M);
+                    num = fmaf(wgt, s_part[w0 + w][g][d], num);
+                    den = fmaf(wgt, s_part[w0 + w][g][DMAX + 1], den);
+                }
+            }
+            const float r = den > 0.f ? num / den : 0.f;   // an empty segment gives zeros
+            const size_t oi = ((size_t)sl * p.H + hu * G + g) * p.D + d;
+            if constexpr (BF16) ((bf16_t*)p.out)[oi] = f32_to_bf16(r); else ((float*)p.out)[oi] = r;
+        }
     }
-    // every thread of this workgroup has read lens (before the barrier); count the workgroup in
-    if (threadIdx.x == 0) {
-        const int old = atomicAdd(p.lens + sl, 1 << kLenBits);
-        if ((int)((unsigned)old >> kLenBits) == HU - 1)
-            __hip_atomic_store(p.lens + sl, len_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    // the last unit of the segment to be counted in stores the new length
+    if (counter && (int)((unsigned)counted >> kLenBits) == HU - 1)
+        __hip_atomic_store(p.lens + sl, len_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -816,14 +914,6 @@ decode_gqa_kernel(DecodeParams p) {
 
 
 
-// Launch shapes.  All workgroups of a launch should be resident at once (one round), so short
-// segments get small workgroups with many row loads in flight per wavefront, and long segments get
-// more wavefronts per workgroup to shorten the serial walk over the chunks:
-//   shape 0: 2 wavefronts, 16 loads in flight, 2 wavefronts/SIMD   (segments up to ~1k tokens);
-//            with more than one resident round of workgroups: 4 loads in flight, 4 wavefronts/SIMD
-//   shape 1: 4 wavefronts,  8 loads in flight, 4 wavefronts/SIMD   (up to ~4k tokens)
-//   shape 2: 8 wavefronts,  8 loads in flight, 4 wavefronts/SIMD   (longer)
-// Groups of 4 or 8 query heads keep 8 loads in flight and 2 wavefronts/SIMD (register budget).
 // Number of compute units of the current device (queried once per device).
 static int compute_units() {
     static int cached[64];
@@ -837,50 +927,54 @@ static int compute_units() {
     return cached[dev];
 }
 
+// Launch shapes of decode_attn_kernel.  A unit is one head group of one segment; its rows are dealt to its
+// wavefronts in blocks of NI * 64/LPR rows.  What decides is how many wavefronts a launch has: 16 per compute unit are
+// resident (4 per SIMD), and starting one costs the dispatcher about 7 ns whatever it does (12 800 units: 393 us with
+// four wavefronts each, 173 us with one, for rows that stream in 150 us).  Hence
+//   up to 2 units per compute unit: 8 wavefronts per unit (32 units, one layer of the 7B shape: 8.6 -> 6.1 us);
+//   up to 4: 4 wavefronts per unit, which fill the chip (7B, batch 1: 21.0 -> 18.5 us);
+//   beyond: one wavefront per unit, four units of a segment per workgroup, the longest segments first.  The lengths
+//       differ by up to two orders of magnitude, and in index order the launch ends with a few long segments on a
+//       chip that is otherwise empty: 13B, batch 8: 253 -> 173 us with the ranking.  Up to two rounds of wavefronts
+//       the longest segment alone is a sizeable part of the launch, so the longest eighth of the segments gets four
+//       wavefronts per unit and the next eighth two (7B, batch 2: 46.5 -> 33.5 us; one wavefront each: 55 us).
+// Four row loads of K and of V in flight per wavefront; the next block is not requested ahead of the work on this
+// one (that costs 22 registers and gains nothing: the other three wavefronts of the SIMD fill the gap).
 template <bool BF16, int LPR, int G, bool EV>
-static hipError_t launch_decode_s(const DecodeParams& p, int shape, int nblk, hipStream_t st) {
-    constexpr int RPI = kWave / LPR;
-    constexpr int NI_MAX = kDecodeChunk / RPI;
-    constexpr bool WIDE = G >= 4;
-    constexpr int NI16 = WIDE ? (NI_MAX < 8 ? NI_MAX : 8) : (NI_MAX < 16 ? NI_MAX : 16);
-    constexpr int NI8 = NI_MAX < 8 ? NI_MAX : 8;
-    constexpr int OCC4 = WIDE ? 2 : 3;   // the 4- and 8-wavefront shapes spill at 4 wavefronts/SIMD (8-9 % slower)
-    if constexpr (!WIDE) {
-        // more workgroups than fit on the chip at once: smaller register footprint, twice as many resident
-        // workgroups with a quarter of the loads in flight each (measured 4-27 % faster from batch 2 on)
-        constexpr int NI4 = NI_MAX < 4 ? NI_MAX : 4;
-        const bool one_round = nblk <= 4 * compute_units();
-        // bf16 rows: the two-wavefront shapes also serve longer prompts (measured at N = 1500 .. 8192: 4-18 %
-        // faster than four or eight wavefronts per workgroup, whose register budget spills) except when
-        // segments of more than 4096 rows meet a launch of several rounds
-        if (BF16 && (shape == 1 || (shape == 2 && one_round))) shape = 0;
-        if (shape == 0 && !one_round) {
-            // the pruning variant needs more registers: at 4 wavefronts/SIMD it spills (measured 10-22 % slower)
-            constexpr int OCC_MANY = EV ? 3 : 4;
-            hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI4, 2, OCC_MANY, EV>), dim3(nblk), dim3(2 * kWave), 0, st, p);
-            return hipGetLastError();
-        }
+static hipError_t launch_decode_s(DecodeParams p, int nblk, hipStream_t st) {
+    constexpr int NI = 4;
+    constexpr int OCC = G >= 4 ? 2 : 4;
+    const int HU = p.H / G, cus = compute_units();
+    p.n_seg = nblk / HU;
+    if (nblk <= 2 * cus) {
+        hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 8, OCC, EV, 0>), dim3(nblk), dim3(8 * kWave), 0, st, p);
+        return hipGetLastError();
     }
-    if (shape == 0)
-        hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI16, 2, 2, EV>), dim3(nblk), dim3(2 * kWave), 0, st, p);
-    else if (shape == 1)
-        hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI8, 4, OCC4, EV>), dim3(nblk), dim3(4 * kWave), 0, st, p);
-    else
-        hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI8, 8, OCC4, EV>), dim3(nblk), dim3(8 * kWave), 0, st, p);
+    if (nblk <= 4 * cus) {
+        hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, 0>), dim3(nblk), dim3(4 * kWave), 0, st, p);
+        return hipGetLastError();
+    }
+    const int ngrp = (p.n_seg + kRankRegs * kWave - 1) / (kRankRegs * kWave);
+    p.gsz = (p.n_seg + ngrp - 1) / ngrp;
+    p.n4 = p.n2 = nblk <= 2 * 16 * cus ? p.gsz / 8 : 0;
+    const int per_group = p.n4 * HU + p.n2 * ((HU + 1) / 2) + (p.gsz - p.n4 - p.n2) * ((HU + 3) / 4);
+    const dim3 grid(per_group * ngrp), block(4 * kWave);
+    if (p.gsz <= kWave) hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, 1>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, kRankRegs>), grid, block, 0, st, p);
     return hipGetLastError();
 }
 
 template <bool BF16, int LPR, bool EV>
-static hipError_t launch_decode_g(const DecodeParams& p, int G, int shape, int nblk, hipStream_t st) {
+static hipError_t launch_decode_g(const DecodeParams& p, int G, int nblk, hipStream_t st) {
     if constexpr (!BF16) {   // bf16 caches with several query heads per KV head use decode_gqa_kernel instead
         switch (G) {
-            case 8: return launch_decode_s<BF16, LPR, 8, EV>(p, shape, nblk, st);
-            case 4: return launch_decode_s<BF16, LPR, 4, EV>(p, shape, nblk, st);
-            case 2: return launch_decode_s<BF16, LPR, 2, EV>(p, shape, nblk, st);
+            case 8: return launch_decode_s<BF16, LPR, 8, EV>(p, nblk, st);
+            case 4: return launch_decode_s<BF16, LPR, 4, EV>(p, nblk, st);
+            case 2: return launch_decode_s<BF16, LPR, 2, EV>(p, nblk, st);
             default: break;
         }
     }
-    return launch_decode_s<BF16, LPR, 1, EV>(p, shape, nblk, st);
+    return launch_decode_s<BF16, LPR, 1, EV>(p, nblk, st);
 }
 
 // Workspace layout of the grouped-query path for n_seg segments (see decode_plan_kernel).
@@ -946,13 +1040,12 @@ static hipError_t launch_decode_any(const pkv_shape& s, const DecodeParams& p, v
     if (bf16 && G >= 2)     // several query heads share the cached rows: scores on the matrix cores
         return s.D == 128 ? launch_gqa<128, EV>(p, s, G, (int*)ws, st) : launch_gqa<64, EV>(p, s, G, (int*)ws, st);
     const int lpr = s.D * (bf16 ? 2 : 4) / 16;
-    const int shape = s.N <= 1024 ? 0 : s.N <= 4096 ? 1 : 2;   // segments hold at most N + appended tokens
     if (bf16) {
-        if (lpr == 8) return launch_decode_g<true, 8, EV>(p, G, shape, nblk, st);
-        return launch_decode_g<true, 16, EV>(p, G, shape, nblk, st);
+        if (lpr == 8) return launch_decode_g<true, 8, EV>(p, G, nblk, st);
+        return launch_decode_g<true, 16, EV>(p, G, nblk, st);
     }
-    if (lpr == 16) return launch_decode_g<false, 16, EV>(p, G, shape, nblk, st);
-    return launch_decode_g<false, 32, EV>(p, G, shape, nblk, st);
+    if (lpr == 16) return launch_decode_g<false, 16, EV>(p, G, nblk, st);
+    return launch_decode_g<false, 32, EV>(p, G, nblk, st);
 }
 
 static DecodeParams make_params(const pkv_shape& s, int l0, int l1, const void* q, const void* k_new,
@@ -967,6 +1060,7 @@ static DecodeParams make_params(const pkv_shape& s, int l0, int l1, const void* 
     p.lens = lens; p.out = (unsigned char*)out;
     p.N = s.N; p.t = 0; p.d = 0; p.base_lens = nullptr; p.kept_pos = nullptr;
     p.G = 1; p.n_seg = 0; p.S0 = 0; p.pieces_cap = 0; p.record_word = 0; p.partial_word = 0; p.plan = nullptr;
+    p.gsz = 0; p.n4 = 0; p.n2 = 0;
     return p;
 }
 
