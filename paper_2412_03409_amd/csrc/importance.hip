@@ -8,7 +8,7 @@
 // in the second (the column sum of a key is a sum inside the lane).
 //
 // The head mean is a second, tiny kernel that adds the per-workgroup partial sums in (head, workgroup)
-// order, so the result is bitwise reproducible.  fp32 inputs (small validation shapes) use plain kernels.
+// order, so the result is bitwise reproducible.  fp32 inputs (small validation shapes) have kernels of their own.
 #include "pkv_common.hpp"
 
 namespace pkv {
@@ -505,59 +505,137 @@ __global__ void head_mean_kernel(int H, int N, long long total, const float* __r
     importance[i] = acc / (float)H;
 }
 
-// ---- plain kernels for fp32 storage -----------------------------------------------------------------
-struct NaiveParams {
-    int B, L, H, Hkv, N, D;
+// ---- fp32 storage --------------------------------------------------------------------------------------
+// Both products on v_mfma_f32_16x16x4_f32 (fp32 operands, so nothing is rounded that one-thread-per-row loops would
+// keep).  A workgroup owns 16 rows of one head -- queries for the log-sum-exp, keys for the column sums -- as the
+// B operand in registers; its wavefronts take the 16-row tiles of the other tensor in turn as the A operand, so
+// that a lane holds one stationary row (lane % 16) and four streamed ones.  The four quarters of a row's columns are
+// the four k-slots of the MFMA: lane quarter kq loads columns kq*D/4 ... of its row with 16-byte loads, the same for
+// both operands, and no data goes through LDS.  Bound: latency at the small shapes that fp32 storage is used with
+// (B1 L4 H2 N128 D64: one row per thread on 8 workgroups took 637 + 831 us, these take 5 + 5), else the fp32 matrix
+// rate.
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+struct F32Params {
+    int B, L, H, Hkv, N;
     const float* q; Strides qs;
     const float* k; Strides ks;
     const float* scale;
-    const float* lse_in;
-    float* lse_out;
-    float* partial;
+    const float* lse_in;       // column sums
+    float* out;                // log-sum-exp (natural log) or column sums, [B,L,H,N]
 };
 
-__global__ void lse_naive_kernel(NaiveParams p) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (long long)p.B * p.L * p.H * p.N) return;
-    const int m = (int)(i % p.N);
-    long long r = i / p.N;
-    const int h = (int)(r % p.H); r /= p.H;
-    const int l = (int)(r % p.L), b = (int)(r / p.L);
-    const float* qr = p.q + p.qs.b * b + p.qs.l * l + p.qs.h * h + p.qs.n * m;
-    const float* kb = p.k + p.ks.b * b + p.ks.l * l + p.ks.h * (h / (p.H / p.Hkv));
-    const float c = p.scale[l] * kLog2e;
-    float mrun = -INFINITY, srun = 0.f;
-    for (int n = 0; n <= m; ++n) {
-        const float* kr = kb + p.ks.n * n;
-        float d = 0.f;
-        for (int x = 0; x < p.D; ++x) d = fmaf(qr[x], kr[x], d);
-        d *= c;
-        const float mnew = fmaxf(mrun, d);
-        srun = srun * exp2f(mrun - mnew) + exp2f(d - mnew);
-        mrun = mnew;
-    }
-    p.lse_out[i] = (mrun + log2f(srun)) * kLn2;
+constexpr int kF32Waves = 4;
+
+template <int D>
+__device__ __forceinline__ void load_f32_rows(f32x4 (&f)[D / 16], const float* base, int64_t ld, int row0, int N, int lane) {
+    int row = row0 + (lane & 15);
+    row = row < N ? row : N - 1;
+    const float* src = base + (int64_t)row * ld + (lane >> 4) * (D / 4);
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i) f[i] = *(const f32x4*)(src + 4 * i);
 }
 
-__global__ void colsum_naive_kernel(NaiveParams p) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (long long)p.B * p.L * p.H * p.N) return;
-    const int n = (int)(i % p.N);
-    long long r = i / p.N;
-    const int h = (int)(r % p.H); r /= p.H;
-    const int l = (int)(r % p.L), b = (int)(r / p.L);
+// LSE: 16 queries against the keys they see.  Otherwise: 16 keys against the queries that see them.
+template <int D, bool LSE>
+__global__ void __launch_bounds__(kF32Waves * kWave)
+importance_f32_kernel(F32Params p) {
+    constexpr int KF = D / 16;
+    __shared__ float s_m[kF32Waves][16], s_s[kF32Waves][16];
+    const int T = (p.N + 15) / 16;
+    const long long id = (long long)blockIdx.y * gridDim.x + blockIdx.x;
+    const int t = (int)(id % T);
+    const long long head = id / T;
+    if (head >= (long long)p.B * p.L * p.H) return;
+    const int h = (int)(head % p.H), l = (int)((head / p.H) % p.L), b = (int)(head / ((long long)p.H * p.L));
     const float* qb = p.q + p.qs.b * b + p.qs.l * l + p.qs.h * h;
-    const float* kr = p.k + p.ks.b * b + p.ks.l * l + p.ks.h * (h / (p.H / p.Hkv)) + p.ks.n * n;
-    const float* lse = p.lse_in + (i - n);
+    const float* kb = p.k + p.ks.b * b + p.ks.l * l + p.ks.h * (h / (p.H / p.Hkv));
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    const int col = lane & 15, rq = lane >> 4;            // stationary row, streamed rows 4*rq .. 4*rq + 3
     const float c = p.scale[l] * kLog2e;
-    float acc = 0.f;
-    for (int m = n; m < p.N; ++m) {
-        const float* qr = qb + p.qs.n * m;
-        float d = 0.f;
-        for (int x = 0; x < p.D; ++x) d = fmaf(qr[x], kr[x], d);
-        acc += exp2f(d * c - lse[m] * kLog2e);
+    const float* sb = LSE ? kb : qb;
+    const int64_t sld = LSE ? p.ks.n : p.qs.n;
+    const int first = LSE ? 0 : t, last = LSE ? t : T - 1;
+    f32x4 st[KF], cur[KF], nxt[KF];
+    load_f32_rows<D>(st, LSE ? qb : kb, LSE ? p.qs.n : p.ks.n, 16 * t, p.N, lane);
+    float mrun = -INFINITY, srun = 0.f;
+    const int mine = 16 * t + col;
+    if (first + wv <= last) load_f32_rows<D>(cur, sb, sld, 16 * (first + wv), p.N, lane);
+    for (int u = first + wv; u <= last; u += kF32Waves) {
+        const bool more = u + kF32Waves <= last;
+        if (more) load_f32_rows<D>(nxt, sb, sld, 16 * (u + kF32Waves), p.N, lane);
+        float nl[4];
+        if constexpr (!LSE) {
+            const float* lse = p.lse_in + (size_t)head * p.N;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) nl[r] = lse[min(16 * u + 4 * rq + r, p.N - 1)] * -kLog2e;
+        }
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < KF; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(cur[i][e], st[i][e], acc, 0, 0, 0);
+        float x[4];
+        bool see[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int other = 16 * u + 4 * rq + r;         // key (LSE) or query
+            see[r] = other < p.N && (LSE ? other <= mine : other >= mine);
+            x[r] = acc[r] * c;
+        }
+        if constexpr (LSE) {
+            float mnew = mrun;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mnew = see[r] ? fmaxf(mnew, x[r]) : mnew;
+            const float mref = mnew == -INFINITY ? 0.f : mnew;
+            float ps = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ps += see[r] ? __builtin_amdgcn_exp2f(x[r] - mref) : 0.f;
+            srun = srun * __builtin_amdgcn_exp2f(mrun - mref) + ps;
+            mrun = mnew;
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) srun += see[r] ? __builtin_amdgcn_exp2f(x[r] + nl[r]) : 0.f;
+        }
+        if (more) {
+#pragma unroll
+            for (int i = 0; i < KF; ++i) cur[i] = nxt[i];
+        }
     }
-    p.partial[i] = acc;
+    // the four lanes of a stationary row, then the wavefronts, in a fixed order
+    auto merge = [](float& m, float& sum, float mo, float so) {
+        const float M = fmaxf(m, mo), ref = M == -INFINITY ? 0.f : M;
+        sum = sum * __builtin_amdgcn_exp2f(m - ref) + so * __builtin_amdgcn_exp2f(mo - ref);
+        m = M;
+    };
+#pragma unroll
+    for (int sh = 16; sh < kWave; sh <<= 1) {
+        const float so = __shfl_xor(srun, sh, kWave);
+        if constexpr (LSE) { const float mo = __shfl_xor(mrun, sh, kWave); merge(mrun, srun, mo, so); }
+        else srun += so;
+    }
+    if (rq == 0) { s_m[wv][col] = mrun; s_s[wv][col] = srun; }
+    __syncthreads();
+    if (threadIdx.x < 16 && mine < p.N) {
+        float m = s_m[0][col], sum = s_s[0][col];
+#pragma unroll
+        for (int w = 1; w < kF32Waves; ++w) {
+            if constexpr (LSE) merge(m, sum, s_m[w][col], s_s[w][col]);
+            else sum += s_s[w][col];
+        }
+        p.out[(size_t)head * p.N + mine] = LSE ? (m + __log2f(sum)) * kLn2 : sum;
+    }
+}
+
+template <bool LSE>
+static hipError_t launch_importance_f32(const pkv_shape& s, const F32Params& p, hipStream_t st) {
+    const long long nblk = (long long)s.B * s.L * s.H * ((s.N + 15) / 16);
+    const long long gx = nblk < (1 << 23) ? nblk : (1 << 23), gy = (nblk + gx - 1) / gx;   // fewer than 2^32 threads each way
+    if (gy > 65535) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)gx, (unsigned)gy), block(kF32Waves * kWave);
+    if (s.D == 128) hipLaunchKernelGGL((importance_f32_kernel<128, LSE>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((importance_f32_kernel<64, LSE>), grid, block, 0, st, p);
+    return hipGetLastError();
 }
 
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -583,20 +661,14 @@ hipError_t launch_importance(const pkv_shape& s, const void* q, Strides qs, cons
                              hipStream_t st) {
     const size_t per = align_up((size_t)s.B * s.L * s.H * s.N * sizeof(float), 256);
     float* partial = (float*)ws;
-    const long long rows = (long long)s.B * s.L * s.H * s.N;
     const long long total = (long long)s.B * s.L * s.N;
     hipError_t e;
     if (s.dtype == PKV_F32) {
         float* lse_ws = (float*)((unsigned char*)ws + per);
-        NaiveParams p{s.B, s.L, s.H, s.Hkv, s.N, s.D, (const float*)q, qs, (const float*)k, ks, scale,
-                      lse ? lse : lse_ws, lse_ws, partial};
-        const int nb = (int)((rows + 127) / 128);
-        if (!lse) {
-            hipLaunchKernelGGL(lse_naive_kernel, dim3(nb), dim3(128), 0, st, p);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL(colsum_naive_kernel, dim3(nb), dim3(128), 0, st, p);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        F32Params p{s.B, s.L, s.H, s.Hkv, s.N, (const float*)q, qs, (const float*)k, ks, scale, nullptr, lse_ws};
+        if (!lse && (e = launch_importance_f32<true>(s, p, st)) != hipSuccess) return e;
+        p.lse_in = lse ? lse : lse_ws; p.out = partial;
+        if ((e = launch_importance_f32<false>(s, p, st)) != hipSuccess) return e;
         hipLaunchKernelGGL(head_mean_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, s.H, s.N,
                            total, partial, importance);
         return hipGetLastError();

@@ -1,9 +1,12 @@
 """Parity at the sizes where a launch rule changes its form (edges of its ranges, remainders, the smallest and
 largest counts), against the CPU oracle and with the bars of the other GPU tests."""
+import numpy as np
 import pytest
 import torch
 
-from test_gpu_parity import run_decode_case, run_evict_case
+import oracle
+import paper_2412_03409_amd as P
+from test_gpu_parity import DEV, check_importance, np32, rand_qk, run_decode_case, run_evict_case
 
 pytestmark = pytest.mark.gpu
 
@@ -33,3 +36,22 @@ def test_decode_launch_shapes(B, L, H, Hkv, N, D, dtype, frac, steps, layers):
 ])
 def test_decode_evict_launch_shapes(B, L, H, Hkv, N, D, dtype, frac, d, steps):
     run_evict_case(B, L, H, Hkv, N, D, dtype, frac, d, steps, seed=B * L + H)
+
+
+def run_importance_case(B, L, H, Hkv, N, D, dtype, negative=False):
+    """Importance with and without the caller's log-sum-exp; rows at twice their length apart."""
+    q, k, scale = rand_qk(N + D + H, B, L, H, Hkv, N, D, dtype)
+    scale = -scale if negative else scale
+    want, lse = oracle.importance(np32(q), np32(k), scale.numpy(), want_lse=True)
+    qd = torch.cat([q, q], dim=-1).to(DEV)[..., :D]
+    kd = torch.cat([k, k], dim=-1).to(DEV)[..., D:]
+    check_importance(np32(P.prefixkv_importance(qd, kd, scale.to(DEV))), want)
+    lse_d = torch.from_numpy(lse.astype(np.float32)).to(DEV)
+    check_importance(np32(P.prefixkv_importance(qd, kd, scale.to(DEV), lse=lse_d)), want)
+
+
+# importance_f32_kernel: 16-row tiles dealt to four wavefronts
+@pytest.mark.parametrize("N", [1, 15, 16, 17, 64, 65, 129, 300])
+@pytest.mark.parametrize("H,Hkv,D,negative", [(2, 2, 64, False), (4, 1, 128, True)])
+def test_importance_f32_tiles(N, H, Hkv, D, negative):
+    run_importance_case(2, 2, H, Hkv, N, D, torch.float32, negative)
