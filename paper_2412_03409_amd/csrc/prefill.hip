@@ -16,6 +16,8 @@
 //                       4 keys x 16 columns of row-major V and each receives 4 keys of one column.
 #include "pkv_common.hpp"
 
+#include <type_traits>
+
 namespace pkv {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
@@ -27,6 +29,7 @@ typedef __attribute__((address_space(3))) v4i16_t lds_v4i16_t;
 
 struct PrefillParams {
     int B, L, H, Hkv, N, D;
+    int tail;             // heads of an XCD whose blocks run longest first (see the kernel)
     const bf16_t* q; Strides qs;
     const bf16_t* k; Strides ks;
     const bf16_t* v; Strides vs;
@@ -36,9 +39,8 @@ struct PrefillParams {
 };
 
 constexpr int kPfQueries = 128;   // queries per workgroup (4 wavefronts x 2 tiles x 16)
-constexpr int kPfKeys = 32;       // keys per product V^T . P^T (two S^T tiles)
 constexpr int kPfStage = 64;      // keys per LDS stage
-
+constexpr int kPfTailBlocks = 256;   // workgroups of an XCD at the end of a launch that run longest first (4 per slot)
 // two floats to packed bf16, round to nearest even (the hardware conversion of gfx950)
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     const f32x2_t f = {a, b};
@@ -67,6 +69,7 @@ prefill_attn_kernel(PrefillParams p) {
     constexpr int CPR = D / 8;            // 16-byte chunks per row
     constexpr int NJ = D / 16;            // MFMAs per S^T tile
     constexpr int NDT = D / 32;           // 32-column tiles of the output
+    constexpr int NKT = kPfStage / 32;
     constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
     // rows are stored unpadded, their 16-byte chunks swizzled (see swz).
     // Two statically separate buffer pairs: while one is read, the asynchronous copy of the next stage
@@ -80,25 +83,31 @@ prefill_attn_kernel(PrefillParams p) {
     const int nqb = (p.N + kPfQueries - 1) / kPfQueries;
     // The query blocks of one head run next to each other on one XCD (the hardware deals consecutive workgroups
     // out to the eight XCDs in turn) and share the head's K and V through that XCD's L2, as do the query heads
-    // of one KV head; within a head the long (late) query blocks start first.
+    // of one KV head; within a head the long (late) query blocks start first.  The last p.tail heads of an XCD are
+    // taken together, all their longest blocks first: in head order the launch would end on a few long blocks
+    // (64 heads of 2048 positions: 107 -> 86 us; 320 heads of 1021: 164 -> 154; all heads that way loses the
+    // sharing: 1024 heads of 680 positions 253 -> 309 us).
     const int per_xcd = (int)(gridDim.x / kXcds);         // a whole number of heads
-    const int j = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
-    const int qb = nqb - 1 - j % nqb;
-    const int hh = j / nqb;
+    const int j = (int)(blockIdx.x / kXcds);              // index inside the XCD
+    const int hx = per_xcd / nqb, lead = hx - p.tail;     // the XCD's heads; the last p.tail of them longest block first
+    int qb, hl;
+    if (j < lead * nqb) { hl = j / nqb; qb = nqb - 1 - (j - hl * nqb); }
+    else { const int i = j - lead * nqb; const int c = i / p.tail; qb = nqb - 1 - c; hl = lead + i - c * p.tail; }
+    const int hh = (int)(blockIdx.x % kXcds) * hx + hl;
     if (hh >= heads) return;
     const int h = hh % p.H, l = (hh / p.H) % p.L, b = hh / (p.H * p.L);
     const int kvh = h / (p.H / p.Hkv);
     const bf16_t* qbase = p.q + p.qs.b * b + p.qs.l * l + p.qs.h * h;
     const bf16_t* kbase = p.k + p.ks.b * b + p.ks.l * l + p.ks.h * kvh;
     const bf16_t* vbase = p.v + p.vs.b * b + p.vs.l * l + p.vs.h * kvh;
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int ln = lane & 31, hf = lane >> 5;               // MFMA operand row / column, and k-half
     const int q0 = qb * kPfQueries + wv * 32;               // first query of this wavefront
     const int query = q0 + ln;
     // a negative logit scale is moved into the queries (negation is exact in bf16), so that the running
     // maximum can be taken on the raw products
     const float sc_l = p.scale[l];
-    const float qs = fabsf(sc_l) * kLog2e;
+    const float qs = fmaxf(fabsf(sc_l) * kLog2e, 1e-30f);   // > 0: a masked -inf stays one
     const uint32_t sgn = sc_l < 0.f ? 0x80008000u : 0u;
 
     // the queries: B operand of the score products, one fragment per 16 columns of the head dimension
@@ -147,93 +156,127 @@ prefill_attn_kernel(PrefillParams p) {
         }
     };
 
-    auto step = [&](int st, const unsigned char* stK, const unsigned char* stV, unsigned char* nK, unsigned char* nV) {
-        __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wavefront's part of stage st has landed
-        __syncthreads();                                     // ... and everybody's; the other pair is free again
-        if (st + 1 < nst) issue(st + 1, nK, nV);
-      for (int half = 0; half < kPfStage / kPfKeys; ++half) {
-        const int key0 = st * kPfStage + half * kPfKeys;
-        const unsigned char* sK = stK + half * kPfKeys * ROWB;
-        const unsigned char* sV = stV + half * kPfKeys * ROWB;
-        if (key0 > q0 + 31 || q0 >= p.N) return;             // every further key is in this wavefront's future
-        const bool mask = key0 + kPfKeys - 1 > q0 || key0 + kPfKeys > p.N;
 
-        // scores S^T[32 keys x 32 queries] = K . Q^T
-        f32x16_t s;
+    // byte offsets of this lane's fragment reads inside a staged tile: computed once (a 16-row step of the swizzled
+    // layout is a plain offset)
+    uint32_t koff[NJ], voff[NDT][2];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+    for (int j = 0; j < NJ; ++j) {
+        koff[j] = (uint32_t)(ln * ROWB + (((2 * j + hf) ^ swz<CPR>(ln)) * 16));
+        asm volatile("" : "+v"(koff[j]));
+    }
+    {
+        // the 16 lanes of a group point at 4 consecutive keys x 16 columns and each receives the 4 keys of its column
+        const int g2 = (lane >> 4) & 1, i16 = lane & 15;
+        const int vrow = 4 * hf + (i16 >> 2);
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int pos = (2 * j + hf) ^ swz<CPR>(ln);
-            const bf16x8_t kf = __builtin_bit_cast(bf16x8_t, *(const uint4*)(sK + ln * ROWB + pos * 16));
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[j], s, 0, 0, 0);
-        }
-        // online softmax per query (= per lane column); register r holds key 8*(r/4) + 4*hf + r%4
-        // (the running maximum m_run is kept in scaled units, log2 domain; the products stay raw)
-        if (mask) {
+        for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int key = key0 + 8 * (r >> 2) + 4 * hf + (r & 3);
-                s[r] = (key <= query && key < p.N) ? s[r] : -INFINITY;
+            for (int x = 0; x < 2; ++x) {
+                const int chunk = 4 * dt + 2 * g2 + ((i16 & 3) >> 1), r = vrow + 8 * x;
+                voff[dt][x] = (uint32_t)(r * ROWB + ((chunk ^ swz<CPR>(r)) * 16) + (i16 & 1) * 8);
+                asm volatile("" : "+v"(voff[dt][x]));
+            }
+    }
+    // One stage of kPfStage keys for this wavefront, both 32-key tiles at once: one maximum, one look at the reference,
+    // and the second tile's products cover the latency of the first.  MASKED: the stage holds keys some of its
+    // queries must not see; a plain stage costs no compare (the masks cost 70 vector instructions per tile when
+    // one body served both).  Measured against 32 keys at a time:
+    // 196 -> 158 us at B8 H40 N1021, 2486 -> 2170 us at B4 H32/8 N8192 (1010 TFLOP/s).  There the matrix cores are
+    // busy 51 % and the vector ALU 50 % of the cycles, LDS 25 %, at a clock that the power limit holds near 1.6 GHz;
+    // forcing the exponentials between the matrix instructions (scheduling groups) changed nothing.
+    auto attend = [&](auto masked_tag, int key0, const unsigned char* sK, const unsigned char* sV) {
+        constexpr bool MASKED = decltype(masked_tag)::value;
+        // scores S^T[64 keys x 32 queries] = K . Q^T, two 32-key products
+        f32x16_t s[NKT];
+#pragma unroll
+        for (int kt = 0; kt < NKT; ++kt) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[kt][r] = 0.f;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const bf16x8_t kf = __builtin_bit_cast(bf16x8_t, *(const uint4*)(sK + kt * 32 * ROWB + koff[j]));
+                s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[j], s[kt], 0, 0, 0);
             }
         }
-        float mx = s[0];
+        if constexpr (MASKED) {
+            const int lim = min(query, p.N - 1) - key0 - 4 * hf;     // register r holds key 8*(r/4) + r%4 + 4*hf
 #pragma unroll
-        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, kWave)) * qs;
-        const float mnew = fmaxf(m_run, mx);
-        // a query that has seen no key yet (only possible for padding queries beyond N) keeps its state
-        const float corr = mnew == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - mnew);
-        const float mref = mnew == -INFINITY ? 0.f : mnew;
-        m_run = mnew;
-        // probabilities as the B operand of the second product: the 8 keys this lane contributes to the
-        // 16-key product `sl` are registers 8*sl .. 8*sl+7, i.e. keys 16*sl + {4*hf .. 4*hf+3, 8+4*hf .. 8+4*hf+3}
-        bf16x8_t pf[2];
-        float psum = 0.f;
+            for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
-            uint32_t pk[4];
-#pragma unroll
-            for (int e = 0; e < 8; e += 2) {
-                const float p0 = __builtin_amdgcn_exp2f(fmaf(s[8 * sl + e], qs, -mref));
-                const float p1 = __builtin_amdgcn_exp2f(fmaf(s[8 * sl + e + 1], qs, -mref));
-                psum += p0 + p1;
-                pk[e / 2] = pack_bf16(p0, p1);
-            }
-            pf[sl] = __builtin_bit_cast(bf16x8_t, make_uint4(pk[0], pk[1], pk[2], pk[3]));
+                for (int r = 0; r < 16; ++r) s[kt][r] = 32 * kt + 8 * (r >> 2) + (r & 3) <= lim ? s[kt][r] : -INFINITY;
         }
-        l_run = l_run * corr + psum;
-        if (__builtin_amdgcn_ballot_w64(corr != 1.f)) {      // the running maximum moved for some query
+        float mx = s[0][0];
+#pragma unroll
+        for (int kt = 0; kt < NKT; ++kt)
+#pragma unroll
+            for (int r = kt == 0 ? 1 : 0; r + 1 < 16; r += 2) mx = fmaxf(fmaxf(mx, s[kt][r]), s[kt][r + 1]);
+        mx = fmaxf(mx, s[0][15]);
+        {
+            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+            mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * qs;
+        }
+        // the output is rescaled only when some query's running maximum moved.  (Letting the maximum grow by 2^8 first is
+        // 4 % faster, but the largest probability is then no longer exactly 1 and its rounding to bf16 adds up: error
+        // of the output against fp64 1.5e-3 -> 1.7e-3 at B4 H32/8 N8192.)
+        if (__builtin_amdgcn_ballot_w64(mx > m_run)) {
+            const float mnew = fmaxf(m_run, mx);
+            const float corr = mnew == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - mnew);
+            m_run = mnew;
+            l_run *= corr;
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o[dt][r] *= corr;
         }
-        // O^T[32 d x 32 queries] += V^T[32 d x 16 keys] . P^T.  The V^T operand in the key order above comes from
-        // two transposing reads: the 16 lanes of a group point at 4 consecutive keys x 16 columns and each
-        // receives the 4 keys of its own column
-        const int g2 = (lane >> 4) & 1, i16 = lane & 15;
-        const int vrow = 4 * hf + (i16 >> 2);                // key within the 16-key product this lane points at
-        const int sub8 = (i16 & 1) * 8;
+        const float mref = m_run == -INFINITY ? 0.f : m_run;      // no finite score so far
 #pragma unroll
-        for (int dt = 0; dt < NDT; ++dt) {
-            const int chunk = 4 * dt + 2 * g2 + ((i16 & 3) >> 1);
+        for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
             for (int sl = 0; sl < 2; ++sl) {
-                const int r0 = 16 * sl + vrow, r1 = r0 + 8;
-                const v4i16_t a0 = lds_read_tr(sV + r0 * ROWB + ((chunk ^ swz<CPR>(r0)) * 16) + sub8);
-                const v4i16_t a1 = lds_read_tr(sV + r1 * ROWB + ((chunk ^ swz<CPR>(r1)) * 16) + sub8);
-                const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
-                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[sl], o[dt], 0, 0, 0);
+                uint32_t pk[4];
+                float psum = 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; e += 2) {
+                    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kt][8 * sl + e], qs, -mref));
+                    const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kt][8 * sl + e + 1], qs, -mref));
+                    psum += p0 + p1;
+                    pk[e / 2] = pack_bf16(p0, p1);
+                }
+                l_run += psum;
+                const bf16x8_t pf = __builtin_bit_cast(bf16x8_t, make_uint4(pk[0], pk[1], pk[2], pk[3]));
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) {
+                    const unsigned char* sVs = sV + (32 * kt + 16 * sl) * ROWB;
+                    const v4i16_t a0 = lds_read_tr(sVs + voff[dt][0]), a1 = lds_read_tr(sVs + voff[dt][1]);
+                    const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
+                    o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf, o[dt], 0, 0, 0);
+                }
             }
-        }
-      }
     };
-
+    // Stages 0 .. 2*qb - 1 lie wholly in the past of every query of the workgroup; the last one or two hold the
+    // diagonal.
+    auto sync = [&]() {
+        __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wavefront's part of the stage has landed
+        __syncthreads();                                     // ... and everybody's; the other pair is free again
+    };
+    constexpr std::true_type masked{};
+    constexpr std::false_type plain{};
     issue(0, sKa, sVa);
-    for (int st = 0; st < nst; st += 2) {
-        step(st, sKa, sVa, sKb, sVb);
-        if (st + 1 < nst) step(st + 1, sKb, sVb, sKa, sVa);
+    for (int st = 0; st < 2 * qb; st += 2) {
+        sync();
+        issue(st + 1, sKb, sVb);
+        attend(plain, st * kPfStage, sKa, sVa);
+        sync();
+        issue(st + 2, sKa, sVa);
+        attend(plain, (st + 1) * kPfStage, sKb, sVb);
+    }
+    sync();
+    if (2 * qb + 1 < nst) issue(2 * qb + 1, sKb, sVb);
+    if (q0 < p.N) attend(masked, 2 * qb * kPfStage, sKa, sVa);
+    if (2 * qb + 1 < nst) {
+        sync();
+        if (wv >= 2 && q0 < p.N) attend(masked, (2 * qb + 1) * kPfStage, sKb, sVb);
     }
 
     // epilogue: the two halves of a query column hold partial row sums; the output tile is transposed:
@@ -247,10 +290,17 @@ prefill_attn_kernel(PrefillParams p) {
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const uint32_t w0 = pack_bf16(o[dt][4 * g] * inv, o[dt][4 * g + 1] * inv);
-                const uint32_t w1 = pack_bf16(o[dt][4 * g + 2] * inv, o[dt][4 * g + 3] * inv);
-                *(uint2*)(p.out + row * D + 32 * dt + 8 * g + 4 * hf) = make_uint2(w0, w1);
+            for (int g = 0; g < 4; g += 2) {
+                // the two halves of a query swap, so that a lane stores 16 bytes: lane half hf gets columns 8*(g + hf) ...
+                uint32_t w[2][2];
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    w[x][0] = pack_bf16(o[dt][4 * (g + x)] * inv, o[dt][4 * (g + x) + 1] * inv);
+                    w[x][1] = pack_bf16(o[dt][4 * (g + x) + 2] * inv, o[dt][4 * (g + x) + 3] * inv);
+                }
+                const auto s0 = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+                *(uint4*)(p.out + row * D + 32 * dt + 8 * (g + hf)) = make_uint4(s0[0], s1[0], s0[1], s1[1]);
             }
     }
 }
@@ -266,6 +316,9 @@ hipError_t launch_prefill_attn(const pkv_shape& s, const void* q, Strides qs, co
     const long long nqb = (s.N + kPfQueries - 1) / kPfQueries;
     const long long nblk = (heads + kXcds - 1) / kXcds * nqb * kXcds;   // whole heads per XCD
     if (nblk > 0x7fffffffll) return hipErrorInvalidValue;
+    const int hx = (int)((heads + kXcds - 1) / kXcds);
+    p.tail = (int)((kPfTailBlocks + nqb - 1) / nqb);
+    if (p.tail > hx) p.tail = hx;
     const dim3 grid((unsigned)nblk);
     if (s.D == 128) hipLaunchKernelGGL(prefill_attn_kernel<128>, grid, dim3(256), 0, st, p);
     else hipLaunchKernelGGL(prefill_attn_kernel<64>, grid, dim3(256), 0, st, p);

@@ -6,7 +6,8 @@ import torch
 
 import oracle
 import paper_2412_03409_amd as P
-from test_gpu_parity import DEV, check_importance, np32, rand_qk, run_decode_case, run_evict_case
+from test_gpu_parity import DEV, OUT_ATOL, check_importance, np32, rand_qk, run_decode_case, run_evict_case
+from tolerances import LSE_ATOL, LSE_RTOL
 
 pytestmark = pytest.mark.gpu
 
@@ -55,3 +56,40 @@ def run_importance_case(B, L, H, Hkv, N, D, dtype, negative=False):
 @pytest.mark.parametrize("H,Hkv,D,negative", [(2, 2, 64, False), (4, 1, 128, True)])
 def test_importance_f32_tiles(N, H, Hkv, D, negative):
     run_importance_case(2, 2, H, Hkv, N, D, torch.float32, negative)
+
+
+# prefill_attn_kernel: 128-query blocks, 64-key stages, plain stages below the diagonal; the last heads of an XCD run
+# longest block first
+@pytest.mark.parametrize("B,L,H,Hkv,N,D,negative", [
+    (1, 1, 1, 1, 1, 128, False), (1, 1, 3, 1, 63, 64, False), (1, 1, 2, 2, 64, 128, True), (1, 2, 4, 2, 65, 128, False),
+    (1, 1, 2, 1, 127, 64, True), (1, 1, 9, 3, 129, 128, False), (2, 1, 5, 5, 192, 64, False),
+    (1, 1, 2, 2, 193, 128, False), (1, 1, 3, 3, 321, 128, True), (1, 3, 4, 4, 257, 64, False),
+    (2, 5, 30, 30, 257, 64, False),      # 300 heads of 3 blocks: heads in order, then the longest-first tail
+])
+def test_prefill_stages(B, L, H, Hkv, N, D, negative):
+    q, k, scale = rand_qk(N + D + H, B, L, H, Hkv, N, D, torch.bfloat16)
+    scale = -scale if negative else scale
+    v = torch.randn(k.shape, generator=torch.Generator().manual_seed(N)).to(torch.bfloat16)
+    out, lse = P.prefixkv_prefill_attn(q.to(DEV), k.to(DEV), v.to(DEV), scale.to(DEV))
+    want, want_lse = oracle.prefill_attn(np32(q), np32(k), np32(v), scale.numpy(), out_bf16=True)
+    assert np.abs(np32(out) - want).max() <= OUT_ATOL
+    np.testing.assert_allclose(lse.cpu().numpy(), want_lse, rtol=LSE_RTOL, atol=LSE_ATOL)
+
+
+def test_prefill_moving_reference_and_infinite_keys():
+    """Scores that grow along the keys, a scale of zero, and keys
+    that score -inf for a whole stage (the rows of the oracle are fp64)."""
+    N, D = 300, 64
+    g = torch.Generator().manual_seed(5)
+    q = torch.randn((1, 3, 1, N, D), generator=g).abs()
+    k = torch.randn((1, 3, 1, N, D), generator=g).abs() * torch.linspace(0, 1, N).view(1, 1, 1, N, 1) ** 2
+    k[:, 2, :, 64:128] = -float("inf")
+    v = torch.randn((1, 3, 1, N, D), generator=g)
+    q, k, v = (x.to(torch.bfloat16) for x in (q, k, v))
+    scale = torch.tensor([1.0, 0.0, 0.3])
+    out, lse = P.prefixkv_prefill_attn(q.to(DEV), k.to(DEV), v.to(DEV), scale.to(DEV))
+    s = torch.einsum("blhmd,blhnd->blhmn", q.double(), k.double()) * scale.double().view(1, 3, 1, 1, 1)
+    s = s.masked_fill(torch.ones(N, N).triu(1).bool(), -float("inf"))
+    want = torch.softmax(s, -1) @ v.double()
+    assert (out.cpu().double() - want).abs().max() <= OUT_ATOL
+    np.testing.assert_allclose(lse.cpu().numpy(), torch.logsumexp(s, -1).numpy(), rtol=LSE_RTOL, atol=LSE_ATOL)
