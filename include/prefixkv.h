@@ -81,7 +81,7 @@ size_t prefixkv_workspace_bytes(int op, const pkv_shape *shape, int has_lse);
  *   scale [dev] fp32 [L]
  *   lse [dev] fp32 [B,L,H,N] = log sum_{j<=m} exp(scale*q_m.k_j) of every causal row if the caller
  *       already has it from its prefill attention, or NULL: it is then computed here (a first sweep over
- *       the keys inside the same kernel).
+ *       the keys).
  *   importance [dev] fp32 [B,L,N], out (dense).
  * bf16 inputs use bf16 MFMA with fp32 accumulation; exp and all sums are fp32. */
 int prefixkv_importance(const pkv_shape *shape, const void *q, pkv_strides qs, const void *k,

@@ -72,9 +72,9 @@ int prefixkv_importance(const pkv_shape* s, const void* q, pkv_strides qs, const
     // the bf16 kernels address the rows of one head with 32-bit element offsets
     if ((uint64_t)s->N * (uint64_t)qs.n >= (1ull << 31) || (uint64_t)s->N * (uint64_t)ks.n >= (1ull << 31))
         return PKV_ERR_UNSUPPORTED;
-    if (!ws || ws_bytes < importance_ws_bytes(*s, lse != nullptr)) return PKV_ERR_WORKSPACE;
+    if (!ws || ws_bytes < importance_ws_min_bytes(*s, lse != nullptr)) return PKV_ERR_WORKSPACE;
     const hipError_t e = launch_importance(*s, q, to_strides(qs), k, to_strides(ks), scale, lse, importance,
-                                           ws, (hipStream_t)stream);
+                                           ws, ws_bytes, (hipStream_t)stream);
     return e == hipSuccess ? PKV_OK : PKV_ERR_HIP;
 }
 

@@ -915,7 +915,7 @@ decode_gqa_kernel(DecodeParams p) {
 
 
 // Number of compute units of the current device (queried once per device).
-static int compute_units() {
+int compute_units() {
     static int cached[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;

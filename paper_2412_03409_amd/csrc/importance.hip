@@ -1,15 +1,17 @@
 // Stage 1: KV importance (Sec. 3.2) -- column sums of the causal softmax, averaged over heads.
 //
-// bf16 inputs run on the matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulate) in ONE kernel that reads
-// the queries and the keys of a head from HBM once (importance_fused_kernel, below): the queries stay in
-// registers, the keys stream through LDS twice -- first for the row log-sum-exp, then for the column sums --
-// and swapping the MFMA operands between the two sweeps gives the layout each of them wants: a lane holds one
-// query and 16 keys in the first (the running max / sum of a row is a scalar per lane), one key and 16 queries
-// in the second (the column sum of a key is a sum inside the lane).
+// bf16 inputs run on the matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulate), in one of two forms:
+//   importance_stream_kernel, one sweep over the score matrix per launch: the log-sum-exp of the rows (queries
+//       stationary in registers, keys stream through LDS), unless the caller has it, then the column sums (keys
+//       stationary, queries stream).  The stationary row of a lane never changes, so its running maximum and sum, or
+//       its column sum, is one register.
+//   importance_fused_kernel, both sweeps in one launch that reads the queries and the keys of a head from HBM once:
+//       for prompts of up to 768 positions without a given log-sum-exp, when the heads fill the chip.
 //
-// The head mean is a second, tiny kernel that adds the per-workgroup partial sums in (head, workgroup)
-// order, so the result is bitwise reproducible.  fp32 inputs (small validation shapes) have kernels of their own.
+// The head mean is another, tiny kernel that adds the heads' column sums in head order, so the result is bitwise reproducible.  fp32 inputs (small validation shapes) have kernels of their own.
 #include "pkv_common.hpp"
+
+#include <type_traits>
 
 namespace pkv {
 
@@ -111,32 +113,28 @@ __device__ __forceinline__ f32x16 mma_tile(const bf16x8 (&stat)[KS], const bf16x
     return acc;
 }
 // ---- fused kernel: Q and K are read from HBM once -------------------------------------------------------
-// One workgroup of WV wavefronts owns up to WV PAIRS of 32-query tiles of one (sequence, layer, head): tile i
-// is paired with tile T-1-i, so that every pair -- and therefore every wavefront -- has the same amount of
-// causal work (T+1 tile products per sweep).  With WV = 12 a head of up to 768 positions is ONE workgroup (one
-// per CU, three wavefronts per SIMD: their MFMA chains and softmax phases overlap each other) and its keys pass
-// through LDS exactly once per sweep.  The wavefront keeps its two query tiles in registers for the whole
+// One workgroup of WV = 12 wavefronts owns one (sequence, layer, head) of up to 768 positions (one workgroup per CU,
+// three wavefronts per SIMD: their MFMA chains and softmax phases overlap each other).  Its 32-query tiles are taken
+// in PAIRS: tile i with tile T-1-i, so that every pair -- and therefore every wavefront -- has the same amount of
+// causal work (T+1 tile products per sweep).
+// The wavefront keeps its two query tiles in registers for the whole
 // kernel and the keys stream through LDS (128-row stages, asynchronous copies, double-buffered) twice:
 //   sweep 1:  S^T = K.Q^T (a lane holds one query): online max / sum -> lse of the wavefront's 64 rows
-//   sweep 2:  S   = Q.K^T (a lane holds one key):   exp2(c*s - lse) summed over the lane's 32 query rows,
-//             i.e. the column sums of this workgroup's rows; the keys come back from L2 / the last-level cache.
+//   sweep 2:  S   = Q.K^T (a lane holds one key):   exp2(c*s - lse) summed over the lane's 32 query rows;
+//             the keys come back from L2 / the last-level cache.
 // Swapping the MFMA operands transposes the product, so the same stationary fragments serve both sweeps.  The
 // column sums of one 128-key stage leave the workgroup once per stage: the wavefronts' values meet in LDS
 // behind the barrier the stage needs anyway and are added in a fixed order (no atomics, bitwise reproducible).
-// The workgroups of one head (long prompts) sit on one XCD next to each other in dispatch order and share the
-// head's keys through that XCD's L2.
 struct FusedParams {
     int B, L, H, Hkv, N, D;
     int T;                     // 32-row tiles: ceil(N / 32)
-    int npairs;                // ceil(T / 2)
-    int G;                     // workgroups per head: ceil(npairs / wavefronts per workgroup)
+    int npairs;                // ceil(T / 2), at most the wavefronts of a workgroup
     long long nheads;          // B*L*H
-    long long chunk;           // logical workgroup ids per XCD (a multiple of G)
+    long long chunk;           // heads per XCD
     const bf16_t* q; Strides qs;
     const bf16_t* k; Strides ks;
     const float* scale;        // [L]
-    const float* lse_in;       // [B,L,H,N] natural log, or unused
-    float* partial;            // [B*L*H][G][N]: workgroup g's column sums of keys [0, min(N, 32*(T-4g)))
+    float* partial;            // [B*L*H][N] column sums
 };
 
 // barrier that orders LDS traffic only: loads from global memory that are still in flight stay in flight
@@ -175,11 +173,10 @@ __device__ __forceinline__ void load_stationary_one(bf16x8 (&f)[D / 16], const b
 }
 
 // WV wavefronts per workgroup; OCC wavefronts per SIMD the register allocation must allow.
-// SPREAD (short prompts without a given lse, last wavefront without tiles): see the start of the kernel.
-template <int D, bool HAS_LSE, int WV, int OCC, bool SPREAD>
+// SPREAD (last wavefront without tiles): see the start of the kernel.
+template <int D, int WV, int OCC, bool SPREAD>
 __global__ void __launch_bounds__(WV * kWave, OCC)
 importance_fused_kernel(FusedParams p) {
-    static_assert(!(SPREAD && HAS_LSE), "the spread start belongs to the first sweep");
     constexpr int KS = D / 16;
     constexpr int NSUB = kStage / 32;
     using St = Stage<D, WV>;
@@ -192,36 +189,30 @@ importance_fused_kernel(FusedParams p) {
     // the wavefront index as a scalar: everything derived from it (which tiles exist, which sub-tiles are
     // needed) is then known to be uniform and branches on it are scalar branches
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long long id = (long long)(blockIdx.x % kXcds) * p.chunk + blockIdx.x / kXcds;
-    const int g = (int)(id % p.G);
-    const long long head = id / p.G;
+    const long long head = (long long)(blockIdx.x % kXcds) * p.chunk + blockIdx.x / kXcds;
     if (head >= p.nheads) return;
     const int h = (int)(head % p.H), l = (int)((head / p.H) % p.L), b = (int)(head / ((long long)p.H * p.L));
     const bf16_t* qb = p.q + p.qs.b * b + p.qs.l * l + p.qs.h * h;
     const bf16_t* kb = p.k + p.ks.b * b + p.ks.l * l + p.ks.h * (h / (p.H / p.Hkv));
-    float* part = p.partial + ((size_t)head * p.G + g) * p.N;
+    float* part = p.partial + (size_t)head * p.N;
     float c = p.scale[l] * kLog2e;
     const bool flip = c < 0.f;
     c = fmaxf(fabsf(c), 1e-30f);                           // > 0, so that c * (-inf) of a masked entry stays -inf
 
     // this wavefront's pair: the early tile tE and the late tile tL (only tL for the middle tile of an odd T)
-    const int pi = WV * g + wv;
-    int tE = pi < p.npairs ? pi : -1, tL = pi < p.npairs ? p.T - 1 - pi : -1;
+    int tE = wv < p.npairs ? wv : -1, tL = wv < p.npairs ? p.T - 1 - wv : -1;
     if (tE == tL) tE = -1;
     const int qlo0 = 32 * tE, qlo1 = 32 * tL;             // negative: tile absent
-    const int klim = min(p.N, 32 * (p.T - WV * g));       // keys this workgroup's rows can see
-    const int S = (klim + kStage - 1) / kStage;           // key stages per sweep
-    // Steps t = t0 .. 2S-1: step t works on key stage t mod S, sweep 1 for t < S and sweep 2 from S on, out of
-    // s_tile{(t - t0) & 1}; the stage of step t+1 is copied into the other buffer meanwhile.
-    const int t0 = HAS_LSE ? S : 0;
+    const int S = (p.N + kStage - 1) / kStage;            // key stages per sweep
+    // Steps t = 0 .. 2S-1: step t works on key stage t mod S, sweep 1 for t < S and sweep 2 from S on, out of
+    // s_tile{t & 1}; the stage of step t+1 is copied into the other buffer meanwhile.
 
     // SPREAD: the first sweep walks the key stages downwards: the late tiles are needed first (the last stage by
     // the two latest tiles only), the early tiles not before the low stages, so the queries are requested late
     // tile first and arrive while the first stages are worked on, instead of all before the first product.
     // For that the key copies are issued by the last wavefront alone -- the launcher picks this form only when
     // that wavefront has no tiles (fewer pairs than wavefronts) -- and the barriers order LDS traffic only: a
-    // wavefront's query loads then stay in flight across barriers.  (Measured: -2..3 % at 680 positions; with
-    // every wavefront busy and several workgroups per head it loses, 80 against 73 ms at 8192 positions.)
+    // wavefront's query loads then stay in flight across barriers.  (Measured: -2..3 % at 680 positions.)
     const bool copier = wv == WV - 1;
     bf16x8 bq[2][KS];
     if constexpr (SPREAD) {
@@ -235,17 +226,6 @@ importance_fused_kernel(FusedParams p) {
         load_stationary<D>(bq, qb, p.qs.n, tE < 0 ? 0 : qlo0, tL < 0 ? 0 : qlo1, p.N, lane, flip);
     }
     float mrun[2] = {-INFINITY, -INFINITY}, srun[2] = {0.f, 0.f};
-    if (HAS_LSE) {
-        const float* lse = p.lse_in + (size_t)head * p.N;
-        if (lane < 32) {
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                const int t = a == 0 ? tE : tL, m = 32 * t + lane;
-                const float v = lse[min(max(m, 0), p.N - 1)];
-                s_nl2[wv][a][lane] = (t >= 0 && m < p.N) ? -v * kLog2e : -INFINITY;   // rows >= N weigh 0
-            }
-        }
-    }
     if constexpr (SPREAD) {
         if (copier) wait_async_copies();
         lds_barrier();
@@ -379,13 +359,13 @@ importance_fused_kernel(FusedParams p) {
 #pragma unroll
                 for (int w = 0; w < WV; ++w) sum += s_red[par][w][sub][c32];
                 const int n = s * kStage + threadIdx.x;
-                if (n < klim) part[n] = sum;
+                if (n < p.N) part[n] = sum;
             }
             par ^= 1;
         }
     };
     if constexpr (!SPREAD) {
-        for (int t = t0; t < 2 * S; t += 2) {
+        for (int t = 0; t < 2 * S; t += 2) {
             step(s_tile0, s_tile1, t);
             if (t + 1 < 2 * S) step(s_tile1, s_tile0, t + 1);
         }
@@ -398,7 +378,7 @@ importance_fused_kernel(FusedParams p) {
 #pragma unroll
                 for (int w = 0; w < WV; ++w) sum += s_red[par][w][sub][c32];
                 const int n = s * kStage + threadIdx.x;
-                if (n < klim) part[n] = sum;
+                if (n < p.N) part[n] = sum;
             }
             par ^= 1;
         };
@@ -428,51 +408,261 @@ importance_fused_kernel(FusedParams p) {
     }
 }
 
-// importance[b,l,n] = (1/H) * sum_h sum_g partial[b,l,h,g,n] over the workgroups g whose rows see key n.
-// A workgroup takes 64 consecutive keys; its four wavefronts each add a quarter of the heads in (h, g) order
+struct StreamParams {
+    int H, Hkv, L, N;
+    int nblk;                  // blocks of stationary rows per head
+    int tail;                  // heads of an XCD whose blocks run longest first
+    long long nheads;          // B*L*H
+    const bf16_t* q; Strides qs;
+    const bf16_t* k; Strides ks;
+    const float* scale;        // [L]
+    const float* lse_in;       // column sums: [B,L,H,N], times nl_scale the negative log-sum-exp in log2 units
+    float nl_scale;
+    float* out;                // [B,L,H,N]: column sums, or the negative log-sum-exp in log2 units
+};
+constexpr int kStWaves = 4, kStStage = 64;   // wavefronts that share a stage, streamed rows per stage
+constexpr int kStTailBlocks = 256;
+
+// ---- streamed kernels: one sweep each ------------------------------------------------------------------
+// COLS = true: a wavefront owns NK tiles of 32 keys as the B operand of the product and the queries that see them
+// stream through LDS as the A operand: a lane holds one key and 16 queries of each product, and the column sum of a
+// key is one register from the first query to the last -- nothing meets in LDS, one store per key at the end.
+// COLS = false: the same with 32 * NK queries stationary and the keys streaming: running maximum and sum per lane,
+// the row log-sum-exp at the end.
+// Bound by the vector ALU (fma, exp2, add per score: 276 cycles per 32x32 product) with the matrix cores next to it
+// (256).  NK = 2: a fragment read from LDS feeds two products; from two rounds of workgroups on (B4 H32/8 N8192, column
+// sums: 1105 us = 995 TFLOP/s, NK = 1 1230), below NK = 1 fills the chip better (B2 H32 N2048: 58 against 71 us).
+// GS = 2: two groups of four wavefronts share a block and take its stages in turn, for launches of about one
+// workgroup per CU, whose time is the longest block's (one layer, H32 N680: 17 against 19 us with the head mean).
+// Against the fused kernel with a given log-sum-exp, which kept the queries stationary, let the wavefronts' column
+// sums meet in LDS at every stage and had one workgroup per head: 31 -> 17 us there, 115 -> 77 us at B8 H40 N1021,
+// 1256 -> 1105 us at B4 H32/8 N8192.
+template <int D, int NK, int GS, bool COLS>
+__global__ void __launch_bounds__(GS * kStWaves * kWave, GS == 4 ? 4 : 3)
+importance_stream_kernel(StreamParams p) {
+    constexpr int KS = D / 16;
+    constexpr int ROWB = D * 2, CPR = D / 8, RPB = 256 / ROWB;
+    constexpr int BLK = kStWaves * 32 * NK;               // stationary rows per workgroup
+    constexpr int INSTS = kStStage * ROWB / 1024 / kStWaves;
+    __shared__ __attribute__((aligned(1024))) unsigned char s_a[GS][kStStage * ROWB];
+    __shared__ __attribute__((aligned(1024))) unsigned char s_b[GS][kStStage * ROWB];
+    __shared__ __attribute__((aligned(16))) float s_nl[2][GS][kStStage];
+    __shared__ float s_part[2][kStWaves][kWave];           // GS > 1: one group's shares at a time
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int wv = wave % kStWaves, gs = wave / kStWaves;  // the groups of four wavefronts take the stages in turn
+    const int ln = lane & 31, hf = lane >> 5;
+    // blocks of a head next to each other on one XCD, longest first; the XCD's last p.tail heads longest block first
+    const int per_xcd = (int)(gridDim.x / kXcds), j = (int)(blockIdx.x / kXcds);
+    const int hx = per_xcd / p.nblk, lead = hx - p.tail;
+    int rank, hl;                                         // rank 0: the longest block of a head
+    if (j < lead * p.nblk) { hl = j / p.nblk; rank = j - hl * p.nblk; }
+    else { const int i = j - lead * p.nblk; rank = i / p.tail; hl = lead + i - rank * p.tail; }
+    const long long head = (long long)(blockIdx.x % kXcds) * hx + hl;
+    if (head >= p.nheads) return;
+    const int blk = COLS ? rank : p.nblk - 1 - rank;
+    const int h = (int)(head % p.H), l = (int)((head / p.H) % p.L), b = (int)(head / ((long long)p.H * p.L));
+    const bf16_t* qb = p.q + p.qs.b * b + p.qs.l * l + p.qs.h * h;
+    const bf16_t* kb = p.k + p.ks.b * b + p.ks.l * l + p.ks.h * (h / (p.H / p.Hkv));
+    const bf16_t* st_base = COLS ? kb : qb;
+    const bf16_t* sm_base = COLS ? qb : kb;
+    const int64_t st_ld = COLS ? p.ks.n : p.qs.n;
+    const uint32_t sm_ld = (uint32_t)(COLS ? p.qs.n : p.ks.n);    // N * stride < 2^31, checked by the launcher
+    float c = p.scale[l] * kLog2e;
+    const bool flip = c < 0.f;
+    c = fmaxf(fabsf(c), 1e-30f);
+    const int x0 = blk * BLK, xw = x0 + wv * 32 * NK;     // first stationary row of the workgroup, of the wavefront
+    const int first = COLS ? x0 : 0;                      // first streamed row
+    const int nst = COLS ? (p.N - x0 + kStStage - 1) / kStStage : (min(p.N, x0 + BLK) + kStStage - 1) / kStStage;
+
+    int cp_row[INSTS], cp_col[INSTS];
+#pragma unroll
+    for (int i = 0; i < INSTS; ++i) {
+        const int idx = (wv * INSTS + i) * kWave + lane;
+        const int r = idx / CPR, pos = idx % CPR;
+        cp_row[i] = r;
+        cp_col[i] = 8 * (pos ^ ((r / RPB) & (CPR - 1)));
+    }
+    float nl_next = 0.f;
+    auto issue = [&](int st, unsigned char* dst) {
+#pragma unroll
+        for (int i = 0; i < INSTS; ++i) {
+            int row = first + st * kStStage + cp_row[i];
+            row = row < p.N ? row : p.N - 1;
+            __builtin_amdgcn_global_load_lds((glb_void_t*)(sm_base + ((uint32_t)row * sm_ld + (uint32_t)cp_col[i])),
+                                             (lds_void_t*)(dst + (wv * INSTS + i) * 1024), 16, 0, 0);
+        }
+        if (COLS && wv == 0) {
+            const int m = first + st * kStStage + lane;
+            nl_next = m < p.N ? p.nl_scale * p.lse_in[(size_t)head * p.N + m] : -INFINITY;   // rows past the end weigh 0
+        }
+    };
+    if (gs < nst) issue(gs, s_a[gs]);
+    bf16x8 f[NK][KS];
+#pragma unroll
+    for (int t = 0; t < NK; ++t) {
+        int row = xw + 32 * t + ln;
+        row = row < p.N ? row : p.N - 1;
+        const uint32_t sgn = flip ? 0x80008000u : 0u;
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+            uint4 v = *(const uint4*)(st_base + (int64_t)row * st_ld + 16 * kk + 8 * hf);
+            v.x ^= sgn; v.y ^= sgn; v.z ^= sgn; v.w ^= sgn;
+            f[t][kk] = as_bf16x8(v);
+        }
+    }
+    uint32_t aoff[KS];
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+        aoff[kk] = (uint32_t)(ln * ROWB + (((2 * kk + hf) ^ ((ln / RPB) & (CPR - 1))) * 16));
+        asm volatile("" : "+v"(aoff[kk]));
+    }
+    float mrun[NK], srun[NK];
+#pragma unroll
+    for (int t = 0; t < NK; ++t) { mrun[t] = -INFINITY; srun[t] = 0.f; }
+
+    // one stage; MASKED: some of its pairs are in the future
+    auto attend = [&](auto masked_tag, int st, const unsigned char* buf, int par) {
+        constexpr bool MASKED = decltype(masked_tag)::value;
+        const int r0 = first + st * kStStage;
+#pragma unroll
+        for (int u = 0; u < kStStage / 32; ++u) {
+            bf16x8 fr[KS];
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) fr[kk] = as_bf16x8(*(const uint4*)(buf + u * 32 * ROWB + aoff[kk]));
+            float nl[16];
+            if constexpr (COLS) {
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const float4 x = *(const float4*)&s_nl[par][gs][32 * u + 8 * q4 + 4 * hf];
+                    nl[4 * q4] = x.x; nl[4 * q4 + 1] = x.y; nl[4 * q4 + 2] = x.z; nl[4 * q4 + 3] = x.w;
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < NK; ++t) {
+                f32x16 acc = {0};
+#pragma unroll
+                for (int kk = 0; kk < KS; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[kk], f[t][kk], acc, 0, 0, 0);
+                // register r holds streamed row r0 + 32*u + 4*hf + 8*(r/4) + r%4
+                const int d = xw + 32 * t + ln - (r0 + 32 * u + 4 * hf);
+                if constexpr (COLS) {
+                    float ps = 0.f;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const float e = __builtin_amdgcn_exp2f(fmaf(acc[r], c, nl[r]));
+                        ps += !MASKED || 8 * (r >> 2) + (r & 3) >= d ? e : 0.f;
+                    }
+                    srun[t] += ps;
+                } else {
+                    if constexpr (MASKED) {
+                        const int lim = min(d, p.N - 1 - (r0 + 32 * u + 4 * hf));
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[r] = 8 * (r >> 2) + (r & 3) <= lim ? acc[r] : -INFINITY;
+                    }
+                    float mx = max3(acc[0], acc[1], acc[2]);
+#pragma unroll
+                    for (int r = 3; r < 15; r += 2) mx = max3(mx, acc[r], acc[r + 1]);
+                    mx = fmaxf(mx, acc[15]) * c;
+                    const float mnew = fmaxf(mrun[t], mx);
+                    const float mref = mnew == -INFINITY ? 0.f : mnew;
+                    float ps = 0.f;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) ps += __builtin_amdgcn_exp2f(fmaf(acc[r], c, -mref));
+                    srun[t] = srun[t] * __builtin_amdgcn_exp2f(mrun[t] - mref) + ps;
+                    mrun[t] = mnew;
+                }
+            }
+        }
+    };
+    constexpr std::true_type masked{};
+    constexpr std::false_type plain{};
+    auto sync = [&](int par) {
+        if (COLS && wv == 0) s_nl[par][gs][lane] = nl_next;
+        wait_async_copies();
+        __syncthreads();
+    };
+    // a stage in the future of, across or past the wavefront's rows
+    auto step = [&](int st, const unsigned char* buf, int par) {
+        const int r0 = first + st * kStStage, r1 = r0 + kStStage - 1, xe = xw + 32 * NK - 1;
+        if (xw >= p.N || st >= nst || (COLS ? r1 < xw : r0 > xe)) return;
+        if (COLS ? r0 >= xe : r1 <= xw && r1 < p.N) attend(plain, st, buf, par); else attend(masked, st, buf, par);
+    };
+    for (int i = 0; i < nst; i += 2 * GS) {
+        const int st = i + gs;
+        sync(0);
+        if (st + GS < nst) issue(st + GS, s_b[gs]);
+        step(st, s_a[gs], 0);
+        if (i + GS >= nst) break;
+        sync(1);
+        if (st + 2 * GS < nst) issue(st + 2 * GS, s_a[gs]);
+        step(st + GS, s_b[gs], 1);
+    }
+    // the groups' shares of a stationary row, in group order
+    if constexpr (GS > 1) {
+        static_assert(NK == 1, "one stationary tile per wavefront");
+        for (int g = 1; g < GS; ++g) {
+            __syncthreads();
+            if (gs == g) {
+                // lane -> slot of the same wavefront index in group 0
+                s_part[0][wv][lane] = srun[0];
+                if (!COLS) s_part[1][wv][lane] = mrun[0];
+            }
+            __syncthreads();
+            if (gs == 0) {
+                const float so = s_part[0][wv][lane];
+                if constexpr (COLS) srun[0] += so;
+                else {
+                    const float mo = s_part[1][wv][lane], M = fmaxf(mrun[0], mo), ref = M == -INFINITY ? 0.f : M;
+                    srun[0] = srun[0] * __builtin_amdgcn_exp2f(mrun[0] - ref) + so * __builtin_amdgcn_exp2f(mo - ref);
+                    mrun[0] = M;
+                }
+            }
+        }
+        if (gs != 0) return;
+    }
+    // the two halves of a stationary row
+#pragma unroll
+    for (int t = 0; t < NK; ++t) {
+        const int row = xw + 32 * t + ln;
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(srun[t]), __float_as_uint(srun[t]), false, false);
+        const float s0 = __uint_as_float(sw[0]), s1 = __uint_as_float(sw[1]);
+        float res = s0 + s1;
+        if constexpr (!COLS) {
+            const auto mw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mrun[t]), __float_as_uint(mrun[t]), false, false);
+            const float m0 = __uint_as_float(mw[0]), m1 = __uint_as_float(mw[1]);
+            const float M = fmaxf(m0, m1);
+            res = -(M + __log2f(s0 * __builtin_amdgcn_exp2f(m0 - M) + s1 * __builtin_amdgcn_exp2f(m1 - M)));
+        }
+        if (hf == 0 && row < p.N) p.out[(size_t)head * p.N + row] = res;
+    }
+}
+
+// importance[b,l,n] = (1/H) * sum_h partial[b,l,h,n].
+// A workgroup takes 64 consecutive keys; its four wavefronts each add a quarter of the heads in order
 // (several loads in flight: the sum is bound by memory latency, not by bytes) and the four sums are added in
 // wavefront order, so the result does not depend on timing.
 constexpr int kMeanKeys = 64, kMeanParts = 4;
 __global__ void __launch_bounds__(kMeanKeys * kMeanParts)
-head_mean_fused_kernel(int H, int G, int N, int T, int WV, long long total, const float* __restrict__ partial,
-                       float* __restrict__ importance) {
+head_mean_parts_kernel(int H, int N, long long total, const float* __restrict__ partial, float* __restrict__ importance) {
     __shared__ float s_acc[kMeanParts][kMeanKeys];
     const int lane = threadIdx.x % kMeanKeys, part = threadIdx.x / kMeanKeys;
     const long long i = (long long)blockIdx.x * kMeanKeys + lane;
     const bool live = i < total;
     const long long bl = live ? i / N : 0;
     const int n = live ? (int)(i % N) : 0;
-    // workgroup g covers keys below 32*(T - WV*g): g <= (T - 1 - n/32) / WV
-    const int gmax = min(G - 1, (T - 1 - n / 32) / WV);
     const int per = (H + kMeanParts - 1) / kMeanParts;
     const int h0 = part * per, h1 = min(H, h0 + per);
-    const float* src = partial + (size_t)bl * H * G * N + n;
+    const float* src = partial + (size_t)bl * H * N + n;
     float acc = 0.f;
     if (live) {
-        if (G == 1) {
-            int h = h0;
-            for (; h + 8 <= h1; h += 8) {
-                float v[8];
+        int h = h0;
+        for (; h + 8 <= h1; h += 8) {
+            float v[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) v[j] = src[(size_t)(h + j) * N];
+            for (int j = 0; j < 8; ++j) v[j] = src[(size_t)(h + j) * N];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) acc += v[j];
-            }
-            for (; h < h1; ++h) acc += src[(size_t)h * N];
-        } else {
-            for (int h = h0; h < h1; ++h) {
-                const float* sh = src + (size_t)h * G * N;
-                int g = 0;
-                for (; g + 4 <= gmax + 1; g += 4) {
-                    float v[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) v[j] = sh[(size_t)(g + j) * N];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc += v[j];
-                }
-                for (; g <= gmax; ++g) acc += sh[(size_t)g * N];
-            }
+            for (int j = 0; j < 8; ++j) acc += v[j];
         }
+        for (; h < h1; ++h) acc += src[(size_t)h * N];
     }
     s_acc[part][lane] = acc;
     __syncthreads();
@@ -482,27 +672,6 @@ head_mean_fused_kernel(int H, int G, int N, int T, int WV, long long total, cons
         for (int q = 1; q < kMeanParts; ++q) sum += s_acc[q][lane];
         importance[i] = sum / (float)H;
     }
-}
-
-// importance[b,l,n] = (1/H) * sum_h partial[b,l,h,n], heads added in order.
-__global__ void head_mean_kernel(int H, int N, long long total, const float* __restrict__ partial,
-                                 float* __restrict__ importance) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const long long bl = i / N;
-    const int n = (int)(i % N);
-    const float* src = partial + (size_t)bl * H * N + n;
-    float acc = 0.f;
-    int h = 0;
-    for (; h + 8 <= H; h += 8) {             // eight loads in flight, added in head order
-        float v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = src[(size_t)(h + j) * N];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc += v[j];
-    }
-    for (; h < H; ++h) acc += src[(size_t)h * N];
-    importance[i] = acc / (float)H;
 }
 
 // ---- fp32 storage --------------------------------------------------------------------------------------
@@ -640,65 +809,107 @@ static hipError_t launch_importance_f32(const pkv_shape& s, const F32Params& p, 
 
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// wavefronts per workgroup of the fused kernel: 12 (one workgroup per CU, three wavefronts per SIMD) so that a
-// head of up to 768 positions is one workgroup and its keys pass through LDS once per sweep
+// wavefronts per workgroup of the fused kernel: 12 (one workgroup per CU, three wavefronts per SIMD), a pair of
+// 32-query tiles each: heads of up to 768 positions
 constexpr int kFusedWaves = 12;
 constexpr int kFusedOcc = 1;
-static int fused_groups(int N) {
-    const int T = (N + 31) / 32, npairs = (T + 1) / 2;
-    return (npairs + kFusedWaves - 1) / kFusedWaves;
+constexpr int kFusedMaxN = 64 * kFusedWaves;
+
+// Whether a call without a given log-sum-exp runs on the fused kernel.  It takes one head per CU and round and reads Q
+// and K once; the stream kernels share the chip evenly but read both twice, in two launches.  N = 680, streams against
+// fused: 64 heads 32 / 48 us, 192: 54 / 53, 256: 67 / 58, 320: 81 / 100, 384: 97 / 101, 640: 145 / 149, 768: 170 / 157,
+// 1024: 240 / 213 -- fused when its rounds are nearly full.  Up to 256 positions one round of it is never slower
+// (64 heads of 100: 15.1 / 13.3 us, 256 of 200: 22.1 / 20.2).
+static bool fused_fits(const pkv_shape& s) {
+    if (s.N > kFusedMaxN) return false;
+    const long long heads = (long long)s.B * s.L * s.H, cus = compute_units();
+    const long long rounds = (heads + cus - 1) / cus;
+    return rounds == 1 ? s.N <= 256 || heads * 4 >= cus * 3 : heads * 8 >= rounds * cus * 7;
 }
 
+// What a call accepts at least: a row of N floats per head and 768 positions (fp32 storage: one for the column sums and
+// one for a log-sum-exp that is not given).  The kernels use one or two rows per head.
+size_t importance_ws_min_bytes(const pkv_shape& s, bool has_lse) {
+    const size_t rows = (size_t)s.B * s.L * s.H * s.N * sizeof(float);
+    if (s.dtype == PKV_F32) return align_up(rows, 256) * (has_lse ? 1 : 2);
+    return align_up(rows * ((s.N + kFusedMaxN - 1) / kFusedMaxN), 256);
+}
+// The stream kernels without a given log-sum-exp put theirs behind the column sums; a short prompt whose workspace has no
+// room for it runs on the fused kernel.
+static size_t stream_ws_bytes(const pkv_shape& s) { return align_up(2 * (size_t)s.B * s.L * s.H * s.N * sizeof(float), 256); }
 size_t importance_ws_bytes(const pkv_shape& s, bool has_lse) {
-    const size_t per = align_up((size_t)s.B * s.L * s.H * s.N * sizeof(float), 256);
-    if (s.dtype == PKV_F32) return per * (has_lse ? 1 : 2);
-    // bf16: one row of column sums per (head, workgroup of the head)
-    return align_up((size_t)s.B * s.L * s.H * fused_groups(s.N) * s.N * sizeof(float), 256);
+    const size_t least = importance_ws_min_bytes(s, has_lse);
+    if (has_lse || s.dtype == PKV_F32 || fused_fits(s)) return least;
+    return least > stream_ws_bytes(s) ? least : stream_ws_bytes(s);
+}
+
+template <int NK, int GS, bool COLS>
+static void launch_stream_d(const pkv_shape& s, const StreamParams& p, dim3 grid, hipStream_t st) {
+    const dim3 block(GS * kStWaves * kWave);
+    if (s.D == 128) hipLaunchKernelGGL((importance_stream_kernel<128, NK, GS, COLS>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((importance_stream_kernel<64, NK, GS, COLS>), grid, block, 0, st, p);
+}
+template <bool COLS>
+static hipError_t launch_stream(const pkv_shape& s, StreamParams p, hipStream_t st) {
+    const long long cus = compute_units(), hx = (p.nheads + kXcds - 1) / kXcds;   // heads per XCD
+    // 64 stationary rows per wavefront from two rounds of workgroups on, unless that pads the blocks further (1024
+    // heads of 100 positions: 47 against 32 us)
+    const long long nb2 = (s.N + 255) / 256, nb1 = (s.N + 127) / 128;
+    const bool wide = p.nheads * nb2 >= 4 * cus && (2 * nb2 == nb1 || nb2 > 2);
+    p.nblk = (int)(wide ? nb2 : nb1);
+    if (hx * kXcds * p.nblk > 0x7fffffffll) return hipErrorInvalidValue;
+    const long long tail = (kStTailBlocks + p.nblk - 1) / p.nblk;
+    p.tail = (int)(tail < hx ? tail : hx);
+    const dim3 grid((unsigned)(hx * kXcds * p.nblk));
+    if (wide) launch_stream_d<2, 1, COLS>(s, p, grid, st);
+    else if (p.nheads * p.nblk * 4 <= 5 * cus) launch_stream_d<1, 2, COLS>(s, p, grid, st);
+    else launch_stream_d<1, 1, COLS>(s, p, grid, st);
+    return hipGetLastError();
 }
 
 hipError_t launch_importance(const pkv_shape& s, const void* q, Strides qs, const void* k, Strides ks,
-                             const float* scale, const float* lse, float* importance, void* ws,
+                             const float* scale, const float* lse, float* importance, void* ws, size_t ws_bytes,
                              hipStream_t st) {
-    const size_t per = align_up((size_t)s.B * s.L * s.H * s.N * sizeof(float), 256);
     float* partial = (float*)ws;
+    float* lse_ws = partial + (size_t)s.B * s.L * s.H * s.N;
     const long long total = (long long)s.B * s.L * s.N;
     hipError_t e;
     if (s.dtype == PKV_F32) {
-        float* lse_ws = (float*)((unsigned char*)ws + per);
         F32Params p{s.B, s.L, s.H, s.Hkv, s.N, (const float*)q, qs, (const float*)k, ks, scale, nullptr, lse_ws};
         if (!lse && (e = launch_importance_f32<true>(s, p, st)) != hipSuccess) return e;
         p.lse_in = lse ? lse : lse_ws; p.out = partial;
         if ((e = launch_importance_f32<false>(s, p, st)) != hipSuccess) return e;
-        hipLaunchKernelGGL(head_mean_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, s.H, s.N,
-                           total, partial, importance);
-        return hipGetLastError();
-    }
-    FusedParams p;
-    p.B = s.B; p.L = s.L; p.H = s.H; p.Hkv = s.Hkv; p.N = s.N; p.D = s.D;
-    p.T = (s.N + 31) / 32;
-    p.npairs = (p.T + 1) / 2;
-    p.G = fused_groups(s.N);
-    p.nheads = (long long)s.B * s.L * s.H;
-    p.chunk = (p.nheads + kXcds - 1) / kXcds * p.G;          // whole heads per XCD
-    p.q = (const bf16_t*)q; p.qs = qs; p.k = (const bf16_t*)k; p.ks = ks; p.scale = scale;
-    p.lse_in = lse; p.partial = partial;
-    const long long nblk = p.chunk * kXcds;
-    if (nblk > 0x7fffffffll) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)nblk), block(kFusedWaves * kWave);
-    const bool spread = !lse && p.G == 1 && p.npairs < kFusedWaves;   // the last wavefront only copies
-    if (lse) {
-        if (s.D == 128) hipLaunchKernelGGL((importance_fused_kernel<128, true, kFusedWaves, kFusedOcc, false>), grid, block, 0, st, p);
-        else hipLaunchKernelGGL((importance_fused_kernel<64, true, kFusedWaves, kFusedOcc, false>), grid, block, 0, st, p);
-    } else if (spread) {
-        if (s.D == 128) hipLaunchKernelGGL((importance_fused_kernel<128, false, kFusedWaves, kFusedOcc, true>), grid, block, 0, st, p);
-        else hipLaunchKernelGGL((importance_fused_kernel<64, false, kFusedWaves, kFusedOcc, true>), grid, block, 0, st, p);
+    } else if (lse || (!fused_fits(s) && ws_bytes >= stream_ws_bytes(s))) {
+        StreamParams p;
+        p.H = s.H; p.Hkv = s.Hkv; p.L = s.L; p.N = s.N; p.nheads = (long long)s.B * s.L * s.H;
+        p.q = (const bf16_t*)q; p.qs = qs; p.k = (const bf16_t*)k; p.ks = ks; p.scale = scale;
+        p.lse_in = nullptr; p.nl_scale = lse ? -kLog2e : 1.f; p.out = lse_ws;
+        if (!lse && (e = launch_stream<false>(s, p, st)) != hipSuccess) return e;
+        p.lse_in = lse ? lse : lse_ws; p.out = partial;
+        if ((e = launch_stream<true>(s, p, st)) != hipSuccess) return e;
     } else {
-        if (s.D == 128) hipLaunchKernelGGL((importance_fused_kernel<128, false, kFusedWaves, kFusedOcc, false>), grid, block, 0, st, p);
-        else hipLaunchKernelGGL((importance_fused_kernel<64, false, kFusedWaves, kFusedOcc, false>), grid, block, 0, st, p);
+        FusedParams p;
+        p.B = s.B; p.L = s.L; p.H = s.H; p.Hkv = s.Hkv; p.N = s.N; p.D = s.D;
+        p.T = (s.N + 31) / 32;
+        p.npairs = (p.T + 1) / 2;
+        p.nheads = (long long)s.B * s.L * s.H;
+        p.chunk = (p.nheads + kXcds - 1) / kXcds;
+        p.q = (const bf16_t*)q; p.qs = qs; p.k = (const bf16_t*)k; p.ks = ks; p.scale = scale;
+        p.partial = partial;
+        if (p.npairs > kFusedWaves || p.chunk * kXcds > 0x7fffffffll) return hipErrorInvalidValue;
+        const dim3 grid((unsigned)(p.chunk * kXcds)), block(kFusedWaves * kWave);
+        const bool spread = p.npairs < kFusedWaves;       // the last wavefront only copies
+        if (spread) {
+            if (s.D == 128) hipLaunchKernelGGL((importance_fused_kernel<128, kFusedWaves, kFusedOcc, true>), grid, block, 0, st, p);
+            else hipLaunchKernelGGL((importance_fused_kernel<64, kFusedWaves, kFusedOcc, true>), grid, block, 0, st, p);
+        } else {
+            if (s.D == 128) hipLaunchKernelGGL((importance_fused_kernel<128, kFusedWaves, kFusedOcc, false>), grid, block, 0, st, p);
+            else hipLaunchKernelGGL((importance_fused_kernel<64, kFusedWaves, kFusedOcc, false>), grid, block, 0, st, p);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(head_mean_fused_kernel, dim3((unsigned)((total + kMeanKeys - 1) / kMeanKeys)),
-                       dim3(kMeanKeys * kMeanParts), 0, st, s.H, p.G, s.N, p.T, kFusedWaves, total, partial, importance);
+    hipLaunchKernelGGL(head_mean_parts_kernel, dim3((unsigned)((total + kMeanKeys - 1) / kMeanKeys)),
+                       dim3(kMeanKeys * kMeanParts), 0, st, s.H, s.N, total, partial, importance);
     return hipGetLastError();
 }
 

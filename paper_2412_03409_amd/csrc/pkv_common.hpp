@@ -35,10 +35,14 @@ __device__ __forceinline__ uint32_t xcd_swizzle(uint32_t bid, uint32_t nblk) {
 struct Strides { int64_t b, l, h, n; };
 inline Strides to_strides(pkv_strides s) { return Strides{s.b, s.l, s.h, s.n}; }
 
+// compute units of the current device (queried once per device)
+int compute_units();
+
 // ---- launchers (return hipError_t of the launches) -------------------------------------------------
 size_t importance_ws_bytes(const pkv_shape& s, bool has_lse);
+size_t importance_ws_min_bytes(const pkv_shape& s, bool has_lse);   // what a call accepts
 hipError_t launch_importance(const pkv_shape& s, const void* q, Strides qs, const void* k, Strides ks,
-                             const float* scale, const float* lse, float* importance, void* ws,
+                             const float* scale, const float* lse, float* importance, void* ws, size_t ws_bytes,
                              hipStream_t st);
 
 hipError_t launch_prefill_attn(const pkv_shape& s, const void* q, Strides qs, const void* k, Strides ks,

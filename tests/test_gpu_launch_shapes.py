@@ -93,3 +93,39 @@ def test_prefill_moving_reference_and_infinite_keys():
     want = torch.softmax(s, -1) @ v.double()
     assert (out.cpu().double() - want).abs().max() <= OUT_ATOL
     np.testing.assert_allclose(lse.cpu().numpy(), torch.logsumexp(s, -1).numpy(), rtol=LSE_RTOL, atol=LSE_ATOL)
+
+
+# importance: fused kernel (up to 768 positions, heads near a multiple of the CUs) or stream kernels, the latter with 32
+# or 64 stationary rows per wavefront and with one or two groups of wavefronts; and the fused kernel again when the
+# workspace holds the column sums alone
+@pytest.mark.parametrize("B,L,H,Hkv,N,D,negative", [
+    (1, 1, 1, 1, 1, 64, False), (1, 1, 2, 1, 127, 128, False), (1, 1, 3, 3, 128, 64, True), (1, 2, 4, 2, 129, 128, False),
+    (1, 1, 2, 2, 257, 128, True), (1, 2, 3, 1, 449, 64, False), (1, 1, 2, 2, 768, 128, False), (1, 1, 2, 1, 769, 64, False),
+    (1, 8, 40, 8, 65, 64, False),        # 320 heads: streams, more than one workgroup per CU
+    (4, 8, 32, 32, 130, 64, False),      # 1024 heads of 2 blocks: 64 rows per wavefront with a given log-sum-exp
+    (4, 8, 32, 32, 100, 64, False),      # ... 1 block: 32 rows
+    (2, 7, 20, 4, 300, 64, False),       # 280 heads, longest-first tail
+])
+def test_importance_launch_shapes(B, L, H, Hkv, N, D, negative):
+    run_importance_case(B, L, H, Hkv, N, D, torch.bfloat16, negative)
+
+
+@pytest.mark.parametrize("N", [300, 768])
+def test_importance_workspace_limits(N):
+    B, L, H, D = 1, 1, 4, 64
+    q, k, scale = rand_qk(N, B, L, H, H, N, D, torch.bfloat16)
+    want = oracle.importance(np32(q), np32(k), scale.numpy())
+    rows = B * L * H * N * 4
+    assert P.prefixkv_workspace_bytes(0, B, L, H, H, N, D, P.PKV_BF16) >= 2 * rows
+    small = torch.empty((rows + 255) // 256 * 256, dtype=torch.uint8, device=DEV)
+    lib = P.load()
+    from paper_2412_03409_amd import binding as bind
+    qd, kd, sd, out = q.to(DEV), k.to(DEV), scale.to(DEV), torch.empty((B, L, N), device=DEV)
+    s = bind._shape(B, L, H, H, N, D, P.PKV_BF16)
+
+    def call(nbytes):
+        return lib.prefixkv_importance(s, bind._ptr(qd), bind._strides5(qd), bind._ptr(kd), bind._strides5(kd),
+                                       bind._ptr(sd), None, bind._ptr(out), bind._ptr(small), nbytes, bind._stream())
+    assert call(small.numel()) == 0
+    check_importance(np32(out), want)
+    assert call(small.numel() - 256) == 5
