@@ -8,6 +8,7 @@ from __future__ import annotations
 import ctypes as C
 import os
 from dataclasses import dataclass
+from functools import lru_cache
 from pathlib import Path
 from typing import Optional
 
@@ -119,8 +120,16 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported storage dtype {t.dtype}")
 
 
+@lru_cache(maxsize=256)
 def _shape(B, L, H, Hkv, N, D, dtype) -> _Shape:
+    """The argument struct of a shape (only read, so one object per value serves every call)."""
     return _Shape(B, L, H, Hkv, N, D, dtype)
+
+
+@lru_cache(maxsize=256)
+def _decode_ws_bytes(B, L, H, Hkv, N, D, dtype) -> int:
+    """Decode workspace of a shape: a pure function of it, asked for in every step."""
+    return int(load().prefixkv_workspace_bytes(OP_DECODE, C.byref(_shape(B, L, H, Hkv, N, D, dtype)), 0))
 
 
 def _strides5(t: torch.Tensor) -> _Strides:
@@ -130,11 +139,12 @@ def _strides5(t: torch.Tensor) -> _Strides:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # with an index: without one torch looks the device up through four layers of its own (4 us a call)
+    return torch.cuda.current_stream(torch.cuda.current_device()).cuda_stream
 
 
 def _need_cuda(*ts):
@@ -444,7 +454,7 @@ def prefixkv_decode_attn(cache: CompactResult, q: torch.Tensor, k_new: Optional[
     if out is None:
         out = torch.empty((B, L, H, D), dtype=q.dtype, device=q.device)
     s = _shape(B, L, H, cache.Hkv, N, D, _dtype_code(q))
-    w = _ws(load().prefixkv_workspace_bytes(OP_DECODE, C.byref(s), 0), q.device, ws)
+    w = _ws(_decode_ws_bytes(B, L, H, cache.Hkv, N, D, _dtype_code(q)), q.device, ws)
     rc = load().prefixkv_decode_attn(C.byref(s), int(l0), int(l1), _ptr(q), _ptr(k_new), _ptr(v_new),
                                      _ptr(scale), _ptr(cache.kc), _ptr(cache.vc), _ptr(cache.seg_off),
                                      _ptr(cache.caps), _ptr(cache.lens), _ptr(out), _ptr(w),
@@ -476,7 +486,7 @@ def prefixkv_decode_attn_evict(cache: CompactResult, base_lens: torch.Tensor, q:
     if out is None:
         out = torch.empty((B, L, H, D), dtype=q.dtype, device=q.device)
     s = _shape(B, L, H, cache.Hkv, N, D, _dtype_code(q))
-    w = _ws(load().prefixkv_workspace_bytes(OP_DECODE, C.byref(s), 0), q.device, ws)
+    w = _ws(_decode_ws_bytes(B, L, H, cache.Hkv, N, D, _dtype_code(q)), q.device, ws)
     rc = load().prefixkv_decode_attn_evict(
         C.byref(s), int(l0), int(l1), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(scale), _ptr(cache.kc),
         _ptr(cache.vc), _ptr(cache.seg_off), _ptr(cache.caps), _ptr(base_lens), _ptr(cache.lens),

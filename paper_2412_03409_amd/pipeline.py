@@ -67,15 +67,19 @@ class HotPath:
                                    self.cache_tokens, out=self.cache)
 
     def run_decode_step(self, t: int, dq, dk, dv):
+        return self._decode(t, dq[t], dk[t], dv[t], self.out[t])
+
+    def _decode(self, t: int, q, k, v, out):
         if self.evict_distance is not None:
-            return B_.prefixkv_decode_attn_evict(self.cache, self.sel.lengths, dq[t], dk[t], dv[t], self.scale,
-                                                 self.N, t + 1, self.evict_distance, out=self.out[t], ws=self.dec_ws)
-        return B_.prefixkv_decode_attn(self.cache, dq[t], dk[t], dv[t], self.scale, self.N, out=self.out[t],
-                                       ws=self.dec_ws)
+            return B_.prefixkv_decode_attn_evict(self.cache, self.sel.lengths, q, k, v, self.scale, self.N, t + 1,
+                                                 self.evict_distance, out=out, ws=self.dec_ws)
+        return B_.prefixkv_decode_attn(self.cache, q, k, v, self.scale, self.N, out=out, ws=self.dec_ws)
 
     def run_decode_loop(self, dq, dk, dv):
-        for t in range(self.T):
-            self.run_decode_step(t, dq, dk, dv)
+        # the steps' tensors as views made once: indexing four tensors per step costs as much as the call
+        steps = [x[:self.T].unbind(0) for x in (dq, dk, dv, self.out)]
+        for t, (q, k, v, out) in enumerate(zip(*steps)):
+            self._decode(t, q, k, v, out)
 
     # ---- the decode loop as one HIP graph (T launches, no host work between them) -----------
     def capture_decode_loop(self, dq, dk, dv):
