@@ -1,8 +1,8 @@
 // Stages 2 and 3 of the PrefixKV hot path.
 //
 //  sort_prefix_kernel  one workgroup per (sequence, layer): the priority sequence of Sec. 3.2 (positions
-//                      by importance, descending) by a bitonic sort of 64-bit keys -- in registers and
-//                      wavefront shuffles wherever a stage stays inside a wavefront, through LDS otherwise --
+//                      by importance, descending) by a sort of 64-bit keys -- bitonic inside a wavefront, in
+//                      registers and lane exchanges, then pairwise merges of the wavefronts' runs in LDS --
 //                      then the cumulative priority as an exact integer scan of fixed-point weights, and the
 //                      layer's prefix lengths at the ratios t/256 (the first eight steps of the search).
 //  search_kernel       one workgroup per sequence, 32 lanes per layer: Algorithm 1 (Sec. 3.3) runs to
@@ -111,9 +111,11 @@ constexpr int kTabN = (1 << kTabBits) - 1;
 // Sort key: high word = ~bits(importance) (non-negative floats order like their bit patterns, so the
 // complement orders them descending), low word = position (ascending among equal values).
 // Padding keys are all ones: they sort last and decode to weight 0.
-// P = E * ns keys, ns = the sorting threads (whole wavefronts, the first of the workgroup); a bitonic network,
-// ascending.  Merge steps up to 64*E keys and the tail of every longer one run in registers inside a
-// wavefront, without a barrier; only the stages that pair keys of different wavefronts go through LDS.
+// P = E * ns keys, ns = the sorting threads (whole wavefronts, the first of the workgroup).  A wavefront sorts its 64*E
+// keys in registers with a bitonic network, without a barrier; its run then merges with its neighbours' by rank.  Bound by
+// latency: a doubling is one binary search (8 ... 13 dependent LDS reads, the lane's keys side by side) and two barriers,
+// where the bitonic merge of the same step took 8 ... 13 exchange stages on 64-bit keys, some of them through LDS as well.
+// prefixkv_select at L = 32: N = 680 23.4 -> 22.2 us, 2048 31.4 -> 29.2, 8192 71.4 -> 67.1.
 template <int E>
 __global__ void sort_prefix_kernel(int N, int P, const float* __restrict__ importance,
                                    int32_t* __restrict__ order, uint64_t* __restrict__ cum,
@@ -146,40 +148,46 @@ __global__ void sort_prefix_kernel(int N, int P, const float* __restrict__ impor
             }
             r[e] = key;
         }
+        // every wavefront's run ascending (the directions inside it go by the position in the run)
         const int kw = P < kWave * E ? P : kWave * E;
-        for (int k = 2; k <= kw; k <<= 1) wave_stages<E>(r, k, wbase, lane);
-    }
-    __syncthreads();                                      // s_flags = 0 is visible
-    if (flags) atomicOr(&s_flags, flags);
-    for (int k = 2 * kWave * E; k <= P; k <<= 1) {
-        if (sorter) {
-#pragma unroll
-            for (int e = 0; e < E; ++e) skey[wbase + kWave * e + lane] = r[e];
-        }
-        __syncthreads();
-        for (int j = k >> 1; j >= kWave * E; j >>= 1) {
-            for (int t = tid; t < (P >> 1); t += blockDim.x) {
-                const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
-                const int x = i | j;
-                const uint64_t a = skey[i], b = skey[x];
-                const bool up = (i & k) == 0;
-                if ((a > b) == up) { skey[i] = b; skey[x] = a; }
-            }
-            __syncthreads();
-        }
-        if (sorter) {
-#pragma unroll
-            for (int e = 0; e < E; ++e) r[e] = skey[wbase + kWave * e + lane];
-            wave_stages<E>(r, k, wbase, lane);
-        }
-        // the next write of skey (next k, or the sorted keys below) is to this wavefront's own block, which
-        // only this wavefront has read since the last barrier
-    }
-    if (sorter) {
+        for (int k = 2; k <= kw; k <<= 1) wave_stages<E>(r, k, 0, lane);
 #pragma unroll
         for (int e = 0; e < E; ++e) skey[wbase + kWave * e + lane] = r[e];
     }
-    __syncthreads();
+    __syncthreads();                                      // the runs, and s_flags = 0, are visible
+    if (flags) atomicOr(&s_flags, flags);
+    // Neighbouring runs of m keys merge: a key's place in the merged run is its place in its own plus the number of keys of
+    // the other run in front of it (keys are unique but for the padding: equal keys of the left run come first).
+    for (int m = kWave * E; m < P; m <<= 1) {
+        int dst[E];
+        if (sorter) {
+            const uint64_t* other = skey + ((wbase & ~(m - 1)) ^ m);     // a wavefront's keys lie in one run
+            const bool left = (wbase & m) == 0;
+            int cnt[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) { cnt[e] = 0; r[e] -= left ? 1 : 0; }   // key <= r with r one less: key < own
+            for (int h = m >> 1; h > 0; h >>= 1) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) cnt[e] += other[cnt[e] + h - 1] <= r[e] ? h : 0;
+            }
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                cnt[e] += other[cnt[e]] <= r[e] ? 1 : 0;
+                r[e] += left ? 1 : 0;
+                dst[e] = (wbase & ~(2 * m - 1)) + ((wbase + kWave * e + lane) & (m - 1)) + cnt[e];
+            }
+        }
+        __syncthreads();
+        if (sorter) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) skey[dst[e]] = r[e];
+        }
+        __syncthreads();
+        if (sorter && 2 * m < P) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) r[e] = skey[wbase + kWave * e + lane];
+        }
+    }
 
     // fixed-point weights and their inclusive scan; each thread owns E consecutive sorted entries
     const int base = tid * E;                 // threads beyond the sorting ones own nothing

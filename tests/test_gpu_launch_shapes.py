@@ -6,7 +6,8 @@ import torch
 
 import oracle
 import paper_2412_03409_amd as P
-from test_gpu_parity import DEV, OUT_ATOL, check_importance, np32, rand_qk, run_decode_case, run_evict_case
+from test_gpu_parity import DEV, OUT_ATOL, check_importance, check_select, np32, rand_qk, run_decode_case, run_evict_case
+from pkv_workloads import synthetic_importance
 from tolerances import LSE_ATOL, LSE_RTOL
 
 pytestmark = pytest.mark.gpu
@@ -129,3 +130,11 @@ def test_importance_workspace_limits(N):
     assert call(small.numel()) == 0
     check_importance(np32(out), want)
     assert call(small.numel() - 256) == 5
+
+
+# sort_prefix_kernel: runs of 64 (one key per lane), 128, 256 and 512 keys; no, one and several merges; padding in the last
+# run and in whole runs; ties across runs
+@pytest.mark.parametrize("N", [63, 64, 65, 128, 129, 257, 640, 1025, 2048, 2049, 4097, 8191])
+def test_sort_merges(N):
+    check_select(synthetic_importance(1, 3, N, seed=N, ties=True), max(4, N))
+    check_select(synthetic_importance(1, 2, N, seed=N + 1), max(3, N // 2))
