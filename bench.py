@@ -258,7 +258,7 @@ def measure(P, HotPath, w, r, K, W, use_graph, d_ev=None, x=None, dec=None):
     cmp_bytes = 2 * int(lens0.sum()) * w.Hkv * w.D * esz * 2 + w.B * w.L * w.N * 4
     stages = {
         "importance": {"ms": round(imp_ms, 4), "tflops": round(imp_tflops, 1),
-                       "frac_mfma_bf16": round(imp_tflops / MFMA_BF16_PEAK_TFLOPS, 4), "products": 2, "kernels": 1},
+                       "frac_mfma_bf16": round(imp_tflops / MFMA_BF16_PEAK_TFLOPS, 4), "products": 2, "kernels": 1 if w.dtype == "bf16" and w.N <= 768 else 2},
         "select": {"ms": round(sel_ms, 4), "iters": hp.sel.iters.tolist()[:4], "p": hp.sel.p.tolist()[:2]},
         "compact": {"ms": round(cmp_ms, 4), "GBps": round(cmp_bytes / (cmp_ms * 1e-3) / 1e9, 1)},
         "decode_loop": {"ms": round(dec_ms, 4), "us_per_decode_step": round(dec_ms * 1e3 / T, 2),

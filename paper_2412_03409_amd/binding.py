@@ -120,13 +120,13 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported storage dtype {t.dtype}")
 
 
-@lru_cache(maxsize=256)
+@lru_cache(maxsize=256, typed=True)
 def _shape(B, L, H, Hkv, N, D, dtype) -> _Shape:
     """The argument struct of a shape (only read, so one object per value serves every call)."""
     return _Shape(B, L, H, Hkv, N, D, dtype)
 
 
-@lru_cache(maxsize=256)
+@lru_cache(maxsize=256, typed=True)
 def _decode_ws_bytes(B, L, H, Hkv, N, D, dtype) -> int:
     """Decode workspace of a shape: a pure function of it, asked for in every step."""
     return int(load().prefixkv_workspace_bytes(OP_DECODE, C.byref(_shape(B, L, H, Hkv, N, D, dtype)), 0))

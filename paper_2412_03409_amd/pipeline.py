@@ -77,7 +77,9 @@ class HotPath:
 
     def run_decode_loop(self, dq, dk, dv):
         # the steps' tensors as views made once: indexing four tensors per step costs as much as the call
-        steps = [x[:self.T].unbind(0) for x in (dq, dk, dv, self.out)]
+        steps = [x[:self.T].unbind(0) if isinstance(x, torch.Tensor) else x[:self.T] for x in (dq, dk, dv, self.out)]
+        if min(len(x) for x in steps) < self.T:
+            raise IndexError(f"{self.T} decode steps need as many tensors")
         for t, (q, k, v, out) in enumerate(zip(*steps)):
             self._decode(t, q, k, v, out)
 
