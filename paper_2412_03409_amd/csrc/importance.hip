@@ -681,7 +681,7 @@ head_mean_parts_kernel(int H, int N, long long total, const float* __restrict__ 
 // that a lane holds one stationary row (lane % 16) and four streamed ones.  The four quarters of a row's columns are
 // the four k-slots of the MFMA: lane quarter kq loads columns kq*D/4 ... of its row with 16-byte loads, the same for
 // both operands, and no data goes through LDS.  Bound: latency at the small shapes that fp32 storage is used with
-// (B1 L4 H2 N128 D64: one row per thread on 8 workgroups took 637 + 831 us, these take 5 + 5), else the fp32 matrix
+// (B1 L4 H2 N128 D64: one row per thread on 8 workgroups took 637 + 831 us, these take 6.6 + 4.9), else the fp32 matrix
 // rate.
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
