@@ -178,13 +178,12 @@ prefill_attn_kernel(PrefillParams p) {
                 asm volatile("" : "+v"(voff[dt][x]));
             }
     }
-    // One stage of kPfStage keys for this wavefront, both 32-key tiles at once: one maximum, one look at the reference,
+    // One stage of kPfStage keys for this wavefront, both 32-key tiles at once: one look at the reference,
     // and the second tile's products cover the latency of the first.  MASKED: the stage holds keys some of its
     // queries must not see; a plain stage costs no compare (the masks cost 70 vector instructions per tile when
-    // one body served both).  Measured against 32 keys at a time:
-    // 196 -> 158 us at B8 H40 N1021, 2486 -> 2170 us at B4 H32/8 N8192 (1010 TFLOP/s).  There the matrix cores are
-    // busy 51 % and the vector ALU 50 % of the cycles, LDS 25 %, at a clock that the power limit holds near 1.6 GHz;
-    // forcing the exponentials between the matrix instructions (scheduling groups) changed nothing.
+    // one body served both).  Measured against 32 keys at a time, in turn on one card:
+    // 202 -> 145 us at B8 H40 N1021, 2660 -> 2385 us at B4 H32/8 N8192 (922 TFLOP/s), 26.6 -> 22.5 us at H32 N680.
+    // Forcing the exponentials between the matrix instructions (scheduling groups) changed nothing.
     auto attend = [&](auto masked_tag, int key0, const unsigned char* sK, const unsigned char* sV) {
         constexpr bool MASKED = decltype(masked_tag)::value;
         // scores S^T[64 keys x 32 queries] = K . Q^T, two 32-key products
@@ -206,53 +205,75 @@ prefill_attn_kernel(PrefillParams p) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) s[kt][r] = 32 * kt + 8 * (r >> 2) + (r & 3) <= lim ? s[kt][r] : -INFINITY;
         }
-        float mx = s[0][0];
+        // The reference of a tile's probabilities is the maximum over the keys up to the end of that 32-key tile: they are
+        // rounded to bf16, and against the maximum over both tiles the largest of the first would not be exactly 1.
+        // (One reference for both is 2 ... 8 % faster -- 142 and 2310 us at the sizes above, 20.8 at H32 N680 -- but its
+        // error against fp64 was larger for each of 15 inputs, 1.4687e-3 -> 1.4718e-3 at N680, 1.6439e-3 -> 1.6492e-3 at
+        // N200.  Letting the maximum grow by 2^8 first: 1.5e-3 -> 1.7e-3.)
+        // Most stages of a long prompt move no query's maximum: that takes one look, before the two halves of a query
+        // exchange theirs.  Otherwise the output is rescaled in front of each tile that moves it.
+        float mx[NKT];
 #pragma unroll
-        for (int kt = 0; kt < NKT; ++kt)
+        for (int kt = 0; kt < NKT; ++kt) {
+            mx[kt] = s[kt][0];
 #pragma unroll
-            for (int r = kt == 0 ? 1 : 0; r + 1 < 16; r += 2) mx = fmaxf(fmaxf(mx, s[kt][r]), s[kt][r + 1]);
-        mx = fmaxf(mx, s[0][15]);
-        {
-            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-            mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * qs;
+            for (int r = 1; r + 1 < 16; r += 2) mx[kt] = fmaxf(fmaxf(mx[kt], s[kt][r]), s[kt][r + 1]);
+            mx[kt] = fmaxf(mx[kt], s[kt][15]);
         }
-        // the output is rescaled only when some query's running maximum moved.  (Letting the maximum grow by 2^8 first is
-        // 4 % faster, but the largest probability is then no longer exactly 1 and its rounding to bf16 adds up: error
-        // of the output against fp64 1.5e-3 -> 1.7e-3 at B4 H32/8 N8192.)
-        if (__builtin_amdgcn_ballot_w64(mx > m_run)) {
-            const float mnew = fmaxf(m_run, mx);
-            const float corr = mnew == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - mnew);
-            m_run = mnew;
-            l_run *= corr;
+        float mref[NKT], corr[NKT];
+        bool later = false;                                  // the second tile moves it
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt)
+        for (int kt = 0; kt < NKT; ++kt) { mref[kt] = m_run; corr[kt] = 1.f; }
+        if (__builtin_amdgcn_ballot_w64(fmaxf(mx[0], mx[1]) * qs > m_run)) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) o[dt][r] *= corr;
+            for (int kt = 0; kt < NKT; ++kt) {
+                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx[kt]), __float_as_uint(mx[kt]), false, false);
+                mref[kt] = fmaxf(m_run, fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * qs);
+                corr[kt] = mref[kt] == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - mref[kt]);
+                if (kt == 1) later = __builtin_amdgcn_ballot_w64(mref[kt] > m_run) != 0;
+                m_run = mref[kt];
+            }
+            if (__builtin_amdgcn_ballot_w64(corr[0] != 1.f)) {
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o[dt][r] *= corr[0];
+            }
         }
-        const float mref = m_run == -INFINITY ? 0.f : m_run;      // no finite score so far
 #pragma unroll
-        for (int kt = 0; kt < NKT; ++kt)
+        for (int kt = 0; kt < NKT; ++kt) {
+            const float ref = mref[kt] == -INFINITY ? 0.f : mref[kt];      // no finite score so far
+            bf16x8_t pf[2];
+            float psum = 0.f;
 #pragma unroll
             for (int sl = 0; sl < 2; ++sl) {
                 uint32_t pk[4];
-                float psum = 0.f;
 #pragma unroll
                 for (int e = 0; e < 8; e += 2) {
-                    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kt][8 * sl + e], qs, -mref));
-                    const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kt][8 * sl + e + 1], qs, -mref));
+                    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kt][8 * sl + e], qs, -ref));
+                    const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kt][8 * sl + e + 1], qs, -ref));
                     psum += p0 + p1;
                     pk[e / 2] = pack_bf16(p0, p1);
                 }
-                l_run += psum;
-                const bf16x8_t pf = __builtin_bit_cast(bf16x8_t, make_uint4(pk[0], pk[1], pk[2], pk[3]));
+                pf[sl] = __builtin_bit_cast(bf16x8_t, make_uint4(pk[0], pk[1], pk[2], pk[3]));
+            }
+            l_run = fmaf(l_run, corr[kt], psum);
+            if (kt == 1 && later) {
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o[dt][r] *= corr[kt];
+            }
+#pragma unroll
+            for (int sl = 0; sl < 2; ++sl)
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt) {
                     const unsigned char* sVs = sV + (32 * kt + 16 * sl) * ROWB;
                     const v4i16_t a0 = lds_read_tr(sVs + voff[dt][0]), a1 = lds_read_tr(sVs + voff[dt][1]);
                     const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
-                    o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf, o[dt], 0, 0, 0);
+                    o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[sl], o[dt], 0, 0, 0);
                 }
-            }
+        }
     };
     // Stages 0 .. 2*qb - 1 lie wholly in the past of every query of the workgroup; the last one or two hold the
     // diagonal.

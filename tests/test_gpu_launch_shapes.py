@@ -138,3 +138,28 @@ def test_importance_workspace_limits(N):
 def test_sort_merges(N):
     check_select(synthetic_importance(1, 3, N, seed=N, ties=True), max(4, N))
     check_select(synthetic_importance(1, 2, N, seed=N + 1), max(3, N // 2))
+
+
+# The probabilities of a 32-key tile are rounded to bf16 against the maximum over the keys up to the end of that tile.  Here
+# key 0 scores 0, key 32 of the same 64-key stage scores d > 0 and every other key e^-60 less: a query that sees both weighs
+# key 0 with exp(-d), in fp32, while its probability is exactly 1.  Values 1 and -bf16(exp(-d)) cancel but for the rounding
+# of exp(-d) to 8 bits, which a reference taken over both tiles would put into the probability: the result would be 0.
+def test_prefill_reference_per_tile():
+    N, D = 192, 64
+    d = torch.tensor([0.53125, 0.578125, 0.59375, 0.6875, 0.9375, 1.359375])      # exact in bf16
+    H = d.numel()
+    w = torch.exp(-d.double())
+    wb = w.to(torch.bfloat16).double()
+    want = (w - wb) / (1 + w)
+    assert (want.abs() > 6e-4).all()
+    q, k, v = (torch.zeros((1, 1, H, N, D), dtype=torch.float32) for _ in range(3))
+    q[..., 0] = 1
+    k[..., 0] = -60
+    k[0, 0, :, 0, 0] = 0
+    k[0, 0, :, 32, 0] = d
+    v[0, 0, :, 0, :] = 1
+    v[0, 0, :, 32, :] = -wb.float().view(H, 1)
+    out, _ = P.prefixkv_prefill_attn(*(x.to(torch.bfloat16).to(DEV) for x in (q, k, v)), torch.ones(1, device=DEV))
+    got = out[0, 0, :, 32:].cpu().double()
+    # one bf16 rounding of the result, and a few fp32 roundings of the two terms of order one
+    assert ((got - want.view(H, 1, 1)).abs() <= 2.0 ** -8 * want.abs().view(H, 1, 1) + 1e-6).all()
