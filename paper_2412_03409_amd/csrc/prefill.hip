@@ -186,6 +186,9 @@ prefill_attn_kernel(PrefillParams p) {
     // Forcing the exponentials between the matrix instructions (scheduling groups) changed nothing.
     auto attend = [&](auto masked_tag, int key0, const unsigned char* sK, const unsigned char* sV) {
         constexpr bool MASKED = decltype(masked_tag)::value;
+        // The second tile of the wavefront's own stage may lie wholly in its queries' future.  It is left out, so that no
+        // value in it -- infinite or NaN -- is multiplied by a probability of zero.
+        const bool second = !MASKED || key0 + 32 <= q0;
         // scores S^T[64 keys x 32 queries] = K . Q^T, two 32-key products
         f32x16_t s[NKT];
 #pragma unroll
@@ -242,6 +245,7 @@ prefill_attn_kernel(PrefillParams p) {
         }
 #pragma unroll
         for (int kt = 0; kt < NKT; ++kt) {
+            if (kt == 1 && !second) break;
             const float ref = mref[kt] == -INFINITY ? 0.f : mref[kt];      // no finite score so far
             bf16x8_t pf[2];
             float psum = 0.f;

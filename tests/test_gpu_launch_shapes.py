@@ -163,3 +163,20 @@ def test_prefill_reference_per_tile():
     got = out[0, 0, :, 32:].cpu().double()
     # one bf16 rounding of the result, and a few fp32 roundings of the two terms of order one
     assert ((got - want.view(H, 1, 1)).abs() <= 2.0 ** -8 * want.abs().view(H, 1, 1) + 1e-6).all()
+
+
+# Values in the future of a query do not reach it, whatever they are, unless they lie in its own 32-key tile (there they
+# meet a probability of zero).
+@pytest.mark.parametrize("N,D,rows", [(192, 128, (40, 97)), (192, 64, (32, 159)), (161, 128, (64, 160)), (300, 64, (224, 299))])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_prefill_non_finite_values(N, D, rows, bad):
+    q, k, scale = rand_qk(N, 1, 2, 3, 3, N, D, torch.bfloat16)
+    v = torch.randn(k.shape, generator=torch.Generator().manual_seed(N)).to(torch.bfloat16)
+    clean, _ = P.prefixkv_prefill_attn(q.to(DEV), k.to(DEV), v.to(DEV), scale.to(DEV))
+    for row in rows:
+        vb = v.clone()
+        vb[..., row, :] = bad
+        out, _ = P.prefixkv_prefill_attn(q.to(DEV), k.to(DEV), vb.to(DEV), scale.to(DEV))
+        first = row // 32 * 32
+        assert torch.equal(out[..., :first, :], clean[..., :first, :])
+        assert not torch.isfinite(out[..., row:, :]).any()
