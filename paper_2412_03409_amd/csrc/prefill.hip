@@ -107,7 +107,8 @@ prefill_attn_kernel(PrefillParams p) {
     // a negative logit scale is moved into the queries (negation is exact in bf16), so that the running
     // maximum can be taken on the raw products
     const float sc_l = p.scale[l];
-    const float qs = fmaxf(fabsf(sc_l) * kLog2e, 1e-30f);   // > 0: a masked -inf stays one
+    const float qs0 = fabsf(sc_l) * kLog2e;
+    const float qs = qs0 < 1e-30f ? 1e-30f : qs0;           // > 0, so that a masked -inf stays one; NaN stays NaN
     const uint32_t sgn = sc_l < 0.f ? 0x80008000u : 0u;
 
     // the queries: B operand of the score products, one fragment per 16 columns of the head dimension

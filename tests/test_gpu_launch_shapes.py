@@ -180,3 +180,13 @@ def test_prefill_non_finite_values(N, D, rows, bad):
         first = row // 32 * 32
         assert torch.equal(out[..., :first, :], clean[..., :first, :])
         assert not torch.isfinite(out[..., row:, :]).any()
+
+
+# A layer whose logit scale is NaN has no result; its neighbours do.
+@pytest.mark.parametrize("D", [64, 128])
+def test_prefill_nan_scale(D):
+    q, k, scale = rand_qk(D, 1, 3, 2, 1, 200, D, torch.bfloat16)
+    scale[1] = float("nan")
+    out, lse = P.prefixkv_prefill_attn(q.to(DEV), k.to(DEV), k.to(DEV), scale.to(DEV))
+    assert out[:, 1].isnan().all() and lse[:, 1].isnan().all()
+    assert out[:, ::2].isfinite().all() and lse[:, ::2].isfinite().all()
