@@ -83,6 +83,8 @@ size_t prefixkv_workspace_bytes(int op, const pkv_shape *shape, int has_lse);
  *       already has it from its prefill attention, or NULL: it is then computed here (a first sweep over
  *       the keys).
  *   importance [dev] fp32 [B,L,N], out (dense).
+ *   ws: the size query returns what gives the fastest form.  A call runs with one row, 4*B*L*H*N bytes
+ *       rounded up to 256, if lse is given or the prompt is bf16 of up to 768 positions, else with two.
  * bf16 inputs use bf16 MFMA with fp32 accumulation; exp and all sums are fp32. */
 int prefixkv_importance(const pkv_shape *shape, const void *q, pkv_strides qs, const void *k,
                         pkv_strides ks, const float *scale, const float *lse, float *importance,

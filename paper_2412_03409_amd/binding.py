@@ -18,6 +18,7 @@ _HERE = Path(__file__).resolve().parent
 _LIB_PATH = _HERE / "libprefixkv.so"
 
 PKV_F32, PKV_BF16 = 0, 1
+_ERR_WORKSPACE = 5   # PKV_ERR_WORKSPACE
 OP_IMPORTANCE, OP_SELECT, OP_COMPACT, OP_DECODE, OP_MERGE_FEATURE = 0, 1, 2, 3, 4
 
 
@@ -193,10 +194,13 @@ def prefixkv_importance(q: torch.Tensor, k: torch.Tensor, scale: torch.Tensor,
     s = _shape(B, L, H, Hkv, N, D, _dtype_code(q))
     if out is None:
         out = torch.empty((B, L, N), dtype=torch.float32, device=q.device)
-    nbytes = load().prefixkv_workspace_bytes(OP_IMPORTANCE, C.byref(s), int(lse is not None))
-    w = _ws(nbytes, q.device, ws)
+    # a workspace of the caller's may be smaller than the recommended one: the library says what it accepts
+    w = ws if ws is not None else _ws(load().prefixkv_workspace_bytes(OP_IMPORTANCE, C.byref(s), int(lse is not None)),
+                                      q.device, None)
     rc = load().prefixkv_importance(C.byref(s), _ptr(q), _strides5(q), _ptr(k), _strides5(k), _ptr(scale),
                                     _ptr(lse), _ptr(out), _ptr(w), w.numel() * w.element_size(), _stream())
+    if rc == _ERR_WORKSPACE:
+        raise ValueError("workspace too small")
     if rc != 0:
         raise PrefixKVError(rc, "prefixkv_importance")
     return out

@@ -820,27 +820,31 @@ constexpr int kFusedMaxN = 64 * kFusedWaves;
 // fused: 64 heads 32 / 48 us, 192: 54 / 53, 256: 67 / 58, 320: 81 / 100, 384: 97 / 101, 640: 145 / 149, 768: 170 / 157,
 // 1024: 240 / 213 -- fused when its rounds are nearly full.  Up to 256 positions one round of it is never slower
 // (64 heads of 100: 15.1 / 13.3 us, 256 of 200: 22.1 / 20.2).
-static bool fused_fits(const pkv_shape& s) {
+static bool fused_fits(const pkv_shape& s, long long cus) {
     if (s.N > kFusedMaxN) return false;
-    const long long heads = (long long)s.B * s.L * s.H, cus = compute_units();
+    const long long heads = (long long)s.B * s.L * s.H;
     const long long rounds = (heads + cus - 1) / cus;
     return rounds == 1 ? s.N <= 256 || heads * 4 >= cus * 3 : heads * 8 >= rounds * cus * 7;
 }
 
-// What a call accepts at least: a row of N floats per head and 768 positions (fp32 storage: one for the column sums and
-// one for a log-sum-exp that is not given).  The kernels use one or two rows per head.
-size_t importance_ws_min_bytes(const pkv_shape& s, bool has_lse) {
-    const size_t rows = (size_t)s.B * s.L * s.H * s.N * sizeof(float);
-    if (s.dtype == PKV_F32) return align_up(rows, 256) * (has_lse ? 1 : 2);
-    return align_up(rows * ((s.N + kFusedMaxN - 1) / kFusedMaxN), 256);
+// Rows of N floats per head that the kernels use: the column sums and, without a given log-sum-exp, the call's own behind
+// them.  Only the fused kernel keeps that to itself: a short bf16 prompt without room for it runs there.
+static size_t ws_rows_bytes(const pkv_shape& s, int rows) {
+    return align_up(rows * (size_t)s.B * s.L * s.H * s.N * sizeof(float), 256);
 }
-// The stream kernels without a given log-sum-exp put theirs behind the column sums; a short prompt whose workspace has no
-// room for it runs on the fused kernel.
-static size_t stream_ws_bytes(const pkv_shape& s) { return align_up(2 * (size_t)s.B * s.L * s.H * s.N * sizeof(float), 256); }
+static size_t stream_ws_bytes(const pkv_shape& s) { return ws_rows_bytes(s, 2); }
+// What a call accepts at least.
+size_t importance_ws_min_bytes(const pkv_shape& s, bool has_lse) {
+    if (s.dtype == PKV_F32) return ws_rows_bytes(s, 1) * (has_lse ? 1 : 2);
+    return has_lse || s.N <= kFusedMaxN ? ws_rows_bytes(s, 1) : stream_ws_bytes(s);
+}
+// What the size query returns: for bf16 one row per 768 positions, what earlier versions of the kernels used and callers
+// have sized by, or the stream kernels' two where they are the faster form for a short prompt.  The query knows no device:
+// it asks for the 256 compute units of the MI355X, and the launcher decides by those there are.
 size_t importance_ws_bytes(const pkv_shape& s, bool has_lse) {
-    const size_t least = importance_ws_min_bytes(s, has_lse);
-    if (has_lse || s.dtype == PKV_F32 || fused_fits(s)) return least;
-    return least > stream_ws_bytes(s) ? least : stream_ws_bytes(s);
+    if (s.dtype == PKV_F32) return importance_ws_min_bytes(s, has_lse);
+    if (s.N <= kFusedMaxN && !has_lse && !fused_fits(s, 256)) return stream_ws_bytes(s);
+    return ws_rows_bytes(s, (s.N + kFusedMaxN - 1) / kFusedMaxN);
 }
 
 template <int NK, int GS, bool COLS>
@@ -879,7 +883,7 @@ hipError_t launch_importance(const pkv_shape& s, const void* q, Strides qs, cons
         if (!lse && (e = launch_importance_f32<true>(s, p, st)) != hipSuccess) return e;
         p.lse_in = lse ? lse : lse_ws; p.out = partial;
         if ((e = launch_importance_f32<false>(s, p, st)) != hipSuccess) return e;
-    } else if (lse || (!fused_fits(s) && ws_bytes >= stream_ws_bytes(s))) {
+    } else if (lse || (!fused_fits(s, compute_units()) && ws_bytes >= stream_ws_bytes(s))) {
         StreamParams p;
         p.H = s.H; p.Hkv = s.Hkv; p.L = s.L; p.N = s.N; p.nheads = (long long)s.B * s.L * s.H;
         p.q = (const bf16_t*)q; p.qs = qs; p.k = (const bf16_t*)k; p.ks = ks; p.scale = scale;

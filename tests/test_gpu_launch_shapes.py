@@ -190,3 +190,30 @@ def test_prefill_nan_scale(D):
     out, lse = P.prefixkv_prefill_attn(q.to(DEV), k.to(DEV), k.to(DEV), scale.to(DEV))
     assert out[:, 1].isnan().all() and lse[:, 1].isnan().all()
     assert out[:, ::2].isfinite().all() and lse[:, ::2].isfinite().all()
+
+
+# prefixkv_importance takes every workspace that holds what its kernels use, through the Python entry point as well: one
+# sized for more layers, one sized for a given log-sum-exp (bf16, up to 768 positions), two rows for a long prompt.
+@pytest.mark.parametrize("N,dtype,sized_for", [
+    (680, torch.bfloat16, (32, False)), (680, torch.bfloat16, (2, True)), (300, torch.bfloat16, (2, False)),
+    (801, torch.bfloat16, (2, False)), (1537, torch.bfloat16, (2, False)), (120, torch.float32, (2, False)),
+])
+def test_importance_workspace_of_other_calls(N, dtype, sized_for):
+    B, L, H, D = 1, 2, 2, 64
+    q, k, scale = rand_qk(N, B, L, H, H, N, D, dtype)
+    want = oracle.importance(np32(q), np32(k), scale.numpy())
+    code = P.PKV_BF16 if dtype == torch.bfloat16 else P.PKV_F32
+    nbytes = P.prefixkv_workspace_bytes(0, B, sized_for[0], H, H, N, D, code, sized_for[1])
+    row, rows = ((r * 4 * B * L * H * N + 255) // 256 * 256 for r in (1, 2))
+    nbytes = min(nbytes, 2 * row)
+    guarded = torch.full((nbytes + 4096,), 0x5a, dtype=torch.uint8, device=DEV)
+    args = q.to(DEV), k.to(DEV), scale.to(DEV)
+    check_importance(np32(P.prefixkv_importance(*args, ws=guarded[:nbytes])), want)
+    assert (guarded[nbytes:] == 0x5a).all()
+    least = 2 * row if dtype == torch.float32 else row if N <= 768 else rows
+    check_importance(np32(P.prefixkv_importance(*args, ws=guarded[:least])), want)
+    assert (guarded[nbytes:] == 0x5a).all()
+    with pytest.raises(ValueError):
+        P.prefixkv_importance(*args, ws=guarded[:least - 256])
+    with pytest.raises(ValueError):
+        P.prefixkv_importance(*args, ws=guarded[:0])
