@@ -19,6 +19,7 @@
 // counted stores the new plain length, which also clears the count.  Between launches lens holds plain
 // lengths (< 2^20).  The ranking of the segments goes by capacity, which no launch changes.
 #include "pkv_common.hpp"
+#include "decode_rows.hpp"
 
 namespace pkv {
 
@@ -53,15 +54,6 @@ struct DecodeParams {
 
 constexpr int kRankRegs = 8;      // capacities per lane of a ranked launch: groups of up to 512 segments
 
-// Virtual row numbering of a segment under pruning: rows [0, perm) are the permanent slots, rows
-// perm + j are ring slot j (the last d+1 slots of the segment).  r_new is the row of the token stored
-// in this step, r_mask the row of a token pruned in this step (-1 if none).
-struct RingMap {
-    int shift;    // ring slot j is physical slot perm + j + shift
-    int r_new;
-    int r_mask;
-};
-
 // Cache rows are read once per decode step and never reused by the same launch: stream them past the
 // caches (nontemporal) so that they do not evict each other on the way in.
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
@@ -86,7 +78,7 @@ __device__ __forceinline__ void unpack16(const uint4& r, float* f) {
 // Rows r0 .. r0 + BR - 1 of one block (BR = NI * 64/LPR; LPR lanes cover a row with 16 bytes each) into registers.
 // Blocks of occupied cache slots only take the plain path.  In the guarded one the row being appended comes from
 // k_new / v_new, under pruning ring rows map to the ring slots, and rows that do not take part (past the end, or
-// pruned in this step) are read from the block's first slot and ignored by attend_block: every load is issued
+// pruned in this step) are read like the block's first row and ignored by attend_block: every load is issued
 // without a branch.
 template <int LPR, int NI, bool EV>
 __device__ __forceinline__ void load_block(uint4 (&kr)[NI], uint4 (&vr)[NI], int r0, int len, int len_old, bool app,
@@ -105,18 +97,10 @@ __device__ __forceinline__ void load_block(uint4 (&kr)[NI], uint4 (&vr)[NI], int
     } else {
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-            const int r = r0 + i * RPI + rg;
-            int slot = r;
-            bool valid = r < len, isnew = app && r == len_old;
-            if constexpr (EV) {
-                valid = valid && r != ring.r_mask;
-                isnew = valid && r == ring.r_new;
-                slot = r >= len_old ? r + ring.shift : r;
-            }
-            slot = valid ? slot : (EV && r0 >= len_old ? r0 + ring.shift : r0);
-            const uint32_t o_i = (uint32_t)slot * (uint32_t)row_bytes + (uint32_t)sub * 16u;
-            kr[i] = load_stream16(isnew ? knew + sub * 16 : kseg + o_i);
-            vr[i] = load_stream16(isnew ? vnew + sub * 16 : vseg + o_i);
+            const RowSource s = row_source<EV>(r0 + i * RPI + rg, r0, len, len_old, app, ring);
+            const uint32_t o_i = (uint32_t)s.slot * (uint32_t)row_bytes + (uint32_t)sub * 16u;
+            kr[i] = load_stream16(s.from_new ? knew + sub * 16 : kseg + o_i);
+            vr[i] = load_stream16(s.from_new ? vnew + sub * 16 : vseg + o_i);
         }
     }
 }
