@@ -150,9 +150,10 @@ __device__ __forceinline__ void attend_block(const uint4 (&kr)[NI], uint4 (&vr)[
         for (int i = 1; i < NI; ++i) mx = fmaxf(mx, s[g][i]);
 #pragma unroll
         for (int sh = LPR; sh < kWave; sh <<= 1) mx = fmaxf(mx, __shfl_xor(mx, sh, kWave));
-        // r0 < len: some row is valid and mx finite, unless the only one is the row pruned in this step
+        // no score above -inf so far: all keys of the wavefront's blocks are that far off, or the only row of the first
+        // one is pruned in this step
         const float mnew = fmaxf(mrun[g], mx);
-        const float mref = EV && mnew == -INFINITY ? 0.f : mnew;
+        const float mref = mnew == -INFINITY ? 0.f : mnew;
         const float corr = __builtin_amdgcn_exp2f(mrun[g] - mref);  // 0 on the first block
         mrun[g] = mnew;
         srun[g] *= corr;

@@ -217,3 +217,32 @@ def test_importance_workspace_of_other_calls(N, dtype, sized_for):
         P.prefixkv_importance(*args, ws=guarded[:least - 256])
     with pytest.raises(ValueError):
         P.prefixkv_importance(*args, ws=guarded[:0])
+
+
+# Keys that score -inf weigh nothing, also where they fill the blocks a wavefront starts with (16 rows at D = 128 in bf16,
+# 8 in fp32): with 8 and 4 wavefronts per unit and in the ranked launches.
+@pytest.mark.parametrize("B,L,H,D,dtype,distance", [
+    (1, 2, 2, 128, torch.bfloat16, 0), (1, 2, 2, 64, torch.float32, 0), (1, 18, 32, 128, torch.bfloat16, 0),
+    (2, 18, 32, 128, torch.bfloat16, 0), (1, 2, 2, 128, torch.bfloat16, 3), (2, 18, 32, 64, torch.bfloat16, 3),
+])
+def test_decode_keys_at_minus_infinity(B, L, H, D, dtype, distance):
+    N, inf_rows = 90, [*range(0, 33), *range(48, 64)]
+    g = torch.Generator().manual_seed(B * L + D)
+    k = torch.randn((B, L, H, N, D), generator=g).abs()
+    k[:, :, :, inf_rows] = -float("inf")
+    v, kn, vn = (torch.randn((B, L, H, n, D), generator=g).to(dtype) for n in (N, 1, 1))
+    q = (torch.randn((B, L, H, D), generator=g).abs() + 0.1).to(dtype)
+    k, scale = k.to(dtype), torch.full((L,), D ** -0.5)
+    order = torch.arange(N, dtype=torch.int32).expand(B, L, N).contiguous().to(DEV)
+    lengths = torch.full((B, L), N, dtype=torch.int32, device=DEV)
+    cap = 1 + 2 * distance
+    cache = P.prefixkv_compact(k.to(DEV), v.to(DEV), order, lengths, cap, B * L * (N + cap))
+    new = kn[:, :, :, 0].contiguous().to(DEV), vn[:, :, :, 0].contiguous().to(DEV)
+    if distance:
+        out = P.prefixkv_decode_attn_evict(cache, lengths, q.to(DEV), *new, scale.to(DEV), N, 1, distance)
+    else:
+        out = P.prefixkv_decode_attn(cache, q.to(DEV), *new, scale.to(DEV), N)
+    keys = torch.cat([k, kn], 3).double()
+    s = (keys * q.double().unsqueeze(3)).sum(-1) * D ** -0.5
+    want = (torch.softmax(s, -1).unsqueeze(-1) * torch.cat([v, vn], 3).double()).sum(3)
+    assert (out.cpu().double() - want).abs().max() <= OUT_ATOL
