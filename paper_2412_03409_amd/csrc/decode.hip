@@ -47,9 +47,7 @@ struct DecodeParams {
     // work list of the grouped-query kernel (see decode_plan_kernel)
     int G, n_seg, S0, pieces_cap, record_word, partial_word;
     int* plan;
-    // ranked launches of decode_attn_kernel (n_seg above): segments per group, and how many of the longest ones get
-    // four and two wavefronts per unit
-    int gsz, n4, n2;
+    RankedShape rank;   // ranked launches of decode_attn_kernel
 };
 
 constexpr int kRankRegs = 8;      // capacities per lane of a ranked launch: groups of up to 512 segments
@@ -228,25 +226,17 @@ decode_attn_kernel(DecodeParams p) {
     const int HU = p.H / G;                      // units per segment
     const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     int UW = W, hu, i_seg;
+    bool live = true;
     if constexpr (RANK > 0) {
-        // groups of p.gsz segments; in each the p.n4 longest get four wavefronts per unit, the next p.n2 two and
-        // the others one
         static_assert(W == 4, "a workgroup holds one, two or four units");
-        const int w2 = (HU + 1) / 2, w1 = (HU + 3) / 4;
-        const int bpg = p.n4 * HU + p.n2 * w2 + (p.gsz - p.n4 - p.n2) * w1;
-        const int grp = blockIdx.x / bpg;
-        int j = blockIdx.x - grp * bpg;
-        const int first = grp * p.gsz, n = min(p.gsz, p.n_seg - first);
-        int r;
-        if (j < p.n4 * HU) { r = j / HU; hu = j - r * HU; }
-        else if ((j -= p.n4 * HU) < p.n2 * w2) { r = j / w2; hu = 2 * (j - r * w2) + wv / 2; r += p.n4; UW = 2; }
-        else { j -= p.n2 * w2; r = j / w1; hu = 4 * (j - r * w1) + wv; r += p.n4 + p.n2; UW = 1; }
-        if (r >= n) return;
-        i_seg = first + ranked_segment<RANK>(p.caps, n, p.nl, p.L, p.l0, first, r, lane);
+        const RankedUnit x = ranked_unit(blockIdx.x, wv, p.rank, HU, p.n_seg);
+        UW = x.UW; hu = x.hu; live = x.live;
+        if (!live && UW != 2) return;                      // no barrier ahead, or the whole workgroup has none
+        i_seg = 0;
+        if (live) i_seg = x.first + ranked_segment<RANK>(p.caps, x.n, p.nl, p.L, p.l0, x.first, x.rank, lane);
     } else {
         hu = blockIdx.x % HU; i_seg = blockIdx.x / HU;
     }
-    const bool live = hu < HU;
     const int uw = wv & (UW - 1);
     const int b = i_seg / p.nl, l = p.l0 + i_seg % p.nl, sl = b * p.L + l;
     const int sub = lane % LPR, rg = lane / LPR;
@@ -350,7 +340,7 @@ decode_attn_kernel(DecodeParams p) {
             *(uint4*)(kseg + (size_t)len_old * row_bytes + sub * 16) = *(const uint4*)src_k;
             *(uint4*)(vseg + (size_t)len_old * row_bytes + sub * 16) = *(const uint4*)src_v;
         }
-        if (p.kept_pos && app && hu == 0 && uw == 0 && lane == 0) {
+        if (p.kept_pos && app && live && hu == 0 && uw == 0 && lane == 0) {
             int32_t* kp = p.kept_pos + off;
             kp[ring0 + (p.t - 1) % (p.d + 1)] = p.N + p.t - 1;
             if (decide) {
@@ -918,7 +908,7 @@ int compute_units() {
 // four wavefronts each, 173 us with one, for rows that stream in 150 us).  Hence
 //   up to 2 units per compute unit: 8 wavefronts per unit (32 units, one layer of the 7B shape: 8.6 -> 6.1 us);
 //   up to 4: 4 wavefronts per unit, which fill the chip (7B, batch 1: 21.0 -> 18.5 us);
-//   beyond: one wavefront per unit, four units of a segment per workgroup, the longest segments first.  The lengths
+//   beyond: one wavefront per unit, four units per workgroup, the longest segments first.  The lengths
 //       differ by up to two orders of magnitude, and in index order the launch ends with a few long segments on a
 //       chip that is otherwise empty: 13B, batch 8: 253 -> 173 us with the ranking.  Up to two rounds of wavefronts
 //       the longest segment alone is a sizeable part of the launch, so the longest eighth of the segments gets four
@@ -940,11 +930,10 @@ static hipError_t launch_decode_s(DecodeParams p, int nblk, hipStream_t st) {
         return hipGetLastError();
     }
     const int ngrp = (p.n_seg + kRankRegs * kWave - 1) / (kRankRegs * kWave);
-    p.gsz = (p.n_seg + ngrp - 1) / ngrp;
-    p.n4 = p.n2 = nblk <= 2 * 16 * cus ? p.gsz / 8 : 0;
-    const int per_group = p.n4 * HU + p.n2 * ((HU + 1) / 2) + (p.gsz - p.n4 - p.n2) * ((HU + 3) / 4);
-    const dim3 grid(per_group * ngrp), block(4 * kWave);
-    if (p.gsz <= kWave) hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, 1>), grid, block, 0, st, p);
+    p.rank.gsz = (p.n_seg + ngrp - 1) / ngrp;
+    p.rank.n4 = p.rank.n2 = nblk <= 2 * 16 * cus ? p.rank.gsz / 8 : 0;
+    const dim3 grid(ranked_blocks(p.rank, HU) * ngrp), block(4 * kWave);
+    if (p.rank.gsz <= kWave) hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, 1>), grid, block, 0, st, p);
     else hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, kRankRegs>), grid, block, 0, st, p);
     return hipGetLastError();
 }
@@ -1045,7 +1034,7 @@ static DecodeParams make_params(const pkv_shape& s, int l0, int l1, const void* 
     p.lens = lens; p.out = (unsigned char*)out;
     p.N = s.N; p.t = 0; p.d = 0; p.base_lens = nullptr; p.kept_pos = nullptr;
     p.G = 1; p.n_seg = 0; p.S0 = 0; p.pieces_cap = 0; p.record_word = 0; p.partial_word = 0; p.plan = nullptr;
-    p.gsz = 0; p.n4 = 0; p.n2 = 0;
+    p.rank = RankedShape{0, 0, 0};
     return p;
 }
 

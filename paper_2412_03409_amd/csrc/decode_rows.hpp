@@ -1,5 +1,5 @@
-// Where the rows of a segment come from in one decode step.  Plain integer rules, apart from the kernels so that they can
-// be compiled and enumerated on the host.
+// Where the rows of a segment come from in one decode step, and which unit a wavefront of a ranked launch works on.  Plain
+// integer rules, apart from the kernels so that they can be compiled and enumerated on the host.
 #pragma once
 
 namespace pkv {
@@ -30,6 +30,39 @@ __device__ __forceinline__ RowSource row_source(int r, int r0, int len, int len_
     s.from_new = EV ? x == ring.r_new : app && x == len_old;
     s.slot = EV && x >= len_old ? x + ring.shift : x;
     return s;
+}
+
+// Ranked launches: the segments are cut into groups of gsz; in each the units (HU per segment) of the n4 longest get four
+// wavefronts, those of the next n2 two and the others one.  Workgroups of four wavefronts; the units of a class follow each
+// other without gaps, so a workgroup may hold units of two segments, and the last of a class fewer than fit.
+struct RankedShape { int gsz, n4, n2; };
+
+__host__ __device__ __forceinline__ int ranked_blocks(const RankedShape& s, int HU) {   // per group
+    return s.n4 * HU + (s.n2 * HU + 1) / 2 + ((s.gsz - s.n4 - s.n2) * HU + 3) / 4;
+}
+
+struct RankedUnit {
+    bool live;       // the wavefront has a unit
+    int UW;          // wavefronts that share it (the same for the whole workgroup)
+    int first, n;    // the group's first segment and number of segments
+    int rank, hu;    // which of them, longest first, and which unit of it
+};
+
+__device__ __forceinline__ RankedUnit ranked_unit(int block, int wv, const RankedShape& s, int HU, int n_seg) {
+    RankedUnit x;
+    const int b4 = s.n4 * HU, b2 = (s.n2 * HU + 1) / 2, bpg = ranked_blocks(s, HU);
+    const int grp = block / bpg, j = block - grp * bpg;
+    int r0, nc, u;                                        // the class's first rank and segments, the unit in it
+    if (j < b4) { x.UW = 4; r0 = 0; nc = s.n4; u = j; }
+    else if (j < b4 + b2) { x.UW = 2; r0 = s.n4; nc = s.n2; u = 2 * (j - b4) + wv / 2; }
+    else { x.UW = 1; r0 = s.n4 + s.n2; nc = s.gsz - r0; u = 4 * (j - b4 - b2) + wv; }
+    x.first = grp * s.gsz;
+    x.n = n_seg - x.first < s.gsz ? n_seg - x.first : s.gsz;
+    const int r = u / HU;
+    x.hu = u - r * HU;
+    x.rank = r0 + r;
+    x.live = r < nc && x.rank < x.n;
+    return x;
 }
 
 }  // namespace pkv

@@ -1,5 +1,6 @@
-"""Where the rows of a decode step come from (csrc/decode_rows.hpp, compiled for the host): every row that takes part has
-its own source, and no row, taking part or not, is read from a slot that the step writes or that holds nothing."""
+"""csrc/decode_rows.hpp, compiled for the host.  Where the rows of a decode step come from: every row that takes part has
+its own source, and no row, taking part or not, is read from a slot that the step writes or that holds nothing.  Ranked
+launches: every unit of every segment has its wavefronts exactly once."""
 import ctypes as C
 import os
 import subprocess
@@ -9,6 +10,7 @@ import pytest
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2412_03409_amd", "csrc")
 SHIM = """
 #define __device__
+#define __host__
 #define __forceinline__ inline
 #include "decode_rows.hpp"
 extern "C" int row(int ev, int r, int r0, int len, int len_old, int app, int shift, int r_new, int r_mask) {
@@ -17,16 +19,27 @@ extern "C" int row(int ev, int r, int r0, int len, int len_old, int app, int shi
                                 : pkv::row_source<false>(r, r0, len, len_old, app, ring);
     return s.slot * 4 + s.from_new * 2 + s.valid;
 }
+extern "C" void unit(int block, int wv, int gsz, int n4, int n2, int HU, int n_seg, int* out) {
+    const pkv::RankedShape s = {gsz, n4, n2};
+    const pkv::RankedUnit x = pkv::ranked_unit(block, wv, s, HU, n_seg);
+    const int v[7] = {x.live, x.UW, x.first, x.n, x.rank, x.hu, pkv::ranked_blocks(s, HU)};
+    for (int i = 0; i < 7; ++i) out[i] = v[i];
+}
 """
 
 
 @pytest.fixture(scope="module")
-def row(tmp_path_factory):
+def shim(tmp_path_factory):
     d = tmp_path_factory.mktemp("rows")
     (d / "shim.cpp").write_text(SHIM)
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cpp"), "-o",
                            str(d / "shim.so")])
-    f = C.CDLL(str(d / "shim.so")).row
+    return C.CDLL(str(d / "shim.so"))
+
+
+@pytest.fixture(scope="module")
+def row(shim):
+    f = shim.row
 
     def call(*a):
         x = f(*map(int, a))
@@ -75,3 +88,37 @@ def test_pruning_step(row, block, d):
                             if not new:
                                 assert 0 <= slot < perm or ring0 <= slot < ring0 + held
                                 assert slot not in written, (base, t, perm, grad, r0, r)
+
+
+@pytest.mark.parametrize("HU", [1, 2, 3, 4, 5, 6, 7, 32, 41])
+@pytest.mark.parametrize("n_seg,gsz,n4,n2", [
+    (33, 33, 4, 4), (7, 7, 0, 0), (9, 9, 1, 8), (64, 64, 64, 0), (65, 65, 0, 65), (70, 35, 5, 3), (71, 36, 1, 1),
+    (540, 270, 33, 33), (1037, 346, 43, 43), (13, 4, 2, 1), (5, 2, 0, 1), (1030, 344, 0, 0),
+])
+def test_ranked_units(shim, HU, n_seg, gsz, n4, n2):
+    out = (C.c_int * 7)()
+    groups = (n_seg + gsz - 1) // gsz
+    shim.unit(0, 0, gsz, n4, n2, HU, n_seg, out)
+    seen, without = {}, 0
+    for block in range(out[6] * groups):
+        uws, lives = set(), []
+        for wv in range(4):
+            shim.unit(block, wv, gsz, n4, n2, HU, n_seg, out)
+            live, UW, first, n, rank, hu, _ = out
+            uws.add(UW)
+            lives.append(bool(live))
+            without += not live and block < out[6] and n_seg >= gsz
+            if live:
+                assert 0 <= hu < HU and 0 <= rank < n <= gsz and first + n <= n_seg and first % gsz == 0
+                assert UW == (4 if rank < n4 else 2 if rank < n4 + n2 else 1)
+                seen.setdefault((first, rank, hu), []).append((block, wv))
+        assert len(uws) == 1
+        UW = uws.pop()      # the wavefronts of a unit agree, so a workgroup of one unit may leave as a whole
+        assert all(len(set(lives[i:i + UW])) == 1 for i in range(0, 4, UW))
+    assert len(seen) == n_seg * HU
+    assert without <= 2 + 3      # wavefronts of a full group without a unit: at most the last workgroups of two classes
+    for (first, rank, hu), who in seen.items():
+        UW = 4 if rank < n4 else 2 if rank < n4 + n2 else 1
+        assert len(who) == UW and len({b for b, _ in who}) == 1
+        assert sorted(w & (UW - 1) for _, w in who) == list(range(UW))
+        assert len({w & ~(UW - 1) for _, w in who}) == 1

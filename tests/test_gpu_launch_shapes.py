@@ -13,8 +13,9 @@ from tolerances import LSE_ATOL, LSE_RTOL
 pytestmark = pytest.mark.gpu
 
 
-# decode_attn_kernel: 8 wavefronts per unit up to 512 units, 4 up to 1024, ranked launches beyond (one to four units
-# per workgroup), one capacity register per lane up to 64 segments of a launch, groups of segments beyond 512
+# decode_attn_kernel on 256 compute units: 8 wavefronts per unit up to 512 units, 4 up to 1024, ranked launches beyond (one,
+# two or four units per workgroup), one capacity register per lane up to 64 segments of a launch, groups of segments
+# beyond 512
 @pytest.mark.parametrize("B,L,H,Hkv,N,D,dtype,frac,steps,layers", [
     (1, 16, 32, 32, 150, 64, torch.bfloat16, 0.4, 2, None),     # 512 units
     (1, 19, 27, 27, 60, 64, torch.bfloat16, 0.4, 2, None),      # 513
@@ -246,3 +247,29 @@ def test_decode_keys_at_minus_infinity(B, L, H, D, dtype, distance):
     s = (keys * q.double().unsqueeze(3)).sum(-1) * D ** -0.5
     want = (torch.softmax(s, -1).unsqueeze(-1) * torch.cat([v, vn], 3).double()).sum(3)
     assert (out.cpu().double() - want).abs().max() <= OUT_ATOL
+
+
+# Ranked launches of heads that do not fill workgroups of four, so that these hold units of two segments; all three classes
+# of segments, none, and the index order of many short units; groups of 2, 4 and 8 query heads in fp32.
+@pytest.mark.parametrize("B,L,H,Hkv,N,D,dtype,frac,steps,layers", [
+    (1, 50, 27, 27, 60, 64, torch.bfloat16, 0.4, 2, None),      # 1350 units: a quarter with four wavefronts, the others two
+    (4, 23, 21, 21, 90, 128, torch.bfloat16, 0.4, 2, (1, 22)),  # 1764: an eighth with four and two each, 84 segments
+    (7, 60, 7, 7, 60, 128, torch.bfloat16, 0.5, 2, None),       # 2940 units of 420 segments
+    (33, 64, 1, 1, 40, 128, torch.bfloat16, 0.5, 1, None),      # one head: 2112 segments in five groups
+    (12, 64, 6, 6, 30, 64, torch.bfloat16, 0.5, 1, None),       # 4608 units: index order
+    (6, 60, 6, 3, 40, 64, torch.float32, 0.5, 2, None),         # fp32, groups of 2
+    (9, 50, 12, 3, 40, 64, torch.float32, 0.5, 2, None),        # groups of 4
+    (10, 40, 24, 3, 40, 128, torch.float32, 0.5, 1, None),      # groups of 8
+    (2, 32, 160, 20, 60, 64, torch.float32, 0.4, 2, None),      # groups of 8, 64 segments
+])
+def test_decode_ranked_classes(B, L, H, Hkv, N, D, dtype, frac, steps, layers):
+    run_decode_case(B, L, H, Hkv, N, D, dtype, frac, steps, seed=B * L + H, layer_range=layers)
+
+
+@pytest.mark.parametrize("B,L,H,Hkv,N,D,dtype,frac,d,steps", [
+    (2, 32, 18, 18, 40, 64, torch.bfloat16, 0.5, 2, 6),         # 1152 units of 64 segments
+    (2, 32, 33, 33, 30, 128, torch.bfloat16, 0.5, 3, 7),        # 2112: one, two and four wavefronts per unit
+    (8, 40, 14, 7, 24, 64, torch.float32, 0.5, 2, 5),           # fp32, groups of 2: 2240 units of 320 segments
+])
+def test_decode_evict_ranked_classes(B, L, H, Hkv, N, D, dtype, frac, d, steps):
+    run_evict_case(B, L, H, Hkv, N, D, dtype, frac, d, steps, seed=B * L + H)
