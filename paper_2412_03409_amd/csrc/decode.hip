@@ -173,40 +173,53 @@ __device__ __forceinline__ void attend_block(const uint4 (&kr)[NI], uint4 (&vr)[
     }
 }
 
-// The segment of rank `r` when the n segments are ordered by capacity, largest first (equal ones by index): found
-// by every wavefront for itself, with a radix selection on ballots.  n <= 64 * PER.
+// Maximum over the wavefront.
+__device__ __forceinline__ int wave_max(int x) {
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, true));    // quad_perm [1,0,3,2]
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, true));    // quad_perm [2,3,0,1]
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x124, 0xF, 0xF, true));   // row_ror:4
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, true));   // row_ror:8
+    const auto h = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = max((int)h[0], (int)h[1]);
+    const auto w = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return __builtin_amdgcn_readfirstlane(max((int)w[0], (int)w[1]));
+}
+
+// The segment of rank `r` when the n segments are ordered by length class, longest first, and by index inside a class:
+// found by every wavefront for itself.  A class is a quarter octave of capacity below the largest one, the last of sixteen
+// holds everything shorter than a thirteenth of it: enough to start the long segments early, at four ballots per 64
+// segments.  (The exact order takes a ballot for every bit of the capacities: 1 ... 2 us at the start of every unit, which
+// short units do not earn back.)  n <= 64 * PER.
 template <int PER>
 __device__ __forceinline__ int ranked_segment(const int32_t* __restrict__ caps, int n, int nl, int L, int l0, int first, int r, int lane) {
     int c[PER];
-    int any = 0;
+    int top = 0;
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         const int i = u * kWave + lane;
-        c[u] = -1;
+        c[u] = 0;
         if (i < n) { const int j = first + i; c[u] = caps[nl == L ? j : (j / nl) * L + l0 + j % nl] & kLenMask; }
-        any |= c[u] < 0 ? 0 : c[u];
+        top = max(top, c[u]);
     }
-    int prefix = 0, left = r;               // the value found so far (high bits), rank among those that share it
-    for (int bit = kLenBits - 1; bit >= 0; --bit) {
-        if (__builtin_amdgcn_ballot_w64((any >> bit) & 1) == 0) continue;
-        const int want = prefix | (1 << bit);
+    top = wave_max(top);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) c[u] = u * kWave + lane < n ? length_class(c[u], top) : kLengthClasses;
+    int cls = 0, left = r;                  // the class found so far (high bits), rank among those that share it
+#pragma unroll
+    for (int half = kLengthClasses / 2; half >= 1; half >>= 1) {
         int cnt = 0;
 #pragma unroll
-        for (int u = 0; u < PER; ++u)
-            cnt += __builtin_popcountll(__builtin_amdgcn_ballot_w64(c[u] >= 0 && (c[u] >> bit) == (want >> bit)));
-        if (left < cnt) prefix = want; else left -= cnt;
+        for (int u = 0; u < PER; ++u) cnt += __builtin_popcountll(__builtin_amdgcn_ballot_w64((c[u] & -half) == cls));
+        if (left >= cnt) { left -= cnt; cls |= half; }
     }
     int found = 0;
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-        const unsigned long long m = __builtin_amdgcn_ballot_w64(c[u] == prefix);
-        const int cnt = __builtin_popcountll(m);
-        if (left >= 0 && left < cnt) {
-            unsigned long long x = m;
-            for (int k = 0; k < left; ++k) x &= x - 1;
-            found = u * kWave + __builtin_ctzll(x);
-        }
-        left -= cnt;
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(c[u] == cls);
+        const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+        const unsigned long long hit = __builtin_amdgcn_ballot_w64(c[u] == cls && before == left);
+        if (hit) found = u * kWave + __builtin_ctzll(hit);
+        left -= __builtin_popcountll(m);
     }
     return found;
 }

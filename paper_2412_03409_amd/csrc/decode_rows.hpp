@@ -41,6 +41,14 @@ __host__ __device__ __forceinline__ int ranked_blocks(const RankedShape& s, int 
     return s.n4 * HU + (s.n2 * HU + 1) / 2 + ((s.gsz - s.n4 - s.n2) * HU + 3) / 4;
 }
 
+// Length class of a segment: quarter octaves of its capacity below that of the longest one, the last class open.
+constexpr int kLengthClasses = 16;
+__host__ __device__ __forceinline__ int length_class(int cap, int longest) {
+    const auto quarters = [](int x) { return (int)(__builtin_bit_cast(unsigned, (float)x) >> 21); };   // exponent, two bits
+    const int d = quarters(longest) - quarters(cap);
+    return d < kLengthClasses - 1 ? d : kLengthClasses - 1;
+}
+
 struct RankedUnit {
     bool live;       // the wavefront has a unit
     int UW;          // wavefronts that share it (the same for the whole workgroup)

@@ -25,6 +25,7 @@ extern "C" void unit(int block, int wv, int gsz, int n4, int n2, int HU, int n_s
     const int v[7] = {x.live, x.UW, x.first, x.n, x.rank, x.hu, pkv::ranked_blocks(s, HU)};
     for (int i = 0; i < 7; ++i) out[i] = v[i];
 }
+extern "C" int length_class(int cap, int longest) { return pkv::length_class(cap, longest); }
 """
 
 
@@ -122,3 +123,13 @@ def test_ranked_units(shim, HU, n_seg, gsz, n4, n2):
         assert len(who) == UW and len({b for b, _ in who}) == 1
         assert sorted(w & (UW - 1) for _, w in who) == list(range(UW))
         assert len({w & ~(UW - 1) for _, w in who}) == 1
+
+
+def test_length_classes(shim):
+    for longest in (1, 2, 3, 100, 8192, (1 << 20) - 1):
+        last = 15
+        for cap in range(0, longest + 1, max(1, longest // 3000)):
+            c = shim.length_class(cap, longest)
+            assert 0 <= c <= last
+            last = c
+        assert shim.length_class(longest, longest) == 0
