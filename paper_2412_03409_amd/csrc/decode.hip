@@ -246,7 +246,7 @@ decode_attn_kernel(DecodeParams p) {
         UW = x.UW; hu = x.hu; live = x.live;
         if (!live && UW != 2) return;                      // no barrier ahead, or the whole workgroup has none
         i_seg = 0;
-        if (live) i_seg = x.first + ranked_segment<RANK>(p.caps, x.n, p.nl, p.L, p.l0, x.first, x.rank, lane);
+        if (live) i_seg = x.first + (p.rank.by_length ? ranked_segment<RANK>(p.caps, x.n, p.nl, p.L, p.l0, x.first, x.rank, lane) : x.rank);
     } else {
         hu = blockIdx.x % HU; i_seg = blockIdx.x / HU;
     }
@@ -921,11 +921,9 @@ int compute_units() {
 // four wavefronts each, 173 us with one, for rows that stream in 150 us).  Hence
 //   up to 2 units per compute unit: 8 wavefronts per unit (32 units, one layer of the 7B shape: 8.6 -> 6.1 us);
 //   up to 4: 4 wavefronts per unit, which fill the chip (7B, batch 1: 21.0 -> 18.5 us);
-//   beyond: one wavefront per unit, four units per workgroup, the longest segments first.  The lengths
-//       differ by up to two orders of magnitude, and in index order the launch ends with a few long segments on a
-//       chip that is otherwise empty: 13B, batch 8: 253 -> 173 us with the ranking.  Up to two rounds of wavefronts
-//       the longest segment alone is a sizeable part of the launch, so the longest eighth of the segments gets four
-//       wavefronts per unit and the next eighth two (7B, batch 2: 46.5 -> 33.5 us; one wavefront each: 55 us).
+//   beyond: one, two or four wavefronts per unit, the longest segments first (see ranked_shape).  The lengths differ by up
+//       to two orders of magnitude, and in index order the launch ends with a few long segments on a chip that is
+//       otherwise empty.
 // Four row loads of K and of V in flight per wavefront; the next block is not requested ahead of the work on this
 // one (that costs 22 registers and gains nothing: the other three wavefronts of the SIMD fill the gap).
 template <bool BF16, int LPR, int G, bool EV>
@@ -944,7 +942,7 @@ static hipError_t launch_decode_s(DecodeParams p, int nblk, hipStream_t st) {
     }
     const int ngrp = (p.n_seg + kRankRegs * kWave - 1) / (kRankRegs * kWave);
     p.rank.gsz = (p.n_seg + ngrp - 1) / ngrp;
-    p.rank.n4 = p.rank.n2 = nblk <= 2 * 16 * cus ? p.rank.gsz / 8 : 0;
+    ranked_shape(p.rank, nblk, cus, p.N, p.D * (BF16 ? 2 : 4));
     const dim3 grid(ranked_blocks(p.rank, HU) * ngrp), block(4 * kWave);
     if (p.rank.gsz <= kWave) hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, 1>), grid, block, 0, st, p);
     else hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, kRankRegs>), grid, block, 0, st, p);
@@ -1047,7 +1045,7 @@ static DecodeParams make_params(const pkv_shape& s, int l0, int l1, const void* 
     p.lens = lens; p.out = (unsigned char*)out;
     p.N = s.N; p.t = 0; p.d = 0; p.base_lens = nullptr; p.kept_pos = nullptr;
     p.G = 1; p.n_seg = 0; p.S0 = 0; p.pieces_cap = 0; p.record_word = 0; p.partial_word = 0; p.plan = nullptr;
-    p.rank = RankedShape{0, 0, 0};
+    p.rank = RankedShape{0, 0, 0, false};
     return p;
 }
 

@@ -33,9 +33,41 @@ __device__ __forceinline__ RowSource row_source(int r, int r0, int len, int len_
 }
 
 // Ranked launches: the segments are cut into groups of gsz; in each the units (HU per segment) of the n4 longest get four
-// wavefronts, those of the next n2 two and the others one.  Workgroups of four wavefronts; the units of a class follow each
-// other without gaps, so a workgroup may hold units of two segments, and the last of a class fewer than fit.
-struct RankedShape { int gsz, n4, n2; };
+// wavefronts, those of the next n2 two and the others one; `by_length` false: in index order instead.  Workgroups of four
+// wavefronts; the units of a class follow each other without gaps, so a workgroup may hold units of two segments, and the
+// last of a class fewer than fit.
+struct RankedShape { int gsz, n4, n2; bool by_length; };
+
+// The shape of a launch of `units` units (more than four per compute unit) on `cus` compute units, N prompt positions with
+// rows of row_bytes, gsz given.  A compute unit holds 16 wavefronts, and what a launch loses most on is a second round that is nearly empty.  Times
+// against a launch of two wavefronts per unit in index order, 256 compute units, bf16, D 128; lengths of the segments equal /
+// within a factor 3 / within a factor 30:
+//   as long as a quarter of the units with four wavefronts and the others with two fit one round, that: 1280 units of 136
+//     rows on average x1.00 / 1.03 / 1.25, of 410 x0.98 / 1.06 / 1.32, of 1638 x1.05 / 1.06 / 1.03 (an eighth with four, an
+//     eighth with two, the rest one: x1.03 / 1.03 / 1.17, 0.97 / 0.98 / 1.10, 1.10 / 0.98 / 0.86); prompts of more than 4096
+//     positions, whose wavefronts run long, up to a third over one round too (3072 units of 1638 rows x1.05 / 1.02 / 1.05
+//     against 1.00 / 0.97 / 0.95; 8192 units of 410 x1.45 / 1.66 / 1.66 against 1.55 / 1.66 / 1.65);
+//   beyond, an eighth each of the segments with four and two wavefronts, fewer where that is more than one round, but a
+//     sixteenth: 2048 units of 410 rows x0.98 / 1.08 / 1.34, 3072 of 205 x1.01 / 1.05 / 1.25 (an eighth: 0.94 / 1.01 / 1.11);
+//   from two rounds of single wavefronts on, one each: 12 288 units of 136 rows x1.04 / 1.00 / 1.21 (a sixteenth: 0.95 / 0.99 /
+//     1.21);
+//   from one round on, prompts with keys of up to 96 KB per head in index order, one wavefront each: finding the rank costs
+//     about as much as such a unit's rows (300 positions at 20 % and 128 at 20 %: 4096 units of 60 rows x1.28 / - / 1.03, by length 1.21 / - / 0.88; 16 384 of 26 rows x1.37 /
+//     - / 1.20, by length 0.93 / - / 1.12).
+inline void ranked_shape(RankedShape& s, long long units, long long cus, int N, int row_bytes) {
+    const double per_unit = 16.0 * cus / units;           // wavefronts of one round for each unit
+    double f4 = 0, f2 = 0;
+    s.by_length = N * row_bytes > 96 << 10 || per_unit > 1;
+    if (per_unit >= 2.5 || (N > 4096 && per_unit >= 0.75)) {
+        f4 = 0.25; f2 = 0.75;
+    } else if (s.by_length && per_unit >= 0.5) {
+        f4 = (per_unit - 1) / 4;
+        f4 = f2 = f4 > 0.125 ? 0.125 : f4 < 0.0625 ? 0.0625 : f4;
+    }
+    s.n4 = (int)(s.gsz * f4 + 0.5);
+    s.n2 = (int)(s.gsz * f2 + 0.5);
+    if (s.n2 > s.gsz - s.n4) s.n2 = s.gsz - s.n4;
+}
 
 __host__ __device__ __forceinline__ int ranked_blocks(const RankedShape& s, int HU) {   // per group
     return s.n4 * HU + (s.n2 * HU + 1) / 2 + ((s.gsz - s.n4 - s.n2) * HU + 3) / 4;

@@ -20,10 +20,15 @@ extern "C" int row(int ev, int r, int r0, int len, int len_old, int app, int shi
     return s.slot * 4 + s.from_new * 2 + s.valid;
 }
 extern "C" void unit(int block, int wv, int gsz, int n4, int n2, int HU, int n_seg, int* out) {
-    const pkv::RankedShape s = {gsz, n4, n2};
+    const pkv::RankedShape s = {gsz, n4, n2, true};
     const pkv::RankedUnit x = pkv::ranked_unit(block, wv, s, HU, n_seg);
     const int v[7] = {x.live, x.UW, x.first, x.n, x.rank, x.hu, pkv::ranked_blocks(s, HU)};
     for (int i = 0; i < 7; ++i) out[i] = v[i];
+}
+extern "C" void shape(int gsz, long long units, long long cus, int N, int row_bytes, int* out) {
+    pkv::RankedShape s = {gsz, -1, -1, false};
+    pkv::ranked_shape(s, units, cus, N, row_bytes);
+    out[0] = s.n4; out[1] = s.n2; out[2] = s.by_length;
 }
 extern "C" int length_class(int cap, int longest) { return pkv::length_class(cap, longest); }
 """
@@ -123,6 +128,21 @@ def test_ranked_units(shim, HU, n_seg, gsz, n4, n2):
         assert len(who) == UW and len({b for b, _ in who}) == 1
         assert sorted(w & (UW - 1) for _, w in who) == list(range(UW))
         assert len({w & ~(UW - 1) for _, w in who}) == 1
+
+
+def test_ranked_shapes(shim):
+    out = (C.c_int * 3)()
+    for cus in (32, 256, 304):
+        for gsz in (1, 5, 8, 33, 64, 65, 512):
+            for units in [4 * cus + 1, *(int(4 * cus * 1.07 ** i) for i in range(1, 60))]:
+                for N, row_bytes in ((1, 128), (384, 256), (385, 256), (192, 512), (4096, 256), (4097, 128), (8192, 512)):
+                    shim.shape(gsz, units, cus, N, row_bytes, out)
+                    n4, n2, by_length = out
+                    assert 0 <= n4 and 0 <= n2 and n4 + n2 <= gsz
+                    assert by_length or n4 == n2 == 0
+                    waves = 4 * n4 + 2 * n2 + (gsz - n4 - n2)
+                    if N <= 4096 and gsz >= 64 and units <= 3 * 4 * cus:      # one round as long as that is possible
+                        assert waves * units <= 1.03 * 16 * cus * gsz, (cus, gsz, units, N, n4, n2)
 
 
 def test_length_classes(shim):
