@@ -1,0 +1,30 @@
+// Order of the blocks of a launch whose blocks differ in length.  Plain integer rules, apart from the kernels so that they
+// can be compiled and enumerated on the host.
+#pragma once
+
+namespace pkv {
+
+struct HeadBlock { int head, rank; };     // head of the XCD, rank of the block in it: 0 is the longest
+
+// Block j of an XCD that works on `heads` heads of nblk blocks each: head by head, the last `tail` heads longest block
+// first.  With an even number of blocks every head starts at another rank, one further for each head and each 32
+// workgroups: the hardware deals workgroups out in turn, and with ranks that repeat every 4, 6, 8, 12 or 16 of them some of
+// an XCD's 32 compute units got the long blocks time and again (importance without a given log-sum-exp, B4 L32 H32/8 D128,
+// us, ranks repeating / moving on: N900 1637 / 1343, N1500 3154 / 3014, N2048 5646 / 5052, N3000 11316 / 10655, N4096 20233
+// / 18751; an odd number does that by itself, and moving on costs it 2 % at N2300).
+__host__ __device__ __forceinline__ HeadBlock head_block(int j, int heads, int nblk, int tail) {
+    const int lead = heads - tail;
+    HeadBlock x;
+    if (j < lead * nblk) {
+        x.head = j / nblk;
+        x.rank = j - x.head * nblk;
+        if ((nblk & 1) == 0) x.rank = (x.rank + x.head + x.head * nblk / 32) % nblk;
+    } else {
+        const int i = j - lead * nblk;
+        x.rank = i / tail;
+        x.head = lead + i - x.rank * tail;
+    }
+    return x;
+}
+
+}  // namespace pkv

@@ -10,6 +10,7 @@
 //
 // The head mean is another, tiny kernel that adds the heads' column sums in head order, so the result is bitwise reproducible.  fp32 inputs (small validation shapes) have kernels of their own.
 #include "pkv_common.hpp"
+#include "block_order.hpp"
 
 #include <type_traits>
 
@@ -451,15 +452,13 @@ importance_stream_kernel(StreamParams p) {
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int wv = wave % kStWaves, gs = wave / kStWaves;  // the groups of four wavefronts take the stages in turn
     const int ln = lane & 31, hf = lane >> 5;
-    // blocks of a head next to each other on one XCD, longest first; the XCD's last p.tail heads longest block first
+    // blocks of a head next to each other on one XCD, the XCD's last p.tail heads longest block first
     const int per_xcd = (int)(gridDim.x / kXcds), j = (int)(blockIdx.x / kXcds);
-    const int hx = per_xcd / p.nblk, lead = hx - p.tail;
-    int rank, hl;                                         // rank 0: the longest block of a head
-    if (j < lead * p.nblk) { hl = j / p.nblk; rank = j - hl * p.nblk; }
-    else { const int i = j - lead * p.nblk; rank = i / p.tail; hl = lead + i - rank * p.tail; }
-    const long long head = (long long)(blockIdx.x % kXcds) * hx + hl;
+    const int hx = per_xcd / p.nblk;
+    const HeadBlock hb = head_block(j, hx, p.nblk, p.tail);
+    const long long head = (long long)(blockIdx.x % kXcds) * hx + hb.head;
     if (head >= p.nheads) return;
-    const int blk = COLS ? rank : p.nblk - 1 - rank;
+    const int blk = COLS ? hb.rank : p.nblk - 1 - hb.rank;
     const int h = (int)(head % p.H), l = (int)((head / p.H) % p.L), b = (int)(head / ((long long)p.H * p.L));
     const bf16_t* qb = p.q + p.qs.b * b + p.qs.l * l + p.qs.h * h;
     const bf16_t* kb = p.k + p.ks.b * b + p.ks.l * l + p.ks.h * (h / (p.H / p.Hkv));
