@@ -856,9 +856,13 @@ template <bool COLS>
 static hipError_t launch_stream(const pkv_shape& s, StreamParams p, hipStream_t st) {
     const long long cus = compute_units(), hx = (p.nheads + kXcds - 1) / kXcds;   // heads per XCD
     // 64 stationary rows per wavefront from two rounds of workgroups on, unless that pads the blocks further (1024
-    // heads of 100 positions: 47 against 32 us)
-    const long long nb2 = (s.N + 255) / 256, nb1 = (s.N + 127) / 128;
-    const bool wide = p.nheads * nb2 >= 4 * cus && (2 * nb2 == nb1 || nb2 > 2);
+    // heads of 100 positions: 47 against 32 us); for the column sums of D = 128 with three to six blocks per head also
+    // where these just fill one round of three workgroups per CU (256 heads of 680: 36.3 against 39.2 us, of 768: 40.3
+    // against 43.7; 192 of 768: 37.1 against 36.3; six blocks, 128 heads of 1500: 61.6 against 62.5; 96 of 2048 with eight:
+    // 83.0 against 79.9)
+    const long long nb2 = (s.N + 255) / 256, nb1 = (s.N + 127) / 128, blocks = p.nheads * nb2;
+    const bool wide = (blocks >= 4 * cus && (2 * nb2 == nb1 || nb2 > 2)) ||
+                      (COLS && s.D == 128 && nb2 >= 3 && nb2 <= 6 && 2 * blocks >= 5 * cus && blocks <= 3 * cus);
     p.nblk = (int)(wide ? nb2 : nb1);
     if (hx * kXcds * p.nblk > 0x7fffffffll) return hipErrorInvalidValue;
     const long long tail = (kStTailBlocks + p.nblk - 1) / p.nblk;

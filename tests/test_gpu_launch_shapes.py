@@ -273,3 +273,27 @@ def test_decode_ranked_classes(B, L, H, Hkv, N, D, dtype, frac, steps, layers):
 ])
 def test_decode_evict_ranked_classes(B, L, H, Hkv, N, D, dtype, frac, d, steps):
     run_evict_case(B, L, H, Hkv, N, D, dtype, frac, d, steps, seed=B * L + H)
+
+
+# The column sums with 64 rows per wavefront where their blocks fill one round of three workgroups per compute unit, next to
+# the 32-row form just below and above (256 compute units)
+@pytest.mark.parametrize("B,L,H,Hkv,N,D", [
+    (8, 1, 27, 27, 513, 128),            # 648 blocks of 256 keys: 64 rows
+    (8, 1, 26, 26, 513, 128),            # 624: 32 rows
+    (8, 4, 8, 2, 521, 128),              # 768: 64 rows
+    (8, 4, 9, 3, 521, 128),              # 864: 32 rows
+    (1, 3, 36, 36, 1530, 128),           # 648 of six blocks: 64 rows
+])
+def test_importance_columns_one_round(B, L, H, Hkv, N, D):
+    q, k, scale = rand_qk(N + H, B, L, H, Hkv, N, D, torch.bfloat16)
+    lse = torch.empty((B, L, H, N), device=DEV)
+    want = torch.empty((B, L, N), dtype=torch.float64, device=DEV)
+    qd, kd, future = q.to(DEV), k.to(DEV), torch.ones((N, N), dtype=torch.bool, device=DEV).triu_(1)
+    for b in range(B):
+        for l in range(L):
+            kk = kd[b, l].double().repeat_interleave(H // Hkv, 0)
+            s = torch.stack([qd[b, l, h].double() @ kk[h].t().contiguous() for h in range(H)]) * scale[l].item()
+            s.masked_fill_(future, -float("inf"))
+            lse[b, l] = torch.logsumexp(s, -1)
+            want[b, l] = torch.softmax(s, -1).sum(1).mean(0)
+    check_importance(np32(P.prefixkv_importance(qd, kd, scale.to(DEV), lse=lse)), want.cpu().numpy())
