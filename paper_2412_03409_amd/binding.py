@@ -9,6 +9,7 @@ import ctypes as C
 import os
 from dataclasses import dataclass
 from functools import lru_cache
+from operator import index
 from pathlib import Path
 from typing import Optional
 
@@ -122,15 +123,24 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 
 @lru_cache(maxsize=256, typed=True)
-def _shape(B, L, H, Hkv, N, D, dtype) -> _Shape:
-    """The argument struct of a shape (only read, so one object per value serves every call)."""
+def _shape_of(B, L, H, Hkv, N, D, dtype) -> _Shape:
     return _Shape(B, L, H, Hkv, N, D, dtype)
 
 
+def _shape(B, L, H, Hkv, N, D, dtype) -> _Shape:
+    """The argument struct of a shape (only read, so one object per value serves every call).  Any integer will do, an
+    array or tensor of no dimension too: the cache is asked for its value."""
+    return _shape_of(index(B), index(L), index(H), index(Hkv), index(N), index(D), index(dtype))
+
+
 @lru_cache(maxsize=256, typed=True)
+def _decode_ws_bytes_of(B, L, H, Hkv, N, D, dtype) -> int:
+    return int(load().prefixkv_workspace_bytes(OP_DECODE, C.byref(_shape(B, L, H, Hkv, N, D, dtype)), 0))
+
+
 def _decode_ws_bytes(B, L, H, Hkv, N, D, dtype) -> int:
     """Decode workspace of a shape: a pure function of it, asked for in every step."""
-    return int(load().prefixkv_workspace_bytes(OP_DECODE, C.byref(_shape(B, L, H, Hkv, N, D, dtype)), 0))
+    return _decode_ws_bytes_of(B, L, H, Hkv, index(N), D, dtype)
 
 
 def _strides5(t: torch.Tensor) -> _Strides:

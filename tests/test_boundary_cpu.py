@@ -227,3 +227,25 @@ def test_binding_refuses_cpu_tensors():
     import torch
     with pytest.raises(ValueError):
         P.prefixkv_select(torch.ones(1, 2, 8), 4)
+
+
+def test_sizes_of_any_integer_type():
+    """Sizes are taken by value: integers that are not plain ints, arrays and tensors of no dimension, whose value may
+    change between calls."""
+    import numpy as np
+    import torch
+    plain = lambda N: P.prefixkv_workspace_bytes(Bd.OP_IMPORTANCE, 1, 2, 4, 4, N, 64, P.PKV_F32)
+    assert plain(128) != plain(256)
+    for make in (np.int64, np.array, torch.tensor):
+        n = make(128)
+        assert P.prefixkv_workspace_bytes(Bd.OP_IMPORTANCE, 1, 2, 4, 4, n, 64, P.PKV_F32) == plain(128)
+        if not isinstance(n, np.int64):
+            n += 128
+            assert P.prefixkv_workspace_bytes(Bd.OP_IMPORTANCE, 1, 2, 4, 4, n, 64, P.PKV_F32) == plain(256)
+    n = torch.tensor(2000)
+    decode = lambda n: Bd._decode_ws_bytes(1, 2, 8, 2, n, 64, P.PKV_BF16)
+    first = decode(n)
+    n += 6000
+    assert first == decode(2000) != decode(8000) == decode(n)
+    with pytest.raises(TypeError):
+        plain(128.0)
