@@ -76,8 +76,14 @@ class HotPath:
         return B_.prefixkv_decode_attn(self.cache, q, k, v, self.scale, self.N, out=out, ws=self.dec_ws)
 
     def run_decode_loop(self, dq, dk, dv):
+        step_own = getattr(self.run_decode_step, "__func__", None) is not HotPath.run_decode_step
+        if step_own or not all(isinstance(x, torch.Tensor) for x in (dq, dk, dv)):
+            # steps that are made when they are asked for, or a step of the caller's own
+            for t in range(self.T):
+                self.run_decode_step(t, dq, dk, dv)
+            return
         # the steps' tensors as views made once: indexing four tensors per step costs as much as the call
-        steps = [x[:self.T].unbind(0) if isinstance(x, torch.Tensor) else x[:self.T] for x in (dq, dk, dv, self.out)]
+        steps = [x[:self.T].unbind(0) for x in (dq, dk, dv, self.out)]
         if min(len(x) for x in steps) < self.T:
             raise IndexError(f"{self.T} decode steps need as many tensors")
         for t, (q, k, v, out) in enumerate(zip(*steps)):
