@@ -109,7 +109,7 @@ constexpr int kTabBits = 8;
 constexpr int kTabN = (1 << kTabBits) - 1;
 
 // Sort key: high word = ~bits(importance) (non-negative floats order like their bit patterns, so the
-// complement orders them descending), low word = position (ascending among equal values).
+// complement orders them descending), low word = position + 1 (ascending among equal values).
 // Padding keys are all ones: they sort last and decode to weight 0.
 // P = E * ns keys, ns = the sorting threads (whole wavefronts, the first of the workgroup).  A wavefront sorts its 64*E
 // keys in registers with a bitonic network, without a barrier; its run then merges with its neighbours' by rank.  Bound by
@@ -144,7 +144,7 @@ __global__ void sort_prefix_kernel(int N, int P, const float* __restrict__ impor
                 if ((bits & 0x7f800000u) == 0x7f800000u) flags |= PKV_DEV_NONFINITE;
                 else if (bits == 0x80000000u) bits = 0;  // -0.0 counts as +0.0
                 else if (bits & 0x80000000u) flags |= PKV_DEV_NEGATIVE;
-                key = ((uint64_t)(~bits) << 32) | (uint32_t)i;
+                key = ((uint64_t)(~bits) << 32) | (uint32_t)(i + 1);   // never 0: a NaN of all ones has no high word
             }
             r[e] = key;
         }
@@ -201,7 +201,7 @@ __global__ void sort_prefix_kernel(int N, int P, const float* __restrict__ impor
         uint64_t w = 0;
         if (base + e < N) {
             if (wd >= 9007199254740992.0) flags |= PKV_DEV_RANGE; else w = (uint64_t)wd;
-            order[seg * (size_t)N + base + e] = (int32_t)(uint32_t)key;
+            order[seg * (size_t)N + base + e] = (int32_t)(uint32_t)key - 1;
         }
         local = sat_add(local, w);
         skey[base + e] = local;  // thread-local inclusive sums, rebased below

@@ -297,3 +297,16 @@ def test_importance_columns_one_round(B, L, H, Hkv, N, D):
             lse[b, l] = torch.logsumexp(s, -1)
             want[b, l] = torch.softmax(s, -1).sum(1).mean(0)
     check_importance(np32(P.prefixkv_importance(qd, kd, scale.to(DEV), lse=lse)), want.cpu().numpy())
+
+
+# A row that holds NaN is refused by its status word, but its order stays a permutation, whatever the bits of the NaN: with a
+# shared configuration the compaction reads it.
+@pytest.mark.parametrize("N", [64, 200, 1025, 4097])
+def test_order_of_nan_rows(N):
+    imp = synthetic_importance(1, 3, N, seed=N)
+    imp[0, 0] = torch.full((N,), -1, dtype=torch.int32).view(torch.float32)
+    imp[0, 1, 0] = torch.tensor(-1, dtype=torch.int32).view(torch.float32)
+    imp[0, 2, N // 2] = float("nan")
+    r = P.prefixkv_rank(imp.to(DEV))
+    assert r.status.item() & 1
+    assert torch.equal(r.order.cpu().sort(-1).values, torch.arange(N, dtype=torch.int32).expand(1, 3, N))
