@@ -644,7 +644,7 @@ __global__ void __launch_bounds__(kMeanKeys * kMeanParts)
 head_mean_parts_kernel(int H, int N, long long total, const float* __restrict__ partial, float* __restrict__ importance) {
     __shared__ float s_acc[kMeanParts][kMeanKeys];
     const int lane = threadIdx.x % kMeanKeys, part = threadIdx.x / kMeanKeys;
-    const long long i = (long long)blockIdx.x * kMeanKeys + lane;
+    const long long i = ((long long)blockIdx.y * gridDim.x + blockIdx.x) * kMeanKeys + lane;
     const bool live = i < total;
     const long long bl = live ? i / N : 0;
     const int n = live ? (int)(i % N) : 0;
@@ -795,10 +795,12 @@ importance_f32_kernel(F32Params p) {
     }
 }
 
+constexpr long long kMaxGridX = 1 << 23;   // workgroups of 256 threads: fewer than 2^32 threads in a grid's row
+
 template <bool LSE>
 static hipError_t launch_importance_f32(const pkv_shape& s, const F32Params& p, hipStream_t st) {
     const long long nblk = (long long)s.B * s.L * s.H * ((s.N + 15) / 16);
-    const long long gx = nblk < (1 << 23) ? nblk : (1 << 23), gy = (nblk + gx - 1) / gx;   // fewer than 2^32 threads each way
+    const long long gx = nblk < kMaxGridX ? nblk : kMaxGridX, gy = (nblk + gx - 1) / gx;
     if (gy > 65535) return hipErrorInvalidValue;
     const dim3 grid((unsigned)gx, (unsigned)gy), block(kF32Waves * kWave);
     if (s.D == 128) hipLaunchKernelGGL((importance_f32_kernel<128, LSE>), grid, block, 0, st, p);
@@ -915,8 +917,11 @@ hipError_t launch_importance(const pkv_shape& s, const void* q, Strides qs, cons
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(head_mean_parts_kernel, dim3((unsigned)((total + kMeanKeys - 1) / kMeanKeys)),
-                       dim3(kMeanKeys * kMeanParts), 0, st, s.H, s.N, total, partial, importance);
+    const long long nblk = (total + kMeanKeys - 1) / kMeanKeys;
+    const long long gx = nblk < kMaxGridX ? nblk : kMaxGridX, gy = (nblk + gx - 1) / gx;
+    if (gy > 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(head_mean_parts_kernel, dim3((unsigned)gx, (unsigned)gy), dim3(kMeanKeys * kMeanParts), 0, st, s.H,
+                       s.N, total, partial, importance);
     return hipGetLastError();
 }
 

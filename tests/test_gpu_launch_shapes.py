@@ -310,3 +310,12 @@ def test_order_of_nan_rows(N):
     r = P.prefixkv_rank(imp.to(DEV))
     assert r.status.item() & 1
     assert torch.equal(r.order.cpu().sort(-1).values, torch.arange(N, dtype=torch.int32).expand(1, 3, N))
+
+
+# The head mean takes 2^30 values (one query expanded over a million sequences, so that they need 12 GB in all)
+def test_importance_f32_largest_grid():
+    B, L, N, D = 1 << 20, 64, 16, 64
+    q, k, scale = rand_qk(3, 1, L, 1, 1, N, D, torch.float32)
+    one = P.prefixkv_importance(q.to(DEV), k.to(DEV), scale.to(DEV))
+    all_ = P.prefixkv_importance(q.to(DEV).expand(B, L, 1, N, D), k.to(DEV).expand(B, L, 1, N, D), scale.to(DEV))
+    assert (all_ == one).all()
