@@ -285,18 +285,39 @@ def test_decode_evict_ranked_classes(B, L, H, Hkv, N, D, dtype, frac, d, steps):
     (1, 3, 36, 36, 1530, 128),           # 648 of six blocks: 64 rows
 ])
 def test_importance_columns_one_round(B, L, H, Hkv, N, D):
+    run_importance_on_gpu(B, L, H, Hkv, N, D, both=False)
+
+
+def run_importance_on_gpu(B, L, H, Hkv, N, D, both=True):
+    """Importance with a given log-sum-exp and, `both`, without, against fp64 on the GPU (the CPU oracle is slow here)."""
     q, k, scale = rand_qk(N + H, B, L, H, Hkv, N, D, torch.bfloat16)
     lse = torch.empty((B, L, H, N), device=DEV)
     want = torch.empty((B, L, N), dtype=torch.float64, device=DEV)
     qd, kd, future = q.to(DEV), k.to(DEV), torch.ones((N, N), dtype=torch.bool, device=DEV).triu_(1)
     for b in range(B):
         for l in range(L):
-            kk = kd[b, l].double().repeat_interleave(H // Hkv, 0)
-            s = torch.stack([qd[b, l, h].double() @ kk[h].t().contiguous() for h in range(H)]) * scale[l].item()
+            kt = kd[b, l].double().transpose(1, 2).contiguous()
+            s = torch.stack([qd[b, l, h].double() @ kt[h // (H // Hkv)] for h in range(H)]) * scale[l].item()
             s.masked_fill_(future, -float("inf"))
             lse[b, l] = torch.logsumexp(s, -1)
             want[b, l] = torch.softmax(s, -1).sum(1).mean(0)
-    check_importance(np32(P.prefixkv_importance(qd, kd, scale.to(DEV), lse=lse)), want.cpu().numpy())
+    want = want.cpu().numpy()
+    check_importance(np32(P.prefixkv_importance(qd, kd, scale.to(DEV), lse=lse)), want)
+    if both:
+        check_importance(np32(P.prefixkv_importance(qd, kd, scale.to(DEV))), want)
+
+
+# Both sweeps of the stream kernels, 256 compute units: 32 rows per wavefront and one group of wavefronts (321 to about 1000
+# blocks of 128 rows) at D = 128, and 64 rows (1024 blocks of 256 and more) with a remainder and with wavefronts wholly past the
+# end at both head dimensions; six and four blocks whose ranks move on from head to head (512 and 672 heads, of which the last
+# 344 and 512 run longest block first)
+@pytest.mark.parametrize("B,L,H,Hkv,N,D", [
+    (1, 7, 20, 4, 300, 128), (1, 2, 20, 4, 1153, 128), (1, 3, 13, 13, 1281, 128),
+    (4, 2, 32, 32, 801, 128), (4, 2, 32, 32, 801, 64), (5, 4, 13, 13, 1030, 128), (3, 4, 17, 17, 1409, 64),
+    (5, 4, 16, 4, 769, 128), (4, 4, 32, 8, 1300, 64), (3, 7, 32, 16, 900, 128),
+])
+def test_importance_stream_forms(B, L, H, Hkv, N, D):
+    run_importance_on_gpu(B, L, H, Hkv, N, D)
 
 
 # A row that holds NaN is refused by its status word, but its order stays a permutation, whatever the bits of the NaN: with a
