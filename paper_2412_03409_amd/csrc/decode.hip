@@ -920,7 +920,9 @@ int compute_units() {
 // resident (4 per SIMD), and starting one costs the dispatcher about 7 ns whatever it does (12 800 units: 393 us with
 // four wavefronts each, 173 us with one, for rows that stream in 150 us).  Hence
 //   up to 2 units per compute unit: 8 wavefronts per unit (32 units, one layer of the 7B shape: 8.6 -> 6.1 us);
-//   up to 4: 4 wavefronts per unit, which fill the chip (7B, batch 1: 21.0 -> 18.5 us);
+//   up to 4: 4 wavefronts per unit, which fill the chip (7B, batch 1, lengths within a factor 30: 21.3 -> 18.7 us; equal: 21.7
+//       -> 21.0; equal lengths of 2048 rows and more are 1 ... 10 % slower than with two wavefronts and 16 loads in flight
+//       each, 164.1 -> 169.6 us at 1024 units);
 //   beyond: one, two or four wavefronts per unit, the longest segments first (see ranked_shape).  The lengths differ by up
 //       to two orders of magnitude, and in index order the launch ends with a few long segments on a chip that is
 //       otherwise empty.

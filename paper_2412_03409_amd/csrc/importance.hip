@@ -8,7 +8,8 @@
 //   importance_fused_kernel, both sweeps in one launch that reads the queries and the keys of a head from HBM once:
 //       for prompts of up to 768 positions without a given log-sum-exp, when the heads fill the chip.
 //
-// The head mean is another, tiny kernel that adds the heads' column sums in head order, so the result is bitwise reproducible.  fp32 inputs (small validation shapes) have kernels of their own.
+// The head mean is another, tiny kernel: four quarters of the heads, each in head order, then their four sums, so the result
+// is bitwise reproducible.  fp32 inputs (small validation shapes) have kernels of their own.
 #include "pkv_common.hpp"
 #include "block_order.hpp"
 
@@ -431,15 +432,16 @@ constexpr int kStTailBlocks = 256;
 // COLS = false: the same with 32 * NK queries stationary and the keys streaming: running maximum and sum per lane,
 // the row log-sum-exp at the end.
 // Bound by the vector ALU (fma, exp2, add per score: 276 cycles per 32x32 product) with the matrix cores next to it
-// (256).  NK = 2: a fragment read from LDS feeds two products; from two rounds of workgroups on (B4 H32/8 N8192, column
-// sums: 1105 us = 995 TFLOP/s, NK = 1 1230), below NK = 1 fills the chip better (B2 H32 N2048: 58 against 71 us).
+// (256); no form spills (NK = 2 at D = 128: 156 and 162 registers of the 170 of three wavefronts per SIMD).  NK = 2: a
+// fragment read from LDS feeds two products; from two rounds of workgroups on (B4 H32/8 N8192, column sums: 1105 us = 995
+// TFLOP/s, NK = 1 1230), below NK = 1 fills the chip better (B2 H32 N2048: 58 against 71 us).
 // GS = 2: two groups of four wavefronts share a block and take its stages in turn, for launches of about one
 // workgroup per CU, whose time is the longest block's (one layer, H32 N680: 17 against 19 us with the head mean).
 // Against the fused kernel with a given log-sum-exp, which kept the queries stationary, let the wavefronts' column
 // sums meet in LDS at every stage and had one workgroup per head: 31 -> 17 us there, 115 -> 77 us at B8 H40 N1021,
-// 1256 -> 1105 us at B4 H32/8 N8192.
+// 1264 -> 1104 us at B4 H32/8 N8192.
 template <int D, int NK, int GS, bool COLS>
-__global__ void __launch_bounds__(GS * kStWaves * kWave, GS == 4 ? 4 : 3)
+__global__ void __launch_bounds__(GS * kStWaves * kWave, 3)
 importance_stream_kernel(StreamParams p) {
     constexpr int KS = D / 16;
     constexpr int ROWB = D * 2, CPR = D / 8, RPB = 256 / ROWB;
