@@ -128,19 +128,15 @@ def _shape_of(B, L, H, Hkv, N, D, dtype) -> _Shape:
 
 
 def _shape(B, L, H, Hkv, N, D, dtype) -> _Shape:
-    """The argument struct of a shape (only read, so one object per value serves every call).  Any integer will do, an
-    array or tensor of no dimension too: the cache is asked for its value."""
+    """The argument struct of a shape (only read, so one object per value serves every call).  Any integer of the caller's
+    will do, an array or tensor of no dimension too: the cache is asked for its value.  (_shape_of: sizes of tensors.)"""
     return _shape_of(index(B), index(L), index(H), index(Hkv), index(N), index(D), index(dtype))
 
 
 @lru_cache(maxsize=256, typed=True)
 def _decode_ws_bytes_of(B, L, H, Hkv, N, D, dtype) -> int:
-    return int(load().prefixkv_workspace_bytes(OP_DECODE, C.byref(_shape(B, L, H, Hkv, N, D, dtype)), 0))
-
-
-def _decode_ws_bytes(B, L, H, Hkv, N, D, dtype) -> int:
     """Decode workspace of a shape: a pure function of it, asked for in every step."""
-    return _decode_ws_bytes_of(B, L, H, Hkv, index(N), D, dtype)
+    return int(load().prefixkv_workspace_bytes(OP_DECODE, C.byref(_shape(B, L, H, Hkv, N, D, dtype)), 0))
 
 
 def _strides5(t: torch.Tensor) -> _Strides:
@@ -201,7 +197,7 @@ def prefixkv_importance(q: torch.Tensor, k: torch.Tensor, scale: torch.Tensor,
         raise ValueError("scale must be contiguous f32 [L]")
     if lse is not None and (lse.dtype != torch.float32 or lse.shape != (B, L, H, N) or not lse.is_contiguous()):
         raise ValueError("lse must be contiguous f32 [B,L,H,N]")
-    s = _shape(B, L, H, Hkv, N, D, _dtype_code(q))
+    s = _shape_of(B, L, H, Hkv, N, D, _dtype_code(q))
     if out is None:
         out = torch.empty((B, L, N), dtype=torch.float32, device=q.device)
     # a workspace of the caller's may be smaller than the recommended one: the library says what it accepts
@@ -231,7 +227,7 @@ def prefixkv_prefill_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, sca
         out = torch.empty((B, L, H, N, D), dtype=q.dtype, device=q.device)
     if lse is None:
         lse = torch.empty((B, L, H, N), dtype=torch.float32, device=q.device)
-    s = _shape(B, L, H, Hkv, N, D, _dtype_code(q))
+    s = _shape_of(B, L, H, Hkv, N, D, _dtype_code(q))
     rc = load().prefixkv_prefill_attn(C.byref(s), _ptr(q), _strides5(q), _ptr(k), _strides5(k), _ptr(v),
                                       _strides5(v), _ptr(scale), _ptr(out), _ptr(lse), _stream())
     if rc != 0:
@@ -386,7 +382,7 @@ def prefixkv_compact(k: torch.Tensor, v: torch.Tensor, order: torch.Tensor, leng
             caps=torch.empty((B, L), dtype=torch.int32, device=dev),
             lens=torch.empty((B, L), dtype=torch.int32, device=dev),
             cache_tokens=int(cache_tokens), Hkv=Hkv, D=D)
-    s = _shape(B, L, Hkv, Hkv, N, D, _dtype_code(k))
+    s = _shape_of(B, L, Hkv, Hkv, N, D, _dtype_code(k))
     rc = load().prefixkv_compact(C.byref(s), _ptr(k), _strides5(k), _ptr(v), _strides5(v), _ptr(order),
                                  _ptr(lengths), int(decode_capacity), _ptr(out.seg_off), _ptr(out.caps),
                                  _ptr(out.kc), _ptr(out.vc), _ptr(out.kept_pos), _ptr(out.lens), None, 0,
@@ -402,7 +398,7 @@ def prefixkv_merge_position(cache: CompactResult, k: torch.Tensor, v: torch.Tens
     B, L, Hkv, N, D = k.shape
     if v.shape != k.shape or v.dtype != k.dtype or k.dtype != cache.kc.dtype or D != cache.D or Hkv != cache.Hkv:
         raise ValueError("k, v must be the [B,L,Hkv,N,D] tensors the cache was compacted from")
-    s = _shape(B, L, Hkv, Hkv, N, D, _dtype_code(k))
+    s = _shape_of(B, L, Hkv, Hkv, N, D, _dtype_code(k))
     rc = load().prefixkv_merge_position(C.byref(s), _ptr(k), _strides5(k), _ptr(v), _strides5(v),
                                         _ptr(cache.seg_off), _ptr(cache.caps), _ptr(cache.kept_pos),
                                         _ptr(cache.lens), _ptr(cache.kc), _ptr(cache.vc), _stream())
@@ -424,7 +420,7 @@ def prefixkv_merge_feature(cache: CompactResult, k: torch.Tensor, v: torch.Tenso
         match = torch.empty((2, B, L, Hkv, N), dtype=torch.int32, device=k.device)
     elif match.dtype != torch.int32 or tuple(match.shape) != (2, B, L, Hkv, N) or not match.is_contiguous():
         raise ValueError("match must be contiguous i32 [2,B,L,Hkv,N]")
-    s = _shape(B, L, Hkv, Hkv, N, D, _dtype_code(k))
+    s = _shape_of(B, L, Hkv, Hkv, N, D, _dtype_code(k))
     w = _ws(load().prefixkv_workspace_bytes(OP_MERGE_FEATURE, C.byref(s), 0), k.device, ws)
     rc = load().prefixkv_merge_feature(C.byref(s), _ptr(k), _strides5(k), _ptr(v), _strides5(v),
                                        _ptr(cache.seg_off), _ptr(cache.caps), _ptr(cache.kept_pos),
@@ -467,8 +463,9 @@ def prefixkv_decode_attn(cache: CompactResult, q: torch.Tensor, k_new: Optional[
         raise ValueError("scale must be contiguous f32 [L]")
     if out is None:
         out = torch.empty((B, L, H, D), dtype=q.dtype, device=q.device)
-    s = _shape(B, L, H, cache.Hkv, N, D, _dtype_code(q))
-    w = _ws(_decode_ws_bytes(B, L, H, cache.Hkv, N, D, _dtype_code(q)), q.device, ws)
+    shape = B, L, H, index(cache.Hkv), index(N), D, _dtype_code(q)
+    s = _shape_of(*shape)
+    w = _ws(_decode_ws_bytes_of(*shape), q.device, ws)
     rc = load().prefixkv_decode_attn(C.byref(s), int(l0), int(l1), _ptr(q), _ptr(k_new), _ptr(v_new),
                                      _ptr(scale), _ptr(cache.kc), _ptr(cache.vc), _ptr(cache.seg_off),
                                      _ptr(cache.caps), _ptr(cache.lens), _ptr(out), _ptr(w),
@@ -499,8 +496,9 @@ def prefixkv_decode_attn_evict(cache: CompactResult, base_lens: torch.Tensor, q:
         raise ValueError("base_lens must be contiguous i32 [B,L]")
     if out is None:
         out = torch.empty((B, L, H, D), dtype=q.dtype, device=q.device)
-    s = _shape(B, L, H, cache.Hkv, N, D, _dtype_code(q))
-    w = _ws(_decode_ws_bytes(B, L, H, cache.Hkv, N, D, _dtype_code(q)), q.device, ws)
+    shape = B, L, H, index(cache.Hkv), index(N), D, _dtype_code(q)
+    s = _shape_of(*shape)
+    w = _ws(_decode_ws_bytes_of(*shape), q.device, ws)
     rc = load().prefixkv_decode_attn_evict(
         C.byref(s), int(l0), int(l1), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(scale), _ptr(cache.kc),
         _ptr(cache.vc), _ptr(cache.seg_off), _ptr(cache.caps), _ptr(base_lens), _ptr(cache.lens),

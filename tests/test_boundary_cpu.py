@@ -242,10 +242,28 @@ def test_sizes_of_any_integer_type():
         if not isinstance(n, np.int64):
             n += 128
             assert P.prefixkv_workspace_bytes(Bd.OP_IMPORTANCE, 1, 2, 4, 4, n, 64, P.PKV_F32) == plain(256)
-    n = torch.tensor(2000)
-    decode = lambda n: Bd._decode_ws_bytes(1, 2, 8, 2, n, 64, P.PKV_BF16)
-    first = decode(n)
-    n += 6000
-    assert first == decode(2000) != decode(8000) == decode(n)
     with pytest.raises(TypeError):
         plain(128.0)
+
+
+def test_decode_takes_the_value_of_its_size(monkeypatch):
+    """The number of prompt positions of a decode step as a tensor that changes in place: each call gets its value."""
+    import types
+    import torch
+    seen = []
+
+    class Lib:
+        prefixkv_workspace_bytes = staticmethod(lambda op, shape, has_lse: 0)
+        prefixkv_decode_attn = staticmethod(lambda shape, *a: seen.append(shape._obj.N) or 0)
+
+    monkeypatch.setattr(Bd, "load", lambda path=None: Lib)
+    monkeypatch.setattr(Bd, "_need_cuda", lambda *a: None)
+    monkeypatch.setattr(Bd, "_stream", lambda: 0)
+    x = torch.zeros((1, 2, 2, 64))
+    i = torch.zeros((1, 2), dtype=torch.int32)
+    cache = types.SimpleNamespace(kc=x, vc=x, seg_off=i, caps=i, lens=i, Hkv=2, D=64)
+    n = torch.tensor(100)
+    for _ in range(2):
+        Bd.prefixkv_decode_attn(cache, x, None, None, torch.ones(2), n)
+        n += 11
+    assert seen == [100, 111]
