@@ -154,22 +154,20 @@ __device__ __forceinline__ void attend_block(const uint4 (&kr)[NI], uint4 (&vr)[
         const float mref = mnew == -INFINITY ? 0.f : mnew;
         const float corr = __builtin_amdgcn_exp2f(mrun[g] - mref);  // 0 on the first block
         mrun[g] = mnew;
-        srun[g] *= corr;
+        // the block's own sums first, so that a long segment adds one value per block to the running ones and not one per row
+        float sum = 0.f, ob[EPL];
 #pragma unroll
-        for (int x = 0; x < EPL; ++x) o[g][x] *= corr;
+        for (int i = 0; i < NI; ++i) {
+            const float pr = __builtin_amdgcn_exp2f(s[g][i] - mref);
+            sum += pr;
+            float vf[EPL];
+            unpack16<BF16>(vr[i], vf);
 #pragma unroll
-        for (int i = 0; i < NI; ++i) s[g][i] = __builtin_amdgcn_exp2f(s[g][i] - mref);
-    }
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        float vf[EPL];
-        unpack16<BF16>(vr[i], vf);
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            srun[g] += s[g][i];   // per row group; the groups are merged at the end
-#pragma unroll
-            for (int x = 0; x < EPL; ++x) o[g][x] = fmaf(s[g][i], vf[x], o[g][x]);
+            for (int x = 0; x < EPL; ++x) ob[x] = i == 0 ? pr * vf[x] : fmaf(pr, vf[x], ob[x]);
         }
+        srun[g] = fmaf(srun[g], corr, sum);   // per row group; the groups are merged at the end
+#pragma unroll
+        for (int x = 0; x < EPL; ++x) o[g][x] = fmaf(o[g][x], corr, ob[x]);
     }
 }
 

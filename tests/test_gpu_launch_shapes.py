@@ -340,3 +340,22 @@ def test_importance_f32_largest_grid():
     one = P.prefixkv_importance(q.to(DEV), k.to(DEV), scale.to(DEV))
     all_ = P.prefixkv_importance(q.to(DEV).expand(B, L, 1, N, D), k.to(DEV).expand(B, L, 1, N, D), scale.to(DEV))
     assert (all_ == one).all()
+
+
+# One wavefront walks 4096 fp32 rows (2048 per half of its lanes) and adds a block of four of them at a time to its running
+# sums.  With equal weights and one value v everywhere the sum of n blocks errs by at most half an ulp of every partial
+# result, 2^-24 * (n + 1) / 2 of the total; adding row by row errs by 3e-5 for this v, whose remainder in the last binades is
+# close to half an ulp.
+def test_decode_long_sums():
+    B, L, H, N, D = 2, 32, 32, 4096, 128
+    v = np.uint32(0x3ffd8c03).view(np.float32)
+    rows = B * L * N
+    cache = P.CompactResult(
+        kc=torch.zeros(rows * H * D, device=DEV), vc=torch.full((rows * H * D,), float(v), device=DEV),
+        kept_pos=torch.zeros(rows, dtype=torch.int32, device=DEV),
+        seg_off=(torch.arange(B * L, device=DEV) * N).view(B, L).contiguous(),
+        caps=torch.full((B, L), N, dtype=torch.int32, device=DEV), lens=torch.full((B, L), N, dtype=torch.int32, device=DEV),
+        cache_tokens=rows, Hkv=H, D=D)
+    out = P.prefixkv_decode_attn(cache, torch.ones((B, L, H, D), device=DEV), None, None, torch.ones(L, device=DEV), N)
+    blocks, rest = 512, 16       # rest: the block's own sum, the row groups, the quotient
+    assert (out.double() / float(v) - 1).abs().max() <= 2.0 ** -24 * ((blocks + 1) / 2 + rest)
