@@ -1,6 +1,6 @@
 // Stage 4b: one decode step over the ragged compressed cache (Sec. 3.1: the newest token's query
 // interacts with the cached KV vectors of every layer).  ONE kernel per step (two for bf16 caches whose
-// KV heads serve several query heads: a planning kernel and decode_gqa_kernel, further down):
+// KV heads serve several query heads: decode_gqa_kernel and decode_gqa_merge_kernel, further down):
 //
 //  decode_attn_kernel   a unit is one (sequence, layer, kv head), or a sub-group of G of its query heads.  One to
 //                       eight wavefronts work on a unit (see the launcher) and take its row blocks round-robin.  A
@@ -13,13 +13,15 @@
 // Append: the new token's k/v are taken from k_new/v_new in place of the slot they are written to, so
 // no wavefront reads a slot that is written in the same launch.
 //
-// lens is advanced inside the same launch without a second kernel: every wavefront reads the old
+// lens is advanced inside the launch of decode_attn_kernel without a second kernel: every wavefront reads the old
 // length of its segment when it starts, and every unit, once its wavefronts have, adds 1 to the
 // bits above kLenBits of lens[b,l].  The unit that finds all others of the segment already
 // counted stores the new plain length, which also clears the count.  Between launches lens holds plain
 // lengths (< 2^20).  The ranking of the segments goes by capacity, which no launch changes.
 #include "pkv_common.hpp"
 #include "decode_rows.hpp"
+
+#include <type_traits>
 
 namespace pkv {
 
@@ -44,9 +46,10 @@ struct DecodeParams {
     int N, t, d;                  // prompt length, 1-based decode step, distance
     const int32_t* base_lens;     // [B,L] entries kept after prefill
     int32_t* kept_pos;            // one int per slot, may be null
-    // work list of the grouped-query kernel (see decode_plan_kernel)
-    int G, n_seg, S0, pieces_cap, record_word, partial_word;
-    int* plan;
+    int n_seg;
+    // grouped-query kernels: wavefronts, workspace
+    int waves;
+    int* ws;
     RankedShape rank;   // ranked launches of decode_attn_kernel
 };
 
@@ -421,32 +424,32 @@ decode_attn_kernel(DecodeParams p) {
 
 // ---------------------------------------------------------------------------------------------------
 // Grouped-query variant on the matrix cores (bf16 storage, G = 2, 4 or 8 query heads per KV head).
-// With several query heads per cached row the dot products dominate the vector ALU, so they move to
-// MFMA: scores^T[16 rows x 16 head columns] = K[16 rows x D] . Q^T[D x heads] with
-// v_mfma_f32_16x16x32_bf16 (A = cache rows, one row per lane%16, 8 consecutive bf16 per lane; B = the
-// queries, head lane%16, columns >= G are zero).  A lane then holds the scores of one head for 4 rows;
-// softmax runs in that layout (one exp per (row, head) instead of one per lane of the row), the
-// probabilities go through a per-wavefront LDS tile to the layout of the V rows (LPR lanes per row, as in
-// the kernel above), and the weighted V sum stays on the vector ALU with fp32 accumulators.
+//
+// The rows of a launch are one stream: the units (segment by segment, its head groups one after the other) cut into blocks of
+// BR rows, and every wavefront takes the same number of consecutive blocks (gqa_share), wherever the units' borders lie.  So
+// the work is even whatever the lengths (they differ by up to two orders of magnitude), and the next two blocks, of this unit
+// or of later ones, are on their way to LDS while a wavefront works on one: it does not wait between units.  What it has of a
+// unit that other wavefronts share goes to the workspace as (numerators, max, denominator); decode_gqa_merge_kernel adds
+// those up in block order and advances lens, so nothing counts arrivals and the result does not depend on timing.
+//
+// Long caches are bound by the rate at which a compute unit's reads are served (6.6 TB/s while all wavefronts are at work; they
+// end between 59 and 80 us, and larger first shares with smaller ones dispatched behind them cost more in starts than they
+// even out: 84 -> 90 us), short ones by the chain lengths -> block counts -> state -> first block and by the two launches.
+// Against the kernel before, which claimed pieces of 1024 rows from a planned list, one workgroup each, and handed a split
+// segment to the last arriver (7 us per piece between the streams of rows), us per step, D 128, lengths within a factor 30:
+//   B4 H32/8 N8192 10 % 97 -> 84 (equal lengths 84 -> 87), B1 50 % 109 -> 94, B8 N1000 20 % 65 -> 51, B1 N2000 20 % 33 -> 21, with pruning
+//   B4 N2000 45 -> 35, H32/4 B8 N2000 10 % 56 -> 44, B2 N8192 49 -> 34; one layer a call: B4 N8192 28 -> 16, B1 N2000 17 -> 11.
+//   scores^T[16 rows x 16 head columns] = K[16 rows x D] . Q^T with v_mfma_f32_16x16x32_bf16 (A = cache rows from LDS, B = the
+//   queries, head lane%16, columns >= G are zero): a lane holds four rows of one head, and softmax runs in that layout.  The
+//   weighted sum stays on the vector ALU with fp32 probabilities: a group of 16 lanes takes the V rows whose probabilities
+//   it holds, so that they reach it as row broadcasts (DPP), without LDS.
+// K and V go to LDS by the 16-byte copies: the matrix operand wants a row per lane, and 16 bytes per lane at row distance
+// take 64 cycles of the compute unit's address unit, whole rows 16.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((address_space(3))) void lds_void_t;
 
-// Partial results cross workgroups (and XCDs) inside one launch: device-scope relaxed atomics go straight
-// to the coherent level and need no cache-wide write-back or invalidate.
-__device__ __forceinline__ void st_agent(float* p, float v) {
-    __hip_atomic_store((unsigned*)p, __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float ld_agent(const float* p) {
-    return __uint_as_float(__hip_atomic_load((const unsigned*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-}
-
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// State of one segment for this step, computed identically by every workgroup that touches it.
+// State of one segment for this step, computed identically by every wavefront that touches it.
 struct SegState {
     int len_old;   // occupied slots before the step (under pruning: permanent entries)
     int cap;
@@ -459,18 +462,15 @@ struct SegState {
 };
 
 template <bool EV>
-__device__ __forceinline__ SegState seg_state(const DecodeParams& p, int sl) {
+__device__ __forceinline__ SegState seg_state(const DecodeParams& p, int len_old, int cap, int64_t off, int base) {
     SegState s;
-    s.len_old = __hip_atomic_load(p.lens + sl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kLenMask;
-    s.cap = p.caps[sl];
-    s.off = p.seg_off[sl];
+    s.len_old = len_old; s.cap = cap; s.off = off;
     s.app = p.append && s.len_old < s.cap;
     s.len = s.len_old + (s.app ? 1 : 0);
     s.len_next = s.len;
     s.ring = {0, s.app ? s.len_old : -1, -1};
     s.ring0 = 0; s.cs = 0; s.grad = false; s.decide = false;
     if constexpr (EV) {
-        const int base = p.base_lens[sl];
         s.ring0 = s.cap - (p.d + 1);
         s.app = base >= 0 && s.ring0 >= base && s.len_old <= s.ring0;
         s.decide = s.app && p.t > p.d;
@@ -487,254 +487,283 @@ __device__ __forceinline__ SegState seg_state(const DecodeParams& p, int sl) {
     return s;
 }
 
-// Work list for the grouped-query kernel.  PrefixKV gives the layers very different lengths (tens of rows
-// next to thousands), so a segment is cut into pieces of S rows and every (piece, head group) is one
-// work item of similar size.  The planning kernel (one workgroup) evaluates the state of every segment
-// once, writes one 64-byte record per piece with everything the attention kernel needs, and advances
-// lens itself, so the attention kernel neither reads nor counts on lens.
-// Layout of the workspace, in 32-bit words:
-//   [0] next item to claim  [1] number of items  [2] S  [3] number of pieces  [4] number of full pieces
-//   [16 ...]  arrive[n_seg * HU], records[pieces_cap][16] (64-byte aligned),
-//   then the partial results of split segments: [pieces_cap * HU][G][D + 2] floats.
-// S starts at S0 and doubles until the pieces fit the table.
-constexpr int kPlanThreads = 1024;
-constexpr int kPlanHdr = 16;
-constexpr int kRecWords = 16;
-enum { REC_SL = 0, REC_SPLIT, REC_NSPLIT, REC_FIRST, REC_LEN_OLD, REC_LEN, REC_CAP, REC_FLAGS, REC_OFF_LO,
-       REC_OFF_HI, REC_SHIFT, REC_RNEW, REC_RMASK, REC_RING0, REC_CS, REC_LAST };
-enum { RECF_APP = 1, RECF_GRAD = 2, RECF_DECIDE = 4 };
 
-constexpr int kPlanClasses = 16;
-// Size class of a segment's last piece: 0 for the longest remainders.
-__device__ __forceinline__ int last_piece_class(int len, int S) {
-    int np = (len + S - 1) / S;
-    np = np < 1 ? 1 : np;
-    const int rows = len - (np - 1) * S;                 // 0 .. S
-    const int c = (int)(((long long)rows * kPlanClasses) / ((long long)S + 1));   // 0 .. kPlanClasses-1
-    return kPlanClasses - 1 - c;
-}
-
-// sum over the workgroup and exclusive prefix of v (blockDim.x a multiple of 64, at most 1024): wavefront
-// shuffles and one pass over the wavefront totals
-__device__ __forceinline__ int plan_scan(int v, int* s_wave, int& total) {
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave, nw = blockDim.x / kWave;
-    int incl = v;
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int up = __shfl_up(incl, d, kWave);
-        if (lane >= d) incl += up;
-    }
-    __syncthreads();                         // s_wave may still be read from the previous call
-    if (lane == kWave - 1) s_wave[wv] = incl;
-    __syncthreads();
-    int base = 0, tot = 0;
-    for (int w = 0; w < nw; ++w) {
-        const int t = s_wave[w];
-        if (w < wv) base += t;
-        tot += t;
-    }
-    total = tot;
-    return base + incl - v;
-}
-
+// Rows of a segment that a step attends to: SegState::len without the rest.
 template <bool EV>
-__global__ void __launch_bounds__(kPlanThreads)
-decode_plan_kernel(DecodeParams p) {
-    __shared__ int s_wave[kPlanThreads / kWave];
-    __shared__ int s_cls[kPlanClasses];
-    const int tid = threadIdx.x, n = p.n_seg;
-    const int nt = blockDim.x;               // a power of two, 64 .. kPlanThreads: no more wavefronts than the segments need
-    const int per = (n + nt - 1) / nt;
-    const int lo = tid * per < n ? tid * per : n, hi = lo + per < n ? lo + per : n;
-    int* hdr = p.plan;
-    int* arrive = p.plan + kPlanHdr;
-    int* records = p.plan + p.record_word;
-    auto seg_of = [&](int i) { return (i / p.nl) * p.L + p.l0 + i % p.nl; };
-    // Up to kPlanThreads segments (the usual case) are one per thread: its state is read once and kept.
-    const bool single = per == 1;
-    SegState mine_ss;
-    if (single && lo < hi) mine_ss = seg_state<EV>(p, seg_of(lo));
-    auto state = [&](int i) { return single ? mine_ss : seg_state<EV>(p, seg_of(i)); };
-    if (tid < kPlanClasses) s_cls[tid] = 0;
-    // Items are claimed from a counter in list order, so the list holds the full pieces first and the last
-    // (shorter) piece of every segment at the end: the tail of the launch is made of small items.
-    int S = p.S0, total_full = 0, mine = 0, at = 0;
-    for (;;) {
-        mine = 0;
-        for (int i = lo; i < hi; ++i) {
-            const int len = state(i).len;
-            const int np = (len + S - 1) / S;
-            mine += np < 1 ? 0 : np - 1;      // full pieces; every segment has exactly one last piece
-        }
-        at = plan_scan(mine, s_wave, total_full);
-        if (total_full + n <= p.pieces_cap || S >= (1 << 24)) break;
-        S *= 2;
+__device__ __forceinline__ int seg_rows(const DecodeParams& p, int sl) {
+    const int len_old = p.lens[sl] & kLenMask, cap = p.caps[sl];
+    if constexpr (!EV) return len_old + (p.append && len_old < cap ? 1 : 0);
+    const int base = p.base_lens[sl], ring0 = cap - (p.d + 1);
+    const bool app = base >= 0 && ring0 >= base && len_old <= ring0;
+    return app ? len_old + (p.t < p.d + 1 ? p.t : p.d + 1) : 0;
+}
+__device__ __forceinline__ int seg_slot(const DecodeParams& p, int i) { return (i / p.nl) * p.L + p.l0 + i % p.nl; }
+
+// Workspace: [0] the share, from word 16 the first block / HU of every segment and their total (n_seg + 1), then, 16-word
+// aligned, the partial results: [G][D] numerators, [G][2] max and denominator.  What wavefront w has of unit u sits in slot w + u:
+// along the stream one of the two goes up from one piece to the next, so no two pieces share a slot.
+constexpr int kGqaHdr = 16;
+__host__ __device__ inline int gqa_partial_word(int n_seg) { return (kGqaHdr + n_seg + 1 + 15) / 16 * 16; }
+
+// A word at a uniform address that no wavefront of the launch writes, by the scalar unit: a vector load would make its user
+// wait for the copies that were requested before it.
+template <class T>
+__device__ __forceinline__ T uniform_load(const T* x) { return *(const __attribute__((address_space(4))) T*)(uintptr_t)x; }
+
+// inclusive sum over the lanes
+__device__ __forceinline__ int wave_scan(int v, int lane) {
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int up = __shfl_up(v, d, kWave);
+        v += lane >= d ? up : 0;
     }
-    const int total = total_full + n;
-    const bool ok = total <= p.pieces_cap;   // cannot fail for pieces_cap >= n_seg
-    // the last pieces go into the list by size class, largest first (the order inside a class is arbitrary;
-    // results do not depend on the order of the list); s_cls was cleared before the barriers of the scan
-    for (int i = lo; i < hi; ++i) atomicAdd(&s_cls[last_piece_class(state(i).len, S)], 1);
-    __syncthreads();
-    if (tid == 0) {
-        int run = 0;
-        for (int c = 0; c < kPlanClasses; ++c) { const int v = s_cls[c]; s_cls[c] = run; run += v; }
-    }
-    __syncthreads();
-    if (ok) {
-        for (int i = lo; i < hi; ++i) {
-            const int sl = seg_of(i);
-            const SegState ss = state(i);
-            int np = (ss.len + S - 1) / S;
-            np = np < 1 ? 1 : np;
-            const int last = total_full + atomicAdd(&s_cls[last_piece_class(ss.len, S)], 1);
-            for (int k = 0; k < np; ++k) {
-                int* r = records + (size_t)(k < np - 1 ? at + k : last) * kRecWords;
-                r[REC_SL] = sl; r[REC_SPLIT] = k; r[REC_NSPLIT] = np; r[REC_FIRST] = at;
-                r[REC_LEN_OLD] = ss.len_old; r[REC_LEN] = ss.len; r[REC_CAP] = ss.cap;
-                r[REC_FLAGS] = (ss.app ? RECF_APP : 0) | (ss.grad ? RECF_GRAD : 0) | (ss.decide ? RECF_DECIDE : 0);
-                r[REC_OFF_LO] = (int)(uint32_t)ss.off; r[REC_OFF_HI] = (int)(ss.off >> 32);
-                r[REC_SHIFT] = ss.ring.shift; r[REC_RNEW] = ss.ring.r_new; r[REC_RMASK] = ss.ring.r_mask;
-                r[REC_RING0] = ss.ring0; r[REC_CS] = ss.cs; r[REC_LAST] = last;
-            }
-            at += np - 1;
-            p.lens[sl] = ss.len_next;        // the records carry the old state; nobody else reads lens in this step
-        }
-    }
-    const int HU = p.H / p.G;
-    for (int i = tid; i < n * HU; i += nt) arrive[i] = 0;
-    if (tid == 0) { hdr[0] = 0; hdr[1] = ok ? total * HU : 0; hdr[2] = S; hdr[3] = ok ? total : 0; hdr[4] = total_full; }
+    return v;
 }
 
-// Persistent kernel: as many workgroups as fit on the chip; a workgroup starts with the item of its own
-// index and claims further items of the list from a counter.
-template <int D, int G, int NT, int W, int OCC, bool EV>
-__global__ void __launch_bounds__(W * kWave, OCC)
+// 16 bytes per lane from global memory to LDS[dst + 16 * lane] (nothing else here uses m0)
+__device__ __forceinline__ void copy16(const unsigned char* base, uint32_t off, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(dst), "v"(off), "s"(base) : "memory");
+}
+__device__ __forceinline__ void copy16_any(const unsigned char* src, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst), "v"(src) : "memory");
+}
+
+__device__ __forceinline__ float swap_add16(float a, float b) {   // lanes with bit 4 clear: a of both rows of 16, set: b
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+__device__ __forceinline__ float swap_add32(float a, float b) {   // lower half: a of both halves, upper: b
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+// value of lane `g` of the own 16 lanes
+template <int g>
+__device__ __forceinline__ float row_bcast(float x) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x150 + g, 0xF, 0xF, true));
+}
+template <int G, class F> __device__ __forceinline__ void for_heads(F f) {
+    f(std::integral_constant<int, 0>{}); f(std::integral_constant<int, 1>{});
+    if constexpr (G > 2) { f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{}); }
+    if constexpr (G > 4) {
+        f(std::integral_constant<int, 4>{}); f(std::integral_constant<int, 5>{});
+        f(std::integral_constant<int, 6>{}); f(std::integral_constant<int, 7>{});
+    }
+}
+
+constexpr int kGqaWaves = 4, kGqaHeld = 4;   // wavefronts of a workgroup; block counts per lane that are held between the passes
+
+template <int D, int G, bool EV>
+__global__ void __launch_bounds__(kGqaWaves * kWave, 2)
 decode_gqa_kernel(DecodeParams p) {
-    constexpr int LPR = D / 8;                   // lanes per V row (16 bytes each)
-    constexpr int RPI = kWave / LPR;             // V rows per wavefront-wide load
-    constexpr int NJ = D / 32;                   // MFMAs per 16-row tile
-    constexpr int BR = NT * 16;                  // rows per block
-    constexpr int VI = BR / RPI;                 // V loads per block
-    constexpr int GP = G < 4 ? 4 : G;            // head columns kept in LDS
-    constexpr int DMAX = 128;
-    constexpr int ROWB = D * 2;
-    constexpr int PST = D + 2;                   // floats per (item, head) partial: numerators, max, denominator
-    static_assert(D == 64 || D == 128, "head dimension");
-    __shared__ float s_part[2][W][G][DMAX + 2];   // double-buffered across items: no barrier at the end of an item
-    __shared__ __attribute__((aligned(16))) float s_p[W][BR * GP];
-    __shared__ __attribute__((aligned(16))) float s_corr[W][GP];
-    __shared__ int s_last[2];
-    __shared__ int s_next[2];
+    constexpr int ROWB = D * 2, LPR = D / 8, RPI = kWave / LPR;   // bytes of a row, lanes and rows of a copy instruction
+    constexpr int NT = 128 / D;                   // 16-row tiles of a block
+    constexpr int BR = 16 * NT;
+    constexpr int NJ = D / 32;                    // MFMAs per tile
+    constexpr int NI = BR / RPI;                  // copy instructions per tensor: 4
+    constexpr int TB = BR * ROWB;                 // bytes of a block of K: 4096
+    static_assert(NI == 4 && TB == 4096, "block of 4 KB per tensor");
+    constexpr int QB = G * ROWB;                  // bytes of a unit's queries
+    __shared__ __attribute__((aligned(1024))) unsigned char s_ring[kGqaWaves][2][2 * TB];   // [wavefront][stage][K, V]
+    __shared__ __attribute__((aligned(1024))) unsigned char s_q[kGqaWaves][2][QB < 1024 ? 1024 : QB];   // the queries of two units
 
-    const int HU = p.H / G;
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    const int sub = lane % LPR, rg = lane / LPR;     // V layout
-    const int kr = lane & 15, kq = lane >> 4;        // K / score layout: row (or head) kr, quad kq
-    int* hdr = p.plan;
-    int* arrive = p.plan + kPlanHdr;
-    const int* records = p.plan + p.record_word;
-    float* partial = (float*)(p.plan + p.partial_word);
-    const int total = hdr[1], S = hdr[2];
+    const int HU = p.H / G, n = p.n_seg;
+    const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int gid = blockIdx.x * kGqaWaves + wv;
+    const int kr = lane & 15, kq = lane >> 4;            // K / score layout: row (or head) kr, quad kq
+    const int sub = lane % LPR, rg = lane / LPR;         // V layout
 
-  // every workgroup starts with the item of its own index and claims further ones from a counter; the claim
-  // for the next item is issued first, so its round trip is hidden behind the work on this one
-  for (int item = blockIdx.x, it = 0; item < total; ++it) {
-    if (threadIdx.x == 0) s_next[it & 1] = atomicAdd(hdr, 1) + (int)gridDim.x;
-    const int piece = item / HU, hu = item % HU;
-    const int* rec = records + (size_t)piece * kRecWords;
-    const int sl = rec[REC_SL], split = rec[REC_SPLIT], nsplit = rec[REC_NSPLIT], first_full = rec[REC_FIRST];
-    const int len_old = rec[REC_LEN_OLD], len = rec[REC_LEN], cap = rec[REC_CAP], flags = rec[REC_FLAGS];
-    const int64_t seg_tok = (int64_t)(((uint64_t)(uint32_t)rec[REC_OFF_HI] << 32) | (uint32_t)rec[REC_OFF_LO]);
-    const RingMap ring = {rec[REC_SHIFT], rec[REC_RNEW], rec[REC_RMASK]};
-    const int l = sl % p.L;
-    const int row_lo = split * S;
-    const int row_hi = len < row_lo + S ? len : row_lo + S;
-    const int nblk = row_hi > row_lo ? (row_hi - row_lo + BR - 1) / BR : 0;
-    const int kvh = (hu * G) / p.grp;
-    const bool writer = (flags & RECF_APP) && ((hu * G) % p.grp == 0);
-    const int64_t segbase = (seg_tok * p.Hkv + (int64_t)kvh * cap) * ROWB;
-    const unsigned char* knew = p.k_new + ((int64_t)sl * p.Hkv + kvh) * ROWB;
-    const unsigned char* vnew = p.v_new + ((int64_t)sl * p.Hkv + kvh) * ROWB;
-    unsigned char* kseg = p.kc + segbase;
-    unsigned char* vseg = p.vc + segbase;
-    float (*spart)[G][DMAX + 2] = s_part[it & 1];
-
-    float o[G][8], m_run = -INFINITY, l_run = 0.f;
+    // ---- where this wavefront's blocks are: block counts of all segments, their sum, the segment of the first block
+    auto blocks_of = [&](int i) {
+        const int rows = i < n ? seg_rows<EV>(p, seg_slot(p, i)) : 0;
+        const int nb = (rows + BR - 1) / BR;
+        return i < n ? (nb < 1 ? 1 : nb) : 0;            // an empty segment has an output too
+    };
+    int held[kGqaHeld], sum = 0;
 #pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int x = 0; x < 8; ++x) o[g][x] = 0.f;
-
-    if (wv < nblk) {
-        const float qs = p.scale[l] * 1.4426950408889634f;
-        bf16x8_t qb[NJ];
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            uint4 t = make_uint4(0, 0, 0, 0);
-            if (kr < G) t = *(const uint4*)(p.q + ((int64_t)sl * p.H + hu * G + kr) * ROWB + (4 * j + kq) * 16);
-            qb[j] = __builtin_bit_cast(bf16x8_t, t);
+    for (int u = 0; u < kGqaHeld; ++u) { held[u] = u * kWave < n ? blocks_of(u * kWave + lane) : 0; sum += held[u]; }
+    for (int i = kGqaHeld * kWave; i < n; i += kWave) sum += blocks_of(i + lane);
+    const int total = __builtin_amdgcn_readlane(wave_scan(sum, lane), kWave - 1);   // of one head group
+    const int all = total * HU;
+    const int share = gqa_share(all, p.waves);
+    if (gid == 0 && lane == 0) { p.ws[0] = share; p.ws[kGqaHdr + n] = total; }
+    const int x0 = gid * share, x1 = x0 + share < all ? x0 + share : all;
+    if (x0 >= all) return;
+    const int y0 = x0 / HU;
+    int seg = 0, first = 0, before = 0;                  // the segment of block x0, first block of it (per head group)
+    auto look = [&](int u, int nb) {
+        const int incl = before + wave_scan(nb, lane), excl = incl - nb;
+        if (gid == 0 && u * kWave + lane < n) p.ws[kGqaHdr + u * kWave + lane] = excl;
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(nb > 0 && excl <= y0);
+        if (m) {
+            const int at = 63 - __builtin_clzll(m);
+            seg = u * kWave + at;
+            first = __builtin_amdgcn_readlane(excl, at);
         }
-        float* ps = s_p[wv];
-        float* cr = s_corr[wv];
-        for (int blk = wv; blk < nblk; blk += W) {
-            const int r0 = row_lo + blk * BR;
-            const bool full = r0 + BR <= len_old;
-            if constexpr (EV) {
-                const int hi = len < r0 + BR ? len : r0 + BR;
-                if (hi - r0 == 1 && ring.r_mask == r0) continue;
+        before = __builtin_amdgcn_readlane(incl, kWave - 1);
+    };
+#pragma unroll
+    for (int u = 0; u < kGqaHeld; ++u)
+        if (u * kWave < n && (before <= y0 || gid == 0)) look(u, held[u]);
+    for (int u = kGqaHeld; u * kWave < n && (before <= y0 || gid == 0); ++u) look(u, blocks_of(u * kWave + lane));
+    seg = __builtin_amdgcn_readfirstlane(seg);
+
+    // ---- the unit under way
+    struct Unit {
+        SegState ss;
+        int sl, hu, nb;
+        unsigned char *k, *v;                            // its rows in the cache
+        int64_t fresh;                                   // byte offset of its row in k_new / v_new
+    };
+    auto enter_segment = [&](Unit& u, int i) {
+        u.sl = __builtin_amdgcn_readfirstlane(seg_slot(p, i));
+        u.ss = seg_state<EV>(p, uniform_load(p.lens + u.sl) & kLenMask, uniform_load(p.caps + u.sl), uniform_load(p.seg_off + u.sl), EV ? uniform_load(p.base_lens + u.sl) : 0);
+        const int nb = (u.ss.len + BR - 1) / BR;
+        u.nb = nb < 1 ? 1 : nb;
+    };
+    auto enter_head = [&](Unit& u, int hu) {
+        const int kvh = (hu * G) / p.grp;
+        u.hu = hu;
+        int64_t at = (u.ss.off * p.Hkv + (int64_t)kvh * u.ss.cap) * ROWB;
+        at = ((int64_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        u.k = p.kc + at; u.v = p.vc + at;
+        u.fresh = ((int64_t)u.sl * p.Hkv + kvh) * ROWB;
+    };
+    // two cursors: the block that is worked on and, two blocks ahead, the one that is requested
+    Unit cur;
+    enter_segment(cur, seg);
+    int blk;
+    {
+        const int rem = x0 - first * HU, hu = rem / cur.nb;
+        blk = rem - hu * cur.nb;
+        enter_head(cur, hu);
+    }
+    auto advance = [&](Unit& u, int& b, int& i) {          // true: a new unit
+        if (b + 1 < u.nb) { ++b; return false; }
+        b = 0;
+        if (u.hu + 1 < HU) enter_head(u, u.hu + 1);
+        else { ++i; enter_segment(u, i); enter_head(u, 0); }
+        return true;
+    };
+    // copies of a block; K's chunks swizzled so that 16 rows at one chunk lie in different banks
+    auto kpos = [](int row) { return LPR == 16 ? row & 15 : (row >> 1) & 7; };
+    const uint32_t ring = (uint32_t)(uintptr_t)(lds_void_t*)&s_ring[wv][0][0];
+    uint32_t koff[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) koff[i] = (uint32_t)(rg * ROWB + ((sub ^ kpos(i * RPI + rg)) * 16));
+    // K or V of a block into its half of a stage; how many instructions that were
+    auto issue = [&](const Unit& u, int b, int stage, auto is_v) {
+        constexpr bool V = decltype(is_v)::value;
+        const int r0 = b * BR;
+        const uint32_t dst = __builtin_amdgcn_readfirstlane(ring + stage * 2 * TB + (V ? TB : 0));
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // what was there has been read
+        if (r0 + BR <= u.ss.len_old) {
+            const unsigned char* base = (V ? u.v : u.k) + (size_t)r0 * ROWB;
+#pragma unroll
+            for (int i = 0; i < NI; ++i) copy16(base + i * 1024, V ? (uint32_t)lane * 16u : koff[i], dst + i * 1024);
+        } else if (r0 < u.ss.len) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const int r = i * RPI + rg;
+                const RowSource src = row_source<EV>(r0 + r, r0, u.ss.len, u.ss.len_old, u.ss.app, u.ss.ring);
+                const unsigned char* from = src.from_new ? (V ? p.v_new : p.k_new) + u.fresh : (V ? u.v : u.k) + (int64_t)src.slot * ROWB;
+                copy16_any(from + (V ? sub : sub ^ kpos(r)) * 16, dst + i * 1024);
             }
-            uint4 kf[NT][NJ], vr[VI];
-            if (full) {
+        } else {
+            return 0;
+        }
+        return NI;
+    };
+    const uint32_t ldsq = (uint32_t)(uintptr_t)(lds_void_t*)&s_q[wv][0][0];
+    int q_put = 0, q_get = 0;                             // the slots take turns
+    auto issue_q = [&](const Unit& u) {
+        const unsigned char* src = p.q + ((int64_t)u.sl * p.H + u.hu * G) * ROWB;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        const uint32_t dst = __builtin_amdgcn_readfirstlane(ldsq + q_put * (QB < 1024 ? 1024 : QB));
 #pragma unroll
-                for (int t = 0; t < NT; ++t)
+        for (int i = 0; i < (QB + 1023) / 1024; ++i) copy16_any(src + i * 1024 + (lane * 16) % (QB < 1024 ? QB : 1024), dst + i * 1024);
+        q_put ^= 1;
+    };
+    constexpr std::false_type of_k{};
+    constexpr std::true_type of_v{};
+    Unit ahead = cur;
+    int a_blk = blk, a_seg = seg;
+    issue_q(ahead);
+    issue(ahead, a_blk, 0, of_k);
+    issue(ahead, a_blk, 0, of_v);
+    int flying = 0;                                       // copies of the block after the next to work on
+    if (x0 + 1 < x1) {
+        if (advance(ahead, a_blk, a_seg)) issue_q(ahead);
+        flying = issue(ahead, a_blk, 1, of_k);
+        flying += issue(ahead, a_blk, 1, of_v);
+    }
+    bf16x8_t qb[NJ];
+
+    // The older wavefronts of a SIMD are served first and are done (at 59 of 84 us) when the younger, too few to keep the
+    // memory busy, have a fifth of their blocks left.  So every wavefront gives way as it gets on (then 63 and 69 of 80).
+    const int quarter = (x1 - x0 + 3) / 4;
+    int next_prio = x0 + quarter;
+    __builtin_amdgcn_s_setprio(3);
+    float o[G * 8], m_run = -INFINITY, l_run = 0.f, qs = 0.f;
+    bool fresh_unit = true;
+    int begun = x0 - blk;                                // flat number of the unit's first block
+    for (int x = x0;; ++x) {
+        const int stage = (x - x0) & 1;
+        // the block and, with it, the queries of a new unit are here; the block after it may be on its way
+        if (flying) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (fresh_unit) {
 #pragma unroll
-                    for (int j = 0; j < NJ; ++j)
-                        kf[t][j] = load_stream16(kseg + (uint32_t)(r0 + 16 * t + kr) * ROWB + (4 * j + kq) * 16);
-#pragma unroll
-                for (int i = 0; i < VI; ++i)
-                    vr[i] = load_stream16(vseg + (uint32_t)(r0 + i * RPI + rg) * ROWB + sub * 16);
-            } else {
-                // guarded path: rows past the end are zero, the new row comes from k_new / v_new and is stored,
-                // under pruning ring rows map to the ring slots and the pruned row is left out
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const int r = r0 + 16 * t + kr;
-                    const bool valid = r < len && r != ring.r_mask;
-                    const bool isnew = r == ring.r_new;
-                    const uint32_t so = (uint32_t)(r + ((EV && r >= len_old) ? ring.shift : 0)) * ROWB;
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j) {
-                        const int c16 = (4 * j + kq) * 16;
-                        kf[t][j] = make_uint4(0, 0, 0, 0);
-                        if (valid) {
-                            kf[t][j] = load_stream16(isnew ? knew + c16 : kseg + so + c16);
-                            if (isnew && writer) *(uint4*)(kseg + so + c16) = kf[t][j];
-                        }
-                    }
-                }
-#pragma unroll
-                for (int i = 0; i < VI; ++i) {
-                    const int r = r0 + i * RPI + rg;
-                    const bool valid = r < len && r != ring.r_mask;
-                    const bool isnew = r == ring.r_new;
-                    const uint32_t so = (uint32_t)(r + ((EV && r >= len_old) ? ring.shift : 0)) * ROWB;
-                    vr[i] = make_uint4(0, 0, 0, 0);
-                    if (valid) {
-                        vr[i] = load_stream16(isnew ? vnew + sub * 16 : vseg + so + sub * 16);
-                        if (isnew && writer) *(uint4*)(vseg + so + sub * 16) = vr[i];
-                    }
-                }
+            for (int j = 0; j < NJ; ++j) {
+                uint4 t = *(const uint4*)(&s_q[wv][q_get][0] + (kr < G ? kr : 0) * ROWB + (4 * j + kq) * 16);
+                if (kr >= G) t = make_uint4(0, 0, 0, 0);
+                qb[j] = __builtin_bit_cast(bf16x8_t, t);
             }
-            // scores: one MFMA chain per 16-row tile
-            f32x4_t acc[NT];
+            q_get ^= 1;
+            qs = uniform_load(p.scale + cur.sl % p.L) * 1.4426950408889634f;
+            m_run = -INFINITY; l_run = 0.f;
+#pragma unroll
+            for (int e = 0; e < G * 8; ++e) o[e] = 0.f;
+            fresh_unit = false;
+        }
+        const bool more = x + 1 < x1, ends = blk + 1 == cur.nb;
+        if (x >= next_prio) {
+            const int k = (x - x0) / quarter;
+            if (k == 1) __builtin_amdgcn_s_setprio(2); else if (k == 2) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
+            next_prio += quarter;
+        }
+        const int r0 = blk * BR;
+        const unsigned char *sk = &s_ring[wv][stage][0], *sv = sk + TB;
+        const SegState& ss = cur.ss;
+        f32x4_t acc[NT];
+        const bool some = r0 < ss.len, full = r0 + BR <= ss.len_old;
+        if (some) {
+            // the appended row goes to its slot out of the stage (only the first head group of a KV head writes)
+            const int rn = ss.ring.r_new - r0;
+            if (rn >= 0 && rn < BR && ss.app && (cur.hu * G) % p.grp == 0 && lane < 2 * LPR) {
+                const bool is_v = lane >= LPR;
+                const uint4 t = *(const uint4*)(is_v ? sv + rn * ROWB + sub * 16 : sk + rn * ROWB + ((sub ^ kpos(rn)) * 16));
+                const size_t slot = (size_t)(ss.ring.r_new + (EV ? ss.ring.shift : 0));
+                *(uint4*)((is_v ? cur.v : cur.k) + slot * ROWB + sub * 16) = t;
+            }
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 acc[t] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kf[t][j]), qb[j],
-                                                                     acc[t], 0, 0, 0);
+                for (int j = 0; j < NJ; ++j) {
+                    const int row = 16 * t + kr;
+                    const bf16x8_t kf = __builtin_bit_cast(bf16x8_t, *(const uint4*)(sk + row * ROWB + (((4 * j + kq) ^ kpos(row)) * 16)));
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qb[j], acc[t], 0, 0, 0);
+                }
             }
+        }
+        // the block after the next takes the place of this one, K now and V below
+        const bool request = x + 2 < x1;
+        flying = 0;
+        if (request) {
+            if (advance(ahead, a_blk, a_seg)) issue_q(ahead);
+            flying = issue(ahead, a_blk, stage, of_k);
+        }
+        if (some) {
             float mx = -INFINITY;
 #pragma unroll
             for (int t = 0; t < NT; ++t)
@@ -743,162 +772,181 @@ decode_gqa_kernel(DecodeParams p) {
                     float sc = acc[t][r] * qs;
                     if (!full) {
                         const int row = r0 + 16 * t + 4 * kq + r;
-                        sc = (row < len && row != ring.r_mask) ? sc : -INFINITY;
+                        sc = (row < ss.len && row != ss.ring.r_mask) ? sc : -INFINITY;
                     }
                     acc[t][r] = sc;
                     mx = fmaxf(mx, sc);
                 }
-            mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
-            mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-            const float mnew = fmaxf(m_run, mx);              // finite: the block has an occupied row
-            const float corr = __builtin_amdgcn_exp2f(m_run - mnew);
+            {
+                auto s2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+                mx = fmaxf(__uint_as_float(s2[0]), __uint_as_float(s2[1]));
+                s2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+                mx = fmaxf(__uint_as_float(s2[0]), __uint_as_float(s2[1]));
+            }
+            const float mnew = fmaxf(m_run, mx), mref = mnew == -INFINITY ? 0.f : mnew;
+            const float corr = __builtin_amdgcn_exp2f(m_run - mref);
             m_run = mnew;
             float psum = 0.f;
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float pr = __builtin_amdgcn_exp2f(acc[t][r] - mnew);
-                    psum += pr;
-                    if (kr < GP) ps[(16 * t + 4 * kq + r) * GP + kr] = pr;
+                    acc[t][r] = __builtin_amdgcn_exp2f(acc[t][r] - mref);
+                    psum += acc[t][r];
                 }
-            l_run = l_run * corr + psum;
-            if (kq == 0 && kr < GP) cr[kr] = corr;
-            wave_lds_sync();
-            float cg[GP];
+            l_run = fmaf(l_run, corr, psum);
+            if (__builtin_amdgcn_ballot_w64(kr < G && corr != 1.f)) {
+                for_heads<G>([&](auto g) {
+                    const float cg = row_bcast<g.value>(corr);
 #pragma unroll
-            for (int g4 = 0; g4 < GP; g4 += 4) {
-                const float4 c4 = *(const float4*)(cr + g4);
-                cg[g4] = c4.x; cg[g4 + 1] = c4.y; cg[g4 + 2] = c4.z; cg[g4 + 3] = c4.w;
+                    for (int e = 0; e < 8; ++e) o[8 * g.value + e] *= cg;
+                });
             }
+            // the rows whose probabilities the own 16 lanes hold: 4 * kq + i, of the tile that the lane's half of them takes
 #pragma unroll
-            for (int g = 0; g < G; ++g)
-#pragma unroll
-                for (int x = 0; x < 8; ++x) o[g][x] *= cg[g];
-#pragma unroll
-            for (int i = 0; i < VI; ++i) {
-                float vf[8], pg[GP];
-                unpack16<true>(vr[i], vf);
-#pragma unroll
-                for (int g4 = 0; g4 < GP; g4 += 4) {
-                    const float4 p4 = *(const float4*)(ps + (i * RPI + rg) * GP + g4);
-                    pg[g4] = p4.x; pg[g4 + 1] = p4.y; pg[g4 + 2] = p4.z; pg[g4 + 3] = p4.w;
+            for (int i = 0; i < NI; ++i) {
+                const int row = NT == 1 ? 4 * kq + i : 16 * (rg & 1) + 4 * kq + i;
+                uint4 vr = *(const uint4*)(sv + row * ROWB + sub * 16);
+                if (!full) {
+                    const bool valid = r0 + row < ss.len && r0 + row != ss.ring.r_mask;
+                    vr.x = valid ? vr.x : 0; vr.y = valid ? vr.y : 0; vr.z = valid ? vr.z : 0; vr.w = valid ? vr.w : 0;
                 }
+                float vf[8];
+                unpack16<true>(vr, vf);
+                for_heads<G>([&](auto g) {
+                    float pg = row_bcast<g.value>(acc[0][i]);
+                    if constexpr (NT == 2) {
+                        const float other = row_bcast<g.value>(acc[NT - 1][i]);   // by all lanes, also those that do not want it
+                        pg = (rg & 1) ? other : pg;
+                    }
 #pragma unroll
-                for (int g = 0; g < G; ++g)
-#pragma unroll
-                    for (int x = 0; x < 8; ++x) o[g][x] = fmaf(pg[g], vf[x], o[g][x]);
-            }
-            wave_lds_sync();
-        }
-        // the four quads hold partial row sums of the same head; the RPI row groups partial outputs
-        l_run += __shfl_xor(l_run, 16, kWave);
-        l_run += __shfl_xor(l_run, 32, kWave);
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-            for (int sh = LPR; sh < kWave; sh <<= 1)
-#pragma unroll
-                for (int x = 0; x < 8; ++x) o[g][x] += __shfl_xor(o[g][x], sh, kWave);
-    }
-    if constexpr (EV) {
-        if (split == 0) {
-            const int ring0 = rec[REC_RING0], cs = rec[REC_CS];
-            if ((flags & RECF_GRAD) && writer && wv == 0 && rg == 0) {
-                const size_t src = (size_t)(ring0 + cs) * ROWB + sub * 16, dst = (size_t)len_old * ROWB + sub * 16;
-                *(uint4*)(kseg + dst) = *(const uint4*)(kseg + src);
-                *(uint4*)(vseg + dst) = *(const uint4*)(vseg + src);
-            }
-            if (p.kept_pos && (flags & RECF_APP) && hu == 0 && threadIdx.x == 0) {
-                int32_t* kp = p.kept_pos + seg_tok;
-                kp[ring0 + (p.t - 1) % (p.d + 1)] = p.N + p.t - 1;
-                if (flags & RECF_DECIDE) {
-                    if (flags & RECF_GRAD) kp[len_old] = p.N + p.t - p.d - 1;
-                    kp[ring0 + cs] = -1;
-                }
+                    for (int e = 0; e < 8; ++e) o[8 * g.value + e] = fmaf(pg, vf[e], o[8 * g.value + e]);
+                });
             }
         }
-    }
-    if (rg == 0) {
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-            for (int x = 0; x < 8; ++x) spart[wv][g][sub * 8 + x] = o[g][x];
-    }
-    if (kq == 0 && kr < G) { spart[wv][kr][DMAX] = m_run; spart[wv][kr][DMAX + 1] = l_run; }
-    __syncthreads();
-    const int item_next = __builtin_amdgcn_readfirstlane(s_next[it & 1]);   // uniform, stays in scalar registers
-    // merge the wavefronts: thread (g, d).  A whole segment is written out; a piece leaves (numerators,
-    // max, denominator) in the workspace and the last piece of the (segment, head group) to arrive adds them up
-    float* mine = partial + ((size_t)piece * HU + hu) * (G * PST);
-    for (int i = threadIdx.x; i < G * D; i += blockDim.x) {
-        const int g = i / D, d = i % D;
-        float M = -INFINITY;
-#pragma unroll
-        for (int w = 0; w < W; ++w) M = fmaxf(M, spart[w][g][DMAX]);
-        float num = 0.f, den = 0.f;
-        if (M > -INFINITY) {
-#pragma unroll
-            for (int w = 0; w < W; ++w) {
-                const float wgt = __builtin_amdgcn_exp2f(spart[w][g][DMAX] - M);
-                num = fmaf(wgt, spart[w][g][d], num);
-                den = fmaf(wgt, spart[w][g][DMAX + 1], den);
-            }
-        }
-        if (nsplit == 1) {
-            const float r = den > 0.f ? num / den : 0.f;   // an empty segment gives zeros
-            ((bf16_t*)p.out)[((size_t)sl * p.H + hu * G + g) * D + d] = f32_to_bf16(r);
-        } else {
-            st_agent(mine + g * PST + d, num);
-            if (d == 0) { st_agent(mine + g * PST + D, M); st_agent(mine + g * PST + D + 1, den); }
-        }
-    }
-    if (nsplit > 1) {
-        // Hand-off of the partial to the last arriver.  Every thread waits until its own partial stores have
-        // been acknowledged (they are device-scope write-through stores, so acknowledged = at the level all
-        // XCDs share), the barrier collects the workgroup, then one thread counts the workgroup in.
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-        __syncthreads();
-        const int i_seg = (sl / p.L) * p.nl + (sl % p.L - p.l0);
-#ifdef PKV_GQA_RELEASE_ACQUIRE
-        // the same hand-off inside the HIP memory model: release on the arrival, acquire in the last arriver
-        if (threadIdx.x == 0)
-            s_last[it & 1] = __hip_atomic_fetch_add(arrive + i_seg * HU + hu, 1, __ATOMIC_ACQ_REL,
-                                                    __HIP_MEMORY_SCOPE_AGENT) == nsplit - 1;
-#else
-        if (threadIdx.x == 0) s_last[it & 1] = atomicAdd(arrive + i_seg * HU + hu, 1) == nsplit - 1;
-#endif
-        __syncthreads();
-        if (s_last[it & 1]) {
-            // the partial of piece k sits at the piece's place in the list
-            const int last_piece = rec[REC_LAST];
-            for (int i = threadIdx.x; i < G * D; i += blockDim.x) {
-                const int g = i / D, d = i % D;
-                float M = -INFINITY;
-                for (int k = 0; k < nsplit; ++k) {
-                    const int pc = k < nsplit - 1 ? first_full + k : last_piece;
-                    M = fmaxf(M, ld_agent(partial + ((size_t)pc * HU + hu) * (G * PST) + g * PST + D));
+        if (request) issue(ahead, a_blk, stage, of_v);
+        if constexpr (EV) {
+            // the surviving token moves from its ring slot to the next permanent slot, which nobody reads in this launch
+            if (blk == 0 && ss.app) {
+                const int ring0 = ss.ring0, cs = ss.cs;
+                if (ss.grad && (cur.hu * G) % p.grp == 0 && lane < 2 * LPR) {
+                    unsigned char* base = lane >= LPR ? cur.v : cur.k;
+                    *(uint4*)(base + (size_t)ss.len_old * ROWB + sub * 16) = *(const uint4*)(base + (size_t)(ring0 + cs) * ROWB + sub * 16);
                 }
-                float num = 0.f, den = 0.f;
-                if (M > -INFINITY) {
-                    for (int k = 0; k < nsplit; ++k) {
-                        const int pc = k < nsplit - 1 ? first_full + k : last_piece;
-                        const float* pk = partial + ((size_t)pc * HU + hu) * (G * PST) + g * PST;
-                        const float wgt = __builtin_amdgcn_exp2f(ld_agent(pk + D) - M);
-                        num = fmaf(wgt, ld_agent(pk + d), num);
-                        den = fmaf(wgt, ld_agent(pk + D + 1), den);
+                if (p.kept_pos && cur.hu == 0 && lane == 0) {
+                    int32_t* kp = p.kept_pos + ss.off;
+                    kp[ring0 + (p.t - 1) % (p.d + 1)] = p.N + p.t - 1;
+                    if (ss.decide) {
+                        if (ss.grad) kp[ss.len_old] = p.N + p.t - p.d - 1;
+                        kp[ring0 + cs] = -1;
                     }
                 }
-                const float r = den > 0.f ? num / den : 0.f;
-                ((bf16_t*)p.out)[((size_t)sl * p.H + hu * G + g) * D + d] = f32_to_bf16(r);
             }
         }
+        if (ends || !more) {
+            // the row groups meet: afterwards register e is value e + 4 G (upper half) + 2 G (odd 16 lanes) of the G * 8
+            float l = swap_add16(l_run, l_run);
+            l = swap_add32(l, l);
+            float f[G * 4], r[G * 2];
+#pragma unroll
+            for (int e = 0; e < G * 4; ++e) f[e] = swap_add32(o[e], o[e + G * 4]);
+#pragma unroll
+            for (int e = 0; e < G * 2; ++e) {
+                r[e] = swap_add16(f[e], f[e + G * 2]);
+                if constexpr (LPR == 8) r[e] += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(r[e]), 0x128, 0xF, 0xF, true));
+            }
+            const int E0 = (lane >> 5) * G * 4 + ((lane >> 4) & 1) * G * 2;
+            const bool whole = ends && begun >= x0;
+            const bool writes = LPR == 16 || (lane & 8) == 0;
+            float* part = (float*)p.ws + gqa_partial_word(n) + (size_t)(gid + seg * HU + cur.hu) * (G * (D + 2));
+#pragma unroll
+            for (int e = 0; e < G * 2; e += 4) {
+                const int g = (E0 + e) / 8, col = sub * 8 + (E0 + e) % 8;
+                if (whole) {
+                    const float den = __shfl(l, g, kWave), inv = den > 0.f ? 1.f : 0.f;     // an empty segment gives zeros
+                    float y[4];
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) y[z] = inv > 0.f ? r[e + z] / den : 0.f;
+                    if (writes)
+                        *(uint2*)((bf16_t*)p.out + ((size_t)cur.sl * p.H + cur.hu * G + g) * D + col) =
+                            make_uint2((uint32_t)f32_to_bf16(y[0]) | ((uint32_t)f32_to_bf16(y[1]) << 16), (uint32_t)f32_to_bf16(y[2]) | ((uint32_t)f32_to_bf16(y[3]) << 16));
+                } else if (writes) {
+                    *(float4*)(part + g * D + col) = make_float4(r[e], r[e + 1], r[e + 2], r[e + 3]);
+                }
+            }
+            if (!whole && lane < G) *(float2*)(part + G * D + 2 * lane) = make_float2(m_run, l);
+            if (!more) break;
+            begun = x + 1;
+            fresh_unit = true;
+        }
+        advance(cur, blk, seg);
     }
-    item = item_next;
-  }
 }
 
-
+// Adds up the partial results of every unit that several wavefronts shared, in groups of consecutive pieces, each in block
+// order, and stores the new lengths.  One workgroup per unit: a unit of a long segment can have as many pieces as there are
+// wavefronts, and in one wavefront their loads would follow each other (B2 H32/4 N8192, 73 pieces: 36 us).
+constexpr int kMergeThreads = 512;
+template <int D, int G, bool EV>
+__global__ void __launch_bounds__(kMergeThreads)
+decode_gqa_merge_kernel(DecodeParams p) {
+    constexpr int NE = G * D / 4, PG = kMergeThreads / NE, PST = G * (D + 2);   // float4 elements, groups of pieces
+    __shared__ float s_m[kMergeThreads / kWave][G], s_d[PG][G];
+    __shared__ __attribute__((aligned(16))) float s_num[PG][G * D];
+    const int HU = p.H / G, tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int i = blockIdx.x / HU, hu = blockIdx.x - i * HU, sl = seg_slot(p, i);
+    const int share = p.ws[0];
+    const int first = p.ws[kGqaHdr + i], nb = p.ws[kGqaHdr + i + 1] - first;
+    if (hu == 0 && tid == 0)
+        p.lens[sl] = seg_state<EV>(p, p.lens[sl] & kLenMask, p.caps[sl], p.seg_off[sl], EV ? p.base_lens[sl] : 0).len_next;
+    const int b0 = first * HU + hu * nb, w0 = b0 / share, np = (b0 + nb - 1) / share - w0 + 1;
+    if (np == 1) return;                                 // one wavefront had it all and wrote the output
+    const float* ws = (const float*)p.ws + gqa_partial_word(p.n_seg);
+    auto piece = [&](int k) { return ws + (size_t)(w0 + k + (int)blockIdx.x) * PST; };
+    // the maximum of each head
+    {
+        const int g = tid % G;
+        float m = -INFINITY;
+        for (int k = tid / G; k < np; k += kMergeThreads / G) m = fmaxf(m, piece(k)[G * D + 2 * g]);
+#pragma unroll
+        for (int d = G; d < kWave; d <<= 1) m = fmaxf(m, __shfl_xor(m, d, kWave));
+        if (lane < G) s_m[wv][lane] = m;
+    }
+    __syncthreads();
+    const int e = tid % NE, pg = tid / NE, g = e * 4 / D;
+    float M = s_m[0][g];
+#pragma unroll
+    for (int w = 1; w < kMergeThreads / kWave; ++w) M = fmaxf(M, s_m[w][g]);
+    const float ref = M == -INFINITY ? 0.f : M;
+    const int per = (np + PG - 1) / PG, k1 = (pg + 1) * per < np ? (pg + 1) * per : np;
+    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+    float den = 0.f;
+#pragma unroll 8
+    for (int k = pg * per; k < k1; ++k) {
+        const float2 md = *(const float2*)(piece(k) + G * D + 2 * g);
+        const float4 v = *(const float4*)(piece(k) + 4 * e);
+        const float wgt = __builtin_amdgcn_exp2f(md.x - ref);
+        num.x = fmaf(wgt, v.x, num.x); num.y = fmaf(wgt, v.y, num.y);
+        num.z = fmaf(wgt, v.z, num.z); num.w = fmaf(wgt, v.w, num.w);
+        den = fmaf(wgt, md.y, den);
+    }
+    if constexpr (PG > 1) {
+        *(float4*)&s_num[pg][4 * e] = num;
+        if (4 * e % D == 0) s_d[pg][g] = den;
+        __syncthreads();
+        if (pg != 0) return;
+#pragma unroll
+        for (int k = 1; k < PG; ++k) {
+            const float4 v = *(const float4*)&s_num[k][4 * e];
+            num.x += v.x; num.y += v.y; num.z += v.z; num.w += v.w;
+            den += s_d[k][g];
+        }
+    }
+    const bool some = den > 0.f;                         // an empty segment gives zeros
+    const float y0 = some ? num.x / den : 0.f, y1 = some ? num.y / den : 0.f, y2 = some ? num.z / den : 0.f, y3 = some ? num.w / den : 0.f;
+    *(uint2*)((bf16_t*)p.out + ((size_t)sl * p.H + hu * G) * D + 4 * e) =
+        make_uint2((uint32_t)f32_to_bf16(y0) | ((uint32_t)f32_to_bf16(y1) << 16), (uint32_t)f32_to_bf16(y2) | ((uint32_t)f32_to_bf16(y3) << 16));
+}
 
 // Number of compute units of the current device (queried once per device).
 int compute_units() {
@@ -962,49 +1010,32 @@ static hipError_t launch_decode_g(const DecodeParams& p, int G, int nblk, hipStr
     return launch_decode_s<BF16, LPR, 1, EV>(p, nblk, st);
 }
 
-// Workspace layout of the grouped-query path for n_seg segments (see decode_plan_kernel).
-struct GqaLayout {
-    int pieces_cap, record_word, partial_word;
-    size_t bytes;
-};
-static GqaLayout gqa_layout(int n_seg, int H, int G, int D, int N) {
-    GqaLayout g;
-    const int HU = H / G;
-    g.pieces_cap = n_seg * (2 + N / 512);
-    g.record_word = (int)(((size_t)kPlanHdr + (size_t)n_seg * HU + 15) / 16 * 16);
-    g.partial_word = g.record_word + g.pieces_cap * kRecWords;
-    g.bytes = ((size_t)g.partial_word + (size_t)g.pieces_cap * HU * G * (D + 2)) * 4;
-    return g;
+// What the size query asks for with grouped queries: (2 + N / 512) partial results per unit and 16 words for each piece of a
+// segment, as earlier versions used it and callers have sized by.  It bounds the number of wavefronts (one slot for each of them
+// and each unit).
+static size_t gqa_ws_words(int n_seg, int H, int G, int D, int N) {
+    const size_t HU = H / G, pieces = (size_t)n_seg * (2 + N / 512);
+    return (kGqaHdr + n_seg * HU + 15) / 16 * 16 + pieces * 16 + pieces * HU * G * (D + 2);
 }
 
 size_t decode_ws_bytes(const pkv_shape& s) {
     const int G = pick_group(s.H / s.Hkv);
     if (s.dtype != PKV_BF16 || G < 2) return 0;
-    return gqa_layout(s.B * s.L, s.H, G, s.D, s.N).bytes;
+    return gqa_ws_words(s.B * s.L, s.H, G, s.D, s.N) * 4;
 }
 
-// Grouped-query bf16 launches: the planning kernel, then one resident round of workgroups of W wavefronts
-// (2 wavefronts per SIMD) that claim (piece, head group) items until the list is empty.
+// Grouped-query bf16 launches: one resident round of wavefronts over the stream of blocks, then the partial results.
 template <int D, int G, bool EV>
 static hipError_t launch_gqa_s(DecodeParams p, const pkv_shape& s, int* ws, hipStream_t st) {
-    constexpr int W = 4;
-    // Only the 4-wavefront workgroup is instantiated.  8-wavefront workgroups (with 2048-row pieces) were slower
-    // on every workload they were measured on, and one run of that shape ended in a GPU fault whose cause is
-    // not known; the shape must not be used until it is.
-    static_assert(W == 4, "decode_gqa_kernel is validated for 4 wavefronts per workgroup only");
-    const GqaLayout lay = gqa_layout(s.B * p.nl, s.H, G, D, s.N);
-    p.G = G; p.n_seg = s.B * p.nl; p.S0 = 1024; p.pieces_cap = lay.pieces_cap; p.record_word = lay.record_word; p.partial_word = lay.partial_word;
-    p.plan = ws;
-    int plan_threads = kWave;
-    while (plan_threads < p.n_seg && plan_threads < kPlanThreads) plan_threads <<= 1;
-    hipLaunchKernelGGL((decode_plan_kernel<EV>), dim3(1), dim3(plan_threads), 0, st, p);
-    int grid = compute_units() * (8 / W);
-    const long long most = (long long)lay.pieces_cap * (s.H / G);
-    if (grid > most) grid = (int)most;
-    // 32-row blocks: with 64-row blocks the eight-head kernel spills at D = 128 (54.1 vs 50.7 us per step) and
-    // the four-head kernel sits at the register limit (124.2 vs 119.9 us per step on the long-context workload)
-    constexpr int NT = 2;
-    hipLaunchKernelGGL((decode_gqa_kernel<D, G, NT, W, 2, EV>), dim3(grid), dim3(W * kWave), 0, st, p);
+    p.n_seg = s.B * p.nl;
+    p.ws = ws;
+    const long long slots = (long long)(gqa_ws_words(s.B * s.L, s.H, G, D, s.N) - gqa_partial_word(p.n_seg)) / (G * (D + 2));
+    const long long units = (long long)p.n_seg * (s.H / G);
+    long long waves = (long long)compute_units() * 8;      // two wavefronts per SIMD
+    if (waves > slots - units) waves = slots - units;
+    p.waves = (int)waves;
+    hipLaunchKernelGGL((decode_gqa_kernel<D, G, EV>), dim3((unsigned)((waves + kGqaWaves - 1) / kGqaWaves)), dim3(kGqaWaves * kWave), 0, st, p);
+    hipLaunchKernelGGL((decode_gqa_merge_kernel<D, G, EV>), dim3((unsigned)units), dim3(kMergeThreads), 0, st, p);
     return hipGetLastError();
 }
 
@@ -1044,7 +1075,7 @@ static DecodeParams make_params(const pkv_shape& s, int l0, int l1, const void* 
     p.kc = (unsigned char*)kc; p.vc = (unsigned char*)vc; p.seg_off = seg_off; p.caps = caps;
     p.lens = lens; p.out = (unsigned char*)out;
     p.N = s.N; p.t = 0; p.d = 0; p.base_lens = nullptr; p.kept_pos = nullptr;
-    p.G = 1; p.n_seg = 0; p.S0 = 0; p.pieces_cap = 0; p.record_word = 0; p.partial_word = 0; p.plan = nullptr;
+    p.n_seg = 0; p.waves = 0; p.ws = nullptr;
     p.rank = RankedShape{0, 0, 0, false};
     return p;
 }

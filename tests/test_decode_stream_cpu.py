@@ -1,0 +1,90 @@
+"""The block stream of the grouped-query decode: gqa_share of csrc/decode_rows.hpp, compiled for the host, and the index rules
+of decode_gqa_kernel and decode_gqa_merge_kernel around it.  Every block of every unit is worked on exactly once; every
+shared unit's pieces lie in slots of their own, which the merge finds, inside the workspace that the size query returns."""
+import ctypes as C
+import os
+import random
+import subprocess
+
+import pytest
+
+import paper_2412_03409_amd as P
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2412_03409_amd", "csrc")
+SHIM = """
+#define __device__
+#define __host__
+#define __forceinline__ inline
+#include "decode_rows.hpp"
+extern "C" int share(int all, int waves) { return pkv::gqa_share(all, waves); }
+"""
+
+
+@pytest.fixture(scope="module")
+def share(tmp_path_factory):
+    d = tmp_path_factory.mktemp("stream")
+    (d / "shim.cpp").write_text(SHIM)
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cpp"), "-o", str(d / "shim.so")])
+    return C.CDLL(str(d / "shim.so")).share
+
+
+def walk(share, lens, HU, BR, waves):
+    """Highest slot used; asserts the rest."""
+    nb = [max(1, -(-n // BR)) for n in lens]
+    first = [0]
+    for x in nb:
+        first.append(first[-1] + x)
+    everything = first[-1] * HU
+    S = share(everything, waves)
+    owner, slots = {}, {}
+    for w in range(waves):
+        x0, x1 = w * S, min(w * S + S, everything)
+        if x0 >= everything:
+            continue
+        y0 = x0 // HU
+        seg = max(i for i in range(len(nb)) if first[i] <= y0)
+        hu, blk = divmod(x0 - first[seg] * HU, nb[seg])
+        assert hu < HU
+        begun = x0 - blk
+        for x in range(x0, x1):
+            assert (seg, hu, blk) not in owner
+            owner[seg, hu, blk] = w
+            ends, more = blk + 1 == nb[seg], x + 1 < x1
+            if (ends or not more) and not (ends and begun >= x0):
+                slot = w + seg * HU + hu
+                assert slot not in slots
+                slots[slot] = seg, hu
+            if ends:
+                seg, hu, blk, begun = (seg, hu + 1, 0, x + 1) if hu + 1 < HU else (seg + 1, 0, 0, x + 1)
+            else:
+                blk += 1
+    assert len(owner) == everything
+    top = max(slots, default=-1)
+    for seg in range(len(nb)):
+        for hu in range(HU):
+            b0 = first[seg] * HU + hu * nb[seg]
+            w0, pieces = b0 // S, (b0 + nb[seg] - 1) // S - b0 // S + 1
+            assert {owner[seg, hu, b] for b in range(nb[seg])} == set(range(w0, w0 + pieces))
+            for k in range(pieces if pieces > 1 else 0):
+                assert slots.pop(w0 + k + seg * HU + hu) == (seg, hu)
+    assert not slots
+    return top
+
+
+def test_every_block_once(share):
+    rng = random.Random(0)
+    for _ in range(1500):
+        n, HU, waves = rng.randint(1, 40), rng.choice([1, 2, 3, 8]), rng.choice([1, 2, 7, 64, 300])
+        lens = [rng.choice([0, 1, rng.randint(0, 40), rng.randint(0, 900)]) for _ in range(n)]
+        assert walk(share, lens, HU, rng.choice([16, 32]), waves) < waves + n * HU
+
+
+@pytest.mark.parametrize("G,HU", [(2, 1), (4, 8), (8, 3)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_slots_fit_the_workspace(G, HU, D):
+    for n_seg, N in [(1, 1), (1, 8192), (5, 300), (64, 511), (64, 512), (640, 100)]:
+        B, L = (n_seg // 64, 64) if n_seg % 64 == 0 else (1, n_seg)
+        words = P.prefixkv_workspace_bytes(3, B, L, G * HU, HU, N, D, P.PKV_BF16) // 4
+        units = n_seg * HU
+        slots = (words - (16 + n_seg + 1 + 15) // 16 * 16) // (G * (D + 2))
+        assert slots - units >= 1                     # at least one wavefront
