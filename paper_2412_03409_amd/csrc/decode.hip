@@ -63,6 +63,11 @@ __device__ __forceinline__ uint4 load_stream16(const unsigned char* p) {
     return make_uint4(t.x, t.y, t.z, t.w);
 }
 
+// A word at a uniform address that no wavefront of the launch writes, by the scalar unit: a vector load would make its user
+// wait for the copies that were requested before it.
+template <class T>
+__device__ __forceinline__ T uniform_load(const T* x) { return *(const __attribute__((address_space(4))) T*)(uintptr_t)x; }
+
 template <bool BF16>
 __device__ __forceinline__ void unpack16(const uint4& r, float* f) {
     if constexpr (BF16) {
@@ -239,26 +244,54 @@ decode_attn_kernel(DecodeParams p) {
 
     const int HU = p.H / G;                      // units per segment
     const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    int UW = W, hu, i_seg;
+    int UW = W, hu, b, l;
     bool live = true;
     if constexpr (RANK > 0) {
         static_assert(W == 4, "a workgroup holds one, two or four units");
         const RankedUnit x = ranked_unit(blockIdx.x, wv, p.rank, HU, p.n_seg);
         UW = x.UW; hu = x.hu; live = x.live;
         if (!live && UW != 2) return;                      // no barrier ahead, or the whole workgroup has none
-        i_seg = 0;
+        int i_seg = 0;
         if (live) i_seg = x.first + (p.rank.by_length ? ranked_segment<RANK>(p.caps, x.n, p.nl, p.L, p.l0, x.first, x.rank, lane) : x.rank);
+        b = i_seg / p.nl; l = p.l0 + i_seg % p.nl;
     } else {
-        hu = blockIdx.x % HU; i_seg = blockIdx.x / HU;
+        hu = blockIdx.x; l = p.l0 + blockIdx.y; b = blockIdx.z;
     }
     const int uw = wv & (UW - 1);
-    const int b = i_seg / p.nl, l = p.l0 + i_seg % p.nl, sl = b * p.L + l;
+    const int sl = b * p.L + l;
     const int sub = lane % LPR, rg = lane / LPR;
     const int row_bytes = p.D * ESZ;
 
-    const int len_old = __builtin_amdgcn_readfirstlane(__hip_atomic_load(p.lens + sl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) & kLenMask;
-    const int cap = p.caps[sl];
-    const int64_t off = p.seg_off[sl];
+    // What the first rows wait for.  One unit per workgroup: in one round trip to memory (left to itself the compiler waits for
+    // the length before it requests the capacity, and for that before the offset and the queries).  The ranked launches have
+    // enough other wavefronts, and there it cost 1 ... 2 %.
+    int len_raw = __hip_atomic_load(p.lens + sl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int cap = uniform_load(p.caps + sl);
+    int64_t off = uniform_load(p.seg_off + sl);
+    int base = EV ? uniform_load(p.base_lens + sl) : 0;
+    float qs = uniform_load(p.scale + l);
+    uint4 qr[G];
+    auto load_q = [&]() {
+#pragma unroll
+        for (int g = 0; g < G; ++g) qr[g] = *(const uint4*)(p.q + ((int64_t)sl * p.H + hu * G + g) * row_bytes + sub * 16);
+    };
+    if constexpr (RANK == 0) {
+        load_q();
+        asm volatile("" : "+v"(len_raw), "+s"(cap), "+s"(off), "+s"(base), "+s"(qs) : : "memory");
+    }
+    const int len_old = __builtin_amdgcn_readfirstlane(len_raw) & kLenMask;
+    // The unit is counted in once every wavefront of it has read lens.  Small launches: here, so that the round trip of the
+    // atomic passes under the rows; it is the last wavefront's, which has the fewest.  (32 units 5.36 -> 4.94 us per launch, 240
+    // 8.5 -> 8.1; not for the larger ones: the atomics of 1024 units meet at the start of the launch, 19.9 -> 25.7.)
+    constexpr bool kEarly = W == 8;
+    const bool counter = live && uw == (kEarly ? UW - 1 : 0) && lane == 0;
+    int counted = 0;
+    if constexpr (kEarly) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        if (counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
+    }
     // plain step: append at slot len_old.  Pruning step: len_old counts the permanent entries, the new
     // token goes to ring slot (t-1) mod (d+1), and the token stored d steps ago (ring slot t mod (d+1))
     // either becomes permanent entry len_old or is left out from now on.
@@ -268,7 +301,6 @@ decode_attn_kernel(DecodeParams p) {
     int ring0 = 0, cs = 0;
     bool grad = false, decide = false;
     if constexpr (EV) {
-        const int base = p.base_lens[sl];
         ring0 = cap - (p.d + 1);
         app = base >= 0 && ring0 >= base && len_old <= ring0;   // else: capacity cannot hold the ring
         decide = app && p.t > p.d;
@@ -283,8 +315,8 @@ decode_attn_kernel(DecodeParams p) {
         len_next = len_old + (grad ? 1 : 0);
     }
     const int nb = live ? (len + BR - 1) / BR : 0;
-    const int kvh = (hu * G) / p.grp;
-    const bool writer = app && live && ((hu * G) % p.grp == 0);
+    const int kvh = p.grp == G ? hu : (hu * G) / p.grp;
+    const bool writer = app && live && (p.grp == G || (hu * G) % p.grp == 0);
     const int64_t segbase = (off * p.Hkv + (int64_t)kvh * cap) * row_bytes;
     const int64_t newrow = ((int64_t)sl * p.Hkv + kvh) * row_bytes;
     unsigned char* kseg = p.kc + segbase;
@@ -299,11 +331,11 @@ decode_attn_kernel(DecodeParams p) {
     }
     if (uw < nb) {
         float qf[G][EPL];
-        const float qs = p.scale[l] * 1.4426950408889634f;
+        if constexpr (RANK > 0) load_q();
+        qs *= 1.4426950408889634f;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const uint4 qr = *(const uint4*)(p.q + ((int64_t)sl * p.H + hu * G + g) * row_bytes + sub * 16);
-            unpack16<BF16>(qr, qf[g]);
+            unpack16<BF16>(qr[g], qf[g]);
 #pragma unroll
             for (int x = 0; x < EPL; ++x) qf[g][x] *= qs;
         }
@@ -363,10 +395,8 @@ decode_attn_kernel(DecodeParams p) {
             }
         }
     }
-    // Count the unit in once every wavefront of it has read lens (UW > 1: behind the barrier below); the round
-    // trip of the atomic passes while the output is written.
-    const bool counter = live && uw == 0 && lane == 0;
-    int counted = 0;
+    // The other launches count the unit in here (UW > 1: behind the barrier below); the round trip of the atomic passes while the
+    // output is written.
     if (UW == 1) {
         if (counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
         if (live && rg == 0) {
@@ -397,7 +427,7 @@ decode_attn_kernel(DecodeParams p) {
             }
         }
         __syncthreads();
-        if (counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
+        if (!kEarly && counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
         // merge the wavefronts of a unit: thread (g, d)
         const int w0 = wv & ~(UW - 1);
         for (int i = uw * kWave + lane; live && i < G * p.D; i += UW * kWave) {
@@ -504,11 +534,6 @@ __device__ __forceinline__ int seg_slot(const DecodeParams& p, int i) { return (
 // along the stream one of the two goes up from one piece to the next, so no two pieces share a slot.
 constexpr int kGqaHdr = 16;
 __host__ __device__ inline int gqa_partial_word(int n_seg) { return (kGqaHdr + n_seg + 1 + 15) / 16 * 16; }
-
-// A word at a uniform address that no wavefront of the launch writes, by the scalar unit: a vector load would make its user
-// wait for the copies that were requested before it.
-template <class T>
-__device__ __forceinline__ T uniform_load(const T* x) { return *(const __attribute__((address_space(4))) T*)(uintptr_t)x; }
 
 // inclusive sum over the lanes
 __device__ __forceinline__ int wave_scan(int v, int lane) {
@@ -965,7 +990,8 @@ int compute_units() {
 // wavefronts in blocks of NI * 64/LPR rows.  What decides is how many wavefronts a launch has: 16 per compute unit are
 // resident (4 per SIMD), and starting one costs the dispatcher about 7 ns whatever it does (12 800 units: 393 us with
 // four wavefronts each, 173 us with one, for rows that stream in 150 us).  Hence
-//   up to 2 units per compute unit: 8 wavefronts per unit (32 units, one layer of the 7B shape: 8.6 -> 6.1 us);
+//   up to 2 units per compute unit: 8 wavefronts per unit (32 units, one layer of the 7B shape: 8.6 -> 6.1 us; 16 wavefronts
+//       per unit 6.2);
 //   up to 4: 4 wavefronts per unit, which fill the chip (7B, batch 1, lengths within a factor 30: 21.3 -> 18.7 us; equal: 21.7
 //       -> 21.0; equal lengths of 2048 rows and more are 1 ... 10 % slower than with two wavefronts and 16 loads in flight
 //       each, 164.1 -> 169.6 us at 1024 units);
@@ -981,11 +1007,11 @@ static hipError_t launch_decode_s(DecodeParams p, int nblk, hipStream_t st) {
     const int HU = p.H / G, cus = compute_units();
     p.n_seg = nblk / HU;
     if (nblk <= 2 * cus) {
-        hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 8, OCC, EV, 0>), dim3(nblk), dim3(8 * kWave), 0, st, p);
+        hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 8, OCC, EV, 0>), dim3(HU, p.nl, p.B), dim3(8 * kWave), 0, st, p);
         return hipGetLastError();
     }
     if (nblk <= 4 * cus) {
-        hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, 0>), dim3(nblk), dim3(4 * kWave), 0, st, p);
+        hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, 0>), dim3(HU, p.nl, p.B), dim3(4 * kWave), 0, st, p);
         return hipGetLastError();
     }
     const int ngrp = (p.n_seg + kRankRegs * kWave - 1) / (kRankRegs * kWave);
