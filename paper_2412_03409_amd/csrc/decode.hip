@@ -81,6 +81,41 @@ __device__ __forceinline__ void unpack16(const uint4& r, float* f) {
     }
 }
 
+// The other lanes' values come by DPP and lane swaps, not through LDS: a step of a shuffle by ds_bpermute is a round trip of
+// some hundred cycles, and a block of rows needs six in a row (32 units, one layer of the 7B shape 5.63 -> 5.36 us per launch,
+// 768 units of 1200 rows 88.5 -> 84.3).  Same sums in the same order.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xF, 0xF, true));
+}
+template <class F> __device__ __forceinline__ float with_xor16(float x, F f) {
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return f(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+template <class F> __device__ __forceinline__ float with_xor32(float x, F f) {
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return f(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+// Sum over the LPR lanes of a row, in all of them.  Once the lanes of a quad (of a half of 16) agree, the mirrored lane has what
+// the lane at distance 4 (8) has.
+template <int LPR>
+__device__ __forceinline__ float row_sum(float x) {
+    static_assert(LPR == 8 || LPR == 16 || LPR == 32, "16 bytes per lane, D 64 or 128");
+    x += dpp<0xB1>(x);                                     // quad_perm [1,0,3,2]
+    x += dpp<0x4E>(x);                                     // quad_perm [2,3,0,1]
+    x += dpp<0x141>(x);                                    // row_half_mirror
+    if constexpr (LPR >= 16) x += dpp<0x140>(x);           // row_mirror
+    if constexpr (LPR >= 32) x = with_xor16(x, [](float a, float b) { return a + b; });
+    return x;
+}
+// f over the row groups: lanes at distances LPR, 2 LPR ... 32.
+template <int LPR, class F>
+__device__ __forceinline__ float over_groups(float x, F f) {
+    if constexpr (LPR <= 8) x = f(x, dpp<0x128>(x));       // row_ror:8
+    if constexpr (LPR <= 16) x = with_xor16(x, f);
+    return with_xor32(x, f);
+}
+
 // Rows r0 .. r0 + BR - 1 of one block (BR = NI * 64/LPR; LPR lanes cover a row with 16 bytes each) into registers.
 // Blocks of occupied cache slots only take the plain path.  In the guarded one the row being appended comes from
 // k_new / v_new, under pruning ring rows map to the ring slots, and rows that do not take part (past the end, or
@@ -133,11 +168,9 @@ __device__ __forceinline__ void attend_block(const uint4 (&kr)[NI], uint4 (&vr)[
         }
     }
 #pragma unroll
-    for (int sh = 1; sh < LPR; sh <<= 1)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int i = 0; i < NI; ++i)
-#pragma unroll
-            for (int g = 0; g < G; ++g) s[g][i] += __shfl_xor(s[g][i], sh, kWave);
+        for (int g = 0; g < G; ++g) s[g][i] = row_sum<LPR>(s[g][i]);
     if (!full) {
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
@@ -154,8 +187,7 @@ __device__ __forceinline__ void attend_block(const uint4 (&kr)[NI], uint4 (&vr)[
         float mx = s[g][0];
 #pragma unroll
         for (int i = 1; i < NI; ++i) mx = fmaxf(mx, s[g][i]);
-#pragma unroll
-        for (int sh = LPR; sh < kWave; sh <<= 1) mx = fmaxf(mx, __shfl_xor(mx, sh, kWave));
+        mx = over_groups<LPR>(mx, [](float a, float b) { return fmaxf(a, b); });
         // no score above -inf so far: all keys of the wavefront's blocks are that far off, or the only row of the first
         // one is pruned in this step
         const float mnew = fmaxf(mrun[g], mx);
@@ -369,12 +401,10 @@ decode_attn_kernel(DecodeParams p) {
         // merge the RPI row groups of the wavefront (they share mrun)
 #pragma unroll
         for (int g = 0; g < G; ++g) {
+            const auto add = [](float a, float b) { return a + b; };
+            srun[g] = over_groups<LPR>(srun[g], add);
 #pragma unroll
-            for (int sh = LPR; sh < kWave; sh <<= 1) {
-                srun[g] += __shfl_xor(srun[g], sh, kWave);
-#pragma unroll
-                for (int x = 0; x < EPL; ++x) o[g][x] += __shfl_xor(o[g][x], sh, kWave);
-            }
+            for (int x = 0; x < EPL; ++x) o[g][x] = over_groups<LPR>(o[g][x], add);
         }
     }
     if constexpr (EV) {
@@ -988,7 +1018,7 @@ int compute_units() {
 
 // Launch shapes of decode_attn_kernel.  A unit is one head group of one segment; its rows are dealt to its
 // wavefronts in blocks of NI * 64/LPR rows.  What decides is how many wavefronts a launch has: 16 per compute unit are
-// resident (4 per SIMD), and starting one costs the dispatcher about 7 ns whatever it does (12 800 units: 393 us with
+// resident (4 per SIMD; 20 of a ranked launch of the plain bf16 step), and starting one costs the dispatcher about 7 ns whatever it does (12 800 units: 393 us with
 // four wavefronts each, 173 us with one, for rows that stream in 150 us).  Hence
 //   up to 2 units per compute unit: 8 wavefronts per unit (32 units, one layer of the 7B shape: 8.6 -> 6.1 us; 16 wavefronts
 //       per unit 6.2);
@@ -1003,7 +1033,7 @@ int compute_units() {
 template <bool BF16, int LPR, int G, bool EV>
 static hipError_t launch_decode_s(DecodeParams p, int nblk, hipStream_t st) {
     constexpr int NI = 4;
-    constexpr int OCC = G >= 4 ? 2 : 4;
+    constexpr int OCC = G >= 4 ? 2 : 4, RES = BF16 && !EV ? kRankedResident : 16, ROCC = RES > 16 ? RES / 4 : OCC;   // (the pruning step spills at five wavefronts per SIMD)
     const int HU = p.H / G, cus = compute_units();
     p.n_seg = nblk / HU;
     if (nblk <= 2 * cus) {
@@ -1016,10 +1046,11 @@ static hipError_t launch_decode_s(DecodeParams p, int nblk, hipStream_t st) {
     }
     const int ngrp = (p.n_seg + kRankRegs * kWave - 1) / (kRankRegs * kWave);
     p.rank.gsz = (p.n_seg + ngrp - 1) / ngrp;
-    ranked_shape(p.rank, nblk, cus, p.N, p.D * (BF16 ? 2 : 4));
+    ranked_shape(p.rank, nblk, cus, p.N, p.D * (BF16 ? 2 : 4), RES);
     const dim3 grid(ranked_blocks(p.rank, HU) * ngrp), block(4 * kWave);
-    if (p.rank.gsz <= kWave) hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, 1>), grid, block, 0, st, p);
-    else hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, kRankRegs>), grid, block, 0, st, p);
+    const int lds = BF16 ? ranked_lds(p.rank, 4ll * grid.x, cus) : 0;
+    if (p.rank.gsz <= kWave) hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, ROCC, EV, 1>), grid, block, lds, st, p);
+    else hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, ROCC, EV, kRankRegs>), grid, block, lds, st, p);
     return hipGetLastError();
 }
 

@@ -54,19 +54,34 @@ struct RankedShape { int gsz, n4, n2; bool by_length; };
 //   from one round on, prompts with keys of up to 96 KB per head in index order, one wavefront each: finding the rank costs
 //     about as much as such a unit's rows (300 positions at 20 % and 128 at 20 %: 4096 units of 60 rows x1.28 / - / 1.03, by length 1.21 / - / 0.88; 16 384 of 26 rows x1.37 /
 //     - / 1.20, by length 0.93 / - / 1.12).
-inline void ranked_shape(RankedShape& s, long long units, long long cus, int N, int row_bytes) {
-    const double per_unit = 16.0 * cus / units;           // wavefronts of one round for each unit
+// (All that with 16 wavefronts per compute unit, which is what fp32 rows and the pruning step have.)  `resident`: how many a
+// compute unit holds.  The plain bf16 step fits 20: launches of up to that many run in one round (us per launch, 16 / 20: 4096
+// units of 136 rows 72 / 56, 4800 79 / 78, 5120 90 / 79, 2048 of 300 64 / 61), and such a launch gives no unit more wavefronts
+// than the round has room for.
+constexpr int kRankedResident = 20;
+inline void ranked_shape(RankedShape& s, long long units, long long cus, int N, int row_bytes, int resident = 16) {
+    const double per_unit = (double)resident * cus / units;   // wavefronts of one round for each unit
     double f4 = 0, f2 = 0;
-    s.by_length = N * row_bytes > 96 << 10 || per_unit > 1;
+    s.by_length = N * row_bytes > 96 << 10 || units < 16 * cus;
     if (per_unit >= 2.5 || (N > 4096 && per_unit >= 0.75)) {
         f4 = 0.25; f2 = 0.75;
     } else if (s.by_length && per_unit >= 0.5) {
         f4 = (per_unit - 1) / 4;
-        f4 = f2 = f4 > 0.125 ? 0.125 : f4 < 0.0625 ? 0.0625 : f4;
+        f4 = f2 = f4 > 0.125 ? 0.125 : f4 < 0.0625 && (per_unit < 1 || resident == 16) ? 0.0625 : f4;
     }
     s.n4 = (int)(s.gsz * f4 + 0.5);
     s.n2 = (int)(s.gsz * f2 + 0.5);
     if (s.n2 > s.gsz - s.n4) s.n2 = s.gsz - s.n4;
+}
+
+// LDS that a bf16 launch of `waves` wavefronts asks for beyond its own 2 KB, to have fewer workgroups resident.  Launches of
+// several rounds are bound by memory, and that serves fewer streams of rows faster: with two workgroups per compute unit
+// instead of five 12 800 units of 136 rows take 179 -> 171 us, 6400 of 400 rows 239 -> 225, 8192 of 136 122 -> 115 (with four
+// 119).  Up to an eighth over one round filling it counts more (2880 units of 480 rows 67 -> 71 with two), and short rows wait
+// for their starts (8192 units of 40 rows 58 -> 79).
+inline int ranked_lds(const RankedShape& s, long long waves, long long cus) {
+    const long long round = kRankedResident * cus;
+    return s.by_length && 8 * waves > 9 * round ? 51 << 10 : 0;
 }
 
 __host__ __device__ __forceinline__ int ranked_blocks(const RankedShape& s, int HU) {   // per group
