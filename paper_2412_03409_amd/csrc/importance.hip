@@ -471,7 +471,15 @@ importance_stream_kernel(StreamParams p) {
     float c = p.scale[l] * kLog2e;
     const bool flip = c < 0.f;
     c = fmaxf(fabsf(c), 1e-30f);
-    const int x0 = blk * BLK, xw = x0 + wv * 32 * NK;     // first stationary row of the workgroup, of the wavefront
+    // The earlier tiles of a block (COLS = false: the later ones) have up to 4 * NK products more than the others, and wavefront w
+    // of every workgroup runs on the same SIMD.  So a wavefront takes tiles w and 7 - w; with one tile each, the order differs
+    // between the two groups and between the workgroups of a compute unit.  (With products in the future left out one by one
+    // instead of a wavefront's stage at a time: attention and importance of B8 H40 N1021 208 -> 204 us, both sweeps of B1 L8
+    // H32/8 N2000 314 -> 303, of H32/4 N8192 602 -> 596.)
+    const int x0 = blk * BLK;                             // first stationary row of the workgroup
+    const int tw = NK == 2 ? wv : GS > 1 ? (gs == 0 ? wv : kStWaves - 1 - wv) : (wv + j / 32) % kStWaves;
+    auto tile = [&](int t) { return x0 + 32 * (t == 0 ? tw : 2 * kStWaves - 1 - tw); };   // first row of the wavefront's tile t
+    const int xw = tile(0), xl = tile(NK - 1);            // of its earliest and its latest one
     const int first = COLS ? x0 : 0;                      // first streamed row
     const int nst = COLS ? (p.N - x0 + kStStage - 1) / kStStage : (min(p.N, x0 + BLK) + kStStage - 1) / kStStage;
 
@@ -501,7 +509,7 @@ importance_stream_kernel(StreamParams p) {
     bf16x8 f[NK][KS];
 #pragma unroll
     for (int t = 0; t < NK; ++t) {
-        int row = xw + 32 * t + ln;
+        int row = tile(t) + ln;
         row = row < p.N ? row : p.N - 1;
         const uint32_t sgn = flip ? 0x80008000u : 0u;
 #pragma unroll
@@ -521,12 +529,15 @@ importance_stream_kernel(StreamParams p) {
 #pragma unroll
     for (int t = 0; t < NK; ++t) { mrun[t] = -INFINITY; srun[t] = 0.f; }
 
-    // one stage; MASKED: some of its pairs are in the future
-    auto attend = [&](auto masked_tag, int st, const unsigned char* buf, int par) {
-        constexpr bool MASKED = decltype(masked_tag)::value;
+    // one stage; DIAG: it holds rows in the future of some of the wavefront's tiles.  There a product wholly in the future is left
+    // out and only the one on the diagonal is masked.
+    auto attend = [&](auto diag_tag, int st, const unsigned char* buf, int par) {
+        constexpr bool DIAG = decltype(diag_tag)::value;
         const int r0 = first + st * kStStage;
 #pragma unroll
         for (int u = 0; u < kStStage / 32; ++u) {
+            const int ru = r0 + 32 * u;
+            if (DIAG && (COLS ? ru < xw : ru > xl)) continue;
             bf16x8 fr[KS];
 #pragma unroll
             for (int kk = 0; kk < KS; ++kk) fr[kk] = as_bf16x8(*(const uint4*)(buf + u * 32 * ROWB + aoff[kk]));
@@ -540,22 +551,29 @@ importance_stream_kernel(StreamParams p) {
             }
 #pragma unroll
             for (int t = 0; t < NK; ++t) {
+                const int xt = tile(t);
+                if (DIAG && (COLS ? ru < xt : ru > xt || xt >= p.N)) continue;
                 f32x16 acc = {0};
 #pragma unroll
                 for (int kk = 0; kk < KS; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[kk], f[t][kk], acc, 0, 0, 0);
-                // register r holds streamed row r0 + 32*u + 4*hf + 8*(r/4) + r%4
-                const int d = xw + 32 * t + ln - (r0 + 32 * u + 4 * hf);
+                // register r holds streamed row ru + 4*hf + 8*(r/4) + r%4
+                const int d = xt + ln - (ru + 4 * hf);
                 if constexpr (COLS) {
                     float ps = 0.f;
+                    if (DIAG && ru == xt) {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const float e = __builtin_amdgcn_exp2f(fmaf(acc[r], c, nl[r]));
-                        ps += !MASKED || 8 * (r >> 2) + (r & 3) >= d ? e : 0.f;
+                        for (int r = 0; r < 16; ++r) {
+                            const float e = __builtin_amdgcn_exp2f(fmaf(acc[r], c, nl[r]));
+                            ps += 8 * (r >> 2) + (r & 3) >= d ? e : 0.f;
+                        }
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) ps += __builtin_amdgcn_exp2f(fmaf(acc[r], c, nl[r]));
                     }
                     srun[t] += ps;
                 } else {
-                    if constexpr (MASKED) {
-                        const int lim = min(d, p.N - 1 - (r0 + 32 * u + 4 * hf));
+                    if (DIAG && ru == xt) {
+                        const int lim = min(d, p.N - 1 - (ru + 4 * hf));
 #pragma unroll
                         for (int r = 0; r < 16; ++r) acc[r] = 8 * (r >> 2) + (r & 3) <= lim ? acc[r] : -INFINITY;
                     }
@@ -574,18 +592,18 @@ importance_stream_kernel(StreamParams p) {
             }
         }
     };
-    constexpr std::true_type masked{};
+    constexpr std::true_type diag{};
     constexpr std::false_type plain{};
     auto sync = [&](int par) {
         if (COLS && wv == 0) s_nl[par][gs][lane] = nl_next;
         wait_async_copies();
         __syncthreads();
     };
-    // a stage in the future of, across or past the wavefront's rows
+    // a stage in the future of, across or past the wavefront's tiles
     auto step = [&](int st, const unsigned char* buf, int par) {
-        const int r0 = first + st * kStStage, r1 = r0 + kStStage - 1, xe = xw + 32 * NK - 1;
-        if (xw >= p.N || st >= nst || (COLS ? r1 < xw : r0 > xe)) return;
-        if (COLS ? r0 >= xe : r1 <= xw && r1 < p.N) attend(plain, st, buf, par); else attend(masked, st, buf, par);
+        const int r0 = first + st * kStStage, r1 = r0 + kStStage - 1;
+        if (xw >= p.N || st >= nst || (COLS ? r1 < xw : r0 > xl + 31)) return;
+        if (xl < p.N && (COLS ? r0 > xl : r1 < xw)) attend(plain, st, buf, par); else attend(diag, st, buf, par);
     };
     for (int i = 0; i < nst; i += 2 * GS) {
         const int st = i + gs;
@@ -603,16 +621,16 @@ importance_stream_kernel(StreamParams p) {
         for (int g = 1; g < GS; ++g) {
             __syncthreads();
             if (gs == g) {
-                // lane -> slot of the same wavefront index in group 0
-                s_part[0][wv][lane] = srun[0];
-                if (!COLS) s_part[1][wv][lane] = mrun[0];
+                // lane -> slot of the wavefront with the same tile in group 0
+                s_part[0][tw][lane] = srun[0];
+                if (!COLS) s_part[1][tw][lane] = mrun[0];
             }
             __syncthreads();
             if (gs == 0) {
-                const float so = s_part[0][wv][lane];
+                const float so = s_part[0][tw][lane];
                 if constexpr (COLS) srun[0] += so;
                 else {
-                    const float mo = s_part[1][wv][lane], M = fmaxf(mrun[0], mo), ref = M == -INFINITY ? 0.f : M;
+                    const float mo = s_part[1][tw][lane], M = fmaxf(mrun[0], mo), ref = M == -INFINITY ? 0.f : M;
                     srun[0] = srun[0] * __builtin_amdgcn_exp2f(mrun[0] - ref) + so * __builtin_amdgcn_exp2f(mo - ref);
                     mrun[0] = M;
                 }
@@ -623,7 +641,7 @@ importance_stream_kernel(StreamParams p) {
     // the two halves of a stationary row
 #pragma unroll
     for (int t = 0; t < NK; ++t) {
-        const int row = xw + 32 * t + ln;
+        const int row = tile(t) + ln;
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(srun[t]), __float_as_uint(srun[t]), false, false);
         const float s0 = __uint_as_float(sw[0]), s1 = __uint_as_float(sw[1]);
         float res = s0 + s1;
