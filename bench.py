@@ -167,7 +167,7 @@ def _decode_source_digest():
 
 def decode_roofline(w, r, lens0, T, dec_ms, d_ev=None):
     """Roofline of the decode launch.  The decode loop is T launches of one kernel (for grouped-query bf16
-    caches: a planning kernel and the attention kernel, timed together) and nothing else, back to back on one
+    caches: the attention kernel and the one that adds up its partial results, timed together) and nothing else, back to back on one
     stream (a HIP graph by default), so the event time of the loop divided by T is the average launch
     duration over the timed region."""
     n_seg, esz = w.B * w.L, w.elem_bytes
