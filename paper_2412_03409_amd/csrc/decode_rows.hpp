@@ -74,14 +74,14 @@ inline void ranked_shape(RankedShape& s, long long units, long long cus, int N, 
     if (s.n2 > s.gsz - s.n4) s.n2 = s.gsz - s.n4;
 }
 
-// LDS that a bf16 launch of `waves` wavefronts asks for beyond its own 2 KB, to have fewer workgroups resident.  Launches of
-// several rounds are bound by memory, and that serves fewer streams of rows faster: with two workgroups per compute unit
-// instead of five 12 800 units of 136 rows take 179 -> 171 us, 6400 of 400 rows 239 -> 225, 8192 of 136 122 -> 115 (with four
-// 119).  Up to an eighth over one round filling it counts more (2880 units of 480 rows 67 -> 71 with two), and short rows wait
-// for their starts (8192 units of 40 rows 58 -> 79).
+// LDS that a bf16 launch of `waves` wavefronts asks for beyond its own 2 KB, to have four workgroups resident and not five.
+// Launches of several rounds are bound by memory, and that serves fewer streams of rows faster (us, five / four: 12 800 units of
+// 136 rows 179 / 176, 8192 of 136 122 / 119, 8192 of 90 100 / 90).  Two are better still for very unequal lengths (171, 115), but
+// 12 800 units of 264 rows on average, as the search finds them, take 298 / 299 / 320 us with five / four / two.  Up to an
+// eighth over one round filling it counts more, and short rows wait for their starts (8192 units of 40 rows 58 / 60).
 inline int ranked_lds(const RankedShape& s, long long waves, long long cus) {
     const long long round = kRankedResident * cus;
-    return s.by_length && 8 * waves > 9 * round ? 51 << 10 : 0;
+    return s.by_length && 8 * waves > 9 * round ? 31 << 10 : 0;
 }
 
 __host__ __device__ __forceinline__ int ranked_blocks(const RankedShape& s, int HU) {   // per group

@@ -42,7 +42,7 @@ def test_shape_and_lds(shim, resident, N, row_bytes):
         assert 0 <= n4 and 0 <= n2 and n4 + n2 <= gsz
         assert by_length or n4 == n2 == 0
         assert by_length or segs * 32 >= 16 * cus
-        assert lds in (0, 51 << 10) and lds + 4 * 130 * 4 <= 64 << 10
+        assert lds in (0, 31 << 10) and lds + 4 * 130 * 4 <= 64 << 10
         if lds:
             assert by_length and waves > 20 * cus
         if 20 * cus >= segs * 32 > 2.5 * 16 * cus and N <= 4096 and resident == 20:
