@@ -605,7 +605,9 @@ template <int G, class F> __device__ __forceinline__ void for_heads(F f) {
     }
 }
 
-constexpr int kGqaWaves = 4, kGqaHeld = 4;   // wavefronts of a workgroup; block counts per lane that are held between the passes
+// wavefronts of a workgroup, of a launch at most (8 on each of 256 compute units); block counts per lane that are held between the
+// passes
+constexpr int kGqaWaves = 4, kGqaWavesMax = 2048, kGqaHeld = 4;
 
 template <int D, int G, bool EV>
 __global__ void __launch_bounds__(kGqaWaves * kWave, 2)
@@ -1067,18 +1069,18 @@ static hipError_t launch_decode_g(const DecodeParams& p, int G, int nblk, hipStr
     return launch_decode_s<BF16, LPR, 1, EV>(p, nblk, st);
 }
 
-// What the size query asks for with grouped queries: (2 + N / 512) partial results per unit and 16 words for each piece of a
-// segment, as earlier versions used it and callers have sized by.  It bounds the number of wavefronts (one slot for each of them
-// and each unit).
-static size_t gqa_ws_words(int n_seg, int H, int G, int D, int N) {
-    const size_t HU = H / G, pieces = (size_t)n_seg * (2 + N / 512);
-    return (kGqaHdr + n_seg * HU + 15) / 16 * 16 + pieces * 16 + pieces * HU * G * (D + 2);
+// Workspace of a grouped-query launch in words: a slot for each unit and each wavefront of the largest launch, whatever N and the
+// layer range (see gqa_partial_word; 4.3 MB with four heads of D 128 at up to 256 units).  A size that followed the prompt's length
+// bounded the wavefronts instead: one layer a call, H 32/8, D 128, kept whole: N 500 8 wavefronts and 42 us, now 11.7; N 1000
+// 44 -> 11.8; B1 L32 N500 50 %, all layers a launch, 33 -> 16.5, H32/4 40 -> 17.5.
+static size_t gqa_ws_words(int n_seg, int H, int G, int D) {
+    return gqa_partial_word(n_seg) + ((size_t)kGqaWavesMax + (size_t)n_seg * (H / G)) * G * (D + 2);
 }
 
 size_t decode_ws_bytes(const pkv_shape& s) {
     const int G = pick_group(s.H / s.Hkv);
     if (s.dtype != PKV_BF16 || G < 2) return 0;
-    return gqa_ws_words(s.B * s.L, s.H, G, s.D, s.N) * 4;
+    return gqa_ws_words(s.B * s.L, s.H, G, s.D) * 4;
 }
 
 // Grouped-query bf16 launches: one resident round of wavefronts over the stream of blocks, then the partial results.
@@ -1086,12 +1088,10 @@ template <int D, int G, bool EV>
 static hipError_t launch_gqa_s(DecodeParams p, const pkv_shape& s, int* ws, hipStream_t st) {
     p.n_seg = s.B * p.nl;
     p.ws = ws;
-    const long long slots = (long long)(gqa_ws_words(s.B * s.L, s.H, G, D, s.N) - gqa_partial_word(p.n_seg)) / (G * (D + 2));
     const long long units = (long long)p.n_seg * (s.H / G);
-    long long waves = (long long)compute_units() * 8;      // two wavefronts per SIMD
-    if (waves > slots - units) waves = slots - units;
-    p.waves = (int)waves;
-    hipLaunchKernelGGL((decode_gqa_kernel<D, G, EV>), dim3((unsigned)((waves + kGqaWaves - 1) / kGqaWaves)), dim3(kGqaWaves * kWave), 0, st, p);
+    p.waves = compute_units() * 8;                         // two wavefronts per SIMD
+    if (p.waves > kGqaWavesMax) p.waves = kGqaWavesMax;
+    hipLaunchKernelGGL((decode_gqa_kernel<D, G, EV>), dim3((unsigned)((p.waves + kGqaWaves - 1) / kGqaWaves)), dim3(kGqaWaves * kWave), 0, st, p);
     hipLaunchKernelGGL((decode_gqa_merge_kernel<D, G, EV>), dim3((unsigned)units), dim3(kMergeThreads), 0, st, p);
     return hipGetLastError();
 }

@@ -88,3 +88,13 @@ def test_slots_fit_the_workspace(G, HU, D):
         units = n_seg * HU
         slots = (words - (16 + n_seg + 1 + 15) // 16 * 16) // (G * (D + 2))
         assert slots - units >= 1                     # at least one wavefront
+
+
+# Whatever the prompt's length and the number of segments there is a slot for each unit and for each of the 2048 wavefronts of a
+# launch on 256 compute units.
+@pytest.mark.parametrize("G,HU,D", [(2, 1, 64), (4, 8, 128), (8, 3, 128), (8, 4, 64)])
+@pytest.mark.parametrize("B,L,N", [(1, 1, 1), (1, 1, 500), (1, 1, 8192), (1, 32, 500), (10, 64, 100)])
+def test_workspace_never_bounds_a_launch(B, L, N, G, HU, D):
+    words = P.prefixkv_workspace_bytes(3, B, L, G * HU, HU, N, D, P.PKV_BF16) // 4
+    slots = (words - (16 + B * L + 1 + 15) // 16 * 16) // (G * (D + 2))
+    assert slots >= 2048 + B * L * HU
