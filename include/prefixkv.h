@@ -256,7 +256,7 @@ int prefixkv_gini(int B, int L, int N, const uint64_t *cum, double *gini, pkv_st
 int64_t prefixkv_cache_tokens_upper_bound(int B, int64_t budget_tokens, int L, int decode_capacity);
 
 /* ---- Stage 4b: one decode step over layers [l0,l1) (Sec. 3.1: the newest token's query
- * interacts with the cached KV vectors).  One kernel launch.
+ * interacts with the cached KV vectors).  One kernel launch, two where a workspace is needed.
  * If k_new/v_new are non-NULL, the new token's key/value of every (b,l,kv head) are first stored
  * in slot lens[b,l] of the segment and lens[b,l] becomes lens[b,l]+1 (the caller guarantees
  * lens < caps; a full segment drops the append and the step attends over the old slots).  Then
@@ -268,10 +268,11 @@ int64_t prefixkv_cache_tokens_upper_bound(int B, int64_t budget_tokens, int L, i
  *   lens [dev] in/out: plain lengths below 2^20 before and after the call.  WHILE the launch runs
  *       the library keeps a completion count in the bits above 2^20 of each entry, so lens must
  *       not be read or written by anything else until the launch has finished.  H <= 2048.
- *   ws: needed when several query heads share a KV head and the cache is bf16 (the segments are cut into
- *       pieces of similar size and the pieces' partial results meet in the workspace);
- *       prefixkv_workspace_bytes(PKV_OP_DECODE, shape, 0) gives the size (0 when none is needed, then
- *       ws may be NULL).  The size is for layer range [0,L); a smaller workspace is PKV_ERR_WORKSPACE. */
+ *   ws: needed when several query heads share a KV head and the cache is bf16 (the rows are shared out
+ *       evenly, and the partial results of a head that several wavefronts worked on meet in the
+ *       workspace); prefixkv_workspace_bytes(PKV_OP_DECODE, shape, 0) gives the size (0 when none is
+ *       needed, then ws may be NULL).  Any alignment; the size serves every layer range; a smaller
+ *       workspace is PKV_ERR_WORKSPACE.  Calls on different streams need workspaces of their own. */
 int prefixkv_decode_attn(const pkv_shape *shape, int l0, int l1, const void *q, const void *k_new,
                          const void *v_new, const float *scale, void *kc, void *vc,
                          const int64_t *seg_off, const int32_t *caps, int32_t *lens, void *out,

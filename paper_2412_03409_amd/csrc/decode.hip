@@ -1080,14 +1080,14 @@ static size_t gqa_ws_words(int n_seg, int H, int G, int D) {
 size_t decode_ws_bytes(const pkv_shape& s) {
     const int G = pick_group(s.H / s.Hkv);
     if (s.dtype != PKV_BF16 || G < 2) return 0;
-    return gqa_ws_words(s.B * s.L, s.H, G, s.D) * 4;
+    return gqa_ws_words(s.B * s.L, s.H, G, s.D) * 4 + kGqaWsAlign;
 }
 
 // Grouped-query bf16 launches: one resident round of wavefronts over the stream of blocks, then the partial results.
 template <int D, int G, bool EV>
-static hipError_t launch_gqa_s(DecodeParams p, const pkv_shape& s, int* ws, hipStream_t st) {
+static hipError_t launch_gqa_s(DecodeParams p, const pkv_shape& s, void* ws, hipStream_t st) {
     p.n_seg = s.B * p.nl;
-    p.ws = ws;
+    p.ws = (int*)gqa_ws_base((uintptr_t)ws);
     const long long units = (long long)p.n_seg * (s.H / G);
     p.waves = compute_units() * 8;                         // two wavefronts per SIMD
     if (p.waves > kGqaWavesMax) p.waves = kGqaWavesMax;
@@ -1097,7 +1097,7 @@ static hipError_t launch_gqa_s(DecodeParams p, const pkv_shape& s, int* ws, hipS
 }
 
 template <int D, bool EV>
-static hipError_t launch_gqa(const DecodeParams& p, const pkv_shape& s, int G, int* ws, hipStream_t st) {
+static hipError_t launch_gqa(const DecodeParams& p, const pkv_shape& s, int G, void* ws, hipStream_t st) {
     switch (G) {
         case 8: return launch_gqa_s<D, 8, EV>(p, s, ws, st);
         case 4: return launch_gqa_s<D, 4, EV>(p, s, ws, st);
@@ -1111,7 +1111,7 @@ static hipError_t launch_decode_any(const pkv_shape& s, const DecodeParams& p, v
     const int nblk = s.B * p.nl * (s.H / G);
     const bool bf16 = s.dtype == PKV_BF16;
     if (bf16 && G >= 2)     // several query heads share the cached rows: scores on the matrix cores
-        return s.D == 128 ? launch_gqa<128, EV>(p, s, G, (int*)ws, st) : launch_gqa<64, EV>(p, s, G, (int*)ws, st);
+        return s.D == 128 ? launch_gqa<128, EV>(p, s, G, ws, st) : launch_gqa<64, EV>(p, s, G, ws, st);
     const int lpr = s.D * (bf16 ? 2 : 4) / 16;
     if (bf16) {
         if (lpr == 8) return launch_decode_g<true, 8, EV>(p, G, nblk, st);

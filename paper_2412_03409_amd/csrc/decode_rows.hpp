@@ -128,4 +128,9 @@ __host__ __device__ __forceinline__ int gqa_share(int all, int waves) {
     return even < 2 ? 2 : even;
 }
 
+// The workspace of a grouped-query launch starts at the first multiple of 16 in the caller's, which may have any address: partial
+// results are written and read by 16 bytes.  The size query adds kGqaWsAlign bytes for it.
+constexpr int kGqaWsAlign = 16;
+inline unsigned long long gqa_ws_base(unsigned long long address) { return (address + kGqaWsAlign - 1) / kGqaWsAlign * kGqaWsAlign; }
+
 }  // namespace pkv

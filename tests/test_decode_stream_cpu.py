@@ -17,15 +17,21 @@ SHIM = """
 #define __forceinline__ inline
 #include "decode_rows.hpp"
 extern "C" int share(int all, int waves) { return pkv::gqa_share(all, waves); }
+extern "C" unsigned long long base(unsigned long long at) { return pkv::gqa_ws_base(at); }
 """
 
 
 @pytest.fixture(scope="module")
-def share(tmp_path_factory):
+def shim(tmp_path_factory):
     d = tmp_path_factory.mktemp("stream")
     (d / "shim.cpp").write_text(SHIM)
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cpp"), "-o", str(d / "shim.so")])
-    return C.CDLL(str(d / "shim.so")).share
+    return C.CDLL(str(d / "shim.so"))
+
+
+@pytest.fixture(scope="module")
+def share(shim):
+    return shim.share
 
 
 def walk(share, lens, HU, BR, waves):
@@ -98,3 +104,15 @@ def test_workspace_never_bounds_a_launch(B, L, N, G, HU, D):
     words = P.prefixkv_workspace_bytes(3, B, L, G * HU, HU, N, D, P.PKV_BF16) // 4
     slots = (words - (16 + B * L + 1 + 15) // 16 * 16) // (G * (D + 2))
     assert slots >= 2048 + B * L * HU
+
+
+# Partial results go by 16 bytes; the caller's workspace may start anywhere.
+def test_workspace_of_any_alignment(shim):
+    shim.base.restype, shim.base.argtypes = C.c_ulonglong, [C.c_ulonglong]
+    G, HU, D = 4, 8, 128
+    slots = 2048 + 5 * HU
+    size = P.prefixkv_workspace_bytes(3, 1, 5, G * HU, HU, 300, D, P.PKV_BF16)
+    for at in range(1 << 40, (1 << 40) + 33):
+        base = shim.base(at)
+        assert base % 16 == 0 and base >= at
+        assert base + 4 * ((16 + 5 + 1 + 15) // 16 * 16 + slots * G * (D + 2)) <= at + size

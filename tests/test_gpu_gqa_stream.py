@@ -58,8 +58,9 @@ def test_keys_at_minus_infinity(H, D):
     assert (out.cpu().double() - want).abs().max() <= OUT_ATOL
 
 
-# The smallest workspace that the size query returns bounds the number of wavefronts; whatever it holds beforehand must not matter.
-def test_dirty_workspace():
+# Whatever the workspace holds beforehand, and whatever its alignment, must not matter; nothing is written past its end.
+@pytest.mark.parametrize("shift", [0, 1, 4, 12])
+def test_dirty_workspace(shift):
     B, L, H, Hkv, N, D = 1, 3, 4, 1, 600, 128
     g = torch.Generator().manual_seed(1)
     rnd = lambda *s: torch.randn(s, generator=g).to(BF16).to(DEV)
@@ -71,6 +72,7 @@ def test_dirty_workspace():
     outs = []
     for fill in (0, 255, 127):
         cache = P.prefixkv_compact(k, v, order, lengths, 0, B * L * N)
-        ws = torch.full((n,), fill, dtype=torch.uint8, device=DEV)
-        outs.append(P.prefixkv_decode_attn(cache, q, None, None, scale, N, ws=ws))
+        buf = torch.full((shift + n + 64,), fill, dtype=torch.uint8, device=DEV)
+        outs.append(P.prefixkv_decode_attn(cache, q, None, None, scale, N, ws=buf[shift:shift + n]))
+        assert (buf[:shift] == fill).all() and (buf[shift + n:] == fill).all()
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
