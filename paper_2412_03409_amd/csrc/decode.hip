@@ -575,9 +575,11 @@ __device__ __forceinline__ int wave_scan(int v, int lane) {
     return v;
 }
 
-// 16 bytes per lane from global memory to LDS[dst + 16 * lane] (nothing else here uses m0)
+// 16 bytes per lane from global memory to LDS[dst + 16 * lane] (nothing else here uses m0); ONCE: without a place in the caches
+template <bool ONCE>
 __device__ __forceinline__ void copy16(const unsigned char* base, uint32_t off, uint32_t dst) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(dst), "v"(off), "s"(base) : "memory");
+    if constexpr (ONCE) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" :: "s"(dst), "v"(off), "s"(base) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(dst), "v"(off), "s"(base) : "memory");
 }
 __device__ __forceinline__ void copy16_any(const unsigned char* src, uint32_t dst) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst), "v"(src) : "memory");
@@ -608,6 +610,12 @@ template <int G, class F> __device__ __forceinline__ void for_heads(F f) {
 // wavefronts of a workgroup, of a launch at most (8 on each of 256 compute units); block counts per lane that are held between the
 // passes
 constexpr int kGqaWaves = 4, kGqaWavesMax = 2048, kGqaHeld = 4;
+
+// Rows of up to so many bytes are read through the caches: the last level holds 256 MiB, and the next step reads them again.
+// Beyond that a pass evicts what the next one looks for, and rows that do not enter are faster.  us per step, through the caches
+// / past them, H 32/8, D 128, B4: equal lengths, 180 MB 40.6 / 41.0, 260 55.0 / 56.1, 340 75.5 / 66.9, 420 91.7 / 79.1, 4.3 GB 737 /
+// 661; within a factor 30, 230 49.1 / 51.7, 300 60.0 / 62.4, 340 67.8 / 68.2, 380 76.0 / 74.6, 700 135 / 123.
+constexpr long long kGqaCached = 320ll << 20;
 
 template <int D, int G, bool EV>
 __global__ void __launch_bounds__(kGqaWaves * kWave, 2)
@@ -643,6 +651,7 @@ decode_gqa_kernel(DecodeParams p) {
     const int all = total * HU;
     const int share = gqa_share(all, p.waves);
     if (gid == 0 && lane == 0) { p.ws[0] = share; p.ws[kGqaHdr + n] = total; }
+    const bool once = (long long)total * p.Hkv * (2 * TB) > kGqaCached;
     const int x0 = gid * share, x1 = x0 + share < all ? x0 + share : all;
     if (x0 >= all) return;
     const int y0 = x0 / HU;
@@ -716,7 +725,10 @@ decode_gqa_kernel(DecodeParams p) {
         if (r0 + BR <= u.ss.len_old) {
             const unsigned char* base = (V ? u.v : u.k) + (size_t)r0 * ROWB;
 #pragma unroll
-            for (int i = 0; i < NI; ++i) copy16(base + i * 1024, V ? (uint32_t)lane * 16u : koff[i], dst + i * 1024);
+            for (int i = 0; i < NI; ++i) {
+                const uint32_t off = V ? (uint32_t)lane * 16u : koff[i];
+                if (once) copy16<true>(base + i * 1024, off, dst + i * 1024); else copy16<false>(base + i * 1024, off, dst + i * 1024);
+            }
         } else if (r0 < u.ss.len) {
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
