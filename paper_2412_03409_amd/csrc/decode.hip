@@ -565,13 +565,14 @@ __device__ __forceinline__ int seg_slot(const DecodeParams& p, int i) { return (
 constexpr int kGqaHdr = 16;
 __host__ __device__ inline int gqa_partial_word(int n_seg) { return (kGqaHdr + n_seg + 1 + 15) / 16 * 16; }
 
-// inclusive sum over the lanes
-__device__ __forceinline__ int wave_scan(int v, int lane) {
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int up = __shfl_up(v, d, kWave);
-        v += lane >= d ? up : 0;
-    }
+// inclusive sum over the lanes, by DPP: every wavefront waits for it before its first rows
+__device__ __forceinline__ int wave_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15, to the odd rows of 16
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31, to the upper half
     return v;
 }
 
@@ -647,7 +648,7 @@ decode_gqa_kernel(DecodeParams p) {
 #pragma unroll
     for (int u = 0; u < kGqaHeld; ++u) { held[u] = u * kWave < n ? blocks_of(u * kWave + lane) : 0; sum += held[u]; }
     for (int i = kGqaHeld * kWave; i < n; i += kWave) sum += blocks_of(i + lane);
-    const int total = __builtin_amdgcn_readlane(wave_scan(sum, lane), kWave - 1);   // of one head group
+    const int total = __builtin_amdgcn_readlane(wave_scan(sum), kWave - 1);   // of one head group
     const int all = total * HU;
     const int share = gqa_share(all, p.waves);
     if (gid == 0 && lane == 0) { p.ws[0] = share; p.ws[kGqaHdr + n] = total; }
@@ -657,7 +658,7 @@ decode_gqa_kernel(DecodeParams p) {
     const int y0 = x0 / HU;
     int seg = 0, first = 0, before = 0;                  // the segment of block x0, first block of it (per head group)
     auto look = [&](int u, int nb) {
-        const int incl = before + wave_scan(nb, lane), excl = incl - nb;
+        const int incl = before + wave_scan(nb), excl = incl - nb;
         if (gid == 0 && u * kWave + lane < n) p.ws[kGqaHdr + u * kWave + lane] = excl;
         const unsigned long long m = __builtin_amdgcn_ballot_w64(nb > 0 && excl <= y0);
         if (m) {
@@ -724,11 +725,13 @@ decode_gqa_kernel(DecodeParams p) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // what was there has been read
         if (r0 + BR <= u.ss.len_old) {
             const unsigned char* base = (V ? u.v : u.k) + (size_t)r0 * ROWB;
+            if (once) {
 #pragma unroll
-            for (int i = 0; i < NI; ++i) {
-                const uint32_t off = V ? (uint32_t)lane * 16u : koff[i];
-                if (once) copy16<true>(base + i * 1024, off, dst + i * 1024); else copy16<false>(base + i * 1024, off, dst + i * 1024);
+                for (int i = 0; i < NI; ++i) copy16<true>(base + i * 1024, V ? (uint32_t)lane * 16u : koff[i], dst + i * 1024);
+                return NI;
             }
+#pragma unroll
+            for (int i = 0; i < NI; ++i) copy16<false>(base + i * 1024, V ? (uint32_t)lane * 16u : koff[i], dst + i * 1024);
         } else if (r0 < u.ss.len) {
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
@@ -954,61 +957,78 @@ decode_gqa_kernel(DecodeParams p) {
 
 // Adds up the partial results of every unit that several wavefronts shared, in groups of consecutive pieces, each in block
 // order, and stores the new lengths.  One workgroup per unit: a unit of a long segment can have as many pieces as there are
-// wavefronts, and in one wavefront their loads would follow each other (B2 H32/4 N8192, 73 pieces: 36 us).
+// wavefronts, and in one wavefront their loads would follow each other (B2 H32/4 N8192, 73 pieces: 36 us).  Bound by its chain of
+// memory round trips, so a group takes its own maximum from the pieces it adds up; with a pass over all maxima and a barrier
+// ahead of that, one layer of 500 positions, H 32/8, D 128, kept whole took 11.7 us per call in both kernels, now 10.4, B4 N8192 10 %
+// 82.6, now 81.0.  Four pieces in flight: the third workgroup of a compute unit costs more registers than eight are worth.
 constexpr int kMergeThreads = 512;
 template <int D, int G, bool EV>
 __global__ void __launch_bounds__(kMergeThreads)
 decode_gqa_merge_kernel(DecodeParams p) {
     constexpr int NE = G * D / 4, PG = kMergeThreads / NE, PST = G * (D + 2);   // float4 elements, groups of pieces
-    __shared__ float s_m[kMergeThreads / kWave][G], s_d[PG][G];
+    constexpr int NP = 4;                                // pieces whose loads are in flight together
+    __shared__ float s_m[PG][G], s_d[PG][G];
     __shared__ __attribute__((aligned(16))) float s_num[PG][G * D];
-    const int HU = p.H / G, tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int HU = p.H / G, tid = threadIdx.x;
     const int i = blockIdx.x / HU, hu = blockIdx.x - i * HU, sl = seg_slot(p, i);
-    const int share = p.ws[0];
-    const int first = p.ws[kGqaHdr + i], nb = p.ws[kGqaHdr + i + 1] - first;
+    const int share = uniform_load(p.ws);
+    const int first = uniform_load(p.ws + kGqaHdr + i), nb = uniform_load(p.ws + kGqaHdr + i + 1) - first;
     if (hu == 0 && tid == 0)
         p.lens[sl] = seg_state<EV>(p, p.lens[sl] & kLenMask, p.caps[sl], p.seg_off[sl], EV ? p.base_lens[sl] : 0).len_next;
     const int b0 = first * HU + hu * nb, w0 = b0 / share, np = (b0 + nb - 1) / share - w0 + 1;
     if (np == 1) return;                                 // one wavefront had it all and wrote the output
-    const float* ws = (const float*)p.ws + gqa_partial_word(p.n_seg);
-    auto piece = [&](int k) { return ws + (size_t)(w0 + k + (int)blockIdx.x) * PST; };
-    // the maximum of each head
-    {
-        const int g = tid % G;
-        float m = -INFINITY;
-        for (int k = tid / G; k < np; k += kMergeThreads / G) m = fmaxf(m, piece(k)[G * D + 2 * g]);
-#pragma unroll
-        for (int d = G; d < kWave; d <<= 1) m = fmaxf(m, __shfl_xor(m, d, kWave));
-        if (lane < G) s_m[wv][lane] = m;
-    }
-    __syncthreads();
+    const float* ws = (const float*)p.ws + gqa_partial_word(p.n_seg) + (size_t)(w0 + (int)blockIdx.x) * PST;
     const int e = tid % NE, pg = tid / NE, g = e * 4 / D;
-    float M = s_m[0][g];
-#pragma unroll
-    for (int w = 1; w < kMergeThreads / kWave; ++w) M = fmaxf(M, s_m[w][g]);
-    const float ref = M == -INFINITY ? 0.f : M;
-    const int per = (np + PG - 1) / PG, k1 = (pg + 1) * per < np ? (pg + 1) * per : np;
+    const int per = (np + PG - 1) / PG, k0 = pg * per, k1 = k0 + per < np ? k0 + per : np;
+    // numerators, denominator and the maximum they refer to of the group's pieces, in one pass over them
     float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-    float den = 0.f;
-#pragma unroll 8
-    for (int k = pg * per; k < k1; ++k) {
-        const float2 md = *(const float2*)(piece(k) + G * D + 2 * g);
-        const float4 v = *(const float4*)(piece(k) + 4 * e);
-        const float wgt = __builtin_amdgcn_exp2f(md.x - ref);
-        num.x = fmaf(wgt, v.x, num.x); num.y = fmaf(wgt, v.y, num.y);
-        num.z = fmaf(wgt, v.z, num.z); num.w = fmaf(wgt, v.w, num.w);
-        den = fmaf(wgt, md.y, den);
+    float den = 0.f, m = -INFINITY;
+    for (int k = k0; k < k1; k += NP) {
+        float2 md[NP];
+        float4 v[NP];
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            md[j] = make_float2(-INFINITY, 0.f);
+            v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (k + j < k1) {
+                const float* piece = ws + (size_t)(k + j) * PST;
+                md[j] = *(const float2*)(piece + G * D + 2 * g);
+                v[j] = *(const float4*)(piece + 4 * e);
+            }
+        }
+        float mn = m;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) mn = fmaxf(mn, md[j].x);
+        const float ref = mn == -INFINITY ? 0.f : mn, corr = __builtin_amdgcn_exp2f(m - ref);
+        m = mn;
+        num.x *= corr; num.y *= corr; num.z *= corr; num.w *= corr;
+        den *= corr;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const float wgt = __builtin_amdgcn_exp2f(md[j].x - ref);
+            num.x = fmaf(wgt, v[j].x, num.x); num.y = fmaf(wgt, v[j].y, num.y);
+            num.z = fmaf(wgt, v[j].z, num.z); num.w = fmaf(wgt, v[j].w, num.w);
+            den = fmaf(wgt, md[j].y, den);
+        }
     }
     if constexpr (PG > 1) {
         *(float4*)&s_num[pg][4 * e] = num;
-        if (4 * e % D == 0) s_d[pg][g] = den;
+        if (4 * e % D == 0) { s_m[pg][g] = m; s_d[pg][g] = den; }
         __syncthreads();
         if (pg != 0) return;
+        float M = m;
+#pragma unroll
+        for (int k = 1; k < PG; ++k) M = fmaxf(M, s_m[k][g]);
+        const float ref = M == -INFINITY ? 0.f : M, own = __builtin_amdgcn_exp2f(m - ref);
+        num.x *= own; num.y *= own; num.z *= own; num.w *= own;
+        den *= own;
 #pragma unroll
         for (int k = 1; k < PG; ++k) {
             const float4 v = *(const float4*)&s_num[k][4 * e];
-            num.x += v.x; num.y += v.y; num.z += v.z; num.w += v.w;
-            den += s_d[k][g];
+            const float wgt = __builtin_amdgcn_exp2f(s_m[k][g] - ref);
+            num.x = fmaf(wgt, v.x, num.x); num.y = fmaf(wgt, v.y, num.y);
+            num.z = fmaf(wgt, v.z, num.z); num.w = fmaf(wgt, v.w, num.w);
+            den = fmaf(wgt, s_d[k][g], den);
         }
     }
     const bool some = den > 0.f;                         // an empty segment gives zeros
