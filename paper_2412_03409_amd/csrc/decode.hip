@@ -525,14 +525,13 @@ template <bool EV>
 __device__ __forceinline__ SegState seg_state(const DecodeParams& p, int len_old, int cap, int64_t off, int base) {
     SegState s;
     s.len_old = len_old; s.cap = cap; s.off = off;
-    s.app = p.append && s.len_old < s.cap;
-    s.len = s.len_old + (s.app ? 1 : 0);
-    s.len_next = s.len;
+    const StepRows r = step_rows<EV>(len_old, cap, base, p.append, p.t, p.d);
+    s.app = r.app;
+    s.len = s.len_next = r.rows;
     s.ring = {0, s.app ? s.len_old : -1, -1};
     s.ring0 = 0; s.cs = 0; s.grad = false; s.decide = false;
     if constexpr (EV) {
         s.ring0 = s.cap - (p.d + 1);
-        s.app = base >= 0 && s.ring0 >= base && s.len_old <= s.ring0;
         s.decide = s.app && p.t > p.d;
         s.cs = p.t % (p.d + 1);
         long long target = (2ll * base * ((long long)p.N + p.t) + p.N) / (2ll * p.N);
@@ -541,22 +540,12 @@ __device__ __forceinline__ SegState seg_state(const DecodeParams& p, int len_old
         s.ring.shift = s.ring0 - s.len_old;
         s.ring.r_new = s.app ? s.len_old + (p.t - 1) % (p.d + 1) : -1;
         s.ring.r_mask = (s.decide && !s.grad) ? s.len_old + s.cs : -1;
-        s.len = s.app ? s.len_old + (p.t < p.d + 1 ? p.t : p.d + 1) : 0;
         s.len_next = s.len_old + (s.grad ? 1 : 0);
     }
     return s;
 }
 
 
-// Rows of a segment that a step attends to: SegState::len without the rest.
-template <bool EV>
-__device__ __forceinline__ int seg_rows(const DecodeParams& p, int sl) {
-    const int len_old = p.lens[sl] & kLenMask, cap = p.caps[sl];
-    if constexpr (!EV) return len_old + (p.append && len_old < cap ? 1 : 0);
-    const int base = p.base_lens[sl], ring0 = cap - (p.d + 1);
-    const bool app = base >= 0 && ring0 >= base && len_old <= ring0;
-    return app ? len_old + (p.t < p.d + 1 ? p.t : p.d + 1) : 0;
-}
 __device__ __forceinline__ int seg_slot(const DecodeParams& p, int i) { return (i / p.nl) * p.L + p.l0 + i % p.nl; }
 
 // Workspace: [0] the share, from word 16 the first block / HU of every segment and their total (n_seg + 1), then, 16-word
@@ -639,15 +628,24 @@ decode_gqa_kernel(DecodeParams p) {
     const int sub = lane % LPR, rg = lane / LPR;         // V layout
 
     // ---- where this wavefront's blocks are: block counts of all segments, their sum, the segment of the first block
-    auto blocks_of = [&](int i) {
-        const int rows = i < n ? seg_rows<EV>(p, seg_slot(p, i)) : 0;
-        const int nb = (rows + BR - 1) / BR;
-        return i < n ? (nb < 1 ? 1 : nb) : 0;            // an empty segment has an output too
+    struct Words { int len, cap, base; int64_t off; };   // of a segment, as they lie in memory
+    auto read = [&](int i) {
+        Words w = {0, 0, 0, 0};
+        if (i < n) {
+            const int sl = seg_slot(p, i);
+            w.len = p.lens[sl] & kLenMask; w.cap = p.caps[sl]; w.off = p.seg_off[sl];
+            if (EV) w.base = p.base_lens[sl];
+        }
+        return w;
     };
-    int held[kGqaHeld], sum = 0;
+    auto blocks_of = [&](int i, const Words& w) {
+        return i < n ? row_blocks(step_rows<EV>(w.len, w.cap, w.base, p.append, p.t, p.d).rows, BR) : 0;
+    };
+    Words held[kGqaHeld];
+    int sum = 0;
 #pragma unroll
-    for (int u = 0; u < kGqaHeld; ++u) { held[u] = u * kWave < n ? blocks_of(u * kWave + lane) : 0; sum += held[u]; }
-    for (int i = kGqaHeld * kWave; i < n; i += kWave) sum += blocks_of(i + lane);
+    for (int u = 0; u < kGqaHeld; ++u) { held[u] = read(u * kWave + lane); sum += blocks_of(u * kWave + lane, held[u]); }
+    for (int i = kGqaHeld * kWave; i < n; i += kWave) sum += blocks_of(i + lane, read(i + lane));
     const int total = __builtin_amdgcn_readlane(wave_scan(sum), kWave - 1);   // of one head group
     const int all = total * HU;
     const int share = gqa_share(all, p.waves);
@@ -657,7 +655,9 @@ decode_gqa_kernel(DecodeParams p) {
     if (x0 >= all) return;
     const int y0 = x0 / HU;
     int seg = 0, first = 0, before = 0;                  // the segment of block x0, first block of it (per head group)
-    auto look = [&](int u, int nb) {
+    Words mine = {0, 0, 0, 0};                           // its words
+    auto look = [&](int u, const Words& w) {
+        const int nb = blocks_of(u * kWave + lane, w);
         const int incl = before + wave_scan(nb), excl = incl - nb;
         if (gid == 0 && u * kWave + lane < n) p.ws[kGqaHdr + u * kWave + lane] = excl;
         const unsigned long long m = __builtin_amdgcn_ballot_w64(nb > 0 && excl <= y0);
@@ -665,13 +665,17 @@ decode_gqa_kernel(DecodeParams p) {
             const int at = 63 - __builtin_clzll(m);
             seg = u * kWave + at;
             first = __builtin_amdgcn_readlane(excl, at);
+            mine.len = __builtin_amdgcn_readlane(w.len, at);
+            mine.cap = __builtin_amdgcn_readlane(w.cap, at);
+            mine.base = __builtin_amdgcn_readlane(w.base, at);
+            mine.off = ((int64_t)__builtin_amdgcn_readlane((int)(w.off >> 32), at) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)w.off, at);
         }
         before = __builtin_amdgcn_readlane(incl, kWave - 1);
     };
 #pragma unroll
     for (int u = 0; u < kGqaHeld; ++u)
         if (u * kWave < n && (before <= y0 || gid == 0)) look(u, held[u]);
-    for (int u = kGqaHeld; u * kWave < n && (before <= y0 || gid == 0); ++u) look(u, blocks_of(u * kWave + lane));
+    for (int u = kGqaHeld; u * kWave < n && (before <= y0 || gid == 0); ++u) look(u, read(u * kWave + lane));
     seg = __builtin_amdgcn_readfirstlane(seg);
 
     // ---- the unit under way
@@ -681,11 +685,13 @@ decode_gqa_kernel(DecodeParams p) {
         unsigned char *k, *v;                            // its rows in the cache
         int64_t fresh;                                   // byte offset of its row in k_new / v_new
     };
+    auto set_segment = [&](Unit& u, const Words& w) {
+        u.ss = seg_state<EV>(p, w.len, w.cap, w.off, w.base);
+        u.nb = row_blocks(u.ss.len, BR);
+    };
     auto enter_segment = [&](Unit& u, int i) {
         u.sl = __builtin_amdgcn_readfirstlane(seg_slot(p, i));
-        u.ss = seg_state<EV>(p, uniform_load(p.lens + u.sl) & kLenMask, uniform_load(p.caps + u.sl), uniform_load(p.seg_off + u.sl), EV ? uniform_load(p.base_lens + u.sl) : 0);
-        const int nb = (u.ss.len + BR - 1) / BR;
-        u.nb = nb < 1 ? 1 : nb;
+        set_segment(u, {uniform_load(p.lens + u.sl) & kLenMask, uniform_load(p.caps + u.sl), EV ? uniform_load(p.base_lens + u.sl) : 0, uniform_load(p.seg_off + u.sl)});
     };
     auto enter_head = [&](Unit& u, int hu) {
         const int kvh = (hu * G) / p.grp;
@@ -697,7 +703,8 @@ decode_gqa_kernel(DecodeParams p) {
     };
     // two cursors: the block that is worked on and, two blocks ahead, the one that is requested
     Unit cur;
-    enter_segment(cur, seg);
+    cur.sl = __builtin_amdgcn_readfirstlane(seg_slot(p, seg));
+    set_segment(cur, mine);
     int blk;
     {
         const int rem = x0 - first * HU, hu = rem / cur.nb;

@@ -32,6 +32,17 @@ __device__ __forceinline__ RowSource row_source(int r, int r0, int len, int len_
     return s;
 }
 
+// Rows that a step attends to in a segment of cap slots, len_old of them stored before (under pruning: permanent ones), and whether
+// the step stores a token: without pruning while a slot is left, with it if the ring of d + 1 slots fits behind the kept entries.
+struct StepRows { bool app; int rows; };
+template <bool EV>
+__host__ __device__ __forceinline__ StepRows step_rows(int len_old, int cap, int base, bool append, int t, int d) {
+    if (!EV) { const bool app = append && len_old < cap; return {app, len_old + (app ? 1 : 0)}; }
+    const int ring0 = cap - (d + 1);
+    const bool app = base >= 0 && ring0 >= base && len_old <= ring0;
+    return {app, app ? len_old + (t < d + 1 ? t : d + 1) : 0};
+}
+
 // Ranked launches: the segments are cut into groups of gsz; in each the units (HU per segment) of the n4 longest get four
 // wavefronts, those of the next n2 two and the others one; `by_length` false: in index order instead.  Workgroups of four
 // wavefronts; the units of a class follow each other without gaps, so a workgroup may hold units of two segments, and the
@@ -119,6 +130,9 @@ __device__ __forceinline__ RankedUnit ranked_unit(int block, int wv, const Ranke
     x.live = r < nc && x.rank < x.n;
     return x;
 }
+
+// Blocks of a grouped-query unit; one without rows has an output too.
+__host__ __device__ __forceinline__ int row_blocks(int rows, int block) { return rows < 1 ? 1 : (rows + block - 1) / block; }
 
 // Blocks of a wavefront when the `all` blocks of a grouped-query launch are dealt out evenly, at least two: a wavefront of a
 // single block costs a start and a partial result to add up (B4 H32/8 N8192, one layer a call: 18.1 us with one, 15.2 with

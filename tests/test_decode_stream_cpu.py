@@ -17,6 +17,11 @@ SHIM = """
 #define __forceinline__ inline
 #include "decode_rows.hpp"
 extern "C" int share(int all, int waves) { return pkv::gqa_share(all, waves); }
+extern "C" int rows(int ev, int len, int cap, int base, int append, int t, int d, int block, int* blocks) {
+    const pkv::StepRows r = ev ? pkv::step_rows<true>(len, cap, base, append, t, d) : pkv::step_rows<false>(len, cap, base, append, t, d);
+    *blocks = pkv::row_blocks(r.rows, block);
+    return r.rows * 2 + r.app;
+}
 extern "C" unsigned long long base(unsigned long long at) { return pkv::gqa_ws_base(at); }
 """
 
@@ -116,3 +121,18 @@ def test_workspace_of_any_alignment(shim):
         base = shim.base(at)
         assert base % 16 == 0 and base >= at
         assert base + 4 * ((16 + 5 + 1 + 15) // 16 * 16 + slots * G * (D + 2)) <= at + size
+
+
+# The rows of a step, which a wavefront's share and its walk both go by.
+def test_rows_of_a_step(shim):
+    rng, nb = random.Random(1), C.c_int()
+    for _ in range(3000):
+        cap, t, d = rng.randint(1, 80), rng.choice([1, 2, 15, 16, 17, 1 << 30]), rng.choice([1, 15, 65535])
+        n, base, append = rng.randint(0, cap), rng.randint(-1, cap), rng.random() < 0.5
+        stores = append and n < cap
+        assert shim.rows(0, n, cap, base, append, t, d, 16, C.byref(nb)) == 2 * (n + stores) + stores
+        assert nb.value == max(1, -(-(n + stores) // 16))
+        fits = base >= 0 and base <= cap - d - 1 and n <= cap - d - 1
+        want = n + min(t, d + 1) if fits else 0
+        assert shim.rows(1, n, cap, base, append, t, d, 32, C.byref(nb)) == 2 * want + fits
+        assert nb.value == max(1, -(-want // 32))
