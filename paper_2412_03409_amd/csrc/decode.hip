@@ -648,7 +648,7 @@ decode_gqa_kernel(DecodeParams p) {
     for (int i = kGqaHeld * kWave; i < n; i += kWave) sum += blocks_of(i + lane, read(i + lane));
     const int total = __builtin_amdgcn_readlane(wave_scan(sum), kWave - 1);   // of one head group
     const int all = total * HU;
-    const int share = gqa_share(all, p.waves);
+    const int share = gqa_share(all, p.waves, gqa_least(all, p.waves, n * HU, G * D));
     if (gid == 0 && lane == 0) { p.ws[0] = share; p.ws[kGqaHdr + n] = total; }
     const bool once = (long long)total * p.Hkv * (2 * TB) > kGqaCached;
     const int x0 = gid * share, x1 = x0 + share < all ? x0 + share : all;

@@ -134,12 +134,18 @@ __device__ __forceinline__ RankedUnit ranked_unit(int block, int wv, const Ranke
 // Blocks of a grouped-query unit; one without rows has an output too.
 __host__ __device__ __forceinline__ int row_blocks(int rows, int block) { return rows < 1 ? 1 : (rows + block - 1) / block; }
 
-// Blocks of a wavefront when the `all` blocks of a grouped-query launch are dealt out evenly, at least two: a wavefront of a
-// single block costs a start and a partial result to add up (B4 H32/8 N8192, one layer a call: 18.1 us with one, 15.2 with
-// two, 16.4 with four; B1 N2000 11.1, 11.4 and 13.7).
-__host__ __device__ __forceinline__ int gqa_share(int all, int waves) {
+// Fewest blocks of a wavefront of a grouped-query launch.  A wavefront costs a start and a partial result of `width` numerators to
+// add up.  One block each while the launch is a wait on chains, up to half the wavefronts, and the merge has up to 16 pieces for
+// each of its 2048 / width groups; else two.  us per call with two / one, D 128: 64 units of width 512, 200 blocks 12.7 / 10.0, 900 12.1 /
+// 11.0, 1400 13.0 / 13.1; 8 units, 400 12.0 / 11.2, 700 12.0 / 12.7, 2000 16.0 / 20.7; width 1024, 16 units, 200 13.5 / 11.7, 700 15.3 / 16.7,
+// 128 units, 900 15.2 / 13.9, 1100 14.7 / 15.6.  (B4 H32/8 N8192, one layer a call, 2300 blocks: four 8 % slower than two.)
+__host__ __device__ __forceinline__ int gqa_least(int all, int waves, int units, int width) {
+    return 2ll * all <= waves && (long long)all * width <= 32768ll * units ? 1 : 2;
+}
+// Blocks of a wavefront when the `all` blocks are dealt out evenly.
+__host__ __device__ __forceinline__ int gqa_share(int all, int waves, int least = 2) {
     const int even = (int)(((long long)all + waves - 1) / waves);
-    return even < 2 ? 2 : even;
+    return even < least ? least : even;
 }
 
 // The workspace of a grouped-query launch starts at the first multiple of 16 in the caller's, which may have any address: partial

@@ -17,6 +17,8 @@ SHIM = """
 #define __forceinline__ inline
 #include "decode_rows.hpp"
 extern "C" int share(int all, int waves) { return pkv::gqa_share(all, waves); }
+extern "C" int least(int all, int waves, int units, int width) { return pkv::gqa_least(all, waves, units, width); }
+extern "C" int share_of(int all, int waves, int least) { return pkv::gqa_share(all, waves, least); }
 extern "C" int rows(int ev, int len, int cap, int base, int append, int t, int d, int block, int* blocks) {
     const pkv::StepRows r = ev ? pkv::step_rows<true>(len, cap, base, append, t, d) : pkv::step_rows<false>(len, cap, base, append, t, d);
     *blocks = pkv::row_blocks(r.rows, block);
@@ -99,6 +101,20 @@ def test_slots_fit_the_workspace(G, HU, D):
         units = n_seg * HU
         slots = (words - (16 + n_seg + 1 + 15) // 16 * 16) // (G * (D + 2))
         assert slots - units >= 1                     # at least one wavefront
+
+
+# Also with a single block for each wavefront, which short launches take: never more of them than half the wavefronts.
+def test_every_block_once_in_short_launches(shim):
+    rng = random.Random(2)
+    for _ in range(300):
+        n, HU = rng.randint(1, 40), rng.choice([1, 2, 3, 8])
+        lens = [rng.choice([0, 1, rng.randint(0, 40), rng.randint(0, 900)]) for _ in range(n)]
+        assert walk(lambda all, waves: shim.share_of(all, waves, 1), lens, HU, rng.choice([16, 32]), 2048) < 2048 + n * HU
+    for width in (128, 256, 512, 1024):
+        for units in (1, 8, 100, 1000):
+            one = [all for all in range(1, 3000) if shim.least(all, 2048, units, width) == 1]
+            assert one == list(range(1, min(1024, 32768 * units // width) + 1))
+            assert all(shim.share_of(x, 2048, 1) == 1 for x in one)
 
 
 # Whatever the prompt's length and the number of segments there is a slot for each unit and for each of the 2048 wavefronts of a
