@@ -47,6 +47,7 @@ struct DecodeParams {
     const int32_t* base_lens;     // [B,L] entries kept after prefill
     int32_t* kept_pos;            // one int per slot, may be null
     int n_seg;
+    bool early;                   // smallest launches of decode_attn_kernel: units are counted in before their rows
     // grouped-query kernels: wavefronts, workspace
     int waves;
     int* ws;
@@ -312,13 +313,13 @@ decode_attn_kernel(DecodeParams p) {
         asm volatile("" : "+v"(len_raw), "+s"(cap), "+s"(off), "+s"(base), "+s"(qs) : : "memory");
     }
     const int len_old = __builtin_amdgcn_readfirstlane(len_raw) & kLenMask;
-    // The unit is counted in once every wavefront of it has read lens.  Small launches: here, so that the round trip of the
-    // atomic passes under the rows; it is the last wavefront's, which has the fewest.  (32 units 5.36 -> 4.94 us per launch, 240
-    // 8.5 -> 8.1; not for the larger ones: the atomics of 1024 units meet at the start of the launch, 19.9 -> 25.7.)
-    constexpr bool kEarly = W == 8;
-    const bool counter = live && uw == (kEarly ? UW - 1 : 0) && lane == 0;
+    // The unit is counted in once every wavefront of it has read lens.  The smallest launches: here, so that the round trip of the
+    // atomic passes under the rows; it is the last wavefront's, which has the fewest.  (32 units 5.36 -> 4.94 us per launch.  Where
+    // units start while others count in, their reads of lens wait for the atomics: 256 units 5 ... 20 % slower, 512 by up to half.)
+    const bool early = W == 8 && p.early;
+    const bool counter = live && uw == (early ? UW - 1 : 0) && lane == 0;
     int counted = 0;
-    if constexpr (kEarly) {
+    if (early) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
@@ -457,7 +458,7 @@ decode_attn_kernel(DecodeParams p) {
             }
         }
         __syncthreads();
-        if (!kEarly && counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
+        if (!early && counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
         // merge the wavefronts of a unit: thread (g, d)
         const int w0 = wv & ~(UW - 1);
         for (int i = uw * kWave + lane; live && i < G * p.D; i += UW * kWave) {
@@ -1077,6 +1078,7 @@ static hipError_t launch_decode_s(DecodeParams p, int nblk, hipStream_t st) {
     constexpr int OCC = G >= 4 ? 2 : 4, RES = BF16 && !EV ? kRankedResident : 16, ROCC = RES > 16 ? RES / 4 : OCC;   // (the pruning step spills at five wavefronts per SIMD)
     const int HU = p.H / G, cus = compute_units();
     p.n_seg = nblk / HU;
+    p.early = 4 * nblk <= cus;
     if (nblk <= 2 * cus) {
         hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 8, OCC, EV, 0>), dim3(HU, p.nl, p.B), dim3(8 * kWave), 0, st, p);
         return hipGetLastError();
@@ -1171,7 +1173,7 @@ static DecodeParams make_params(const pkv_shape& s, int l0, int l1, const void* 
     p.kc = (unsigned char*)kc; p.vc = (unsigned char*)vc; p.seg_off = seg_off; p.caps = caps;
     p.lens = lens; p.out = (unsigned char*)out;
     p.N = s.N; p.t = 0; p.d = 0; p.base_lens = nullptr; p.kept_pos = nullptr;
-    p.n_seg = 0; p.waves = 0; p.ws = nullptr;
+    p.n_seg = 0; p.early = false; p.waves = 0; p.ws = nullptr;
     p.rank = RankedShape{0, 0, 0, false};
     return p;
 }
