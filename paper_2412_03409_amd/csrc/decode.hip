@@ -14,9 +14,9 @@
 // no wavefront reads a slot that is written in the same launch.
 //
 // lens is advanced inside the launch of decode_attn_kernel without a second kernel: every wavefront reads the old
-// length of its segment when it starts, and every unit, once its wavefronts have, adds 1 to the
-// bits above kLenBits of lens[b,l].  The unit that finds all others of the segment already
-// counted stores the new plain length, which also clears the count.  Between launches lens holds plain
+// length of its segment when it starts, and every unit, once its wavefronts have, is counted in the
+// bits above kLenBits of lens[b,l] (by itself, or by the first of its workgroup).  The one that finds all others of
+// the segment already counted stores the new plain length, which also clears the count.  Between launches lens holds plain
 // lengths (< 2^20).  The ranking of the segments goes by capacity, which no launch changes.
 #include "pkv_common.hpp"
 #include "decode_rows.hpp"
@@ -298,7 +298,7 @@ decode_attn_kernel(DecodeParams p) {
     // What the first rows wait for.  One unit per workgroup: in one round trip to memory (left to itself the compiler waits for
     // the length before it requests the capacity, and for that before the offset and the queries).  The ranked launches have
     // enough other wavefronts, and there it cost 1 ... 2 %.
-    int len_raw = __hip_atomic_load(p.lens + sl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int len_raw = __hip_atomic_load(p.lens + sl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);   // from the caches: the length is the same in every value of this launch
     int cap = uniform_load(p.caps + sl);
     int64_t off = uniform_load(p.seg_off + sl);
     int base = EV ? uniform_load(p.base_lens + sl) : 0;
@@ -311,6 +311,8 @@ decode_attn_kernel(DecodeParams p) {
     if constexpr (RANK == 0) {
         load_q();
         asm volatile("" : "+v"(len_raw), "+s"(cap), "+s"(off), "+s"(base), "+s"(qs) : : "memory");
+    } else {
+        asm volatile("" : "+v"(len_raw) : : "memory");
     }
     const int len_old = __builtin_amdgcn_readfirstlane(len_raw) & kLenMask;
     // The unit is counted in once every wavefront of it has read lens.  The smallest launches: here, so that the round trip of the
@@ -318,13 +320,17 @@ decode_attn_kernel(DecodeParams p) {
     // units start while others count in, their reads of lens wait for the atomics: 256 units 5 ... 20 % slower, 512 by up to half.)
     const bool early = W == 8 && p.early;
     const bool counter = live && uw == (early ? UW - 1 : 0) && lane == 0;
-    int counted = 0;
-    if (early) {
+    int counted = 0, count = 1;
+    if (early || (RANK > 0 && UW == 1)) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-        if (counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
     }
+    // Ranked launches: the first of the workgroup's units of a segment counts all of them in, behind a barrier that they have
+    // passed with lens read.  The atomics on the few cache lines of lens were what launches of short rows took: 2048 units of 26 rows
+    // 18.5 ... 34 us in the same shape, now 17 ... 26, 12 800 of 136 rows 172 -> 160.
+    if constexpr (RANK > 0) count = counted_units(wv >> (UW >> 1), W >> (UW >> 1), hu, HU);
+    if (early && counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
     // plain step: append at slot len_old.  Pruning step: len_old counts the permanent entries, the new
     // token goes to ring slot (t-1) mod (d+1), and the token stored d steps ago (ring slot t mod (d+1))
     // either becomes permanent entry len_old or is left out from now on.
@@ -429,7 +435,7 @@ decode_attn_kernel(DecodeParams p) {
     // The other launches count the unit in here (UW > 1: behind the barrier below); the round trip of the atomic passes while the
     // output is written.
     if (UW == 1) {
-        if (counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
+        if (counter && count > 0) counted = atomicAdd(p.lens + sl, count << kLenBits);
         if (live && rg == 0) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
@@ -458,7 +464,7 @@ decode_attn_kernel(DecodeParams p) {
             }
         }
         __syncthreads();
-        if (!early && counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
+        if (!early && counter && count > 0) counted = atomicAdd(p.lens + sl, count << kLenBits);
         // merge the wavefronts of a unit: thread (g, d)
         const int w0 = wv & ~(UW - 1);
         for (int i = uw * kWave + lane; live && i < G * p.D; i += UW * kWave) {
@@ -479,7 +485,7 @@ decode_attn_kernel(DecodeParams p) {
         }
     }
     // the last unit of the segment to be counted in stores the new length
-    if (counter && (int)((unsigned)counted >> kLenBits) == HU - 1)
+    if (counter && count > 0 && (int)((unsigned)counted >> kLenBits) + count == HU)
         __hip_atomic_store(p.lens + sl, len_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 

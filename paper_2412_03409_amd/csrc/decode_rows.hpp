@@ -32,6 +32,14 @@ __device__ __forceinline__ RowSource row_source(int r, int r0, int len, int len_
     return s;
 }
 
+// How many units the unit counts in at its segment: of the `units` consecutive ones of a workgroup, of which it is number `at` and
+// unit hu of the HU of its segment, the first of each segment speaks for all of that segment, the others for none.  (Units of one
+// segment are alive together.)
+__host__ __device__ __forceinline__ int counted_units(int at, int units, int hu, int HU) {
+    if (at > 0 && hu > 0) return 0;
+    return units - at < HU - hu ? units - at : HU - hu;
+}
+
 // Rows that a step attends to in a segment of cap slots, len_old of them stored before (under pruning: permanent ones), and whether
 // the step stores a token: without pruning while a slot is left, with it if the ring of d + 1 slots fits behind the kept entries.
 struct StepRows { bool app; int rows; };

@@ -18,6 +18,12 @@ extern "C" void shape(int gsz, long long units, long long cus, int N, int row_by
     const long long segs = (units + 31) / 32, waves = 4ll * pkv::ranked_blocks(s, 32) * ((segs + gsz - 1) / gsz);
     out[0] = s.n4; out[1] = s.n2; out[2] = s.by_length; out[3] = pkv::ranked_lds(s, waves, cus); out[4] = (int)waves;
 }
+extern "C" int blocks(int gsz, int n4, int n2, int HU) { return pkv::ranked_blocks(pkv::RankedShape{gsz, n4, n2, true}, HU); }
+extern "C" void unit(int block, int wv, int gsz, int n4, int n2, int HU, int n_seg, int* out) {
+    const pkv::RankedUnit x = pkv::ranked_unit(block, wv, pkv::RankedShape{gsz, n4, n2, true}, HU, n_seg);
+    out[0] = x.live; out[1] = x.UW; out[2] = x.first; out[3] = x.rank; out[4] = x.hu;
+    out[5] = pkv::counted_units(wv / x.UW, 4 / x.UW, x.hu, HU);
+}
 """
 
 
@@ -47,3 +53,27 @@ def test_shape_and_lds(shim, resident, N, row_bytes):
             assert by_length and waves > 20 * cus
         if 20 * cus >= segs * 32 > 2.5 * 16 * cus and N <= 4096 and resident == 20:
             assert waves <= 1.03 * 20 * cus              # one round
+
+
+# Every workgroup of a ranked launch counts its units in once for each segment that it has units of, and a segment's counts add up
+# to its units; no unit is counted in by a workgroup other than its own.
+@pytest.mark.parametrize("HU", [1, 2, 3, 12, 25, 32, 40])
+def test_counts_of_a_segment(shim, HU):
+    out = (C.c_int * 6)()
+    for n_seg, gsz, n4, n2 in ((1, 1, 0, 0), (7, 7, 2, 3), (50, 50, 12, 38), (130, 65, 8, 8), (97, 33, 33, 0), (640, 320, 60, 60)):
+        total, units = [0] * n_seg, set()
+        for block in range(shim.blocks(gsz, n4, n2, HU) * -(-n_seg // gsz)):
+            mine = {}
+            for wv in range(4):
+                shim.unit(block, wv, gsz, n4, n2, HU, n_seg, out)
+                live, UW, first, rank, hu, count = out
+                if not live or wv % UW:
+                    continue
+                assert (first + rank, hu) not in units
+                units.add((first + rank, hu))
+                in_block, counts = mine.setdefault(first + rank, [0, 0])
+                mine[first + rank] = [in_block + 1, counts + count]
+            for seg, (in_block, counts) in mine.items():
+                assert counts == in_block
+                total[seg] += counts
+        assert total == [HU] * n_seg and len(units) == n_seg * HU
