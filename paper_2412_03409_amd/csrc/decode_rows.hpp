@@ -55,52 +55,50 @@ __host__ __device__ __forceinline__ StepRows step_rows(int len_old, int cap, int
 // wavefronts, those of the next n2 two and the others one; `by_length` false: in index order instead.  Workgroups of four
 // wavefronts; the units of a class follow each other without gaps, so a workgroup may hold units of two segments, and the
 // last of a class fewer than fit.
-struct RankedShape { int gsz, n4, n2; bool by_length; };
+struct RankedShape { int gsz, n4, n2; bool by_length, large = false; };   // large: keys of more than 192 KB per head
 
-// The shape of a launch of `units` units (more than four per compute unit) on `cus` compute units, N prompt positions with
-// rows of row_bytes, gsz given.  A compute unit holds 16 wavefronts, and what a launch loses most on is a second round that is nearly empty.  Times
-// against a launch of two wavefronts per unit in index order, 256 compute units, bf16, D 128; lengths of the segments equal /
-// within a factor 3 / within a factor 30:
-//   as long as a quarter of the units with four wavefronts and the others with two fit one round, that: 1280 units of 136
-//     rows on average x1.00 / 1.03 / 1.25, of 410 x0.98 / 1.06 / 1.32, of 1638 x1.05 / 1.06 / 1.03 (an eighth with four, an
-//     eighth with two, the rest one: x1.03 / 1.03 / 1.17, 0.97 / 0.98 / 1.10, 1.10 / 0.98 / 0.86); prompts of more than 4096
-//     positions, whose wavefronts run long, up to a third over one round too (3072 units of 1638 rows x1.05 / 1.02 / 1.05
-//     against 1.00 / 0.97 / 0.95; 8192 units of 410 x1.45 / 1.66 / 1.66 against 1.55 / 1.66 / 1.65);
-//   beyond, an eighth each of the segments with four and two wavefronts, fewer where that is more than one round, but a
-//     sixteenth: 2048 units of 410 rows x0.98 / 1.08 / 1.34, 3072 of 205 x1.01 / 1.05 / 1.25 (an eighth: 0.94 / 1.01 / 1.11);
-//   from two rounds of single wavefronts on, one each: 12 288 units of 136 rows x1.04 / 1.00 / 1.21 (a sixteenth: 0.95 / 0.99 /
-//     1.21);
-//   from one round on, prompts with keys of up to 96 KB per head in index order, one wavefront each: finding the rank costs
-//     about as much as such a unit's rows (300 positions at 20 % and 128 at 20 %: 4096 units of 60 rows x1.28 / - / 1.03, by length 1.21 / - / 0.88; 16 384 of 26 rows x1.37 /
-//     - / 1.20, by length 0.93 / - / 1.12).
-// (All that with 16 wavefronts per compute unit, which is what fp32 rows and the pruning step have.)  `resident`: how many a
-// compute unit holds.  The plain bf16 step fits 20: launches of up to that many run in one round (us per launch, 16 / 20: 4096
-// units of 136 rows 72 / 56, 4800 79 / 78, 5120 90 / 79, 2048 of 300 64 / 61), and such a launch gives no unit more wavefronts
-// than the round has room for.
+// The shape of a launch of `units` units (more than four per compute unit) on `cus` compute units, each with room for `resident`
+// wavefronts (20 of the plain bf16 step, else 16); N prompt positions with rows of row_bytes, gsz given.  More wavefronts per unit
+// shorten the longest units, with which a launch ends; but each start costs, and a launch loses most on a second round that is
+// nearly empty.  Only the prompt's length is known here, so the rules have to hold for long rows and for short ones.  Times
+// against a quarter of the segments with four wavefronts and the others with two up to 1638 units, an eighth to a sixteenth each up
+// to 8192, one each beyond, with a count of each unit by itself; 256 compute units, bf16, D 128, lengths of the segments within a
+// factor 30 / 3 / equal:
+//   up to 6.4 units per compute unit, prompts with keys of more than 192 KB per head: a quarter with four, the others with two:
+//     1600 units of 300 rows x0.99 / 0.99 / 0.97 (3/16 as below 1.04 / 1.04 / 0.95, an eighth 1.20 / 1.10 / 1.04); prompts of more than
+//     4096 positions while that is no more than a third over one round of 16: 2048 units of 500 x0.89 / 0.95 / 0.97, 5120 x0.97;
+//   shorter prompts there, 3/16 with four and as many with two, the rest one: 1600 units of 136 rows x0.87 / 0.95 / 0.85 (a quarter
+//     and the others 0.89 / 0.92 / 0.90), of 41 0.72 / 0.73 / 0.77 (0.86 / 1.12 / 0.80);
+//   beyond, an eighth each while that fits one round of 16, then what does, but a sixteenth, up to one round of single ones: 2048 units
+//     of 136 rows x0.90 / 0.91 / 0.90, of 26 0.65 / 0.64 / 0.66; 3648 of 300 an eighth 0.98 on average, a sixteenth 0.97, none 0.99; 4096 of
+//     136 fp32 rows 0.98, none 1.11;
+//   up to two rounds of 16, keys of more than 192 KB: a sixteenth each, 6144 units of 300 rows 0.97 on average, none 0.98 (8 % apart
+//     for lengths within a factor 30); of 136 rows 0.90, none 0.90, of 41 0.70 and 0.64;
+//   all others one each, and from 16 units per compute unit on prompts with keys of up to 96 KB per head in index order: finding
+//     the rank costs too much there, 8192 units of 26 rows x0.65, by length 0.75, of 41 rows 0.78 and 0.85.
 constexpr int kRankedResident = 20;
 inline void ranked_shape(RankedShape& s, long long units, long long cus, int N, int row_bytes, int resident = 16) {
-    const double per_unit = (double)resident * cus / units;   // wavefronts of one round for each unit
+    const double per_unit = 16.0 * cus / units;               // wavefronts of one round of 16 for each unit
+    const bool large = s.large = N * row_bytes > 192 << 10;
     double f4 = 0, f2 = 0;
     s.by_length = N * row_bytes > 96 << 10 || units < 16 * cus;
-    if (per_unit >= 2.5 || (N > 4096 && per_unit >= 0.75)) {
-        f4 = 0.25; f2 = 0.75;
-    } else if (s.by_length && per_unit >= 0.5) {
-        f4 = (per_unit - 1) / 4;
-        f4 = f2 = f4 > 0.125 ? 0.125 : f4 < 0.0625 && (per_unit < 1 || resident == 16) ? 0.0625 : f4;
-    }
+    if ((large && per_unit >= 2.5) || (N > 4096 && per_unit >= 0.75)) { f4 = 0.25; f2 = 0.75; }
+    else if (per_unit >= 2.5) f4 = f2 = 0.1875;
+    else if (s.by_length && units <= resident * cus) f4 = f2 = per_unit > 1.5 ? 0.125 : per_unit < 1.25 ? 0.0625 : (per_unit - 1) / 4;
+    else if (large && per_unit >= 0.5) f4 = f2 = 0.0625;
     s.n4 = (int)(s.gsz * f4 + 0.5);
     s.n2 = (int)(s.gsz * f2 + 0.5);
     if (s.n2 > s.gsz - s.n4) s.n2 = s.gsz - s.n4;
 }
 
 // LDS that a bf16 launch of `waves` wavefronts asks for beyond its own 2 KB, to have four workgroups resident and not five.
-// Launches of several rounds are bound by memory, and that serves fewer streams of rows faster (us, five / four: 12 800 units of
-// 136 rows 179 / 176, 8192 of 136 122 / 119, 8192 of 90 100 / 90).  Two are better still for very unequal lengths (171, 115), but
-// 12 800 units of 264 rows on average, as the search finds them, take 298 / 299 / 320 us with five / four / two.  Up to an
-// eighth over one round filling it counts more, and short rows wait for their starts (8192 units of 40 rows 58 / 60).
+// Launches of several rounds of long rows are bound by memory, and that serves fewer streams of rows faster: lengths within a factor
+// 30, four against five, 6144 units of 300 rows x0.986, 9216 0.973, 12 800 1.00, of 500 0.985, 0.977, 0.991; less unequal ones x0.99 ...
+// 1.01.  Shorter rows wait for their starts (5440 units of 41 rows x1.11, 12 800 1.03), and up to an eighth over one round filling it
+// counts more.
 inline int ranked_lds(const RankedShape& s, long long waves, long long cus) {
     const long long round = kRankedResident * cus;
-    return s.by_length && 8 * waves > 9 * round ? 31 << 10 : 0;
+    return s.large && s.by_length && 8 * waves > 9 * round ? 31 << 10 : 0;
 }
 
 __host__ __device__ __forceinline__ int ranked_blocks(const RankedShape& s, int HU) {   // per group

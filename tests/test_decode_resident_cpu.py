@@ -39,7 +39,7 @@ def shim(tmp_path_factory):
 @pytest.mark.parametrize("resident", [16, 20])
 @pytest.mark.parametrize("N,row_bytes", [(128, 256), (384, 256), (385, 256), (4096, 256), (8192, 256)])
 def test_shape_and_lds(shim, resident, N, row_bytes):
-    cus, out = 256, (C.c_int * 5)()
+    cus, out, one_round = 256, (C.c_int * 5)(), 0
     for segs in range(33, 1025):                          # of 32 units each
         groups = (segs + 511) // 512
         gsz = (segs + groups - 1) // groups
@@ -51,8 +51,11 @@ def test_shape_and_lds(shim, resident, N, row_bytes):
         assert lds in (0, 31 << 10) and lds + 4 * 130 * 4 <= 64 << 10
         if lds:
             assert by_length and waves > 20 * cus
-        if 20 * cus >= segs * 32 > 2.5 * 16 * cus and N <= 4096 and resident == 20:
-            assert waves <= 1.03 * 20 * cus              # one round
+        if segs * 32 <= resident * cus and N <= 4096:
+            # several wavefronts per unit only where one round of 16 has room for them, or for a sixteenth each of the segments
+            assert waves <= 1.03 * max(16 * cus, 1.25 * 32 * segs)
+            one_round += 1
+    assert one_round == (resident * cus // 32 - 32 if N <= 4096 else 0)
 
 
 # Every workgroup of a ranked launch counts its units in once for each segment that it has units of, and a segment's counts add up
