@@ -64,16 +64,17 @@ struct RankedShape { int gsz, n4, n2; bool by_length, large = false; };   // lar
 // against a quarter of the segments with four wavefronts and the others with two up to 1638 units, an eighth to a sixteenth each up
 // to 8192, one each beyond, with a count of each unit by itself; 256 compute units, bf16, D 128, lengths of the segments within a
 // factor 30 / 3 / equal:
-//   up to 6.4 units per compute unit, prompts with keys of more than 192 KB per head: a quarter with four, the others with two:
-//     1600 units of 300 rows x0.99 / 0.99 / 0.97 (3/16 as below 1.04 / 1.04 / 0.95, an eighth 1.20 / 1.10 / 1.04); prompts of more than
-//     4096 positions while that is no more than a third over one round of 16: 2048 units of 500 x0.89 / 0.95 / 0.97, 5120 x0.97;
-//   shorter prompts there, 3/16 with four and as many with two, the rest one: 1600 units of 136 rows x0.87 / 0.95 / 0.85 (a quarter
-//     and the others 0.89 / 0.92 / 0.90), of 41 0.72 / 0.73 / 0.77 (0.86 / 1.12 / 0.80);
-//   beyond, an eighth each while that fits one round of 16, then what does, but a sixteenth, up to one round of single ones: 2048 units
-//     of 136 rows x0.90 / 0.91 / 0.90, of 26 0.65 / 0.64 / 0.66; 3648 of 300 an eighth 0.98 on average, a sixteenth 0.97, none 0.99; 4096 of
-//     136 fp32 rows 0.98, none 1.11;
-//   up to two rounds of 16, keys of more than 192 KB: a sixteenth each, 6144 units of 300 rows 0.97 on average, none 0.98 (8 % apart
-//     for lengths within a factor 30); of 136 rows 0.90, none 0.90, of 41 0.70 and 0.64;
+//   prompts with keys of more than 192 KB per head, as long as it fits one round: a quarter with four, the others with two: 1600
+//     units of 300 rows x0.99 / 0.99 / 0.97 (3/16 as below 1.04 / 1.04 / 0.95, an eighth 1.20 / 1.10 / 1.04), 2048 0.90 / 0.95 / 0.98 (an
+//     eighth 0.91 / 0.97 / 1.00); prompts of more than 4096 positions while that is no more than a third over a round of 16: 5120
+//     units of 500 x0.97;
+//   shorter prompts of up to 6.4 units per compute unit, 3/16 with four and as many with two, the rest one: 1600 units of 136 rows
+//     x0.87 / 0.95 / 0.85 (a quarter and the others 0.89 / 0.92 / 0.90), of 41 0.72 / 0.73 / 0.77 (0.86 / 1.12 / 0.80);
+//   beyond, an eighth each while that fits one round of 16, then what does, but a sixteenth: 2048 units of 136 rows x0.90 / 0.91 / 0.90,
+//     of 26 0.65 / 0.64 / 0.66; 3648 of 300 an eighth 0.98 on average, a sixteenth 0.97, none 0.99; 4096 of 136 fp32 rows 0.98, none 1.11;
+//   the sixteenth up to two rounds of 16, except for the plain bf16 step on keys of up to 192 KB, which has what fits its own round
+//     and then one each: 6144 units of 300 rows 0.97 on average, none 0.98 (8 % apart for lengths within a factor 30); of 136 rows 0.90,
+//     none 0.90, of 41 0.70 and 0.64;
 //   all others one each, and from 16 units per compute unit on prompts with keys of up to 96 KB per head in index order: finding
 //     the rank costs too much there, 8192 units of 26 rows x0.65, by length 0.75, of 41 rows 0.78 and 0.85.
 constexpr int kRankedResident = 20;
@@ -82,10 +83,10 @@ inline void ranked_shape(RankedShape& s, long long units, long long cus, int N, 
     const bool large = s.large = N * row_bytes > 192 << 10;
     double f4 = 0, f2 = 0;
     s.by_length = N * row_bytes > 96 << 10 || units < 16 * cus;
-    if ((large && per_unit >= 2.5) || (N > 4096 && per_unit >= 0.75)) { f4 = 0.25; f2 = 0.75; }
+    if ((large && 5 * units <= 2 * resident * cus) || (N > 4096 && per_unit >= 0.75)) { f4 = 0.25; f2 = 0.75; }
     else if (per_unit >= 2.5) f4 = f2 = 0.1875;
-    else if (s.by_length && units <= resident * cus) f4 = f2 = per_unit > 1.5 ? 0.125 : per_unit < 1.25 ? 0.0625 : (per_unit - 1) / 4;
-    else if (large && per_unit >= 0.5) f4 = f2 = 0.0625;
+    else if (s.by_length && per_unit >= (large || resident == 16 ? 0.5 : 1)) f4 = f2 = per_unit > 1.5 ? 0.125 : per_unit < 1.25 ? 0.0625 : (per_unit - 1) / 4;
+    else if (s.by_length && units <= resident * cus) f4 = f2 = ((double)resident * cus / units - 1) / 4;
     s.n4 = (int)(s.gsz * f4 + 0.5);
     s.n2 = (int)(s.gsz * f2 + 0.5);
     if (s.n2 > s.gsz - s.n4) s.n2 = s.gsz - s.n4;

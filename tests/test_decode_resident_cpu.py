@@ -52,8 +52,8 @@ def test_shape_and_lds(shim, resident, N, row_bytes):
         if lds:
             assert by_length and waves > 20 * cus
         if segs * 32 <= resident * cus and N <= 4096:
-            # several wavefronts per unit only where one round of 16 has room for them, or for a sixteenth each of the segments
-            assert waves <= 1.03 * max(16 * cus, 1.25 * 32 * segs)
+            # several wavefronts per unit only where one round has room for them, or for a sixteenth each of the segments
+            assert waves <= 1.03 * max(resident * cus, 1.25 * 32 * segs)
             one_round += 1
     assert one_round == (resident * cus // 32 - 32 if N <= 4096 else 0)
 
