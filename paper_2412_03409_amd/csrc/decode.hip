@@ -47,7 +47,6 @@ struct DecodeParams {
     const int32_t* base_lens;     // [B,L] entries kept after prefill
     int32_t* kept_pos;            // one int per slot, may be null
     int n_seg;
-    bool early;                   // smallest launches of decode_attn_kernel: units are counted in before their rows
     // grouped-query kernels: wavefronts, workspace
     int waves;
     int* ws;
@@ -264,7 +263,7 @@ __device__ __forceinline__ int ranked_segment(const int32_t* __restrict__ caps, 
 }
 
 // W wavefronts per workgroup; OCC = wavefronts per SIMD the register allocation must allow.  RANK = 0: all W work on
-// one unit.  RANK > 0: units of the longest segments first, with W, W/2 or W/4 wavefronts per unit (see the launcher).
+// one unit, -1: and it is counted in before its rows.  RANK > 0: units of the longest segments first, with W, W/2 or W/4 wavefronts per unit (see the launcher).
 template <bool BF16, int LPR, int G, int NI, int W, int OCC, bool EV, int RANK>
 __global__ void __launch_bounds__(W * kWave, OCC)
 decode_attn_kernel(DecodeParams p) {
@@ -308,7 +307,7 @@ decode_attn_kernel(DecodeParams p) {
 #pragma unroll
         for (int g = 0; g < G; ++g) qr[g] = *(const uint4*)(p.q + ((int64_t)sl * p.H + hu * G + g) * row_bytes + sub * 16);
     };
-    if constexpr (RANK == 0) {
+    if constexpr (RANK <= 0) {
         load_q();
         asm volatile("" : "+v"(len_raw), "+s"(cap), "+s"(off), "+s"(base), "+s"(qs) : : "memory");
     } else {
@@ -318,10 +317,10 @@ decode_attn_kernel(DecodeParams p) {
     // The unit is counted in once every wavefront of it has read lens.  The smallest launches: here, so that the round trip of the
     // atomic passes under the rows; it is the last wavefront's, which has the fewest.  (32 units 5.36 -> 4.94 us per launch.  Where
     // units start while others count in, their reads of lens wait for the atomics: 256 units 5 ... 20 % slower, 512 by up to half.)
-    const bool early = W == 8 && p.early;
-    const bool counter = live && uw == (early ? UW - 1 : 0) && lane == 0;
+    constexpr bool kEarly = RANK < 0;
+    const bool counter = live && uw == (kEarly ? UW - 1 : 0) && lane == 0;
     int counted = 0, count = 1;
-    if (early || (RANK > 0 && UW == 1)) {
+    if (kEarly || (RANK > 0 && UW == 1)) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
@@ -330,7 +329,7 @@ decode_attn_kernel(DecodeParams p) {
     // passed with lens read.  The atomics on the few cache lines of lens were what launches of short rows took: 2048 units of 26 rows
     // 18.5 ... 34 us in the same shape, now 17 ... 26, 12 800 of 136 rows 172 -> 160.
     if constexpr (RANK > 0) count = counted_units(wv >> (UW >> 1), W >> (UW >> 1), hu, HU);
-    if (early && counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
+    if (kEarly && counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
     // plain step: append at slot len_old.  Pruning step: len_old counts the permanent entries, the new
     // token goes to ring slot (t-1) mod (d+1), and the token stored d steps ago (ring slot t mod (d+1))
     // either becomes permanent entry len_old or is left out from now on.
@@ -464,7 +463,7 @@ decode_attn_kernel(DecodeParams p) {
             }
         }
         __syncthreads();
-        if (!early && counter && count > 0) counted = atomicAdd(p.lens + sl, count << kLenBits);
+        if (!kEarly && counter && count > 0) counted = atomicAdd(p.lens + sl, count << kLenBits);
         // merge the wavefronts of a unit: thread (g, d)
         const int w0 = wv & ~(UW - 1);
         for (int i = uw * kWave + lane; live && i < G * p.D; i += UW * kWave) {
@@ -1084,7 +1083,10 @@ static hipError_t launch_decode_s(DecodeParams p, int nblk, hipStream_t st) {
     constexpr int OCC = G >= 4 ? 2 : 4, RES = BF16 && !EV ? kRankedResident : 16, ROCC = RES > 16 ? RES / 4 : OCC;   // (the pruning step spills at five wavefronts per SIMD)
     const int HU = p.H / G, cus = compute_units();
     p.n_seg = nblk / HU;
-    p.early = 4 * nblk <= cus;
+    if (4 * nblk <= cus) {
+        hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 8, OCC, EV, -1>), dim3(HU, p.nl, p.B), dim3(8 * kWave), 0, st, p);
+        return hipGetLastError();
+    }
     if (nblk <= 2 * cus) {
         hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 8, OCC, EV, 0>), dim3(HU, p.nl, p.B), dim3(8 * kWave), 0, st, p);
         return hipGetLastError();
@@ -1179,7 +1181,7 @@ static DecodeParams make_params(const pkv_shape& s, int l0, int l1, const void* 
     p.kc = (unsigned char*)kc; p.vc = (unsigned char*)vc; p.seg_off = seg_off; p.caps = caps;
     p.lens = lens; p.out = (unsigned char*)out;
     p.N = s.N; p.t = 0; p.d = 0; p.base_lens = nullptr; p.kept_pos = nullptr;
-    p.n_seg = 0; p.early = false; p.waves = 0; p.ws = nullptr;
+    p.n_seg = 0; p.waves = 0; p.ws = nullptr;
     p.rank = RankedShape{0, 0, 0, false};
     return p;
 }
