@@ -196,7 +196,6 @@ prefill_attn_kernel(PrefillParams p) {
         for (int kt = 0; kt < NKT; ++kt) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[kt][r] = 0.f;
-            if (kt == 1 && !second) break;
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 const bf16x8_t kf = __builtin_bit_cast(bf16x8_t, *(const uint4*)(sK + kt * 32 * ROWB + koff[j]));
