@@ -19,6 +19,15 @@ BF16 = torch.bfloat16
     (3, 9, 12, 3, 700, 64, 0.5, 2, None),       # a wavefront ends in the middle of units
     (11, 24, 4, 2, 40, 128, 0.5, 2, None),      # 264 segments
     (9, 61, 8, 1, 24, 64, 0.5, 1, (0, 60)),     # 540 segments of a block or two
+    # several head groups per KV head (6: three of 2, 12: three of 4, 16: two of 8): the first one stores the appended row
+    (2, 3, 12, 2, 300, 128, 0.5, 2, None),
+    (1, 2, 12, 2, 700, 64, 0.6, 2, None),
+    (1, 2, 12, 1, 500, 128, 0.9, 2, None),
+    (3, 4, 24, 2, 90, 64, 0.5, 3, (1, 4)),
+    (1, 2, 16, 1, 700, 128, 0.7, 2, None),
+    (2, 3, 32, 2, 200, 64, 0.6, 2, None),
+    (1, 1, 16, 1, 8192, 128, 0.9, 1, None),     # a unit in over 200 wavefronts
+    (1, 9, 12, 2, 4100, 64, 0.9, 1, None),      # three or four blocks a wavefront
 ])
 def test_stream(B, L, H, Hkv, N, D, frac, steps, layers):
     run_decode_case(B, L, H, Hkv, N, D, BF16, frac, steps, seed=B * L + H, layer_range=layers)
@@ -34,6 +43,10 @@ def test_empty_segments(D):
     (2, 3, 8, 2, 90, 64, 0.4, 15, 34),          # ring and survivors cross block borders
     (1, 5, 32, 4, 400, 128, 0.5, 7, 20),
     (11, 24, 4, 2, 33, 64, 0.5, 3, 7),          # 264 segments
+    (2, 3, 12, 2, 90, 128, 0.4, 7, 18),         # several head groups per KV head: the first one moves the survivor
+    (1, 3, 12, 1, 200, 64, 0.5, 5, 14),
+    (2, 2, 16, 1, 120, 64, 0.5, 15, 34),
+    (1, 2, 32, 2, 400, 128, 0.5, 3, 9),
 ])
 def test_stream_with_pruning(B, L, H, Hkv, N, D, frac, d, steps):
     run_evict_case(B, L, H, Hkv, N, D, BF16, frac, d, steps, seed=B * L + H)
