@@ -554,12 +554,6 @@ __device__ __forceinline__ SegState seg_state(const DecodeParams& p, int len_old
 
 __device__ __forceinline__ int seg_slot(const DecodeParams& p, int i) { return (i / p.nl) * p.L + p.l0 + i % p.nl; }
 
-// Workspace: [0] the share, from word 16 the first block / HU of every segment and their total (n_seg + 1), then, 16-word
-// aligned, the partial results: [G][D] numerators, [G][2] max and denominator.  What wavefront w has of unit u sits in slot w + u:
-// along the stream one of the two goes up from one piece to the next, so no two pieces share a slot.
-constexpr int kGqaHdr = 16;
-__host__ __device__ inline int gqa_partial_word(int n_seg) { return (kGqaHdr + n_seg + 1 + 15) / 16 * 16; }
-
 // inclusive sum over the lanes, by DPP: every wavefront waits for it before its first rows
 __device__ __forceinline__ int wave_scan(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
@@ -713,16 +707,16 @@ decode_gqa_kernel(DecodeParams p) {
     set_segment(cur, mine);
     int blk;
     {
-        const int rem = x0 - first * HU, hu = rem / cur.nb;
-        blk = rem - hu * cur.nb;
-        enter_head(cur, hu);
+        const GqaPlace at = gqa_place(x0, first, cur.nb, HU);
+        blk = at.blk;
+        enter_head(cur, at.hu);
     }
     auto advance = [&](Unit& u, int& b, int& i) {          // true: a new unit
-        if (b + 1 < u.nb) { ++b; return false; }
-        b = 0;
-        if (u.hu + 1 < HU) enter_head(u, u.hu + 1);
-        else { ++i; enter_segment(u, i); enter_head(u, 0); }
-        return true;
+        int hu = u.hu;
+        const GqaNext next = gqa_next(b, hu, i, u.nb, HU);
+        if (next == GqaNext::segment) enter_segment(u, i);
+        if (next != GqaNext::block) enter_head(u, hu);
+        return next != GqaNext::block;
     };
     // copies of a block; K's chunks swizzled so that 16 rows at one chunk lie in different banks
     auto kpos = [](int row) { return LPR == 16 ? row & 15 : (row >> 1) & 7; };
@@ -943,7 +937,7 @@ decode_gqa_kernel(DecodeParams p) {
             const int E0 = (lane >> 5) * G * 4 + ((lane >> 4) & 1) * G * 2;
             const bool whole = ends && begun >= x0;
             const bool writes = LPR == 16 || (lane & 8) == 0;
-            float* part = (float*)p.ws + gqa_partial_word(n) + (size_t)(gid + seg * HU + cur.hu) * (G * (D + 2));
+            float* part = (float*)p.ws + gqa_partial_word(n) + (size_t)gqa_slot(gid, seg, cur.hu, HU) * (G * (D + 2));
 #pragma unroll
             for (int e = 0; e < G * 2; e += 4) {
                 const int g = (E0 + e) / 8, col = sub * 8 + (E0 + e) % 8;
@@ -988,9 +982,10 @@ decode_gqa_merge_kernel(DecodeParams p) {
     const int first = uniform_load(p.ws + kGqaHdr + i), nb = uniform_load(p.ws + kGqaHdr + i + 1) - first;
     if (hu == 0 && tid == 0)
         p.lens[sl] = seg_state<EV>(p, p.lens[sl] & kLenMask, p.caps[sl], p.seg_off[sl], EV ? p.base_lens[sl] : 0).len_next;
-    const int b0 = first * HU + hu * nb, w0 = b0 / share, np = (b0 + nb - 1) / share - w0 + 1;
+    const GqaPieces pieces = gqa_pieces(first, nb, hu, HU, share);
+    const int np = pieces.n;
     if (np == 1) return;                                 // one wavefront had it all and wrote the output
-    const float* ws = (const float*)p.ws + gqa_partial_word(p.n_seg) + (size_t)(w0 + (int)blockIdx.x) * PST;
+    const float* ws = (const float*)p.ws + gqa_partial_word(p.n_seg) + (size_t)gqa_slot(pieces.wave, i, hu, HU) * PST;
     const int e = tid % NE, pg = tid / NE, g = e * 4 / D;
     const int per = (np + PG - 1) / PG, k0 = pg * per, k1 = k0 + per < np ? k0 + per : np;
     // numerators, denominator and the maximum they refer to of the group's pieces, in one pass over them

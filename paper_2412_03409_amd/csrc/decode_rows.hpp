@@ -155,6 +155,35 @@ __host__ __device__ __forceinline__ int gqa_share(int all, int waves, int least 
     return even < least ? least : even;
 }
 
+// The stream of blocks of a grouped-query launch: segment by segment, the head groups (HU) of a segment one after the other, nb
+// blocks each, `first` blocks per head group in the segments before.  Wavefront w has blocks [w * share, (w + 1) * share).
+struct GqaPlace { int hu, blk; };
+__host__ __device__ __forceinline__ GqaPlace gqa_place(int x, int first, int nb, int HU) {   // of block x, which lies in the segment
+    const int rem = x - first * HU, hu = rem / nb;
+    return {hu, rem - hu * nb};
+}
+enum class GqaNext { block, head, segment };             // what the following block is the next of
+__host__ __device__ __forceinline__ GqaNext gqa_next(int& blk, int& hu, int& seg, int nb, int HU) {
+    if (++blk < nb) return GqaNext::block;
+    blk = 0;
+    if (++hu < HU) return GqaNext::head;
+    hu = 0;
+    ++seg;
+    return GqaNext::segment;
+}
+// Where wavefront w leaves what it has of a unit that it shares with others: along the stream one of the two goes up from one
+// piece to the next, so no two pieces share a slot.
+__host__ __device__ __forceinline__ int gqa_slot(int w, int seg, int hu, int HU) { return w + seg * HU + hu; }
+struct GqaPieces { int wave, n; };                       // the first wavefront that has some of a unit, and how many do
+__host__ __device__ __forceinline__ GqaPieces gqa_pieces(int first, int nb, int hu, int HU, int share) {
+    const int b0 = first * HU + hu * nb, w = b0 / share;
+    return {w, (b0 + nb - 1) / share - w + 1};
+}
+// Workspace in words: [0] the share, from kGqaHdr the first block / HU of every segment and their total (n_seg + 1), then, 16-word
+// aligned, the slots: [G][D] numerators, [G][2] max and denominator.
+constexpr int kGqaHdr = 16;
+__host__ __device__ inline int gqa_partial_word(int n_seg) { return (kGqaHdr + n_seg + 1 + 15) / 16 * 16; }
+
 // The workspace of a grouped-query launch starts at the first multiple of 16 in the caller's, which may have any address: partial
 // results are written and read by 16 bytes.  The size query adds kGqaWsAlign bytes for it.
 constexpr int kGqaWsAlign = 16;

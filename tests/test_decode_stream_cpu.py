@@ -24,6 +24,24 @@ extern "C" int rows(int ev, int len, int cap, int base, int append, int t, int d
     *blocks = pkv::row_blocks(r.rows, block);
     return r.rows * 2 + r.app;
 }
+// the blocks [w * share, ...) of a launch as the attention kernel walks them from segment `seg` on: seg, hu, blk, slot of each, -1
+// for the slot of one that ends no piece in the workspace
+extern "C" int kernel_walk(int w, int share, int all, int seg, const int* nb, const int* first, int HU, int* out) {
+    const int x0 = w * share, x1 = x0 + share < all ? x0 + share : all;
+    if (x0 >= all) return 0;
+    const pkv::GqaPlace at = pkv::gqa_place(x0, first[seg], nb[seg], HU);
+    int hu = at.hu, blk = at.blk, begun = x0 - blk;
+    for (int x = x0;; ++x, out += 4) {
+        const bool ends = blk + 1 == nb[seg], more = x + 1 < x1, shared = !(ends && begun >= x0);
+        out[0] = seg; out[1] = hu; out[2] = blk; out[3] = (ends || !more) && shared ? pkv::gqa_slot(w, seg, hu, HU) : -1;
+        if (!more) return x1 - x0;
+        if (pkv::gqa_next(blk, hu, seg, nb[seg], HU) != pkv::GqaNext::block) begun = x + 1;
+    }
+}
+extern "C" void merge_slots(int first, int nb, int seg, int hu, int HU, int share, int* out) {
+    const pkv::GqaPieces p = pkv::gqa_pieces(first, nb, hu, HU, share);
+    out[0] = p.n; out[1] = pkv::gqa_slot(p.wave, seg, hu, HU);
+}
 extern "C" unsigned long long base(unsigned long long at) { return pkv::gqa_ws_base(at); }
 """
 
@@ -115,6 +133,35 @@ def test_every_block_once_in_short_launches(shim):
             one = [all for all in range(1, 3000) if shim.least(all, 2048, units, width) == 1]
             assert one == list(range(1, min(1024, 32768 * units // width) + 1))
             assert all(shim.share_of(x, 2048, 1) == 1 for x in one)
+
+
+# The same with the rules that the kernels compile: the walk of a wavefront, the slots it leaves pieces in and those the merge reads.
+def test_rules_of_the_kernels(shim):
+    rng, out = random.Random(3), (C.c_int * 40000)()
+    for _ in range(300):
+        n, HU, BR, waves = rng.randint(1, 40), rng.choice([1, 2, 3, 8]), rng.choice([16, 32]), rng.choice([1, 2, 7, 64, 2048])
+        lens = [rng.choice([0, 1, rng.randint(0, 40), rng.randint(0, 900)]) for _ in range(n)]
+        nb = [max(1, -(-x // BR)) for x in lens]
+        first = [sum(nb[:i]) for i in range(n)]
+        everything = sum(nb) * HU
+        share = shim.share_of(everything, waves, rng.choice([1, 2]))
+        c_nb, c_first = (C.c_int * n)(*nb), (C.c_int * n)(*first)
+        blocks, slots = [], {}
+        for w in range(-(-everything // share)):
+            seg = max(i for i in range(n) if first[i] <= w * share // HU)
+            for i in range(shim.kernel_walk(w, share, everything, seg, c_nb, c_first, HU, out)):
+                blocks.append(tuple(out[4 * i:4 * i + 3]))
+                if out[4 * i + 3] >= 0:
+                    assert out[4 * i + 3] not in slots
+                    slots[out[4 * i + 3]] = blocks[-1][:2]
+        assert blocks == [(s, hu, b) for s in range(n) for hu in range(HU) for b in range(nb[s])]
+        assert max(slots, default=-1) < waves + n * HU
+        for s in range(n):
+            for hu in range(HU):
+                shim.merge_slots(first[s], nb[s], s, hu, HU, share, out)
+                for k in range(out[0] if out[0] > 1 else 0):
+                    assert slots.pop(out[1] + k) == (s, hu)
+        assert not slots
 
 
 # Whatever the prompt's length and the number of segments there is a slot for each unit and for each of the 2048 wavefronts of a
