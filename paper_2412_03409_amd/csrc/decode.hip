@@ -498,13 +498,18 @@ decode_attn_kernel(DecodeParams p) {
 // unit that other wavefronts share goes to the workspace as (numerators, max, denominator); decode_gqa_merge_kernel adds
 // those up in block order and advances lens, so nothing counts arrivals and the result does not depend on timing.
 //
-// Long caches are bound by the rate at which a compute unit's reads are served (6.6 TB/s while all wavefronts are at work; they
-// end between 59 and 80 us, and larger first shares with smaller ones dispatched behind them cost more in starts than they
-// even out: 84 -> 90 us), short ones by the chain lengths -> block counts -> state -> first block and by the two launches.
-// Against the kernel before, which claimed pieces of 1024 rows from a planned list, one workgroup each, and handed a split
-// segment to the last arriver (7 us per piece between the streams of rows), us per step, D 128, lengths within a factor 30:
-//   B4 H32/8 N8192 10 % 97 -> 84 (equal lengths 84 -> 87), B1 50 % 109 -> 94, B8 N1000 20 % 65 -> 51, B1 N2000 20 % 33 -> 21, with pruning
-//   B4 N2000 45 -> 35, H32/4 B8 N2000 10 % 56 -> 44, B2 N8192 49 -> 34; one layer a call: B4 N8192 28 -> 16, B1 N2000 17 -> 11.
+// Long caches are bound by the rate at which a compute unit's reads are served (6.6 TB/s while all wavefronts are at work; at
+// B4 H32/8 N8192 10 % they ended between 59 and 84 us of a launch, between 63 and 80 since they give way as they get on, and
+// larger first shares with smaller ones dispatched behind them cost more in starts than they even out: 84 -> 90 us), short ones
+// by the chain lengths -> block counts -> first block and by the two launches.  Against the kernel before, which claimed pieces of
+// 1024 rows from a planned list, one workgroup each, and handed a split segment to the last arriver (7 us per piece between the
+// streams of rows), us per step, lengths within a factor 30, D 128 (D 64):
+//   B4 H32/8 N8192 10 % 96 -> 81 (61 -> 45), equal lengths 84 -> 75 (54 -> 43), the whole cache 725 -> 665 (382 -> 337); B64 N680 10 %
+//   279 -> 193 (227 -> 135), B8 N680 20 % 57 -> 42, B1 N2000 35 -> 21, N500 18 -> 13 (15 -> 10); with pruning B4 N2000 62 -> 47; H32/4 B32
+//   N2000 10 % 136 -> 119, B1 N2000 20 % 42 -> 20; one layer a call: B1 N2000 20 % 16.5 -> 9.4, a single layer kept whole N500 15.9 ->
+//   9.7 (12.5 -> 8.8), N8192 34 -> 20.
+// The running numerators take one addition per row: 256 of them are off by 2e-7 (fp64), 4096 by 1.3e-6.  The block's own sums first
+// halves that, far below the bf16 output's 2e-3, and costs up to 9 % (H32/4, D 64, B4 260 MB 54 -> 59 us).
 //   scores^T[16 rows x 16 head columns] = K[16 rows x D] . Q^T with v_mfma_f32_16x16x32_bf16 (A = cache rows from LDS, B = the
 //   queries, head lane%16, columns >= G are zero): a lane holds four rows of one head, and softmax runs in that layout.  The
 //   weighted sum stays on the vector ALU with fp32 probabilities: a group of 16 lanes takes the V rows whose probabilities
@@ -1060,8 +1065,8 @@ int compute_units() {
 
 // Launch shapes of decode_attn_kernel.  A unit is one head group of one segment; its rows are dealt to its
 // wavefronts in blocks of NI * 64/LPR rows.  What decides is how many wavefronts a launch has: 16 per compute unit are
-// resident (4 per SIMD; 20 of a ranked launch of the plain bf16 step), and starting one costs the dispatcher about 7 ns whatever it does (12 800 units: 393 us with
-// four wavefronts each, 173 us with one, for rows that stream in 150 us).  Hence
+// resident (4 per SIMD; 20 of a ranked launch of the plain bf16 step), and each start costs (12 800 units of 26 rows, one
+// wavefront each: 42 us, of 136 rows 160, for rows that stream in 30 and 150).  Hence
 //   up to 2 units per compute unit: 8 wavefronts per unit (32 units, one layer of the 7B shape: 8.6 -> 6.1 us; 16 wavefronts
 //       per unit 6.2);
 //   up to 4: 4 wavefronts per unit, which fill the chip (7B, batch 1, lengths within a factor 30: 21.3 -> 18.7 us; equal: 21.7

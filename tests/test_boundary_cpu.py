@@ -206,7 +206,7 @@ def test_compact_and_decode_argument_errors():
     assert dec(l1=5) == 2
     assert dec(sh=_shape(H=4096, Hkv=2)) == 2
     assert dec(q=C.c_void_p(0x1008)) == 4
-    gqa = _shape(H=32, Hkv=8, dtype=P.PKV_BF16)   # grouped-query bf16: the work list lives in the workspace
+    gqa = _shape(H=32, Hkv=8, dtype=P.PKV_BF16)   # grouped-query bf16: partial results meet in the workspace
     need = P.prefixkv_workspace_bytes(Bd.OP_DECODE, gqa.B, gqa.L, gqa.H, gqa.Hkv, gqa.N, gqa.D, gqa.dtype)
     assert need > 0
     assert dec(sh=gqa) == 5

@@ -1,5 +1,8 @@
-"""CPU models of the grouped-query decode path (decode_plan_kernel + decode_gqa_kernel): no attention
-arithmetic, only what decides whether an access is in bounds and whether a read sees its writer.
+"""CPU models of a grouped-query decode path that this library no longer has (a planned list of pieces, claimed by workgroups, whose
+partial results the last arriver added up).  They import nothing of the library and say nothing about its present kernels, which
+claim nothing and count no arrivals (test_decode_stream_cpu.py); they are kept as the record of what was checked about the old
+protocol after a GPU fault whose cause was not found.  No attention arithmetic, only what decides whether an access is in bounds
+and whether a read sees its writer.
 
 1. Index model: the planning rule (pieces of S rows, S doubled until the list fits) and the row walk of the
    attention kernel, checked against the segment capacities for long-context-like length mixes.
