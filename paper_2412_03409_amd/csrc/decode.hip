@@ -42,8 +42,9 @@ struct DecodeParams {
     const int32_t* caps;          // [B,L]
     int32_t* lens;                // [B,L]
     unsigned char* out;           // [B,L,H,D]
-    // pruning at a fixed distance (decode_attn_kernel<..., EV = true> only)
+    // pruning at a fixed distance (EV = true only)
     int N, t, d;                  // prompt length, 1-based decode step, distance
+    int slot_new, slot_due;       // ring slots of the token stored in this step and of the one decided in it
     const int32_t* base_lens;     // [B,L] entries kept after prefill
     int32_t* kept_pos;            // one int per slot, may be null
     int n_seg;
@@ -67,6 +68,10 @@ __device__ __forceinline__ uint4 load_stream16(const unsigned char* p) {
 // wait for the copies that were requested before it.
 template <class T>
 __device__ __forceinline__ T uniform_load(const T* x) { return *(const __attribute__((address_space(4))) T*)(uintptr_t)x; }
+
+__device__ __forceinline__ int64_t uniform64(int64_t x) {   // a value that is the same in all lanes, in scalar registers
+    return ((int64_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
 
 template <bool BF16>
 __device__ __forceinline__ void unpack16(const uint4& r, float* f) {
@@ -116,45 +121,11 @@ __device__ __forceinline__ float over_groups(float x, F f) {
     return with_xor32(x, f);
 }
 
-// Rows r0 .. r0 + BR - 1 of one block (BR = NI * 64/LPR; LPR lanes cover a row with 16 bytes each) into registers.
-// Blocks of occupied cache slots only take the plain path.  In the guarded one the row being appended comes from
-// k_new / v_new, under pruning ring rows map to the ring slots, and rows that do not take part (past the end, or
-// pruned in this step) are read like the block's first row and ignored by attend_block: every load is issued
-// without a branch.
-template <int LPR, int NI, bool EV>
-__device__ __forceinline__ void load_block(uint4 (&kr)[NI], uint4 (&vr)[NI], int r0, int len, int len_old, bool app,
-                                           const RingMap& ring, const unsigned char* kseg, const unsigned char* vseg,
-                                           const unsigned char* knew, const unsigned char* vnew, int row_bytes,
-                                           int sub, int rg) {
-    constexpr int RPI = kWave / LPR;
-    const uint32_t lane_off = (uint32_t)(r0 + rg) * (uint32_t)row_bytes + (uint32_t)sub * 16u;
-    if (r0 + NI * RPI <= len_old) {
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const uint32_t o_i = lane_off + (uint32_t)(i * RPI) * (uint32_t)row_bytes;
-            kr[i] = load_stream16(kseg + o_i);
-            vr[i] = load_stream16(vseg + o_i);
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const RowSource s = row_source<EV>(r0 + i * RPI + rg, r0, len, len_old, app, ring);
-            const uint32_t o_i = (uint32_t)s.slot * (uint32_t)row_bytes + (uint32_t)sub * 16u;
-            kr[i] = load_stream16(s.from_new ? knew + sub * 16 : kseg + o_i);
-            vr[i] = load_stream16(s.from_new ? vnew + sub * 16 : vseg + o_i);
-        }
-    }
-}
-
-// Online-softmax update of (mrun, srun, o) with one block for the G query heads of the group.
-template <bool BF16, int LPR, int G, int NI, bool EV>
-__device__ __forceinline__ void attend_block(const uint4 (&kr)[NI], uint4 (&vr)[NI], int r0, int len, int len_old,
-                                             const RingMap& ring, int rg, const float (&qf)[G][BF16 ? 8 : 4],
-                                             float (&o)[G][BF16 ? 8 : 4], float (&mrun)[G], float (&srun)[G]) {
+// One query head group and one block of NI * 64/LPR rows (LPR lanes cover a row with 16 bytes each, a lane has NI rows).
+// Scores from the K rows, summed over the lanes of a row.
+template <bool BF16, int LPR, int G, int NI>
+__device__ __forceinline__ void block_scores(const uint4 (&kr)[NI], const float (&qf)[G][BF16 ? 8 : 4], float (&s)[G][NI]) {
     constexpr int EPL = BF16 ? 8 : 4;
-    constexpr int RPI = kWave / LPR;
-    const bool full = r0 + NI * RPI <= len_old;
-    float s[G][NI];
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
         float kf[EPL];
@@ -171,17 +142,12 @@ __device__ __forceinline__ void attend_block(const uint4 (&kr)[NI], uint4 (&vr)[
     for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int g = 0; g < G; ++g) s[g][i] = row_sum<LPR>(s[g][i]);
-    if (!full) {
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const int r = r0 + i * RPI + rg;
-            const bool valid = r < len && (!EV || r != ring.r_mask);
-#pragma unroll
-            for (int g = 0; g < G; ++g) s[g][i] = valid ? s[g][i] : -INFINITY;
-            vr[i].x = valid ? vr[i].x : 0; vr[i].y = valid ? vr[i].y : 0;   // 0 * (what is there) could be NaN
-            vr[i].z = valid ? vr[i].z : 0; vr[i].w = valid ? vr[i].w : 0;
-        }
-    }
+}
+// Online-softmax update of (mrun, srun, o) with the block.
+template <bool BF16, int LPR, int G, int NI>
+__device__ __forceinline__ void block_values(const float (&s)[G][NI], const uint4 (&vr)[NI], float (&o)[G][BF16 ? 8 : 4],
+                                             float (&mrun)[G], float (&srun)[G]) {
+    constexpr int EPL = BF16 ? 8 : 4;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         float mx = s[g][0];
@@ -209,6 +175,9 @@ __device__ __forceinline__ void attend_block(const uint4 (&kr)[NI], uint4 (&vr)[
 #pragma unroll
         for (int x = 0; x < EPL; ++x) o[g][x] = fmaf(o[g][x], corr, ob[x]);
     }
+}
+__device__ __forceinline__ uint4 select16(bool first, const uint4& a, const uint4& b) {
+    return make_uint4(first ? a.x : b.x, first ? a.y : b.y, first ? a.z : b.z, first ? a.w : b.w);
 }
 
 // Maximum over the wavefront.
@@ -262,19 +231,32 @@ __device__ __forceinline__ int ranked_segment(const int32_t* __restrict__ caps, 
     return found;
 }
 
-// W wavefronts per workgroup; OCC = wavefronts per SIMD the register allocation must allow.  RANK = 0: all W work on
-// one unit, -1: and it is counted in before its rows.  RANK > 0: units of the longest segments first, with W, W/2 or W/4 wavefronts per unit (see the launcher).
+__device__ __forceinline__ int seg_slot(const DecodeParams& p, int i) { return (i / p.nl) * p.L + p.l0 + i % p.nl; }
+
+// inclusive sum over the lanes, by DPP: every wavefront waits for it before its first rows
+__device__ __forceinline__ int wave_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15, to the odd rows of 16
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31, to the upper half
+    return v;
+}
+
+// W wavefronts per workgroup; OCC = wavefronts per SIMD the register allocation must allow.  RANK = 0: all W are for one unit, -1: and it
+// is counted in before its rows.  RANK > 0: units of the longest segments first, with W, W/2 or W/4 wavefronts per unit (see the launcher).
 template <bool BF16, int LPR, int G, int NI, int W, int OCC, bool EV, int RANK>
 __global__ void __launch_bounds__(W * kWave, OCC)
 decode_attn_kernel(DecodeParams p) {
     constexpr int EPL = BF16 ? 8 : 4;            // elements per lane (16 bytes)
     constexpr int RPI = kWave / LPR;             // rows per wavefront-wide load instruction
     constexpr int BR = NI * RPI;                 // rows per block
-    constexpr int ESZ = BF16 ? 2 : 4;
-    constexpr int DMAX = 128;
-    __shared__ float s_part[W][G][DMAX + 2];
+    constexpr int D = LPR * EPL, ROWB = LPR * 16;
+    __shared__ float s_num[W][G][D];
+    __shared__ float2 s_md[W][G];                // maximum and denominator
 
-    const int HU = p.H / G;                      // units per segment
+    const int HU = p.H / G;                     // units per segment
     const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     int UW = W, hu, b, l;
     bool live = true;
@@ -289,77 +271,90 @@ decode_attn_kernel(DecodeParams p) {
     } else {
         hu = blockIdx.x; l = p.l0 + blockIdx.y; b = blockIdx.z;
     }
-    const int uw = wv & (UW - 1);
     const int sl = b * p.L + l;
     const int sub = lane % LPR, rg = lane / LPR;
-    const int row_bytes = p.D * ESZ;
 
-    // What the first rows wait for.  One unit per workgroup: in one round trip to memory (left to itself the compiler waits for
-    // the length before it requests the capacity, and for that before the offset and the queries).  The ranked launches have
-    // enough other wavefronts, and there it cost 1 ... 2 %.
+    // What the first rows wait for, in one round trip to memory (left to itself the compiler waits for the length before it
+    // requests the capacity, and for that before the offset and the queries): the words of the segment and the other arguments.
     int len_raw = __hip_atomic_load(p.lens + sl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);   // from the caches: the length is the same in every value of this launch
     int cap = uniform_load(p.caps + sl);
     int64_t off = uniform_load(p.seg_off + sl);
     int base = EV ? uniform_load(p.base_lens + sl) : 0;
-    float qs = uniform_load(p.scale + l);
     uint4 qr[G];
     auto load_q = [&]() {
 #pragma unroll
-        for (int g = 0; g < G; ++g) qr[g] = *(const uint4*)(p.q + ((int64_t)sl * p.H + hu * G + g) * row_bytes + sub * 16);
+        for (int g = 0; g < G; ++g) qr[g] = *(const uint4*)(p.q + ((int64_t)sl * p.H + hu * G + g) * ROWB + sub * 16);
     };
-    if constexpr (RANK <= 0) {
-        load_q();
-        asm volatile("" : "+v"(len_raw), "+s"(cap), "+s"(off), "+s"(base), "+s"(qs) : : "memory");
-    } else {
-        asm volatile("" : "+v"(len_raw) : : "memory");
-    }
+    constexpr bool kOne = RANK <= 0;                         // one unit per workgroup
+    if constexpr (kOne) load_q();
+    asm volatile("" : "+v"(len_raw), "+s"(cap), "+s"(off), "+s"(base)
+                 : "s"(p.kc), "s"(p.vc), "s"(p.k_new), "s"(p.v_new), "s"(p.out), "s"(p.scale), "s"(p.Hkv), "s"(p.grp), "s"(p.append) : "memory");
+    const float scale = uniform_load(p.scale + l);
     const int len_old = __builtin_amdgcn_readfirstlane(len_raw) & kLenMask;
+    cap = __builtin_amdgcn_readfirstlane(cap);
+    off = uniform64(off);
+    const int uw = wv & (UW - 1);
     // The unit is counted in once every wavefront of it has read lens.  The smallest launches: here, so that the round trip of the
     // atomic passes under the rows; it is the last wavefront's, which has the fewest.  (32 units 5.36 -> 4.94 us per launch.  Where
     // units start while others count in, their reads of lens wait for the atomics: 256 units 5 ... 20 % slower, 512 by up to half.)
-    constexpr bool kEarly = RANK < 0;
+    constexpr bool kEarly = RANK == -1;
     const bool counter = live && uw == (kEarly ? UW - 1 : 0) && lane == 0;
     int counted = 0, count = 1;
-    if (kEarly || (RANK > 0 && UW == 1)) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    if (kEarly || (!kOne && UW == 1)) {
+        asm volatile("" : : : "memory");                     // nothing but lens is behind this barrier, and its value has arrived
         __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        asm volatile("" : : : "memory");
     }
-    // Ranked launches: the first of the workgroup's units of a segment counts all of them in, behind a barrier that they have
-    // passed with lens read.  The atomics on the few cache lines of lens were what launches of short rows took: 2048 units of 26 rows
-    // 18.5 ... 34 us in the same shape, now 17 ... 26, 12 800 of 136 rows 172 -> 160.
-    if constexpr (RANK > 0) count = counted_units(wv >> (UW >> 1), W >> (UW >> 1), hu, HU);
-    if (kEarly && counter) counted = atomicAdd(p.lens + sl, 1 << kLenBits);
+    // The first of the workgroup's units of a segment counts all of them in, behind a barrier that they have
+    // passed with lens read.  The atomics on the few cache lines of lens were what launches of short rows took, about 8 ns each: 2048 units
+    // of 26 rows 18.5 ... 34 us in the same shape, now 17 ... 26, 12 800 of 136 rows 172 -> 160.
+    if constexpr (!kOne) count = counted_units(wv / UW, W / UW, hu, HU);
+    // The result is wanted at the end only; of an address that it knows to be uniform the compiler makes a sum over the lanes first
+    // and waits for the atomic on the spot.
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    auto count_in = [&]() { counted = atomicAdd(p.lens + sl + zero, count << kLenBits); };
+    if (kEarly && counter) count_in();
     // plain step: append at slot len_old.  Pruning step: len_old counts the permanent entries, the new
     // token goes to ring slot (t-1) mod (d+1), and the token stored d steps ago (ring slot t mod (d+1))
     // either becomes permanent entry len_old or is left out from now on.
-    bool app = p.append && len_old < cap;
-    int len = len_old + (app ? 1 : 0), len_next = len;
+    const StepRows step = step_rows<EV>(len_old, cap, base, p.append, p.t, p.d);   // under pruning nothing if the capacity cannot hold the ring
+    const bool app = step.app;
+    const int len = step.rows;
+    int len_next = len, ring0 = 0;
     RingMap ring = {0, -1, -1};
-    int ring0 = 0, cs = 0;
     bool grad = false, decide = false;
     if constexpr (EV) {
         ring0 = cap - (p.d + 1);
-        app = base >= 0 && ring0 >= base && len_old <= ring0;   // else: capacity cannot hold the ring
         decide = app && p.t > p.d;
-        cs = p.t % (p.d + 1);
-        long long target = (2ll * base * ((long long)p.N + p.t) + p.N) / (2ll * p.N);
-        target = target < 1 ? 1 : target;
-        grad = decide && (long long)len_old + p.d + 1 <= target && len_old < ring0;
+        grad = decide && len_old < ring0 && within_target(len_old + p.d + 1, base, p.N, p.t);
         ring.shift = ring0 - len_old;
-        ring.r_new = len_old + (p.t - 1) % (p.d + 1);
-        ring.r_mask = (decide && !grad) ? len_old + cs : -1;
-        len = app ? len_old + (p.t < p.d + 1 ? p.t : p.d + 1) : 0;
+        ring.r_new = len_old + p.slot_new;
+        ring.r_mask = (decide && !grad) ? len_old + p.slot_due : -1;
         len_next = len_old + (grad ? 1 : 0);
     }
-    const int nb = live ? (len + BR - 1) / BR : 0;
+    const int nb = live ? (len + BR - 1) / BR : 0, nfull = len_old / BR;
     const int kvh = p.grp == G ? hu : (hu * G) / p.grp;
     const bool writer = app && live && (p.grp == G || (hu * G) % p.grp == 0);
-    const int64_t segbase = (off * p.Hkv + (int64_t)kvh * cap) * row_bytes;
-    const int64_t newrow = ((int64_t)sl * p.Hkv + kvh) * row_bytes;
+    const int64_t segbase = uniform64((off * p.Hkv + (int64_t)kvh * cap) * ROWB);
+    const int64_t newrow = ((int64_t)sl * p.Hkv + kvh) * ROWB;
     unsigned char* kseg = p.kc + segbase;
     unsigned char* vseg = p.vc + segbase;
 
+    // The new row: the wavefront that has its block takes it from k_new / v_new, requested ahead of the cached rows, and stores it
+    // behind them.  Under pruning the same one moves the surviving token from its ring slot to the next permanent slot (attention
+    // reads it from the ring slot; nobody reads the permanent slot in this launch).
+    const int r_new = EV ? ring.r_new : len_old;
+    const bool own = app && live && ((r_new / BR) & (UW - 1)) == uw;
+    uint4 nk = make_uint4(0, 0, 0, 0), nv = nk, gk = nk, gv = nk;
+    if (own) {
+        nk = *(const uint4*)(p.k_new + newrow + sub * 16);
+        nv = *(const uint4*)(p.v_new + newrow + sub * 16);
+        if (EV && grad) {
+            gk = *(const uint4*)(kseg + (size_t)(ring0 + p.slot_due) * ROWB + sub * 16);
+            gv = *(const uint4*)(vseg + (size_t)(ring0 + p.slot_due) * ROWB + sub * 16);
+        }
+    }
     float o[G][EPL], mrun[G], srun[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -368,41 +363,82 @@ decode_attn_kernel(DecodeParams p) {
         for (int x = 0; x < EPL; ++x) o[g][x] = 0.f;
     }
     if (uw < nb) {
-        float qf[G][EPL];
-        if constexpr (RANK > 0) load_q();
-        qs *= 1.4426950408889634f;
+        if constexpr (!kOne) load_q();
+        // a segment with no row but the new one: k_new / v_new stand in for its slots
+        const bool lone = app && len == 1;
+        const unsigned char *kload = lone ? p.k_new + newrow : kseg, *vload = lone ? p.v_new + newrow : vseg;
+        float qf[G][EPL] = {};
+        auto scale_q = [&]() {                               // while the first rows are on their way, not ahead of them
+            float qs = scale;
+            asm volatile("" : "+s"(qs));
+            qs *= 1.4426950408889634f;
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            unpack16<BF16>(qr[g], qf[g]);
+            for (int g = 0; g < G; ++g) {
+                uint4 t = qr[g];
+                asm volatile("" : "+v"(t.x), "+v"(t.y), "+v"(t.z), "+v"(t.w));
+                unpack16<BF16>(t, qf[g]);
 #pragma unroll
-            for (int x = 0; x < EPL; ++x) qf[g][x] *= qs;
-        }
-        auto load = [&](uint4 (&kr)[NI], uint4 (&vr)[NI], int blk) {
-            load_block<LPR, NI, EV>(kr, vr, blk * BR, len, len_old, app, ring, kseg, vseg, p.k_new + newrow,
-                                    p.v_new + newrow, row_bytes, sub, rg);
+                for (int x = 0; x < EPL; ++x) qf[g][x] *= qs;
+            }
         };
-        auto attend = [&](const uint4 (&kr)[NI], uint4 (&vr)[NI], int blk) {
-            attend_block<BF16, LPR, G, NI, EV>(kr, vr, blk * BR, len, len_old, ring, rg, qf, o, mrun, srun);
-        };
-        uint4 k0[NI], v0[NI];
-        // the appended row goes to its slot; attention takes it from k_new / v_new
-        const bool put = writer && uw == 0 && rg == 0;
-        uint4 nk = make_uint4(0, 0, 0, 0), nv = nk;
-        if (put) {
-            nk = *(const uint4*)(p.k_new + newrow + sub * 16);
-            nv = *(const uint4*)(p.v_new + newrow + sub * 16);
-        }
-        load(k0, v0, uw);
-        if (put) {
-            const size_t slot = EV ? (size_t)(ring0 + (p.t - 1) % (p.d + 1)) : (size_t)len_old;
-            *(uint4*)(kseg + slot * row_bytes + sub * 16) = nk;
-            *(uint4*)(vseg + slot * row_bytes + sub * 16) = nv;
-        }
-        for (int blk = uw;;) {
-            attend(k0, v0, blk);
+        uint4 kr[NI], vr[NI];
+        float s[G][NI];
+        int blk = uw;
+        // Blocks of stored rows.  The next block's K rows are requested when this one's are used up, its V rows likewise: no register
+        // more, and the wavefronts of the longest units, with which a launch ends, wait less (13B, batch 8:
+        // 158.8 -> 154.6 us a step).
+        if (blk < nfull) {
+            const unsigned char *ka = kseg + (size_t)blk * (NI * 1024), *va = vseg + (size_t)blk * (NI * 1024);
+            const uint32_t lane_off = (uint32_t)lane * 16u;
+            auto load_k = [&]() {
+#pragma unroll
+                for (int i = 0; i < NI; ++i) kr[i] = load_stream16(ka + i * 1024 + lane_off);
+            };
+            auto load_v = [&]() {
+#pragma unroll
+                for (int i = 0; i < NI; ++i) vr[i] = load_stream16(va + i * 1024 + lane_off);
+            };
+            load_k();
+            load_v();
+            scale_q();
+            for (; blk + UW < nfull; blk += UW) {
+                block_scores<BF16, LPR, G, NI>(kr, qf, s);
+                ka += (size_t)UW * (NI * 1024);
+                va += (size_t)UW * (NI * 1024);
+                load_k();
+                __builtin_amdgcn_sched_barrier(0);
+                block_values<BF16, LPR, G, NI>(s, vr, o, mrun, srun);
+                __builtin_amdgcn_sched_barrier(0);
+                load_v();
+            }
+            block_scores<BF16, LPR, G, NI>(kr, qf, s);
+            block_values<BF16, LPR, G, NI>(s, vr, o, mrun, srun);
             blk += UW;
-            if (blk >= nb) break;
-            load(k0, v0, blk);
+        }
+        // Blocks with the new row, ring rows or rows that take no part.
+        for (; blk < nb; blk += UW) {
+            const int r0 = blk * BR + rg;
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const uint32_t at = (lone ? 0 : (uint32_t)row_slot<EV>(r0 + i * RPI, blk * BR, len, len_old, app ? r_new : -1, ring) * (uint32_t)ROWB) + sub * 16;
+                kr[i] = load_stream16(kload + at);
+                vr[i] = load_stream16(vload + at);
+            }
+            if (blk == uw) scale_q();
+            if (own) {
+#pragma unroll
+                for (int i = 0; i < NI; ++i) kr[i] = select16(r0 + i * RPI == r_new, nk, kr[i]);
+            }
+            block_scores<BF16, LPR, G, NI>(kr, qf, s);
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const int r = r0 + i * RPI;
+                const bool valid = r < len && (!EV || r != ring.r_mask);
+#pragma unroll
+                for (int g = 0; g < G; ++g) s[g][i] = valid ? s[g][i] : -INFINITY;
+                vr[i] = select16(valid, select16(own && r == r_new, nv, vr[i]), make_uint4(0, 0, 0, 0));   // 0 * (what is there) could be NaN
+            }
+            block_values<BF16, LPR, G, NI>(s, vr, o, mrun, srun);
         }
         // merge the RPI row groups of the wavefront (they share mrun)
 #pragma unroll
@@ -413,39 +449,40 @@ decode_attn_kernel(DecodeParams p) {
             for (int x = 0; x < EPL; ++x) o[g][x] = over_groups<LPR>(o[g][x], add);
         }
     }
-    if constexpr (EV) {
-        // the surviving token moves from its ring slot to the next permanent slot.  Attention above read it
-        // from the ring slot; nobody reads the permanent slot in this launch.
-        if (grad && writer && uw == 0 && rg == 0) {
-            const unsigned char* src_k = kseg + (size_t)(ring0 + cs) * row_bytes + sub * 16;
-            const unsigned char* src_v = vseg + (size_t)(ring0 + cs) * row_bytes + sub * 16;
-            *(uint4*)(kseg + (size_t)len_old * row_bytes + sub * 16) = *(const uint4*)src_k;
-            *(uint4*)(vseg + (size_t)len_old * row_bytes + sub * 16) = *(const uint4*)src_v;
+    if (own && writer && rg == 0) {
+        const size_t slot = (size_t)(EV ? ring0 + p.slot_new : len_old) * ROWB + sub * 16;
+        *(uint4*)(kseg + slot) = nk;
+        *(uint4*)(vseg + slot) = nv;
+        if (EV && grad) {
+            *(uint4*)(kseg + (size_t)len_old * ROWB + sub * 16) = gk;
+            *(uint4*)(vseg + (size_t)len_old * ROWB + sub * 16) = gv;
         }
+    }
+    if constexpr (EV) {
         if (p.kept_pos && app && live && hu == 0 && uw == 0 && lane == 0) {
             int32_t* kp = p.kept_pos + off;
-            kp[ring0 + (p.t - 1) % (p.d + 1)] = p.N + p.t - 1;
+            kp[ring0 + p.slot_new] = p.N + p.t - 1;
             if (decide) {
                 if (grad) kp[len_old] = p.N + p.t - p.d - 1;
-                kp[ring0 + cs] = -1;
+                kp[ring0 + p.slot_due] = -1;
             }
         }
     }
     // The other launches count the unit in here (UW > 1: behind the barrier below); the round trip of the atomic passes while the
     // output is written.
-    if (UW == 1) {
-        if (counter && count > 0) counted = atomicAdd(p.lens + sl, count << kLenBits);
+    if (!kOne && UW == 1) {
+        if (counter && count > 0) count_in();
         if (live && rg == 0) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const size_t oi = ((size_t)sl * p.H + hu * G + g) * p.D + sub * EPL;
+                const size_t oi = ((size_t)sl * p.H + hu * G + g) * D + sub * EPL;
                 float r[EPL];
 #pragma unroll
                 for (int x = 0; x < EPL; ++x) r[x] = srun[g] > 0.f ? o[g][x] / srun[g] : 0.f;   // an empty segment gives zeros
                 if constexpr (BF16) {
                     uint32_t w[4];
 #pragma unroll
-                    for (int x = 0; x < 4; ++x) w[x] = (uint32_t)f32_to_bf16(r[2 * x]) | ((uint32_t)f32_to_bf16(r[2 * x + 1]) << 16);
+                    for (int x = 0; x < 4; ++x) w[x] = pack_bf16(r[2 * x], r[2 * x + 1]);
                     *(uint4*)((bf16_t*)p.out + oi) = make_uint4(w[0], w[1], w[2], w[3]);
                 } else {
                     *(float4*)((float*)p.out + oi) = make_float4(r[0], r[1], r[2], r[3]);
@@ -456,36 +493,49 @@ decode_attn_kernel(DecodeParams p) {
         if (rg == 0) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                float* dst = s_part[wv][g];
+                float* dst = s_num[wv][g] + sub * EPL;
 #pragma unroll
-                for (int x = 0; x < EPL; ++x) dst[sub * EPL + x] = o[g][x];
-                if (sub == 0) { dst[DMAX] = mrun[g]; dst[DMAX + 1] = srun[g]; }
+                for (int x = 0; x < EPL; x += 4) *(float4*)(dst + x) = make_float4(o[g][x], o[g][x + 1], o[g][x + 2], o[g][x + 3]);
+                if (sub == 0) s_md[wv][g] = make_float2(mrun[g], srun[g]);
             }
         }
         __syncthreads();
-        if (!kEarly && counter && count > 0) counted = atomicAdd(p.lens + sl, count << kLenBits);
-        // merge the wavefronts of a unit: thread (g, d)
+        if (!kEarly && counter && count > 0) count_in();
+        // merge the wavefronts of a unit: thread (g, d); all its values are requested together
         const int w0 = wv & ~(UW - 1);
-        for (int i = uw * kWave + lane; live && i < G * p.D; i += UW * kWave) {
-            const int g = i / p.D, d = i % p.D;
-            float M = -INFINITY;
-            for (int w = 0; w < UW; ++w) M = fmaxf(M, s_part[w0 + w][g][DMAX]);
+        for (int i = uw * kWave + lane; live && i < G * D; i += UW * kWave) {
+            const int g = i / D, d = i % D;
+            float2 md[W];
+            float num_w[W];
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const int at = !kOne ? w0 + (w & (UW - 1)) : w;
+                md[w] = s_md[at][g];
+                num_w[w] = s_num[at][g][d];
+            }
+            float M = md[0].x;
+#pragma unroll
+            for (int w = 1; w < W; ++w) M = fmaxf(M, md[w].x);
+            const float ref = M == -INFINITY ? 0.f : M;
             float num = 0.f, den = 0.f;
-            if (M > -INFINITY) {
-                for (int w = 0; w < UW; ++w) {
-                    const float wgt = __builtin_amdgcn_exp2f(s_part[w0 + w][g][DMAX] - M);
-                    num = fmaf(wgt, s_part[w0 + w][g][d], num);
-                    den = fmaf(wgt, s_part[w0 + w][g][DMAX + 1], den);
-                }
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                if (!kOne && w >= UW) break;
+                const float wgt = __builtin_amdgcn_exp2f(md[w].x - ref);
+                num = fmaf(wgt, num_w[w], num);
+                den = fmaf(wgt, md[w].y, den);
             }
             const float r = den > 0.f ? num / den : 0.f;   // an empty segment gives zeros
-            const size_t oi = ((size_t)sl * p.H + hu * G + g) * p.D + d;
-            if constexpr (BF16) ((bf16_t*)p.out)[oi] = f32_to_bf16(r); else ((float*)p.out)[oi] = r;
+            const size_t oi = ((size_t)sl * p.H + hu * G + g) * D + d;
+            if constexpr (BF16) ((bf16_t*)p.out)[oi] = (bf16_t)pack_bf16(r, r); else ((float*)p.out)[oi] = r;
         }
     }
     // the last unit of the segment to be counted in stores the new length
-    if (counter && count > 0 && (int)((unsigned)counted >> kLenBits) + count == HU)
-        __hip_atomic_store(p.lens + sl, len_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (counter && count > 0) {
+        asm volatile("" : "+v"(counted));
+        if ((int)((unsigned)counted >> kLenBits) + count == HU)
+            __hip_atomic_store(p.lens + sl, len_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -544,31 +594,16 @@ __device__ __forceinline__ SegState seg_state(const DecodeParams& p, int len_old
     if constexpr (EV) {
         s.ring0 = s.cap - (p.d + 1);
         s.decide = s.app && p.t > p.d;
-        s.cs = p.t % (p.d + 1);
-        long long target = (2ll * base * ((long long)p.N + p.t) + p.N) / (2ll * p.N);
-        target = target < 1 ? 1 : target;
-        s.grad = s.decide && (long long)s.len_old + p.d + 1 <= target && s.len_old < s.ring0;
+        s.cs = p.slot_due;
+        s.grad = s.decide && s.len_old < s.ring0 && within_target(s.len_old + p.d + 1, base, p.N, p.t);
         s.ring.shift = s.ring0 - s.len_old;
-        s.ring.r_new = s.app ? s.len_old + (p.t - 1) % (p.d + 1) : -1;
+        s.ring.r_new = s.app ? s.len_old + p.slot_new : -1;
         s.ring.r_mask = (s.decide && !s.grad) ? s.len_old + s.cs : -1;
         s.len_next = s.len_old + (s.grad ? 1 : 0);
     }
     return s;
 }
 
-
-__device__ __forceinline__ int seg_slot(const DecodeParams& p, int i) { return (i / p.nl) * p.L + p.l0 + i % p.nl; }
-
-// inclusive sum over the lanes, by DPP: every wavefront waits for it before its first rows
-__device__ __forceinline__ int wave_scan(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15, to the odd rows of 16
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31, to the upper half
-    return v;
-}
 
 // 16 bytes per lane from global memory to LDS[dst + 16 * lane] (nothing else here uses m0); ONCE: without a place in the caches
 template <bool ONCE>
@@ -919,7 +954,7 @@ decode_gqa_kernel(DecodeParams p) {
                 }
                 if (p.kept_pos && cur.hu == 0 && lane == 0) {
                     int32_t* kp = p.kept_pos + ss.off;
-                    kp[ring0 + (p.t - 1) % (p.d + 1)] = p.N + p.t - 1;
+                    kp[ring0 + p.slot_new] = p.N + p.t - 1;
                     if (ss.decide) {
                         if (ss.grad) kp[ss.len_old] = p.N + p.t - p.d - 1;
                         kp[ring0 + cs] = -1;
@@ -953,7 +988,7 @@ decode_gqa_kernel(DecodeParams p) {
                     for (int z = 0; z < 4; ++z) y[z] = inv > 0.f ? r[e + z] / den : 0.f;
                     if (writes)
                         *(uint2*)((bf16_t*)p.out + ((size_t)cur.sl * p.H + cur.hu * G + g) * D + col) =
-                            make_uint2((uint32_t)f32_to_bf16(y[0]) | ((uint32_t)f32_to_bf16(y[1]) << 16), (uint32_t)f32_to_bf16(y[2]) | ((uint32_t)f32_to_bf16(y[3]) << 16));
+                            make_uint2(pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3]));
                 } else if (writes) {
                     *(float4*)(part + g * D + col) = make_float4(r[e], r[e + 1], r[e + 2], r[e + 3]);
                 }
@@ -1047,7 +1082,7 @@ decode_gqa_merge_kernel(DecodeParams p) {
     const bool some = den > 0.f;                         // an empty segment gives zeros
     const float y0 = some ? num.x / den : 0.f, y1 = some ? num.y / den : 0.f, y2 = some ? num.z / den : 0.f, y3 = some ? num.w / den : 0.f;
     *(uint2*)((bf16_t*)p.out + ((size_t)sl * p.H + hu * G) * D + 4 * e) =
-        make_uint2((uint32_t)f32_to_bf16(y0) | ((uint32_t)f32_to_bf16(y1) << 16), (uint32_t)f32_to_bf16(y2) | ((uint32_t)f32_to_bf16(y3) << 16));
+        make_uint2(pack_bf16(y0, y1), pack_bf16(y2, y3));
 }
 
 // Number of compute units of the current device (queried once per device).
@@ -1067,8 +1102,8 @@ int compute_units() {
 // wavefronts in blocks of NI * 64/LPR rows.  What decides is how many wavefronts a launch has: 16 per compute unit are
 // resident (4 per SIMD; 20 of a ranked launch of the plain bf16 step), and each start costs (12 800 units of 26 rows, one
 // wavefront each: 42 us, of 136 rows 160, for rows that stream in 30 and 150).  Hence
-//   up to 2 units per compute unit: 8 wavefronts per unit (32 units, one layer of the 7B shape: 8.6 -> 6.1 us; 16 wavefronts
-//       per unit 6.2);
+//   up to 1.75 units per compute unit: 8 wavefronts per unit (32 units, one layer of the 7B shape: 8.6 -> 6.1 us; 16 wavefronts
+//       per unit 6.2; 512 units with 4 against 8: N300 10.8 / 12.5 us, N680 11.5 / 12.4, 384 of N680 11.4 / 10.9);
 //   up to 4: 4 wavefronts per unit, which fill the chip (7B, batch 1, lengths within a factor 30: 21.3 -> 18.7 us; equal: 21.7
 //       -> 21.0; equal lengths of 2048 rows and more are 1 ... 10 % slower than with two wavefronts and 16 loads in flight
 //       each, 164.1 -> 169.6 us at 1024 units);
@@ -1087,7 +1122,7 @@ static hipError_t launch_decode_s(DecodeParams p, int nblk, hipStream_t st) {
         hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 8, OCC, EV, -1>), dim3(HU, p.nl, p.B), dim3(8 * kWave), 0, st, p);
         return hipGetLastError();
     }
-    if (nblk <= 2 * cus) {
+    if (4 * nblk <= 7 * cus) {
         hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 8, OCC, EV, 0>), dim3(HU, p.nl, p.B), dim3(8 * kWave), 0, st, p);
         return hipGetLastError();
     }
@@ -1180,7 +1215,7 @@ static DecodeParams make_params(const pkv_shape& s, int l0, int l1, const void* 
     p.v_new = (const unsigned char*)v_new; p.scale = scale;
     p.kc = (unsigned char*)kc; p.vc = (unsigned char*)vc; p.seg_off = seg_off; p.caps = caps;
     p.lens = lens; p.out = (unsigned char*)out;
-    p.N = s.N; p.t = 0; p.d = 0; p.base_lens = nullptr; p.kept_pos = nullptr;
+    p.N = s.N; p.t = 0; p.d = 0; p.slot_new = 0; p.slot_due = 0; p.base_lens = nullptr; p.kept_pos = nullptr;
     p.n_seg = 0; p.waves = 0; p.ws = nullptr;
     p.rank = RankedShape{0, 0, 0, false};
     return p;
@@ -1200,7 +1235,7 @@ hipError_t launch_decode_evict(const pkv_shape& s, int l0, int l1, const void* q
                                int32_t* lens, int32_t* kept_pos, int t, int d, void* out, void* ws,
                                hipStream_t st) {
     DecodeParams p = make_params(s, l0, l1, q, k_new, v_new, scale, kc, vc, seg_off, caps, lens, out);
-    p.t = t; p.d = d; p.base_lens = base_lens; p.kept_pos = kept_pos;
+    p.t = t; p.d = d; p.slot_new = (t - 1) % (d + 1); p.slot_due = t % (d + 1); p.base_lens = base_lens; p.kept_pos = kept_pos;
     return launch_decode_any<true>(s, p, ws, st);
 }
 

@@ -32,6 +32,16 @@ __device__ __forceinline__ RowSource row_source(int r, int r0, int len, int len_
     return s;
 }
 
+// The slot that a wavefront reads for row r of the block that starts at row r0 < len, where the new row (r_new, -1: none) does not
+// come from the cache: its own, and for the new row and rows that take no part the block's first one or, if that is the new one, a
+// neighbour of it.  No slot that the step writes; len > 1 or r_new < 0.
+template <bool EV>
+__host__ __device__ __forceinline__ int row_slot(int r, int r0, int len, int len_old, int r_new, const RingMap& ring) {
+    const int other = r0 != r_new ? r0 : r0 > 0 ? r0 - 1 : 1;
+    const int x = r < len && (!EV || r != ring.r_mask) && r != r_new ? r : other;
+    return EV && x >= len_old ? x + ring.shift : x;
+}
+
 // How many units the unit counts in at its segment: of the `units` consecutive ones of a workgroup, of which it is number `at` and
 // unit hu of the HU of its segment, the first of each segment speaks for all of that segment, the others for none.  (Units of one
 // segment are alive together.)
@@ -49,6 +59,12 @@ __host__ __device__ __forceinline__ StepRows step_rows(int len_old, int cap, int
     const int ring0 = cap - (d + 1);
     const bool app = base >= 0 && ring0 >= base && len_old <= ring0;
     return {app, app ? len_old + (t < d + 1 ? t : d + 1) : 0};
+}
+
+// Whether `entries` >= 2 are within the target of step t, max(1, floor((2 base (N + t) + N) / (2 N))): without the division, which
+// took some two hundred instructions at the start of every unit.
+__host__ __device__ __forceinline__ bool within_target(int entries, int base, int N, int t) {
+    return 2ll * N * entries <= 2ll * base * ((long long)N + t) + N;
 }
 
 // Ranked launches: the segments are cut into groups of gsz; in each the units (HU per segment) of the n4 longest get four

@@ -26,6 +26,14 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
     return (bf16_t)(u >> 16);
 }
 
+// two floats to packed bf16, round to nearest even (the hardware conversion of gfx950)
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+    const f32x2_t f = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
+}
+
 // Consecutive workgroup ids land on different XCDs; map them so that `nblk/8` consecutive logical
 // ids share an XCD (and its L2).  nblk must be a multiple of 8.
 __device__ __forceinline__ uint32_t xcd_swizzle(uint32_t bid, uint32_t nblk) {

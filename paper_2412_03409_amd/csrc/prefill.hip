@@ -22,8 +22,6 @@ namespace pkv {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-typedef __attribute__((ext_vector_type(2))) float f32x2_t;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef short v4i16_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16_t lds_v4i16_t;
 
@@ -41,11 +39,6 @@ struct PrefillParams {
 constexpr int kPfQueries = 128;   // queries per workgroup (4 wavefronts x 2 tiles x 16)
 constexpr int kPfStage = 64;      // keys per LDS stage
 constexpr int kPfTailBlocks = 256;   // workgroups of an XCD at the end of a launch that run longest first (4 per slot)
-// two floats to packed bf16, round to nearest even (the hardware conversion of gfx950)
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-    const f32x2_t f = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
-}
 
 // 4 keys of one column of row-major V: lane r of a 16-lane group points at 4 consecutive columns of key
 // r/4 (columns 4*(r%4) ...); lane i receives column i of keys 0..3.
