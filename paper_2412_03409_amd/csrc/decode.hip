@@ -52,6 +52,7 @@ struct DecodeParams {
     int waves;
     int* ws;
     RankedShape rank;   // ranked launches of decode_attn_kernel
+    int spread;         // grouped launches: blocks of a unit up to which one wavefront has it
 };
 
 constexpr int kRankRegs = 8;      // capacities per lane of a ranked launch: groups of up to 512 segments
@@ -245,7 +246,9 @@ __device__ __forceinline__ int wave_scan(int v) {
 }
 
 // W wavefronts per workgroup; OCC = wavefronts per SIMD the register allocation must allow.  RANK = 0: all W are for one unit, -1: and it
-// is counted in before its rows.  RANK > 0: units of the longest segments first, with W, W/2 or W/4 wavefronts per unit (see the launcher).
+// is counted in before its rows.  kGrouped: W, W/2 ... or one, by the segment's rows.  RANK > 0: units of the longest segments first,
+// with W, W/2 or W/4 wavefronts per unit (see the launcher).
+constexpr int kGrouped = -2;
 template <bool BF16, int LPR, int G, int NI, int W, int OCC, bool EV, int RANK>
 __global__ void __launch_bounds__(W * kWave, OCC)
 decode_attn_kernel(DecodeParams p) {
@@ -268,6 +271,31 @@ decode_attn_kernel(DecodeParams p) {
         int i_seg = 0;
         if (live) i_seg = x.first + (p.rank.by_length ? ranked_segment<RANK>(p.caps, x.n, p.nl, p.L, p.l0, x.first, x.rank, lane) : x.rank);
         b = i_seg / p.nl; l = p.l0 + i_seg % p.nl;
+    } else if constexpr (RANK == kGrouped) {
+        // As many wavefronts for a unit as its rows are worth, and as many units in a workgroup as that makes, all of one segment: fewer
+        // counts on lens.  The workgroups of a segment are found by what no workgroup changes, its capacity or, under pruning, the
+        // entries kept after prefill; the grid is for one unit each, and what is left over ends here.
+        int seg = -1, before = 0, first = 0;
+        for (int i0 = 0; i0 < p.n_seg; i0 += kWave) {
+            const int i = i0 + lane;
+            int rows = 0;
+            if (i < p.n_seg) rows = EV ? p.base_lens[seg_slot(p, i)] + (p.t < p.d + 1 ? p.t : p.d + 1) : p.caps[seg_slot(p, i)];
+            const int waves = active_waves(row_blocks(rows, BR), p.spread, W);
+            const int groups = i < p.n_seg ? (HU * waves + W - 1) / W : 0, incl = before + wave_scan(groups);
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(incl > (int)blockIdx.x);
+            if (m) {
+                const int at = __builtin_ctzll(m);
+                seg = i0 + at;
+                UW = __builtin_amdgcn_readlane(waves, at);
+                first = __builtin_amdgcn_readlane(incl - groups, at);
+                break;
+            }
+            before = __builtin_amdgcn_readlane(incl, kWave - 1);
+        }
+        if (seg < 0) return;
+        hu = ((int)blockIdx.x - first) * (W / UW) + wv / UW;
+        live = hu < HU;
+        b = seg / p.nl; l = p.l0 + seg % p.nl;
     } else {
         hu = blockIdx.x; l = p.l0 + blockIdx.y; b = blockIdx.z;
     }
@@ -285,7 +313,7 @@ decode_attn_kernel(DecodeParams p) {
 #pragma unroll
         for (int g = 0; g < G; ++g) qr[g] = *(const uint4*)(p.q + ((int64_t)sl * p.H + hu * G + g) * ROWB + sub * 16);
     };
-    constexpr bool kOne = RANK <= 0;                         // one unit per workgroup
+    constexpr bool kOne = RANK == 0 || RANK == -1;           // one unit per workgroup
     if constexpr (kOne) load_q();
     asm volatile("" : "+v"(len_raw), "+s"(cap), "+s"(off), "+s"(base)
                  : "s"(p.kc), "s"(p.vc), "s"(p.k_new), "s"(p.v_new), "s"(p.out), "s"(p.scale), "s"(p.Hkv), "s"(p.grp), "s"(p.append) : "memory");
@@ -1106,7 +1134,7 @@ int compute_units() {
 //       per unit 6.2; 512 units with 4 against 8: N300 10.8 / 12.5 us, N680 11.5 / 12.4, 384 of N680 11.4 / 10.9);
 //   up to 4: 4 wavefronts per unit, which fill the chip (7B, batch 1, lengths within a factor 30: 21.3 -> 18.7 us; equal: 21.7
 //       -> 21.0; equal lengths of 2048 rows and more are 1 ... 10 % slower than with two wavefronts and 16 loads in flight
-//       each, 164.1 -> 169.6 us at 1024 units);
+//       each, 164.1 -> 169.6 us at 1024 units); of short prompts several units share a workgroup (units_grouped);
 //   beyond: one, two or four wavefronts per unit, the longest segments first (see ranked_shape).  The lengths differ by up
 //       to two orders of magnitude, and in index order the launch ends with a few long segments on a chip that is
 //       otherwise empty.
@@ -1120,6 +1148,11 @@ static hipError_t launch_decode_s(DecodeParams p, int nblk, hipStream_t st) {
     p.n_seg = nblk / HU;
     if (4 * nblk <= cus) {
         hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 8, OCC, EV, -1>), dim3(HU, p.nl, p.B), dim3(8 * kWave), 0, st, p);
+        return hipGetLastError();
+    }
+    if (nblk <= 4 * cus && units_grouped(nblk, cus, p.N)) {
+        p.spread = spread_blocks(nblk, cus, p.N);
+        hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, kGrouped>), dim3(nblk), dim3(4 * kWave), 0, st, p);
         return hipGetLastError();
     }
     if (4 * nblk <= 7 * cus) {
@@ -1218,6 +1251,7 @@ static DecodeParams make_params(const pkv_shape& s, int l0, int l1, const void* 
     p.N = s.N; p.t = 0; p.d = 0; p.slot_new = 0; p.slot_due = 0; p.base_lens = nullptr; p.kept_pos = nullptr;
     p.n_seg = 0; p.waves = 0; p.ws = nullptr;
     p.rank = RankedShape{0, 0, 0, false};
+    p.spread = 0;
     return p;
 }
 

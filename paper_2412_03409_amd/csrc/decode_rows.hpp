@@ -122,6 +122,26 @@ __host__ __device__ __forceinline__ int ranked_blocks(const RankedShape& s, int 
     return s.n4 * HU + (s.n2 * HU + 1) / 2 + ((s.gsz - s.n4 - s.n2) * HU + 3) / 4;
 }
 
+// Grouped launches: a workgroup of W wavefronts takes as many units of a segment as its rows leave wavefronts for.  A unit has one
+// wavefront up to `spread` blocks of rows, two up to twice as many, and so on.
+__host__ __device__ __forceinline__ int active_waves(int blocks, int spread, int W) {
+    int n = 1;
+    while (n < W && blocks > n * spread) n *= 2;
+    return n;
+}
+inline int spread_blocks(long long units, long long cus, int N) {
+    const int full = N < 320 ? N / 40 : 8, part = units <= 2 * cus ? full : (int)(full * units / (4 * cus));
+    return part < 1 ? 1 : part;
+}
+// Whether a launch of up to 4 units per compute unit is grouped.  The units of a segment are counted by atomics on its word of lens, and
+// all words of a batch share a few cache lines, which take about 8 ns for each: 1024 units of 18 rows 13.4 us, without the count 6.2.  A
+// grouped launch counts less, but it takes one more round trip to memory to find a workgroup's segment, and four units on one compute unit
+// are less even than one.  us per step, one unit per workgroup / grouped: 1024 units, N60 14.3 / 10.4, N128 13.1 / 8.9, N300 at 20 % 13.6 / 12.8, at
+// 50 % 16.8 / 15.4; 768 units, N128 11.6 / 9.3; 512 units, N60 9.9 / 7.9, N128 9.1 / 7.6, N300 at 50 % of unequal lengths 10.9 / 13.6; 192 units,
+// N60 7.7 / 7.8, N128 7.8 / 7.5.  Longer prompts, whose units mostly take all four wavefronts: 1024 units of N680, 17.3 / 17.1 with little room for new
+// tokens, 25.7 / 27.1 (with another spread 32) with room for 256.
+inline bool units_grouped(long long units, long long cus, int N) { return N <= 200 || (units > 2 * cus && N <= 400); }
+
 // Length class of a segment: quarter octaves of its capacity below that of the longest one, the last class open.
 constexpr int kLengthClasses = 16;
 __host__ __device__ __forceinline__ int length_class(int cap, int longest) {

@@ -1,5 +1,5 @@
 """csrc/decode_rows.hpp, compiled for the host: the slot that a wavefront reads for each row of a block whose new row comes from
-k_new, and the target test of a pruning step."""
+k_new, the target test of a pruning step, and how many wavefronts of a unit have blocks."""
 import ctypes as C
 import os
 import subprocess
@@ -17,6 +17,8 @@ extern "C" int slot(int ev, int r, int r0, int len, int len_old, int r_new, int 
     return ev ? pkv::row_slot<true>(r, r0, len, len_old, r_new, ring) : pkv::row_slot<false>(r, r0, len, len_old, r_new, ring);
 }
 extern "C" int within(int entries, int base, int N, int t) { return pkv::within_target(entries, base, N, t); }
+extern "C" int waves(int blocks, int spread, int W) { return pkv::active_waves(blocks, spread, W); }
+extern "C" int spread(long long units, int cus, int N) { return pkv::spread_blocks(units, cus, N); }
 """
 
 
@@ -75,3 +77,16 @@ def test_target_without_a_division(lib):
                     if entries >= 2:
                         assert lib.within(entries, base, N, t) == (entries <= target), (N, base, t, entries)
 
+
+def test_active_waves(lib):
+    for units in (65, 256, 512, 513, 1024):
+        for W, N in ((w, n) for w in (4, 8) for n in (1, 39, 40, 79, 80, 200, 319, 320, 400)):
+            s = lib.spread(units, 256, N)
+            assert 1 <= s <= 8
+            last = 1
+            for blocks in range(0, 600):
+                n = lib.waves(blocks, s, W)
+                assert n in (1, 2, 4, 8) and last <= n <= W
+                assert n == W or blocks <= n * s
+                assert n == 1 or blocks > n // 2 * s
+                last = n

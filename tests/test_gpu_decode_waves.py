@@ -9,7 +9,8 @@ BF16, F32 = torch.bfloat16, torch.float32
 
 
 @pytest.mark.parametrize("B,L,H,Hkv,N,D,dt,frac", [
-    (1, 32, 32, 32, 400, 128, BF16, 0.3),    # 1024 units, four wavefronts
+    (1, 32, 32, 32, 400, 128, BF16, 0.3),    # 1024 units, grouped: four to a workgroup up to 8 blocks, two up to 16
+    (1, 32, 32, 32, 401, 128, BF16, 0.3),    # one to a workgroup
     (2, 17, 20, 20, 130, 128, BF16, 0.5),    # 680 of short prompts
     (6, 1, 32, 32, 100, 128, BF16, 0.6),     # 192
     (70, 1, 2, 2, 64, 64, BF16, 0.7),        # 140 of 70 segments
