@@ -491,7 +491,8 @@ importance_stream_kernel(StreamParams p) {
         cp_row[i] = r;
         cp_col[i] = 8 * (pos ^ ((r / RPB) & (CPR - 1)));
     }
-    float nl_next = 0.f;
+    float nl_next = 0.f;                                  // of row nl_row, as it lies in memory
+    int nl_row = 0;
     auto issue = [&](int st, unsigned char* dst) {
 #pragma unroll
         for (int i = 0; i < INSTS; ++i) {
@@ -500,9 +501,12 @@ importance_stream_kernel(StreamParams p) {
             __builtin_amdgcn_global_load_lds((glb_void_t*)(sm_base + ((uint32_t)row * sm_ld + (uint32_t)cp_col[i])),
                                              (lds_void_t*)(dst + (wv * INSTS + i) * 1024), 16, 0, 0);
         }
-        if (COLS && wv == 0) {
-            const int m = first + st * kStStage + lane;
-            nl_next = m < p.N ? p.nl_scale * p.lse_in[(size_t)head * p.N + m] : -INFINITY;   // rows past the end weigh 0
+        // Without a branch, and as an atomic load so that the compiler neither waits for it here (with the product behind a condition
+        // it waited for the whole stage) nor moves it behind the work on the stage before: one wavefront did, and with it all at
+        // the next barrier.
+        if constexpr (COLS) {
+            nl_row = first + st * kStStage + lane;
+            nl_next = __hip_atomic_load(p.lse_in + (size_t)head * p.N + (nl_row < p.N ? nl_row : p.N - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         }
     };
     if (gs < nst) issue(gs, s_a[gs]);
@@ -595,7 +599,7 @@ importance_stream_kernel(StreamParams p) {
     constexpr std::true_type diag{};
     constexpr std::false_type plain{};
     auto sync = [&](int par) {
-        if (COLS && wv == 0) s_nl[par][gs][lane] = nl_next;
+        if (COLS && wv == 0) s_nl[par][gs][lane] = nl_row < p.N ? p.nl_scale * nl_next : -INFINITY;   // rows past the end weigh 0
         wait_async_copies();
         __syncthreads();
     };
