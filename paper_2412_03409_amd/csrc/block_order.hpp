@@ -2,6 +2,8 @@
 // can be compiled and enumerated on the host.
 #pragma once
 
+#include "fast_div.hpp"
+
 namespace pkv {
 
 struct HeadBlock { int head, rank; };     // head of the XCD, rank of the block in it: 0 is the longest
@@ -12,19 +14,17 @@ struct HeadBlock { int head, rank; };     // head of the XCD, rank of the block 
 // an XCD's 32 compute units got the long blocks time and again (importance without a given log-sum-exp, B4 L32 H32/8 D128,
 // us, ranks repeating / moving on: N900 1637 / 1343, N1500 3154 / 3014, N2048 5646 / 5052, N3000 11316 / 10655, N4096 20233
 // / 18751; an odd number does that by itself, and moving on costs it 2 % at N2300).
-__host__ __device__ __forceinline__ HeadBlock head_block(int j, int heads, int nblk, int tail) {
-    const int lead = heads - tail;
-    HeadBlock x;
-    if (j < lead * nblk) {
-        x.head = j / nblk;
-        x.rank = j - x.head * nblk;
-        if ((nblk & 1) == 0) x.rank = (x.rank + x.head + x.head * nblk / 32) % nblk;
-    } else {
-        const int i = j - lead * nblk;
-        x.rank = i / tail;
-        x.head = lead + i - x.rank * tail;
+__host__ __device__ __forceinline__ HeadBlock head_block(int j, int heads, FastDiv nblk, FastDiv tail) {
+    const int n = (int)nblk.d, lead = heads - (int)tail.d;
+    if (j < lead * n) {
+        const DivMod x = div_mod(j, nblk);
+        return {x.q, (n & 1) == 0 ? div_mod(x.r + x.q + x.q * n / 32, nblk).r : x.r};
     }
-    return x;
+    const DivMod x = div_mod(j - lead * n, tail);
+    return {lead + x.r, x.q};
+}
+__host__ __device__ __forceinline__ HeadBlock head_block(int j, int heads, int nblk, int tail) {
+    return head_block(j, heads, fast_div(nblk), fast_div(tail));
 }
 
 }  // namespace pkv

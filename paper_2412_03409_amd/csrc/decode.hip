@@ -65,11 +65,6 @@ __device__ __forceinline__ uint4 load_stream16(const unsigned char* p) {
     return make_uint4(t.x, t.y, t.z, t.w);
 }
 
-// A word at a uniform address that no wavefront of the launch writes, by the scalar unit: a vector load would make its user
-// wait for the copies that were requested before it.
-template <class T>
-__device__ __forceinline__ T uniform_load(const T* x) { return *(const __attribute__((address_space(4))) T*)(uintptr_t)x; }
-
 __device__ __forceinline__ int64_t uniform64(int64_t x) {   // a value that is the same in all lanes, in scalar registers
     return ((int64_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
 }

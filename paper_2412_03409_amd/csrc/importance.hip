@@ -131,8 +131,9 @@ struct FusedParams {
     int B, L, H, Hkv, N, D;
     int T;                     // 32-row tiles: ceil(N / 32)
     int npairs;                // ceil(T / 2), at most the wavefronts of a workgroup
-    long long nheads;          // B*L*H
-    long long chunk;           // heads per XCD
+    int nheads;                // B*L*H
+    int chunk;                 // heads per XCD
+    FastDiv by_h, by_l, by_grp;   // H, L, H / Hkv
     const bf16_t* q; Strides qs;
     const bf16_t* k; Strides ks;
     const float* scale;        // [L]
@@ -191,13 +192,14 @@ importance_fused_kernel(FusedParams p) {
     // the wavefront index as a scalar: everything derived from it (which tiles exist, which sub-tiles are
     // needed) is then known to be uniform and branches on it are scalar branches
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long long head = (long long)(blockIdx.x % kXcds) * p.chunk + blockIdx.x / kXcds;
+    const int head = (int)(blockIdx.x % kXcds) * p.chunk + (int)(blockIdx.x / kXcds);
     if (head >= p.nheads) return;
-    const int h = (int)(head % p.H), l = (int)((head / p.H) % p.L), b = (int)(head / ((long long)p.H * p.L));
+    const DivMod bl_h = uniform_div_mod(head, p.by_h), b_l = uniform_div_mod(bl_h.q, p.by_l);
+    const int h = bl_h.r, l = b_l.r, b = b_l.q;
     const bf16_t* qb = p.q + p.qs.b * b + p.qs.l * l + p.qs.h * h;
-    const bf16_t* kb = p.k + p.ks.b * b + p.ks.l * l + p.ks.h * (h / (p.H / p.Hkv));
+    const bf16_t* kb = p.k + p.ks.b * b + p.ks.l * l + p.ks.h * uniform_div_mod(h, p.by_grp).q;
     float* part = p.partial + (size_t)head * p.N;
-    float c = p.scale[l] * kLog2e;
+    float c = uniform_load(p.scale + l) * kLog2e;
     const bool flip = c < 0.f;
     c = fmaxf(fabsf(c), 1e-30f);                           // > 0, so that c * (-inf) of a masked entry stays -inf
 
@@ -411,10 +413,12 @@ importance_fused_kernel(FusedParams p) {
 }
 
 struct StreamParams {
-    int H, Hkv, L, N;
-    int nblk;                  // blocks of stationary rows per head
-    int tail;                  // heads of an XCD whose blocks run longest first
-    long long nheads;          // B*L*H
+    int N;
+    int nheads;                // B*L*H
+    int heads_per_xcd;
+    FastDiv nblk;              // blocks of stationary rows per head
+    FastDiv tail;              // heads of an XCD whose blocks run longest first
+    FastDiv by_h, by_l, by_grp;   // H, L, H / Hkv
     const bf16_t* q; Strides qs;
     const bf16_t* k; Strides ks;
     const float* scale;        // [L]
@@ -455,20 +459,23 @@ importance_stream_kernel(StreamParams p) {
     const int wv = wave % kStWaves, gs = wave / kStWaves;  // the groups of four wavefronts take the stages in turn
     const int ln = lane & 31, hf = lane >> 5;
     // blocks of a head next to each other on one XCD, the XCD's last p.tail heads longest block first
-    const int per_xcd = (int)(gridDim.x / kXcds), j = (int)(blockIdx.x / kXcds);
-    const int hx = per_xcd / p.nblk;
-    const HeadBlock hb = head_block(j, hx, p.nblk, p.tail);
-    const long long head = (long long)(blockIdx.x % kXcds) * hx + hb.head;
+    // (all arguments in one round trip to memory: left to itself the compiler asks for them as it comes to them)
+    asm volatile("" : : "s"(p.q), "s"(p.k), "s"(p.qs.b), "s"(p.qs.l), "s"(p.qs.h), "s"(p.qs.n), "s"(p.ks.b), "s"(p.ks.l), "s"(p.ks.h), "s"(p.ks.n), "s"(p.scale));
+    const int j = (int)(blockIdx.x / kXcds);
+    HeadBlock hb = head_block(j, p.heads_per_xcd, p.nblk, p.tail);
+    hb.head = __builtin_amdgcn_readfirstlane(hb.head); hb.rank = __builtin_amdgcn_readfirstlane(hb.rank);
+    const int head = (int)(blockIdx.x % kXcds) * p.heads_per_xcd + hb.head;
     if (head >= p.nheads) return;
-    const int blk = COLS ? hb.rank : p.nblk - 1 - hb.rank;
-    const int h = (int)(head % p.H), l = (int)((head / p.H) % p.L), b = (int)(head / ((long long)p.H * p.L));
+    const int blk = COLS ? hb.rank : (int)p.nblk.d - 1 - hb.rank;
+    const DivMod bl_h = uniform_div_mod(head, p.by_h), b_l = uniform_div_mod(bl_h.q, p.by_l);
+    const int h = bl_h.r, l = b_l.r, b = b_l.q;
     const bf16_t* qb = p.q + p.qs.b * b + p.qs.l * l + p.qs.h * h;
-    const bf16_t* kb = p.k + p.ks.b * b + p.ks.l * l + p.ks.h * (h / (p.H / p.Hkv));
+    const bf16_t* kb = p.k + p.ks.b * b + p.ks.l * l + p.ks.h * uniform_div_mod(h, p.by_grp).q;
     const bf16_t* st_base = COLS ? kb : qb;
     const bf16_t* sm_base = COLS ? qb : kb;
     const int64_t st_ld = COLS ? p.ks.n : p.qs.n;
     const uint32_t sm_ld = (uint32_t)(COLS ? p.qs.n : p.ks.n);    // N * stride < 2^31, checked by the launcher
-    float c = p.scale[l] * kLog2e;
+    float c = uniform_load(p.scale + l) * kLog2e;
     const bool flip = c < 0.f;
     c = fmaxf(fabsf(c), 1e-30f);
     // The earlier tiles of a block (COLS = false: the later ones) have up to 4 * NK products more than the others, and wavefront w
@@ -744,7 +751,7 @@ importance_f32_kernel(F32Params p) {
     const float* kb = p.k + p.ks.b * b + p.ks.l * l + p.ks.h * (h / (p.H / p.Hkv));
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
     const int col = lane & 15, rq = lane >> 4;            // stationary row, streamed rows 4*rq .. 4*rq + 3
-    const float c = p.scale[l] * kLog2e;
+    const float c = uniform_load(p.scale + l) * kLog2e;
     const float* sb = LSE ? kb : qb;
     const int64_t sld = LSE ? p.ks.n : p.qs.n;
     const int first = LSE ? 0 : t, last = LSE ? t : T - 1;
@@ -889,13 +896,14 @@ static hipError_t launch_stream(const pkv_shape& s, StreamParams p, hipStream_t 
     const long long nb2 = (s.N + 255) / 256, nb1 = (s.N + 127) / 128, blocks = p.nheads * nb2;
     const bool wide = (blocks >= 4 * cus && (2 * nb2 == nb1 || nb2 > 2)) ||
                       (COLS && s.D == 128 && nb2 >= 3 && nb2 <= 6 && 2 * blocks >= 5 * cus && blocks <= 3 * cus);
-    p.nblk = (int)(wide ? nb2 : nb1);
-    if (hx * kXcds * p.nblk > 0x7fffffffll) return hipErrorInvalidValue;
-    const long long tail = (kStTailBlocks + p.nblk - 1) / p.nblk;
-    p.tail = (int)(tail < hx ? tail : hx);
-    const dim3 grid((unsigned)(hx * kXcds * p.nblk));
+    const long long nblk = wide ? nb2 : nb1, tail = (kStTailBlocks + nblk - 1) / nblk;
+    if (hx * kXcds * nblk > 0x7fffffffll) return hipErrorInvalidValue;
+    p.nblk = fast_div(nblk);
+    p.tail = fast_div(tail < hx ? tail : hx);
+    p.heads_per_xcd = (int)hx;
+    const dim3 grid((unsigned)(hx * kXcds * nblk));
     if (wide) launch_stream_d<2, 1, COLS>(s, p, grid, st);
-    else if (p.nheads * p.nblk * 4 <= 5 * cus) launch_stream_d<1, 2, COLS>(s, p, grid, st);
+    else if (p.nheads * nblk * 4 <= 5 * cus) launch_stream_d<1, 2, COLS>(s, p, grid, st);
     else launch_stream_d<1, 1, COLS>(s, p, grid, st);
     return hipGetLastError();
 }
@@ -905,7 +913,8 @@ hipError_t launch_importance(const pkv_shape& s, const void* q, Strides qs, cons
                              hipStream_t st) {
     float* partial = (float*)ws;
     float* lse_ws = partial + (size_t)s.B * s.L * s.H * s.N;
-    const long long total = (long long)s.B * s.L * s.N;
+    const long long total = (long long)s.B * s.L * s.N, heads = (long long)s.B * s.L * s.H;
+    if (heads > 0x7fffffffll - kXcds) return hipErrorInvalidValue;   // they are counted in 32 bits, and a grid holds no more
     hipError_t e;
     if (s.dtype == PKV_F32) {
         F32Params p{s.B, s.L, s.H, s.Hkv, s.N, (const float*)q, qs, (const float*)k, ks, scale, nullptr, lse_ws};
@@ -914,7 +923,7 @@ hipError_t launch_importance(const pkv_shape& s, const void* q, Strides qs, cons
         if ((e = launch_importance_f32<false>(s, p, st)) != hipSuccess) return e;
     } else if (lse || (!fused_fits(s, compute_units()) && ws_bytes >= stream_ws_bytes(s))) {
         StreamParams p;
-        p.H = s.H; p.Hkv = s.Hkv; p.L = s.L; p.N = s.N; p.nheads = (long long)s.B * s.L * s.H;
+        p.N = s.N; p.nheads = (int)heads; p.by_h = fast_div(s.H); p.by_l = fast_div(s.L); p.by_grp = fast_div(s.H / s.Hkv);
         p.q = (const bf16_t*)q; p.qs = qs; p.k = (const bf16_t*)k; p.ks = ks; p.scale = scale;
         p.lse_in = nullptr; p.nl_scale = lse ? -kLog2e : 1.f; p.out = lse_ws;
         if (!lse && (e = launch_stream<false>(s, p, st)) != hipSuccess) return e;
@@ -925,12 +934,13 @@ hipError_t launch_importance(const pkv_shape& s, const void* q, Strides qs, cons
         p.B = s.B; p.L = s.L; p.H = s.H; p.Hkv = s.Hkv; p.N = s.N; p.D = s.D;
         p.T = (s.N + 31) / 32;
         p.npairs = (p.T + 1) / 2;
-        p.nheads = (long long)s.B * s.L * s.H;
-        p.chunk = (p.nheads + kXcds - 1) / kXcds;
+        p.nheads = (int)heads;
+        p.chunk = (int)((heads + kXcds - 1) / kXcds);
+        p.by_h = fast_div(s.H); p.by_l = fast_div(s.L); p.by_grp = fast_div(s.H / s.Hkv);
         p.q = (const bf16_t*)q; p.qs = qs; p.k = (const bf16_t*)k; p.ks = ks; p.scale = scale;
         p.partial = partial;
-        if (p.npairs > kFusedWaves || p.chunk * kXcds > 0x7fffffffll) return hipErrorInvalidValue;
-        const dim3 grid((unsigned)(p.chunk * kXcds)), block(kFusedWaves * kWave);
+        if (p.npairs > kFusedWaves) return hipErrorInvalidValue;
+        const dim3 grid((unsigned)p.chunk * kXcds), block(kFusedWaves * kWave);
         const bool spread = p.npairs < kFusedWaves;       // the last wavefront only copies
         if (spread) {
             if (s.D == 128) hipLaunchKernelGGL((importance_fused_kernel<128, kFusedWaves, kFusedOcc, true>), grid, block, 0, st, p);

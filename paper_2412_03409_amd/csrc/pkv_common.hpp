@@ -34,6 +34,11 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
 }
 
+// A word at a uniform address that no wavefront of the launch writes, by the scalar unit: a vector load would make its user
+// wait for the copies that were requested before it.
+template <class T>
+__device__ __forceinline__ T uniform_load(const T* x) { return *(const __attribute__((address_space(4))) T*)(uintptr_t)x; }
+
 // Consecutive workgroup ids land on different XCDs; map them so that `nblk/8` consecutive logical
 // ids share an XCD (and its L2).  nblk must be a multiple of 8.
 __device__ __forceinline__ uint32_t xcd_swizzle(uint32_t bid, uint32_t nblk) {

@@ -15,6 +15,7 @@
 //                       order comes from LDS with gfx950's transposing 64-bit read: 16 lanes point at
 //                       4 keys x 16 columns of row-major V and each receives 4 keys of one column.
 #include "pkv_common.hpp"
+#include "fast_div.hpp"
 
 #include <type_traits>
 
@@ -26,8 +27,11 @@ typedef short v4i16_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16_t lds_v4i16_t;
 
 struct PrefillParams {
-    int B, L, H, Hkv, N, D;
-    int tail;             // heads of an XCD whose blocks run longest first (see the kernel)
+    int N;
+    int heads, heads_per_xcd;      // B*L*H
+    FastDiv nqb;                   // query blocks of a head
+    FastDiv tail;                  // heads of an XCD whose blocks run longest first (see the kernel)
+    FastDiv by_h, by_l, by_grp;    // H, L, H / Hkv
     const bf16_t* q; Strides qs;
     const bf16_t* k; Strides ks;
     const bf16_t* v; Strides vs;
@@ -72,24 +76,26 @@ prefill_attn_kernel(PrefillParams p) {
     __shared__ __attribute__((aligned(1024))) unsigned char sKb[kPfStage * ROWB];
     __shared__ __attribute__((aligned(1024))) unsigned char sVb[kPfStage * ROWB];
 
-    const int heads = p.B * p.L * p.H;
-    const int nqb = (p.N + kPfQueries - 1) / kPfQueries;
+    // (all arguments in one round trip to memory: left to itself the compiler asks for them as it comes to them)
+    asm volatile("" : : "s"(p.q), "s"(p.k), "s"(p.v), "s"(p.qs.b), "s"(p.qs.l), "s"(p.qs.h), "s"(p.qs.n), "s"(p.ks.b), "s"(p.ks.l), "s"(p.ks.h),
+                 "s"(p.ks.n), "s"(p.vs.b), "s"(p.vs.l), "s"(p.vs.h), "s"(p.vs.n), "s"(p.scale));
+    const int nqb = (int)p.nqb.d;
     // The query blocks of one head run next to each other on one XCD (the hardware deals consecutive workgroups
     // out to the eight XCDs in turn) and share the head's K and V through that XCD's L2, as do the query heads
     // of one KV head; within a head the long (late) query blocks start first.  The last p.tail heads of an XCD are
     // taken together, all their longest blocks first: in head order the launch would end on a few long blocks
     // (64 heads of 2048 positions: 107 -> 86 us; 320 heads of 1021: 164 -> 154; all heads that way loses the
     // sharing: 1024 heads of 680 positions 253 -> 309 us).
-    const int per_xcd = (int)(gridDim.x / kXcds);         // a whole number of heads
     const int j = (int)(blockIdx.x / kXcds);              // index inside the XCD
-    const int hx = per_xcd / nqb, lead = hx - p.tail;     // the XCD's heads; the last p.tail of them longest block first
+    const int hx = p.heads_per_xcd, lead = hx - (int)p.tail.d;   // the XCD's heads; the last p.tail of them longest block first
     int qb, hl;
-    if (j < lead * nqb) { hl = j / nqb; qb = nqb - 1 - (j - hl * nqb); }
-    else { const int i = j - lead * nqb; const int c = i / p.tail; qb = nqb - 1 - c; hl = lead + i - c * p.tail; }
+    if (j < lead * nqb) { const DivMod x = uniform_div_mod(j, p.nqb); hl = x.q; qb = nqb - 1 - x.r; }
+    else { const DivMod x = uniform_div_mod(j - lead * nqb, p.tail); qb = nqb - 1 - x.q; hl = lead + x.r; }
     const int hh = (int)(blockIdx.x % kXcds) * hx + hl;
-    if (hh >= heads) return;
-    const int h = hh % p.H, l = (hh / p.H) % p.L, b = hh / (p.H * p.L);
-    const int kvh = h / (p.H / p.Hkv);
+    if (hh >= p.heads) return;
+    const DivMod bl_h = uniform_div_mod(hh, p.by_h), b_l = uniform_div_mod(bl_h.q, p.by_l);
+    const int h = bl_h.r, l = b_l.r, b = b_l.q;
+    const int kvh = uniform_div_mod(h, p.by_grp).q;
     const bf16_t* qbase = p.q + p.qs.b * b + p.qs.l * l + p.qs.h * h;
     const bf16_t* kbase = p.k + p.ks.b * b + p.ks.l * l + p.ks.h * kvh;
     const bf16_t* vbase = p.v + p.vs.b * b + p.vs.l * l + p.vs.h * kvh;
@@ -97,31 +103,7 @@ prefill_attn_kernel(PrefillParams p) {
     const int ln = lane & 31, hf = lane >> 5;               // MFMA operand row / column, and k-half
     const int q0 = qb * kPfQueries + wv * 32;               // first query of this wavefront
     const int query = q0 + ln;
-    // a negative logit scale is moved into the queries (negation is exact in bf16), so that the running
-    // maximum can be taken on the raw products
-    const float sc_l = p.scale[l];
-    const float qs0 = fabsf(sc_l) * kLog2e;
-    const float qs = qs0 < 1e-30f ? 1e-30f : qs0;           // > 0, so that a masked -inf stays one; NaN stays NaN
-    const uint32_t sgn = sc_l < 0.f ? 0x80008000u : 0u;
-
-    // the queries: B operand of the score products, one fragment per 16 columns of the head dimension
-    bf16x8_t qf[NJ];
-    {
-        const int row = query < p.N ? query : p.N - 1;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            uint4 t = *(const uint4*)(qbase + p.qs.n * row + 16 * j + 8 * hf);
-            t.x ^= sgn; t.y ^= sgn; t.z ^= sgn; t.w ^= sgn;
-            qf[j] = __builtin_bit_cast(bf16x8_t, t);
-        }
-    }
-    f32x16_t o[NDT];
-    float m_run = -INFINITY, l_run = 0.f;
-#pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
-
+    float sc_l = uniform_load(p.scale + l);
     const int last_q = min(p.N, (qb + 1) * kPfQueries) - 1;  // last query of the workgroup
     const int nst = last_q / kPfStage + 1;                   // stages that hold a key <= last_q
 
@@ -149,7 +131,33 @@ prefill_attn_kernel(PrefillParams p) {
                                              (__attribute__((address_space(3))) void*)(dV + (wv * kInst + i) * 1024), 16, 0, 0);
         }
     };
+    // The first stage is requested ahead of the queries: the two round trips to memory pass together (one layer of
+    // H32 N680, attention and importance, with the arithmetic at the start 34.6 -> 33.0 us).
+    issue(0, sKa, sVa);
+    // a negative logit scale is moved into the queries (negation is exact in bf16), so that the running
+    // maximum can be taken on the raw products
+    asm volatile("" : "+s"(sc_l));                          // first looked at here
+    const float qs0 = fabsf(sc_l) * kLog2e;
+    const float qs = qs0 < 1e-30f ? 1e-30f : qs0;           // > 0, so that a masked -inf stays one; NaN stays NaN
+    const uint32_t sgn = sc_l < 0.f ? 0x80008000u : 0u;
 
+    // the queries: B operand of the score products, one fragment per 16 columns of the head dimension
+    bf16x8_t qf[NJ];
+    {
+        const int row = query < p.N ? query : p.N - 1;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            uint4 t = *(const uint4*)(qbase + p.qs.n * row + 16 * j + 8 * hf);
+            t.x ^= sgn; t.y ^= sgn; t.z ^= sgn; t.w ^= sgn;
+            qf[j] = __builtin_bit_cast(bf16x8_t, t);
+        }
+    }
+    f32x16_t o[NDT];
+    float m_run = -INFINITY, l_run = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
 
     // byte offsets of this lane's fragment reads inside a staged tile: computed once (a 16-row step of the swizzled
     // layout is a plain offset)
@@ -281,7 +289,6 @@ prefill_attn_kernel(PrefillParams p) {
     };
     constexpr std::true_type masked{};
     constexpr std::false_type plain{};
-    issue(0, sKa, sVa);
     for (int st = 0; st < 2 * qb; st += 2) {
         sync();
         issue(st + 1, sKb, sVb);
@@ -328,16 +335,17 @@ hipError_t launch_prefill_attn(const pkv_shape& s, const void* q, Strides qs, co
                                const void* v, Strides vs, const float* scale, void* out, float* lse,
                                hipStream_t st) {
     PrefillParams p;
-    p.B = s.B; p.L = s.L; p.H = s.H; p.Hkv = s.Hkv; p.N = s.N; p.D = s.D;
+    p.N = s.N;
     p.q = (const bf16_t*)q; p.qs = qs; p.k = (const bf16_t*)k; p.ks = ks; p.v = (const bf16_t*)v; p.vs = vs;
     p.scale = scale; p.out = (bf16_t*)out; p.lse = lse;
     const long long heads = (long long)s.B * s.L * s.H;
     const long long nqb = (s.N + kPfQueries - 1) / kPfQueries;
     const long long nblk = (heads + kXcds - 1) / kXcds * nqb * kXcds;   // whole heads per XCD
     if (nblk > 0x7fffffffll) return hipErrorInvalidValue;
-    const int hx = (int)((heads + kXcds - 1) / kXcds);
-    p.tail = (int)((kPfTailBlocks + nqb - 1) / nqb);
-    if (p.tail > hx) p.tail = hx;
+    const long long hx = (heads + kXcds - 1) / kXcds, tail = (kPfTailBlocks + nqb - 1) / nqb;
+    p.heads = (int)heads; p.heads_per_xcd = (int)hx;
+    p.nqb = fast_div(nqb); p.tail = fast_div(tail < hx ? tail : hx);
+    p.by_h = fast_div(s.H); p.by_l = fast_div(s.L); p.by_grp = fast_div(s.H / s.Hkv);
     const dim3 grid((unsigned)nblk);
     if (s.D == 128) hipLaunchKernelGGL(prefill_attn_kernel<128>, grid, dim3(256), 0, st, p);
     else hipLaunchKernelGGL(prefill_attn_kernel<64>, grid, dim3(256), 0, st, p);
