@@ -134,9 +134,10 @@ def _shape(B, L, H, Hkv, N, D, dtype) -> _Shape:
 
 
 @lru_cache(maxsize=256, typed=True)
-def _decode_ws_bytes_of(B, L, H, Hkv, N, D, dtype) -> int:
-    """Decode workspace of a shape: a pure function of it, asked for in every step."""
-    return int(load().prefixkv_workspace_bytes(OP_DECODE, C.byref(_shape(B, L, H, Hkv, N, D, dtype)), 0))
+def _decode_shape_of(B, L, H, Hkv, N, D, dtype):
+    """A decode step's argument struct by reference, and its workspace: pure functions of the shape, asked for in every step."""
+    s = C.byref(_shape(B, L, H, Hkv, N, D, dtype))
+    return s, int(load().prefixkv_workspace_bytes(OP_DECODE, s, 0))
 
 
 def _strides5(t: torch.Tensor) -> _Strides:
@@ -149,8 +150,14 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
+# The current stream's handle without a Stream object around it (1.2 us a call), where torch has that.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
     # with an index: without one torch looks the device up through four layers of its own (4 us a call)
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
     return torch.cuda.current_stream(torch.cuda.current_device()).cuda_stream
 
 
@@ -171,6 +178,11 @@ def _ws(nbytes: int, device, ws: Optional[torch.Tensor]) -> torch.Tensor:
 def prefixkv_workspace_bytes(op: int, B, L, H, Hkv, N, D, dtype, has_lse: bool = False) -> int:
     s = _shape(B, L, H, Hkv, N, D, dtype)
     return int(load().prefixkv_workspace_bytes(op, C.byref(s), int(has_lse)))
+
+
+@lru_cache(maxsize=256, typed=True)
+def _select_ws_bytes_of(B, L, N) -> int:
+    return select_workspace_bytes(B, L, N)
 
 
 def select_workspace_bytes(B: int, L: int, N: int) -> int:
@@ -267,7 +279,7 @@ def prefixkv_select(importance: torch.Tensor, budget_tokens: int, tol_tokens: in
             raw_total=torch.empty(B, dtype=torch.int64, device=dev),
             status=torch.empty(B, dtype=torch.int32, device=dev))
     prm = _SelectParams(int(budget_tokens), int(tol_tokens), int(max_iters), int(bool(fixup)))
-    w = _ws(select_workspace_bytes(B, L, N), dev, ws)
+    w = _ws(_select_ws_bytes_of(B, L, N), dev, ws)
     rc = load().prefixkv_select(B, L, N, _ptr(importance), C.byref(prm), _ptr(out.order), _ptr(out.cum),
                                 _ptr(out.prefix), _ptr(out.lengths), _ptr(out.p), _ptr(out.iters),
                                 _ptr(out.raw_total), _ptr(out.status), _ptr(w),
@@ -454,25 +466,57 @@ def prefixkv_decode_attn(cache: CompactResult, q: torch.Tensor, k_new: Optional[
     _need_cuda(q, k_new, v_new, scale, out)
     B, L, H, D = q.shape
     l1 = L if l1 is None else l1
-    if not q.is_contiguous() or q.dtype != cache.kc.dtype or D != cache.D:
+    dt = q.dtype
+    if not q.is_contiguous() or dt != cache.kc.dtype or D != cache.D:
         raise ValueError("q must be contiguous [B,L,H,D] in the cache dtype")
     for t in (k_new, v_new):
-        if t is not None and (t.shape != (B, L, cache.Hkv, D) or not t.is_contiguous() or t.dtype != q.dtype):
+        if t is not None and (t.shape != (B, L, cache.Hkv, D) or not t.is_contiguous() or t.dtype != dt):
             raise ValueError("k_new/v_new must be contiguous [B,L,Hkv,D] in the cache dtype")
     if scale.dtype != torch.float32 or scale.shape != (L,) or not scale.is_contiguous():
         raise ValueError("scale must be contiguous f32 [L]")
     if out is None:
-        out = torch.empty((B, L, H, D), dtype=q.dtype, device=q.device)
-    shape = B, L, H, index(cache.Hkv), index(N), D, _dtype_code(q)
-    s = _shape_of(*shape)
-    w = _ws(_decode_ws_bytes_of(*shape), q.device, ws)
-    rc = load().prefixkv_decode_attn(C.byref(s), int(l0), int(l1), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                     _ptr(scale), _ptr(cache.kc), _ptr(cache.vc), _ptr(cache.seg_off),
-                                     _ptr(cache.caps), _ptr(cache.lens), _ptr(out), _ptr(w),
+        out = torch.empty((B, L, H, D), dtype=dt, device=q.device)
+    s, need = _decode_shape_of(B, L, H, index(cache.Hkv), index(N), D, _dtype_code(q))
+    w = _ws(need, q.device, ws)
+    rc = load().prefixkv_decode_attn(s, int(l0), int(l1), q.data_ptr(), _ptr(k_new), _ptr(v_new), scale.data_ptr(),
+                                     cache.kc.data_ptr(), cache.vc.data_ptr(), cache.seg_off.data_ptr(),
+                                     cache.caps.data_ptr(), cache.lens.data_ptr(), out.data_ptr(), w.data_ptr(),
                                      w.numel() * w.element_size(), _stream())
     if rc != 0:
         raise PrefixKVError(rc, "prefixkv_decode_attn")
     return out
+
+
+def decode_attn_steps(cache: CompactResult, q: torch.Tensor, k_new: torch.Tensor, v_new: torch.Tensor, scale: torch.Tensor,
+                      N: int, T: int, out: torch.Tensor, ws: torch.Tensor) -> bool:
+    """prefixkv_decode_attn over all layers for steps 0 .. T-1 of contiguous q, out [>=T,B,L,H,D] and k_new, v_new
+    [>=T,B,L,Hkv,D]: the same calls, whose arguments are looked at once.  False, and nothing is done, where a step by itself
+    has to see to it (other layouts, other types, errors)."""
+    xs = (q, k_new, v_new, out)
+    if T < 1 or any(type(x) is not torch.Tensor or not x.is_cuda or x.dim() != 5 or not x.is_contiguous() or x.shape[0] < T for x in xs):
+        return False
+    _, B, L, H, D = q.shape
+    dt, new = q.dtype, (B, L, cache.Hkv, D)
+    if (dt != cache.kc.dtype or dt not in (torch.float32, torch.bfloat16) or D != cache.D or any(x.dtype != dt for x in xs)
+            or out.shape[1:] != q.shape[1:] or k_new.shape[1:] != new or v_new.shape[1:] != new
+            or any(x.requires_grad or x.is_conj() or x.is_neg() for x in xs) or any(x.device != q.device for x in xs)
+            or not scale.is_cuda or scale.dtype != torch.float32 or scale.shape != (L,) or not scale.is_contiguous()):
+        return False
+    s, need = _decode_shape_of(B, L, H, index(cache.Hkv), index(N), D, _dtype_code(q))
+    nbytes = ws.numel() * ws.element_size()
+    if nbytes < need:
+        return False
+    step = load().prefixkv_decode_attn
+    qs, ns = B * L * H * D * q.element_size(), B * L * cache.Hkv * D * q.element_size()
+    qp, kp, vp, op = (x.data_ptr() for x in xs)
+    args = (scale.data_ptr(), cache.kc.data_ptr(), cache.vc.data_ptr(), cache.seg_off.data_ptr(), cache.caps.data_ptr(),
+            cache.lens.data_ptr())
+    wp, st = ws.data_ptr(), _stream()
+    for t in range(T):
+        rc = step(s, 0, L, qp + t * qs, kp + t * ns, vp + t * ns, *args, op + t * qs, wp, nbytes, st)
+        if rc != 0:
+            raise PrefixKVError(rc, "prefixkv_decode_attn")
+    return True
 
 
 def prefixkv_decode_attn_evict(cache: CompactResult, base_lens: torch.Tensor, q: torch.Tensor,
@@ -496,11 +540,10 @@ def prefixkv_decode_attn_evict(cache: CompactResult, base_lens: torch.Tensor, q:
         raise ValueError("base_lens must be contiguous i32 [B,L]")
     if out is None:
         out = torch.empty((B, L, H, D), dtype=q.dtype, device=q.device)
-    shape = B, L, H, index(cache.Hkv), index(N), D, _dtype_code(q)
-    s = _shape_of(*shape)
-    w = _ws(_decode_ws_bytes_of(*shape), q.device, ws)
+    s, need = _decode_shape_of(B, L, H, index(cache.Hkv), index(N), D, _dtype_code(q))
+    w = _ws(need, q.device, ws)
     rc = load().prefixkv_decode_attn_evict(
-        C.byref(s), int(l0), int(l1), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(scale), _ptr(cache.kc),
+        s, int(l0), int(l1), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(scale), _ptr(cache.kc),
         _ptr(cache.vc), _ptr(cache.seg_off), _ptr(cache.caps), _ptr(base_lens), _ptr(cache.lens),
         _ptr(cache.kept_pos) if track_positions else None, int(t), int(distance), _ptr(out), _ptr(w),
         w.numel() * w.element_size(), _stream())

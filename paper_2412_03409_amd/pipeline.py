@@ -10,6 +10,9 @@ import torch
 from . import binding as B_
 
 
+_DECODE_ATTN = B_.prefixkv_decode_attn
+
+
 class HotPath:
     def __init__(self, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, scale: torch.Tensor,
                  budget_tokens: int, decode_steps: int, tol_tokens: int = 0, max_iters: int = 64,
@@ -82,12 +85,19 @@ class HotPath:
             for t in range(self.T):
                 self.run_decode_step(t, dq, dk, dv)
             return
+        if self._plain() and B_.decode_attn_steps(self.cache, dq, dk, dv, self.scale, self.N, self.T, self.out, self.dec_ws):
+            return
         # the steps' tensors as views made once: indexing four tensors per step costs as much as the call
         steps = [x[:self.T].unbind(0) for x in (dq, dk, dv, self.out)]
         if min(len(x) for x in steps) < self.T:
             raise IndexError(f"{self.T} decode steps need as many tensors")
         for t, (q, k, v, out) in enumerate(zip(*steps)):
             self._decode(t, q, k, v, out)
+
+    def _plain(self) -> bool:
+        """Whether a step is the binding's own call with nothing of the caller's in between."""
+        return (self.evict_distance is None and getattr(self._decode, "__func__", None) is HotPath._decode
+                and B_.prefixkv_decode_attn is _DECODE_ATTN)
 
     # ---- the decode loop as one HIP graph (T launches, no host work between them) -----------
     def capture_decode_loop(self, dq, dk, dv):

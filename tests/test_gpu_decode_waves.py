@@ -2,6 +2,7 @@
 import pytest
 import torch
 
+from paper_2412_03409_amd.pipeline import HotPath
 from test_gpu_parity import run_decode_case, run_evict_case
 
 pytestmark = pytest.mark.gpu
@@ -31,3 +32,36 @@ def test_spread(B, L, H, Hkv, N, D, dt, frac):
 ])
 def test_spread_with_pruning(B, L, H, Hkv, N, D, dt, frac, d, steps):
     run_evict_case(B, L, H, Hkv, N, D, dt, frac, d, steps, seed=N)
+
+
+# The loop of HotPath looks at its arguments once; step by step, and from tensors that are not contiguous, the same bits.
+@pytest.mark.parametrize("dt,Hkv", [(F32, 2), (BF16, 2), (BF16, 4)])
+def test_loop_is_its_steps(dt, Hkv):
+    B, L, H, N, D, T = 2, 3, 4, 40, 64, 5
+    g = torch.Generator().manual_seed(5)
+    rnd = lambda *s: torch.randn(s, generator=g).to(dt).cuda()
+    hp = HotPath(rnd(B, L, H, N, D), rnd(B, L, Hkv, N, D), rnd(B, L, Hkv, N, D), torch.full((L,), 0.1, device="cuda"), 30, T)
+    hp.run_importance(); hp.run_select()
+    dq, dk, dv = rnd(T + 1, B, L, H, D), rnd(T, B, L, Hkv, D), rnd(T, B, L, Hkv, D)
+    wide = torch.zeros((T + 1, B, L, H, 2 * D), dtype=dt, device="cuda")
+    wide[..., :D] = dq
+    seen = []
+    for form in ("loop", "steps", "lists"):
+        hp.run_compact()
+        hp.out.zero_()
+        if form == "loop":
+            hp.run_decode_loop(dq, dk, dv)
+        elif form == "steps":
+            for t in range(T):
+                hp.run_decode_step(t, dq, dk, dv)
+        else:
+            hp.run_decode_loop(list(dq), list(dk), list(dv))
+        torch.cuda.synchronize()
+        seen.append((hp.out.clone(), hp.cache.lens.clone()))
+    for out, lens in seen[1:]:
+        assert torch.equal(out, seen[0][0]) and torch.equal(lens, seen[0][1])
+    hp.run_compact()
+    with pytest.raises(ValueError):
+        hp.run_decode_loop(wide[..., :D], dk, dv)
+    with pytest.raises(IndexError):
+        hp.run_decode_loop(dq, dk[:T - 1], dv)
