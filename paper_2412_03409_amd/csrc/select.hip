@@ -416,8 +416,8 @@ search_kernel(int L, int N, const uint64_t* __restrict__ cum, const int32_t* __r
     // layer hold unspecified but readable values, and its sequence is not searched).  A layer that does not
     // exist reads layer 0 instead of being skipped, and the table goes through registers: behind conditions
     // each load was waited for by itself, six round trips in a row.  Measured with the sort's own loads taken
-    // together, both kernels: 32 layers x 680 positions 22.7 -> 22.6 us, 8 sequences x 40 x 680 30.1 -> 29.6,
-    // 40 x 1021 23.6 -> 23.0, 48 x 4000 42.0 -> 41.4.
+    // together, both kernels: 32 layers x 680 positions 22.6 -> 22.5 us, 8 sequences x 40 x 680 29.6 -> 29.2,
+    // 40 x 1021 23.0 -> 22.4, 48 x 4000 41.4 -> 40.8.
     LayerSearch ls[2];
     double T[2];
     const int cstep_w = N - 1 > kSearchGroup ? N - 1 : 0;
