@@ -670,29 +670,38 @@ importance_stream_kernel(StreamParams p) {
 // A workgroup takes 64 consecutive keys; its four wavefronts each add a quarter of the heads in order
 // (several loads in flight: the sum is bound by memory latency, not by bytes) and the four sums are added in
 // wavefront order, so the result does not depend on timing.
+// The heads past a quarter's last eight are requested together like the others (one after the other before),
+// with the arguments and the divisions by N at the kernel's start this took the whole importance of 4 x 12 heads
+// x 500 keys of 64 from 17.1 to 16.5 us, of 40 layers x 24 heads x 300 from 57.8 to 56.6.
 constexpr int kMeanKeys = 64, kMeanParts = 4;
 __global__ void __launch_bounds__(kMeanKeys * kMeanParts)
-head_mean_parts_kernel(int H, int N, long long total, const float* __restrict__ partial, float* __restrict__ importance) {
+head_mean_parts_kernel(int H, int N, FastDiv by_n, long long total, const float* __restrict__ partial,
+                       float* __restrict__ importance) {
     __shared__ float s_acc[kMeanParts][kMeanKeys];
+    asm volatile("" : : "s"(partial), "s"(importance), "s"(by_n.d), "s"(by_n.mul), "s"(total), "s"(N), "s"(H));   // the arguments at once
     const int lane = threadIdx.x % kMeanKeys, part = threadIdx.x / kMeanKeys;
     const long long i = ((long long)blockIdx.y * gridDim.x + blockIdx.x) * kMeanKeys + lane;
     const bool live = i < total;
-    const long long bl = live ? i / N : 0;
-    const int n = live ? (int)(i % N) : 0;
+    long long bl = 0;
+    int n = 0;
+    if (total <= 0x7fffffff) {                            // (the whole grid: a 64-bit division takes over a hundred instructions)
+        const DivMod x = div_mod(live ? (int)i : 0, by_n);
+        bl = x.q; n = x.r;
+    } else if (live) {
+        bl = i / N; n = (int)(i % N);
+    }
     const int per = (H + kMeanParts - 1) / kMeanParts;
     const int h0 = part * per, h1 = min(H, h0 + per);
     const float* src = partial + (size_t)bl * H * N + n;
     float acc = 0.f;
     if (live) {
-        int h = h0;
-        for (; h + 8 <= h1; h += 8) {
+        for (int h = h0; h < h1; h += 8) {                // (the heads past a quarter's last: its last once more, not added)
             float v[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = src[(size_t)(h + j) * N];
+            for (int j = 0; j < 8; ++j) v[j] = src[(size_t)min(h + j, h1 - 1) * N];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc += v[j];
+            for (int j = 0; j < 8; ++j) acc = h + j < h1 ? acc + v[j] : acc;
         }
-        for (; h < h1; ++h) acc += src[(size_t)h * N];
     }
     s_acc[part][lane] = acc;
     __syncthreads();
@@ -955,7 +964,7 @@ hipError_t launch_importance(const pkv_shape& s, const void* q, Strides qs, cons
     const long long gx = nblk < kMaxGridX ? nblk : kMaxGridX, gy = (nblk + gx - 1) / gx;
     if (gy > 65535) return hipErrorInvalidValue;
     hipLaunchKernelGGL(head_mean_parts_kernel, dim3((unsigned)gx, (unsigned)gy), dim3(kMeanKeys * kMeanParts), 0, st, s.H,
-                       s.N, total, partial, importance);
+                       s.N, fast_div(s.N), total, partial, importance);
     return hipGetLastError();
 }
 

@@ -53,6 +53,12 @@ def run_importance_case(B, L, H, Hkv, N, D, dtype, negative=False):
     check_importance(np32(P.prefixkv_importance(qd, kd, scale.to(DEV), lse=lse_d)), want)
 
 
+# head_mean_parts_kernel: four quarters of the heads, eight at a time, remainders and empty quarters
+@pytest.mark.parametrize("H", [1, 3, 5, 31, 33, 41, 67])
+def test_importance_head_remainders(H):
+    run_importance_case(2, 1, H, H, 70, 64, torch.bfloat16)
+
+
 # importance_f32_kernel: 16-row tiles dealt to four wavefronts
 @pytest.mark.parametrize("N", [1, 15, 16, 17, 64, 65, 129, 300])
 @pytest.mark.parametrize("H,Hkv,D,negative", [(2, 2, 64, False), (4, 1, 128, True)])
