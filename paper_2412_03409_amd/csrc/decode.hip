@@ -370,6 +370,7 @@ decode_attn_kernel(DecodeParams p) {
     const int r_new = EV ? ring.r_new : len_old;
     const bool own = app && live && ((r_new / BR) & (UW - 1)) == uw;
     uint4 nk = make_uint4(0, 0, 0, 0), nv = nk, gk = nk, gv = nk;
+    if constexpr (!kOne) load_q();                           // ahead of the new row: what is requested late waits behind the counts
     if (own) {
         nk = *(const uint4*)(p.k_new + newrow + sub * 16);
         nv = *(const uint4*)(p.v_new + newrow + sub * 16);
@@ -386,7 +387,6 @@ decode_attn_kernel(DecodeParams p) {
         for (int x = 0; x < EPL; ++x) o[g][x] = 0.f;
     }
     if (uw < nb) {
-        if constexpr (!kOne) load_q();
         // a segment with no row but the new one: k_new / v_new stand in for its slots
         const bool lone = app && len == 1;
         const unsigned char *kload = lone ? p.k_new + newrow : kseg, *vload = lone ? p.v_new + newrow : vseg;
