@@ -276,7 +276,7 @@ decode_attn_kernel(DecodeParams p) {
             int rows = 0;
             if (i < p.n_seg) rows = EV ? p.base_lens[seg_slot(p, i)] + (p.t < p.d + 1 ? p.t : p.d + 1) : p.caps[seg_slot(p, i)];
             const int waves = active_waves(row_blocks(rows, BR), p.spread, W);
-            const int groups = i < p.n_seg ? (HU * waves + W - 1) / W : 0, incl = before + wave_scan(groups);
+            const int groups = i < p.n_seg ? grouped_blocks(HU, waves, W) : 0, incl = before + wave_scan(groups);
             const unsigned long long m = __builtin_amdgcn_ballot_w64(incl > (int)blockIdx.x);
             if (m) {
                 const int at = __builtin_ctzll(m);
@@ -288,8 +288,8 @@ decode_attn_kernel(DecodeParams p) {
             before = __builtin_amdgcn_readlane(incl, kWave - 1);
         }
         if (seg < 0) return;
-        hu = ((int)blockIdx.x - first) * (W / UW) + wv / UW;
-        live = hu < HU;
+        const GroupedUnit x = grouped_unit((int)blockIdx.x - first, wv, UW, W, HU);
+        hu = x.hu; live = x.live;
         b = seg / p.nl; l = p.l0 + seg % p.nl;
     } else {
         hu = blockIdx.x; l = p.l0 + blockIdx.y; b = blockIdx.z;

@@ -132,6 +132,14 @@ __host__ __device__ __forceinline__ int active_waves(int blocks, int spread, int
     while (n < W && blocks > n * spread) n *= 2;
     return n;
 }
+// Workgroups of W wavefronts for a segment whose units (HU) have `waves` each, and the unit of a wavefront of one of them.  The last
+// workgroup of a segment may have wavefronts to spare: they stay for its barriers and read what the segment's last unit reads.
+__host__ __device__ __forceinline__ int grouped_blocks(int HU, int waves, int W) { return (HU * waves + W - 1) / W; }
+struct GroupedUnit { int hu; bool live; };
+__host__ __device__ __forceinline__ GroupedUnit grouped_unit(int block_of_segment, int wv, int waves, int W, int HU) {
+    const int u = block_of_segment * (W / waves) + wv / waves;
+    return {u < HU ? u : HU - 1, u < HU};
+}
 inline int spread_blocks(long long units, long long cus, int N) {
     const int full = N < 320 ? N / 40 : 8, part = units <= 2 * cus ? full : (int)(full * units / (4 * cus));
     return part < 1 ? 1 : part;

@@ -1,5 +1,5 @@
 """csrc/decode_rows.hpp, compiled for the host: the slot that a wavefront reads for each row of a block whose new row comes from
-k_new, the target test of a pruning step, and how many wavefronts of a unit have blocks."""
+k_new, the target test of a pruning step, how many wavefronts a unit of a grouped launch has, and which units its workgroups take."""
 import ctypes as C
 import os
 import subprocess
@@ -18,6 +18,9 @@ extern "C" int slot(int ev, int r, int r0, int len, int len_old, int r_new, int 
 }
 extern "C" int within(int entries, int base, int N, int t) { return pkv::within_target(entries, base, N, t); }
 extern "C" int waves(int blocks, int spread, int W) { return pkv::active_waves(blocks, spread, W); }
+extern "C" int blocks(int HU, int waves, int W) { return pkv::grouped_blocks(HU, waves, W); }
+extern "C" int unit(int block, int wv, int waves, int W, int HU) { const pkv::GroupedUnit x = pkv::grouped_unit(block, wv, waves, W, HU); return x.live ? x.hu : -1 - x.hu; }
+extern "C" int counted(int at, int units, int hu, int HU) { return pkv::counted_units(at, units, hu, HU); }
 extern "C" int spread(long long units, int cus, int N) { return pkv::spread_blocks(units, cus, N); }
 """
 
@@ -90,3 +93,24 @@ def test_active_waves(lib):
                 assert n == W or blocks <= n * s
                 assert n == 1 or blocks > n // 2 * s
                 last = n
+
+
+@pytest.mark.parametrize("HU", [1, 2, 3, 9, 10, 12, 14, 32, 40])
+@pytest.mark.parametrize("W", [4, 8])
+def test_units_of_a_grouped_launch(lib, HU, W):
+    """Every unit once with all its wavefronts, counts that add up to HU, and no index beyond HU, in wavefronts to spare too."""
+    for waves in [w for w in (1, 2, 4, 8) if w <= W]:
+        n = lib.blocks(HU, waves, W)
+        assert 1 <= n <= HU                               # a workgroup per unit is enough
+        seen, counts = [], 0
+        for block in range(n):
+            for wv in range(W):
+                x = lib.unit(block, wv, waves, W, HU)
+                hu = x if x >= 0 else -1 - x
+                assert 0 <= hu < HU, (block, wv, waves)
+                if x >= 0:
+                    seen.append(hu)
+                    if wv % waves == 0:
+                        counts += max(0, lib.counted(wv // waves, W // waves, hu, HU))
+        assert seen == [u for u in range(HU) for _ in range(waves)]
+        assert counts == HU
