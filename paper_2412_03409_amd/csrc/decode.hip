@@ -52,7 +52,8 @@ struct DecodeParams {
     int waves;
     int* ws;
     RankedShape rank;   // ranked launches of decode_attn_kernel
-    int spread;         // grouped launches: blocks of a unit up to which one wavefront has it
+    int turn;                // grouped launches: grouped_turn
+    FastDiv by_nl, by_seg;   // nl, n_seg
 };
 
 constexpr int kRankRegs = 8;      // capacities per lane of a ranked launch: groups of up to 512 segments
@@ -227,19 +228,6 @@ __device__ __forceinline__ int ranked_segment(const int32_t* __restrict__ caps, 
     return found;
 }
 
-__device__ __forceinline__ int seg_slot(const DecodeParams& p, int i) { return (i / p.nl) * p.L + p.l0 + i % p.nl; }
-
-// inclusive sum over the lanes, by DPP: every wavefront waits for it before its first rows
-__device__ __forceinline__ int wave_scan(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15, to the odd rows of 16
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31, to the upper half
-    return v;
-}
-
 // W wavefronts per workgroup; OCC = wavefronts per SIMD the register allocation must allow.  RANK = 0: all W are for one unit, -1: and it
 // is counted in before its rows.  kGrouped: W, W/2 ... or one, by the segment's rows.  RANK > 0: units of the longest segments first,
 // with W, W/2 or W/4 wavefronts per unit (see the launcher).
@@ -267,30 +255,10 @@ decode_attn_kernel(DecodeParams p) {
         if (live) i_seg = x.first + (p.rank.by_length ? ranked_segment<RANK>(p.caps, x.n, p.nl, p.L, p.l0, x.first, x.rank, lane) : x.rank);
         b = i_seg / p.nl; l = p.l0 + i_seg % p.nl;
     } else if constexpr (RANK == kGrouped) {
-        // As many wavefronts for a unit as its rows are worth, and as many units in a workgroup as that makes, all of one segment: fewer
-        // counts on lens.  The workgroups of a segment are found by what no workgroup changes, its capacity or, under pruning, the
-        // entries kept after prefill; the grid is for one unit each, and what is left over ends here.
-        int seg = -1, before = 0, first = 0;
-        for (int i0 = 0; i0 < p.n_seg; i0 += kWave) {
-            const int i = i0 + lane;
-            int rows = 0;
-            if (i < p.n_seg) rows = EV ? p.base_lens[seg_slot(p, i)] + (p.t < p.d + 1 ? p.t : p.d + 1) : p.caps[seg_slot(p, i)];
-            const int waves = active_waves(row_blocks(rows, BR), p.spread, W);
-            const int groups = i < p.n_seg ? grouped_blocks(HU, waves, W) : 0, incl = before + wave_scan(groups);
-            const unsigned long long m = __builtin_amdgcn_ballot_w64(incl > (int)blockIdx.x);
-            if (m) {
-                const int at = __builtin_ctzll(m);
-                seg = i0 + at;
-                UW = __builtin_amdgcn_readlane(waves, at);
-                first = __builtin_amdgcn_readlane(incl - groups, at);
-                break;
-            }
-            before = __builtin_amdgcn_readlane(incl, kWave - 1);
-        }
-        if (seg < 0) return;
-        const GroupedUnit x = grouped_unit((int)blockIdx.x - first, wv, UW, W, HU);
-        hu = x.hu; live = x.live;
-        b = seg / p.nl; l = p.l0 + seg % p.nl;
+        // the segment; how many wavefronts its units have, and so which are this workgroup's, when the capacity is there (below)
+        const int seg = __builtin_amdgcn_readfirstlane(grouped_segment((int)blockIdx.x, (int)blockIdx.y, p.turn, p.by_seg));
+        const DivMod bl = uniform_div_mod(seg, p.by_nl);
+        b = bl.q; l = p.l0 + bl.r; hu = 0;
     } else {
         hu = blockIdx.x; l = p.l0 + blockIdx.y; b = blockIdx.z;
     }
@@ -316,6 +284,15 @@ decode_attn_kernel(DecodeParams p) {
     const int len_old = __builtin_amdgcn_readfirstlane(len_raw) & kLenMask;
     cap = __builtin_amdgcn_readfirstlane(cap);
     off = uniform64(off);
+    if constexpr (RANK == kGrouped) {
+        // By what no workgroup changes: the capacity or, under pruning, the entries kept after prefill.  The grid is for one unit
+        // per workgroup, and those that are not needed end here, all their wavefronts and ahead of any barrier.
+        const int rows = EV ? base + (p.t < p.d + 1 ? p.t : p.d + 1) : cap;
+        UW = __builtin_amdgcn_readfirstlane(active_waves(row_blocks(rows, BR), HU, W));
+        if ((int)blockIdx.y >= grouped_blocks(HU, UW, W)) return;
+        const GroupedUnit x = grouped_unit((int)blockIdx.y, wv, UW, W, HU);
+        hu = x.hu; live = x.live;
+    }
     const int uw = wv & (UW - 1);
     // The unit is counted in once every wavefront of it has read lens.  The smallest launches: here, so that the round trip of the
     // atomic passes under the rows; it is the last wavefront's, which has the fewest.  (32 units 5.36 -> 4.94 us per launch.  Where
@@ -331,7 +308,7 @@ decode_attn_kernel(DecodeParams p) {
     // The first of the workgroup's units of a segment counts all of them in, behind a barrier that they have
     // passed with lens read.  The atomics on the few cache lines of lens were what launches of short rows took, about 8 ns each: 2048 units
     // of 26 rows 18.5 ... 34 us in the same shape, now 17 ... 26, 12 800 of 136 rows 172 -> 160.
-    if constexpr (!kOne) count = counted_units(wv / UW, W / UW, hu, HU);
+    if constexpr (!kOne) count = counted_units(wv >> __builtin_ctz(UW), W >> __builtin_ctz(UW), hu, HU);
     // The result is wanted at the end only; of an address that it knows to be uniform the compiler makes a sum over the lanes first
     // and waits for the atomic on the spot.
     int zero = 0;
@@ -627,6 +604,19 @@ __device__ __forceinline__ SegState seg_state(const DecodeParams& p, int len_old
     return s;
 }
 
+
+__device__ __forceinline__ int seg_slot(const DecodeParams& p, int i) { return (i / p.nl) * p.L + p.l0 + i % p.nl; }
+
+// inclusive sum over the lanes, by DPP: every wavefront waits for it before its first rows
+__device__ __forceinline__ int wave_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15, to the odd rows of 16
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31, to the upper half
+    return v;
+}
 
 // 16 bytes per lane from global memory to LDS[dst + 16 * lane] (nothing else here uses m0); ONCE: without a place in the caches
 template <bool ONCE>
@@ -1126,10 +1116,12 @@ int compute_units() {
 // resident (4 per SIMD; 20 of a ranked launch of the plain bf16 step), and each start costs (12 800 units of 26 rows, one
 // wavefront each: 42 us, of 136 rows 160, for rows that stream in 30 and 150).  Hence
 //   up to 1.75 units per compute unit: 8 wavefronts per unit (32 units, one layer of the 7B shape: 8.6 -> 6.1 us; 16 wavefronts
-//       per unit 6.2; 512 units with 4 against 8: N300 10.8 / 12.5 us, N680 11.5 / 12.4, 384 of N680 11.4 / 10.9);
+//       per unit 6.2; 512 units with 4 against 8: N300 10.8 / 12.5 us, N680 11.5 / 12.4, 384 of N680 11.4 / 10.9), of short prompts,
+//       keys of up to 50 KB per head, 4 if a unit is one head (96 units of 24 rows 5.5 / 5.8, 192 6.6 / 6.9, 416 9.4 / 9.6; of 80 rows 5.8 / 5.8, 6.8 / 7.0,
+//       10.3 / 10.6; kept at 50 %, one layer of eight sequences, 100 rows 6.5 / 6.1; four fp32 heads, 128 units of 20 rows 7.4 / 7.1);
 //   up to 4: 4 wavefronts per unit, which fill the chip (7B, batch 1, lengths within a factor 30: 21.3 -> 18.7 us; equal: 21.7
 //       -> 21.0; equal lengths of 2048 rows and more are 1 ... 10 % slower than with two wavefronts and 16 loads in flight
-//       each, 164.1 -> 169.6 us at 1024 units); of short prompts several units share a workgroup (units_grouped);
+//       each, 164.1 -> 169.6 us at 1024 units); of short prompts several units may share a workgroup (units_grouped);
 //   beyond: one, two or four wavefronts per unit, the longest segments first (see ranked_shape).  The lengths differ by up
 //       to two orders of magnitude, and in index order the launch ends with a few long segments on a chip that is
 //       otherwise empty.
@@ -1145,12 +1137,15 @@ static hipError_t launch_decode_s(DecodeParams p, int nblk, hipStream_t st) {
         hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 8, OCC, EV, -1>), dim3(HU, p.nl, p.B), dim3(8 * kWave), 0, st, p);
         return hipGetLastError();
     }
-    if (nblk <= 4 * cus && units_grouped(nblk, cus, p.N)) {
-        p.spread = spread_blocks(nblk, cus, p.N);
-        hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, kGrouped>), dim3(nblk), dim3(4 * kWave), 0, st, p);
+    const int row_bytes = p.D * (BF16 ? 2 : 4);
+    if (units_grouped(p.n_seg, HU, p.nl, p.L, cus, p.N, row_bytes, EV)) {
+        p.turn = grouped_turn(p.n_seg);
+        p.by_nl = fast_div(p.nl);
+        p.by_seg = fast_div(p.n_seg);
+        hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, OCC, EV, kGrouped>), dim3(p.n_seg, HU), dim3(4 * kWave), 0, st, p);
         return hipGetLastError();
     }
-    if (4 * nblk <= 7 * cus) {
+    if (4 * nblk <= 7 * cus && (G > 1 || p.N * row_bytes > 50 << 10)) {
         hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 8, OCC, EV, 0>), dim3(HU, p.nl, p.B), dim3(8 * kWave), 0, st, p);
         return hipGetLastError();
     }
@@ -1160,7 +1155,7 @@ static hipError_t launch_decode_s(DecodeParams p, int nblk, hipStream_t st) {
     }
     const int ngrp = (p.n_seg + kRankRegs * kWave - 1) / (kRankRegs * kWave);
     p.rank.gsz = (p.n_seg + ngrp - 1) / ngrp;
-    ranked_shape(p.rank, nblk, cus, p.N, p.D * (BF16 ? 2 : 4), RES);
+    ranked_shape(p.rank, nblk, cus, p.N, row_bytes, RES);
     const dim3 grid(ranked_blocks(p.rank, HU) * ngrp), block(4 * kWave);
     const int lds = BF16 ? ranked_lds(p.rank, 4ll * grid.x, cus) : 0;
     if (p.rank.gsz <= kWave) hipLaunchKernelGGL((decode_attn_kernel<BF16, LPR, G, NI, 4, ROCC, EV, 1>), grid, block, lds, st, p);
@@ -1246,7 +1241,7 @@ static DecodeParams make_params(const pkv_shape& s, int l0, int l1, const void* 
     p.N = s.N; p.t = 0; p.d = 0; p.slot_new = 0; p.slot_due = 0; p.base_lens = nullptr; p.kept_pos = nullptr;
     p.n_seg = 0; p.waves = 0; p.ws = nullptr;
     p.rank = RankedShape{0, 0, 0, false};
-    p.spread = 0;
+    p.turn = 0; p.by_nl = p.by_seg = FastDiv{1, 0};
     return p;
 }
 

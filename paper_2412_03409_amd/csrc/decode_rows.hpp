@@ -2,6 +2,8 @@
 // integer rules, apart from the kernels so that they can be compiled and enumerated on the host.
 #pragma once
 
+#include "fast_div.hpp"
+
 namespace pkv {
 
 // Virtual row numbering of a segment under pruning: rows [0, perm) are the permanent slots, rows
@@ -126,10 +128,13 @@ __host__ __device__ __forceinline__ int ranked_blocks(const RankedShape& s, int 
 }
 
 // Grouped launches: a workgroup of W wavefronts takes as many units of a segment as its rows leave wavefronts for.  A unit has one
-// wavefront up to `spread` blocks of rows, two up to twice as many, and so on.
-__host__ __device__ __forceinline__ int active_waves(int blocks, int spread, int W) {
+// wavefront up to kSpread blocks of rows, two up to twice as many, and so on, and no fewer than leave the HU units of a segment with
+// a workgroup's.  (1024 units of 32 segments, 3 / 4 / 5 / 6 blocks, us: N200 14.3 / 12.2 / 12.2 / 12.2 at 50 %, 10.9 / 10.0 / 10.2 / 10.4 at 30 %; N300 16.4 /
+// 16.4 / 14.8 / 14.8 and 13.6 / 14.1 / 12.2 / 12.6, 19.1 / 17.9 / 19.3 / 19.1 for lengths within a factor 3; 960 of 40, N250 16.1 / 15.2 / 16.2 / 16.3.)
+constexpr int kSpread = 4;
+__host__ __device__ __forceinline__ int active_waves(int blocks, int HU, int W) {
     int n = 1;
-    while (n < W && blocks > n * spread) n *= 2;
+    while (n < W && (blocks > n * kSpread || n * HU < W)) n *= 2;
     return n;
 }
 // Workgroups of W wavefronts for a segment whose units (HU) have `waves` each, and the unit of a wavefront of one of them.  The last
@@ -137,21 +142,32 @@ __host__ __device__ __forceinline__ int active_waves(int blocks, int spread, int
 __host__ __device__ __forceinline__ int grouped_blocks(int HU, int waves, int W) { return (HU * waves + W - 1) / W; }
 struct GroupedUnit { int hu; bool live; };
 __host__ __device__ __forceinline__ GroupedUnit grouped_unit(int block_of_segment, int wv, int waves, int W, int HU) {
-    const int u = block_of_segment * (W / waves) + wv / waves;
+    const int sh = __builtin_ctz(waves), u = block_of_segment * (W >> sh) + (wv >> sh);   // (a division each at the start of every unit otherwise)
     return {u < HU ? u : HU - 1, u < HU};
 }
-inline int spread_blocks(long long units, long long cus, int N) {
-    const int full = N < 320 ? N / 40 : 8, part = units <= 2 * cus ? full : (int)(full * units / (4 * cus));
-    return part < 1 ? 1 : part;
+// Workgroup (x, y) of n_seg * HU: the first units of all segments, then the next ones, so that the counts of a segment come apart and the
+// workgroups that are not needed come last.  Its segment: an even number of them is turned by one from y to y, else each would be on
+// one or two XCDs.
+inline int grouped_turn(int n_seg) { return n_seg % 2 == 0; }
+__host__ __device__ __forceinline__ int grouped_segment(int x, int y, int turn, FastDiv n_seg) { return div_mod(x + turn * y, n_seg).r; }
+// Whether a launch is grouped.  The units of a segment are counted by atomics on its word of lens, and a cache line of these words
+// takes about 8 ns for each: 1024 units of 18 rows in one line 13.4 us, without the count 6.2.  A grouped launch counts less where the
+// capacity leaves few wavefronts to a unit; where it does not (much room for new tokens, which the launch does not know) it has the order of
+// its workgroups alone.  So where more than 1.5 units per compute unit, and most of the launch's, are counted in a line, on keys of up to
+// 50 KB per head, or 76 from 2.75 units per compute unit on or under pruning, where the rows are known.  us per step, one unit per workgroup /
+// grouped, room for 8 tokens and for 256, D 128, 40 % within a factor 3:
+//   1024 units of 32 segments, N60 13.3 / 7.3 and 13.1 / 10.8, N130 14.2 / 9.3 and 13.5 / 12.4, N200 14.7 / 12.6 and 14.9 / 14.3, N300 17.7 / 16.6 and 17.7 /
+//     16.8, N400 19.8 / 20.2 and 19.9 / 19.7; 960 of 40, N300 15.4 / 15.1 and 15.6 / 15.0, N400 17.5 / 18.4 and 17.9 / 17.9; fp32 N130 17.6 / 16.0 and 18.0 / 16.7;
+//   768 of 24, N60 10.8 / 7.1 and 10.3 / 10.5, N200 12.9 / 10.4 and 12.6 / 12.0, N300 14.7 / 12.6 and 14.7 / 14.0;
+//   512 of 16, N60 10.5 / 6.9 and 9.9 / 10.3, N200 11.3 / 9.2 and 10.8 / 10.9, N300 12.3 / 11.4 and 11.5 / 11.9 (factor 30 with room, N200 10.3 / 11.0, N300 10.7 /
+//     11.2); under pruning at distance 4, N300 12.6 / 12.1; 416 of 13, N60 9.4 / 6.7 and 8.7 / 9.2, N200 9.7 / 8.7 and 9.3 / 9.5;
+//   other lines: 1024 units, 128 in a line (eight sequences, 4 of 32 layers), N60 7.0 / 7.6, N200 11.7 / 14.4; 256 (128 segments of 8), N60 8.1 / 7.9, N200
+//     12.5 / 13.7; 960 units, 384 (80 segments of 12), N200 11.1 / 12.2; 1024 segments of one unit, N60 6.7 / 7.6.
+inline bool units_grouped(long long n_seg, int HU, int nl, int L, long long cus, int N, int row_bytes, bool rows_known) {
+    const long long units = n_seg * HU, apart = nl == L ? 32 : nl < 32 ? nl : 32, line = (n_seg < apart ? n_seg : apart) * HU;   // units in a line of lens
+    return units <= 4 * cus && 2 * line > 3 * cus && 2 * line > units &&
+           (long long)N * row_bytes <= (rows_known || 4 * units > 11 * cus ? 76 : 50) << 10;
 }
-// Whether a launch of up to 4 units per compute unit is grouped.  The units of a segment are counted by atomics on its word of lens, and
-// all words of a batch share a few cache lines, which take about 8 ns for each: 1024 units of 18 rows 13.4 us, without the count 6.2.  A
-// grouped launch counts less, but it takes one more round trip to memory to find a workgroup's segment, and four units on one compute unit
-// are less even than one.  us per step, one unit per workgroup / grouped: 1024 units, N60 14.3 / 10.4, N128 13.1 / 8.9, N300 at 20 % 13.6 / 12.8, at
-// 50 % 16.8 / 15.4; 768 units, N128 11.6 / 9.3; 512 units, N60 9.9 / 7.9, N128 9.1 / 7.6, N300 at 50 % of unequal lengths 10.9 / 13.6; 192 units,
-// N60 7.7 / 7.8, N128 7.8 / 7.5.  Longer prompts, whose units mostly take all four wavefronts: 1024 units of N680, 17.3 / 17.1 with little room for new
-// tokens, 25.7 / 27.1 (with another spread 32) with room for 256.
-inline bool units_grouped(long long units, long long cus, int N) { return N <= 200 || (units > 2 * cus && N <= 400); }
 
 // Length class of a segment: quarter octaves of its capacity below that of the longest one, the last class open.
 constexpr int kLengthClasses = 16;

@@ -17,11 +17,12 @@ extern "C" int slot(int ev, int r, int r0, int len, int len_old, int r_new, int 
     return ev ? pkv::row_slot<true>(r, r0, len, len_old, r_new, ring) : pkv::row_slot<false>(r, r0, len, len_old, r_new, ring);
 }
 extern "C" int within(int entries, int base, int N, int t) { return pkv::within_target(entries, base, N, t); }
-extern "C" int waves(int blocks, int spread, int W) { return pkv::active_waves(blocks, spread, W); }
+extern "C" int waves(int blocks, int HU, int W) { return pkv::active_waves(blocks, HU, W); }
 extern "C" int blocks(int HU, int waves, int W) { return pkv::grouped_blocks(HU, waves, W); }
 extern "C" int unit(int block, int wv, int waves, int W, int HU) { const pkv::GroupedUnit x = pkv::grouped_unit(block, wv, waves, W, HU); return x.live ? x.hu : -1 - x.hu; }
 extern "C" int counted(int at, int units, int hu, int HU) { return pkv::counted_units(at, units, hu, HU); }
-extern "C" int spread(long long units, int cus, int N) { return pkv::spread_blocks(units, cus, N); }
+extern "C" int segment(int x, int y, int n_seg) { return pkv::grouped_segment(x, y, pkv::grouped_turn(n_seg), pkv::fast_div(n_seg)); }
+extern "C" int grouped(int n_seg, int HU, int nl, int L, int N, int row_bytes, int known) { return pkv::units_grouped(n_seg, HU, nl, L, 256, N, row_bytes, known); }
 """
 
 
@@ -82,35 +83,57 @@ def test_target_without_a_division(lib):
 
 
 def test_active_waves(lib):
-    for units in (65, 256, 512, 513, 1024):
-        for W, N in ((w, n) for w in (4, 8) for n in (1, 39, 40, 79, 80, 200, 319, 320, 400)):
-            s = lib.spread(units, 256, N)
-            assert 1 <= s <= 8
+    for W in (4, 8):
+        for HU in (1, 2, 3, 5, 9, 32):
             last = 1
             for blocks in range(0, 600):
-                n = lib.waves(blocks, s, W)
+                n = lib.waves(blocks, HU, W)
                 assert n in (1, 2, 4, 8) and last <= n <= W
-                assert n == W or blocks <= n * s
-                assert n == 1 or blocks > n // 2 * s
+                assert n == W or (blocks <= n * 4 and n * HU >= W)       # no wavefront idle that a unit could have
+                assert n == 1 or blocks > n // 2 * 4 or n // 2 * HU < W
                 last = n
 
 
 @pytest.mark.parametrize("HU", [1, 2, 3, 9, 10, 12, 14, 32, 40])
 @pytest.mark.parametrize("W", [4, 8])
-def test_units_of_a_grouped_launch(lib, HU, W):
-    """Every unit once with all its wavefronts, counts that add up to HU, and no index beyond HU, in wavefronts to spare too."""
-    for waves in [w for w in (1, 2, 4, 8) if w <= W]:
-        n = lib.blocks(HU, waves, W)
-        assert 1 <= n <= HU                               # a workgroup per unit is enough
-        seen, counts = [], 0
-        for block in range(n):
+@pytest.mark.parametrize("n_seg", [1, 2, 7, 13, 16, 24, 40, 63, 64, 65])
+def test_units_of_a_grouped_launch(lib, HU, W, n_seg):
+    """A grid of n_seg x HU: every unit once with all its wavefronts, counts that add up to HU in each segment, and no index beyond the
+    segments or HU, in wavefronts to spare too; the workgroups of a segment on all XCDs."""
+    widths = [w for w in (1, 2, 4, 8) if w <= W]
+    waves = [widths[s % len(widths)] for s in range(n_seg)]              # as the capacities have it
+    seen, counts, xcds = [[] for _ in waves], [0] * n_seg, [[0] * 8 for _ in waves]
+    for y in range(HU):
+        for x in range(n_seg):
+            seg = lib.segment(x, y, n_seg)
+            assert 0 <= seg < n_seg
+            xcds[seg][(y * n_seg + x) % 8] += 1
+            if y >= lib.blocks(HU, waves[seg], W):
+                continue
             for wv in range(W):
-                x = lib.unit(block, wv, waves, W, HU)
-                hu = x if x >= 0 else -1 - x
-                assert 0 <= hu < HU, (block, wv, waves)
-                if x >= 0:
-                    seen.append(hu)
-                    if wv % waves == 0:
-                        counts += max(0, lib.counted(wv // waves, W // waves, hu, HU))
-        assert seen == [u for u in range(HU) for _ in range(waves)]
-        assert counts == HU
+                u = lib.unit(y, wv, waves[seg], W, HU)
+                hu = u if u >= 0 else -1 - u
+                assert 0 <= hu < HU, (seg, y, wv)
+                if u >= 0:
+                    seen[seg].append(hu)
+                    if wv % waves[seg] == 0:
+                        counts[seg] += max(0, lib.counted(wv // waves[seg], W // waves[seg], hu, HU))
+    for s, w in enumerate(waves):
+        assert seen[s] == [u for u in range(HU) for _ in range(w)]
+        assert counts[s] == HU
+        assert max(xcds[s]) <= 2 * -(-HU // 8)
+
+
+def test_which_launches_are_grouped(lib):
+    """Only where many units are counted in one cache line of lens, and never beyond four units per compute unit."""
+    assert lib.grouped(40, 24, 40, 40, 100, 256, 0) and lib.grouped(32, 32, 1, 1, 200, 256, 0) and lib.grouped(32, 32, 32, 32, 608, 128, 0) and not lib.grouped(32, 32, 32, 32, 609, 128, 0)
+    assert not lib.grouped(1024, 1, 32, 32, 60, 256, 0)              # segments of one unit
+    assert not lib.grouped(32, 32, 4, 32, 60, 256, 0)                # eight sequences, 4 of 32 layers
+    assert not lib.grouped(16, 40, 1, 40, 60, 256, 0)                # a layer a call
+    assert not lib.grouped(128, 8, 32, 32, 60, 256, 0)
+    assert not lib.grouped(64, 16, 32, 32, 60, 256, 0)               # half of the units in a line
+    for n_seg in range(1, 34):                                       # a sequence of 32 heads
+        for N in (60, 200, 201, 304, 305):
+            for known in (0, 1):
+                long_ok = N <= 304 and (known or n_seg > 22)
+                assert lib.grouped(n_seg, 32, n_seg, n_seg, N, 256, known) == (12 < n_seg <= 32 and (N <= 200 or long_ok)), (n_seg, N, known)

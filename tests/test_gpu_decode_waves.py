@@ -20,6 +20,10 @@ BF16, F32 = torch.bfloat16, torch.float32
     (1, 40, 12, 12, 610, 128, BF16, 0.3),    # 480
     (2, 14, 12, 12, 1200, 128, BF16, 0.1),   # 336: eight wavefronts, a block each
     (2, 16, 16, 8, 300, 64, F32, 0.3),       # 256 units of two query heads
+    (1, 24, 32, 32, 300, 128, BF16, 0.3),    # 768, several to a workgroup
+    (1, 44, 17, 17, 190, 128, BF16, 0.4),    # 748, wavefronts to spare in a segment's last workgroup
+    (1, 43, 25, 25, 90, 64, BF16, 0.6),      # more than four per compute unit
+    (1, 29, 25, 25, 130, 128, F32, 0.2),     # 725, an odd number of segments
 ])
 def test_spread(B, L, H, Hkv, N, D, dt, frac):
     run_decode_case(B, L, H, Hkv, N, D, dt, frac, 3, seed=N)
@@ -29,6 +33,7 @@ def test_spread(B, L, H, Hkv, N, D, dt, frac):
     (1, 32, 32, 32, 340, 128, BF16, 0.2, 40, 44),
     (1, 24, 20, 20, 200, 64, BF16, 0.1, 1, 5),
     (2, 15, 9, 3, 190, 128, F32, 0.3, 5, 9),
+    (1, 32, 17, 17, 200, 64, BF16, 0.1, 1, 5),
 ])
 def test_spread_with_pruning(B, L, H, Hkv, N, D, dt, frac, d, steps):
     run_evict_case(B, L, H, Hkv, N, D, dt, frac, d, steps, seed=N)
