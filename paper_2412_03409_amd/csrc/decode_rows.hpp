@@ -82,15 +82,20 @@ struct RankedShape { int gsz, n4, n2; bool by_length, large = false; };   // lar
 // against a quarter of the segments with four wavefronts and the others with two up to 1638 units, an eighth to a sixteenth each up
 // to 8192, one each beyond, with a count of each unit by itself; 256 compute units, bf16, D 128, lengths of the segments within a
 // factor 30 / 3 / equal:
-//   prompts of more than 4096 positions up to 5.3 units per compute unit, and from 12.8 on while that is no more than a third over a
-//     round of 16, a quarter with four, the others with two: 5120 units of 500 rows x0.97.  On shorter prompts that has more workgroups, each of which counts, and what the
-//     wavefronts request late waits behind the counts; against it 3/16 and an eighth as below, lengths as above: 1600 units of N818,
-//     77 rows x0.72 / 0.76 / 0.90, 164 rows 0.80 / 1.01 / 0.94, 245 rows 0.91 / 0.97 / 0.93; 2048 of N818, 77 rows 0.59 / 0.69 / 0.91, 245
-//     rows 0.76 / 0.84 / 1.02; of N2000, 400 rows 0.91 / 0.89 / 1.02.  Of N5000 1600 units, 100 rows 0.72 / 0.87 / 0.90, 500 rows 1.03 / 1.00 /
-//     0.99; 3072 units 0.73 / 0.77 / 0.70 and 1.06 / 1.03 / 1.02; but 1120 units 0.96 / 0.98 / 1.00 and 0.99 / 1.00 / 1.05, of N8000, 400 rows 0.97 / 1.05
-//     / 1.06, 3840 units, 500 rows 1.04 / 1.02 / 1.04;
-//   others of up to 6.4 units per compute unit, 3/16 with four and as many with two, the rest one: 1600 units of 136 rows
+//   prompts of more than 4096 positions with keys of more than 1 MB per head, while a quarter with four and the others with two are no more
+//     than a third over a round of 16: those, except where they just fit a round of 20 (1707 to 2275 units: 2048, 400 rows, x1.11, an
+//     eighth each 1.03; 2240, 250 rows 1.12 and 0.98), and for keys of more than 192 KB up to 4.9 units per compute unit.  Other shapes have fewer
+//     workgroups, each of which counts, and win on few rows, but not on the many that such prompts keep, against a quarter and the others:
+//     3200 units, an eighth, N5000, 250 rows 0.93, 400 1.01, 500 1.10, 1000 1.11; 2560, 1000 rows 1.07; 1120 units, 3/16, N818, 40 rows 0.88, 160 rows 1.01,
+//     400 rows 1.04, N2000, 1000 rows 1.12; 1200, N1000, 400 rows 1.12;
+//   of keys of more than 192 KB from there to 7.1 units per compute unit, a quarter each: with the others two / a quarter each / 3/16 each
+//     1280 units, 40 rows x1.11 / 0.89 / 0.84, 400 rows 1.00 / 1.05 / 1.09; 1440 of 60 rows 1.13 / 0.88 / 0.83, of 400 1.01 / 0.96 / 0.99; 1760 of 60 1.16 / 0.92 /
+//     0.81, of 400 1.06 / 1.00 / 1.04, an eighth 1.10;
+//   shorter prompts of up to 6.4 units per compute unit, 3/16 with four and as many with two, the rest one: 1600 units of 136 rows
 //     x0.87 / 0.95 / 0.85 (a quarter and the others 0.89 / 0.92 / 0.90), of 41 0.72 / 0.73 / 0.77 (0.86 / 1.12 / 0.80);
+//   from 8.6 to 11.4 units per compute unit (9.1 for keys of more than 192 KB), where an eighth each is a fifth over a round of 16: a quarter with two, the others
+//     one: 2400 units, N400, 40 rows an eighth 1.02 on average, at worst 1.10, a quarter with two 0.91, 1.01; 160 rows 0.99 and 0.95; 2560, 40 rows 1.02
+//     and 0.91; 2880, N1000 0.99 and 0.97;
 //   beyond, an eighth each while that fits one round of 16, then what does, but a sixteenth: 2048 units of 136 rows x0.90 / 0.91 / 0.90,
 //     of 26 0.65 / 0.64 / 0.66; 3648 of 300 an eighth 0.98 on average, a sixteenth 0.97, none 0.99; 4096 of 136 fp32 rows 0.98, none 1.11;
 //   the sixteenth up to two rounds of 16, except for the plain bf16 step on keys of up to 192 KB, which has what fits its own round
@@ -104,8 +109,11 @@ inline void ranked_shape(RankedShape& s, long long units, long long cus, int N, 
     const bool large = s.large = N * row_bytes > 192 << 10;
     double f4 = 0, f2 = 0;
     s.by_length = N * row_bytes > 96 << 10 || units < 16 * cus;
-    if (N > 4096 && per_unit >= 0.75 && (per_unit < 1.25 || per_unit >= 3)) { f4 = 0.25; f2 = 0.75; }
+    const bool longest = N > 4096 && N * row_bytes > 1 << 20;
+    if (longest ? per_unit >= 0.75 && (per_unit <= 1.8 || per_unit >= 2.4) : large && per_unit >= 3.25) { f4 = 0.25; f2 = 0.75; }
+    else if (large && per_unit >= 2.25) f4 = f2 = 0.25;
     else if (per_unit >= 2.5) f4 = f2 = 0.1875;
+    else if (per_unit >= 1.4 && per_unit <= (large ? 1.75 : 1.85)) f2 = 0.25;
     else if (s.by_length && per_unit >= (large || resident == 16 ? 0.5 : 1)) f4 = f2 = per_unit > 1.5 ? 0.125 : per_unit < 1.25 ? 0.0625 : (per_unit - 1) / 4;
     else if (s.by_length && units <= resident * cus) f4 = f2 = ((double)resident * cus / units - 1) / 4;
     s.n4 = (int)(s.gsz * f4 + 0.5);

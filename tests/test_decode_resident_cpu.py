@@ -80,3 +80,21 @@ def test_counts_of_a_segment(shim, HU):
                 assert counts == in_block
                 total[seg] += counts
         assert total == [HU] * n_seg and len(units) == n_seg * HU
+
+
+def test_shapes_by_length_of_the_prompt(shim):
+    """Where a shape made for few rows would lose on the many rows that a long prompt keeps, and back: bf16 rows of D 128."""
+    out = (C.c_int * 5)()
+
+    def shape(L, H, N):
+        shim.shape(L, L * H, 256, N, 256, 20, out)
+        return out[0] / L, out[1] / L
+
+    for L, H in ((34, 32), (35, 32), (30, 40)):                    # up to 4.9 units per compute unit
+        assert shape(L, H, 1000)[0] >= 0.23 and sum(shape(L, H, 1000)) == 1
+        assert sum(shape(L, H, 400)) < 0.45
+    assert sum(shape(40, 32, 1000)) == 0.5 and sum(shape(40, 32, 5000)) == 1
+    assert sum(shape(64, 32, 5000)) == 0.25                        # what just fits a round of 20 does not do
+    for L, H in ((80, 32), (96, 32), (100, 32)):
+        assert sum(shape(L, H, 5000)) == 1
+    assert shape(75, 32, 400) == (0, 19 / 75) and shape(80, 32, 818) == (0, 0.25)
