@@ -27,4 +27,8 @@ __host__ __device__ __forceinline__ HeadBlock head_block(int j, int heads, int n
     return head_block(j, heads, fast_div(nblk), fast_div(tail));
 }
 
+// Whether the heads (B*L*H) fit a one-dimensional grid of whole heads per XCD, as many to each of the `xcds`, in which the bf16 kernels
+// count them in 32 bits.  (The fp32 kernels have a two-dimensional one.)
+inline bool heads_fit(long long heads, int xcds) { return (heads + xcds - 1) / xcds * xcds <= 0x7fffffffll; }
+
 }  // namespace pkv

@@ -896,7 +896,7 @@ static void launch_stream_d(const pkv_shape& s, const StreamParams& p, dim3 grid
 }
 template <bool COLS>
 static hipError_t launch_stream(const pkv_shape& s, StreamParams p, hipStream_t st) {
-    const long long cus = compute_units(), hx = (p.nheads + kXcds - 1) / kXcds;   // heads per XCD
+    const long long cus = compute_units(), hx = ((long long)p.nheads + kXcds - 1) / kXcds;   // heads per XCD
     // 64 stationary rows per wavefront from two rounds of workgroups on, unless that pads the blocks further (1024
     // heads of 100 positions: 47 against 32 us); for the column sums of D = 128 with three to six blocks per head also
     // where these just fill one round of three workgroups per CU (256 heads of 680: 36.3 against 39.2 us, of 768: 40.3
@@ -923,7 +923,7 @@ hipError_t launch_importance(const pkv_shape& s, const void* q, Strides qs, cons
     float* partial = (float*)ws;
     float* lse_ws = partial + (size_t)s.B * s.L * s.H * s.N;
     const long long total = (long long)s.B * s.L * s.N, heads = (long long)s.B * s.L * s.H;
-    if (heads > 0x7fffffffll - kXcds) return hipErrorInvalidValue;   // they are counted in 32 bits, and a grid holds no more
+    if (s.dtype != PKV_F32 && !heads_fit(heads, kXcds)) return hipErrorInvalidValue;
     hipError_t e;
     if (s.dtype == PKV_F32) {
         F32Params p{s.B, s.L, s.H, s.Hkv, s.N, (const float*)q, qs, (const float*)k, ks, scale, nullptr, lse_ws};

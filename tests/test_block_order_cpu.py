@@ -17,6 +17,7 @@ extern "C" void block(int j, int heads, int nblk, int tail, int* out) {
     out[0] = x.head;
     out[1] = x.rank;
 }
+extern "C" int fit(long long heads, int xcds) { return pkv::heads_fit(heads, xcds); }
 """
 
 
@@ -26,12 +27,14 @@ def block(tmp_path_factory):
     (d / "shim.cpp").write_text(SHIM)
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cpp"), "-o",
                            str(d / "shim.so")])
-    f = C.CDLL(str(d / "shim.so")).block
+    lib = C.CDLL(str(d / "shim.so"))
+    f = lib.block
     out = (C.c_int * 2)()
 
     def call(*a):
         f(*a, out)
         return out[0], out[1]
+    call.fit = lambda heads: lib.fit(C.c_longlong(heads), 8)
     return call
 
 
@@ -55,3 +58,11 @@ def test_blocks_are_dealt_out_evenly(block, nblk):
     for j in range(heads * nblk):
         work[j % 32] += nblk - block(j, heads, nblk, 0)[1]
     assert max(work) <= 1.1 * sum(work) / 32, work
+
+
+def test_heads_of_a_launch(block):
+    """What eight equal shares of heads leave below 2^31, to the last one."""
+    for heads in (1, 7, 8, 9, (1 << 31) - 16, (1 << 31) - 9, (1 << 31) - 8):
+        assert block.fit(heads), heads
+    for heads in ((1 << 31) - 7, (1 << 31) - 1, 1 << 31, 1 << 32, 1 << 40):
+        assert not block.fit(heads), heads
