@@ -10,9 +10,6 @@ import torch
 from . import binding as B_
 
 
-_DECODE_ATTN = B_.prefixkv_decode_attn
-
-
 class HotPath:
     def __init__(self, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, scale: torch.Tensor,
                  budget_tokens: int, decode_steps: int, tol_tokens: int = 0, max_iters: int = 64,
@@ -95,9 +92,8 @@ class HotPath:
             self._decode(t, q, k, v, out)
 
     def _plain(self) -> bool:
-        """Whether a step is the binding's own call with nothing of the caller's in between."""
-        return (self.evict_distance is None and getattr(self._decode, "__func__", None) is HotPath._decode
-                and B_.prefixkv_decode_attn is _DECODE_ATTN)
+        """Whether a step is the binding's call without pruning, with nothing of the caller's in between."""
+        return self.evict_distance is None and getattr(self._decode, "__func__", None) is HotPath._decode
 
     # ---- the decode loop as one HIP graph (T launches, no host work between them) -----------
     def capture_decode_loop(self, dq, dk, dv):

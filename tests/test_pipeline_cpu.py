@@ -64,3 +64,21 @@ def test_too_few_steps(path):
     for x in ((dq[:2], dk, dv), (dq, list(dk)[:2], dv)):
         with pytest.raises(IndexError):
             path.run_decode_loop(*x)
+
+
+def test_a_decode_call_of_the_programs_own(monkeypatch):
+    """A function in the place of the binding's is called for every step, also one put there before the pipeline is imported."""
+    import importlib
+    calls = []
+    monkeypatch.setattr(binding, "prefixkv_decode_attn", lambda *a, **k: calls.append(a))
+    fresh = importlib.util.module_from_spec(pipeline.__spec__)
+    pipeline.__spec__.loader.exec_module(fresh)
+    monkeypatch.setattr(torch.Tensor, "is_cuda", True)     # as on the GPU, where the loop's arguments are looked at once
+    monkeypatch.setattr(binding, "load", lambda *a: pytest.fail("the library was called"))
+    monkeypatch.setattr(binding, "prefixkv_workspace_bytes", lambda *a: 0)
+    monkeypatch.setattr(binding, "select_workspace_bytes", lambda *a: 0)
+    monkeypatch.setattr(binding, "prefixkv_cache_tokens_upper_bound", lambda *a: 8)
+    q = torch.zeros((B, L, H, 16, D))
+    hp = fresh.HotPath(q, q, q, torch.ones(L), 8, T)
+    hp.run_decode_loop(*tensors())
+    assert len(calls) == T
