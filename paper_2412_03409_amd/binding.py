@@ -479,8 +479,8 @@ def prefixkv_decode_attn(cache: CompactResult, q: torch.Tensor, k_new: Optional[
     s, need = _decode_shape_of(B, L, H, index(cache.Hkv), index(N), D, _dtype_code(q))
     w = _ws(need, q.device, ws)
     rc = load().prefixkv_decode_attn(s, int(l0), int(l1), q.data_ptr(), _ptr(k_new), _ptr(v_new), scale.data_ptr(),
-                                     cache.kc.data_ptr(), cache.vc.data_ptr(), cache.seg_off.data_ptr(), cache.caps.data_ptr(),
-                                     cache.lens.data_ptr(), out.data_ptr(), w.data_ptr(), w.numel() * w.element_size(),
+                                     cache.kc.data_ptr(), _ptr(cache.vc), _ptr(cache.seg_off), _ptr(cache.caps),
+                                     _ptr(cache.lens), out.data_ptr(), w.data_ptr(), w.numel() * w.element_size(),
                                      _stream())
     if rc != 0:
         raise PrefixKVError(rc, "prefixkv_decode_attn")
@@ -496,7 +496,7 @@ def decode_attn_steps(cache: CompactResult, q: torch.Tensor, k_new: torch.Tensor
     [>=T,B,L,Hkv,D]: the same calls, whose arguments are looked at once.  False, and nothing is done, where a step by itself
     has to see to it (other layouts, other types, errors) or a program has put a function of its own in the step's place."""
     xs = (q, k_new, v_new, out)
-    if prefixkv_decode_attn is not _own_decode_attn:
+    if prefixkv_decode_attn is not _own_decode_attn or ws is None:
         return False
     if T < 1 or any(type(x) is not torch.Tensor or not x.is_cuda or x.dim() != 5 or not x.is_contiguous() or x.shape[0] < T for x in xs):
         return False
@@ -514,7 +514,7 @@ def decode_attn_steps(cache: CompactResult, q: torch.Tensor, k_new: torch.Tensor
     step = load().prefixkv_decode_attn
     qs, ns = B * L * H * D * q.element_size(), B * L * cache.Hkv * D * q.element_size()
     qp, kp, vp, op = (x.data_ptr() for x in xs)
-    args = (scale.data_ptr(), cache.kc.data_ptr(), cache.vc.data_ptr(), cache.seg_off.data_ptr(), cache.caps.data_ptr(), cache.lens.data_ptr())
+    args = (scale.data_ptr(), cache.kc.data_ptr(), _ptr(cache.vc), _ptr(cache.seg_off), _ptr(cache.caps), _ptr(cache.lens))
     wp, st = ws.data_ptr(), _stream()
     for t in range(T):
         rc = step(s, 0, L, qp + t * qs, kp + t * ns, vp + t * ns, *args, op + t * qs, wp, nbytes, st)

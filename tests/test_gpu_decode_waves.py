@@ -2,6 +2,7 @@
 import pytest
 import torch
 
+from paper_2412_03409_amd import binding
 from paper_2412_03409_amd.pipeline import HotPath
 from test_gpu_parity import run_decode_case, run_evict_case
 
@@ -70,3 +71,43 @@ def test_loop_is_its_steps(dt, Hkv):
         hp.run_decode_loop(wide[..., :D], dk, dv)
     with pytest.raises(IndexError):
         hp.run_decode_loop(dq, dk[:T - 1], dv)
+
+
+# What decode_attn_steps takes, and what it leaves to the steps: nothing is done then, and a step by itself accepts or refuses it as ever.
+@pytest.mark.parametrize("Hkv", [4, 2])
+def test_what_the_loop_takes(Hkv):
+    B, L, H, N, D, T = 1, 3, 4, 40, 64, 3
+    g = torch.Generator().manual_seed(7)
+    rnd = lambda *s: torch.randn(s, generator=g).to(BF16).cuda()
+    hp = HotPath(rnd(B, L, H, N, D), rnd(B, L, Hkv, N, D), rnd(B, L, Hkv, N, D), torch.full((L,), 0.1, device="cuda"), 30, T)
+    hp.run_importance(); hp.run_select(); hp.run_compact()
+    q, k, v = rnd(T, B, L, H, D), rnd(T, B, L, Hkv, D), rnd(T, B, L, Hkv, D)
+    need = binding.prefixkv_workspace_bytes(binding.OP_DECODE, B, L, H, Hkv, N, D, binding.PKV_BF16)
+    assert (need > 0) == (Hkv < H)
+    lens, wide = hp.cache.lens.clone(), torch.cat([q, q], -1)
+    args = dict(cache=hp.cache, q=q, k_new=k, v_new=v, scale=hp.scale, N=N, T=T, out=hp.out, ws=hp.dec_ws)
+    bad = [dict(T=0), dict(T=T + 1), dict(q=q.float()), dict(k_new=k.float()), dict(out=hp.out.float()), dict(q=wide[..., :D]), dict(q=q[0]), dict(k_new=k[:, :, :2]),
+           dict(out=hp.out[:, :, :, :2]), dict(q=q.cpu()), dict(k_new=None), dict(q=q.clone().requires_grad_()), dict(scale=hp.scale.double()), dict(scale=hp.scale[:2]),
+           dict(scale=hp.scale.cpu()), dict(scale=torch.ones(2 * L, device="cuda")[::2]), dict(ws=None)]
+    if need:
+        bad.append(dict(ws=hp.dec_ws[:need - 1]))
+    hp.out.fill_(7)
+    for b in bad:
+        assert binding.decode_attn_steps(**{**args, **b}) is False, list(b)
+    torch.cuda.synchronize()
+    assert torch.equal(hp.cache.lens, lens) and bool((hp.out == 7).all())
+    hp.dec_ws, ws = None, hp.dec_ws                        # the steps have a workspace made then
+    hp.run_decode_loop(q, k, v)
+    want, hp.dec_ws = hp.out.clone(), ws
+    hp.run_compact()
+    assert binding.decode_attn_steps(**args) is True
+    torch.cuda.synchronize()
+    assert torch.equal(hp.out, want) and torch.equal(hp.cache.lens, lens + T)
+    for name in ("vc", "seg_off", "caps", "lens"):         # refused by the library, by either path
+        kept = getattr(hp.cache, name)
+        setattr(hp.cache, name, None)
+        with pytest.raises(binding.PrefixKVError):
+            binding.prefixkv_decode_attn(hp.cache, q[0], k[0], v[0], hp.scale, N, ws=ws)
+        with pytest.raises(binding.PrefixKVError):
+            binding.decode_attn_steps(**args)
+        setattr(hp.cache, name, kept)
