@@ -386,7 +386,9 @@ decode_attn_kernel(DecodeParams p) {
         int blk = uw;
         // Blocks of stored rows.  The next block's K rows are requested when this one's are used up, its V rows likewise: no register
         // more, and the wavefronts of the longest units, with which a launch ends, wait less (13B, batch 8:
-        // 158.8 -> 154.6 us a step).
+        // 158.8 -> 154.6 us a step).  In launches of one round the compiler may request V rows as their registers come free (512 units of
+        // 1200 rows, lengths within a factor 30, 62.8 -> 61.5 us; 480 of 204 14.1 -> 13.8; 0.997 ... 1.00 of the time of others); in ranked ones of
+        // short rows that is 2 ... 10 % slower.
         if (blk < nfull) {
             const unsigned char *ka = kseg + (size_t)blk * (NI * 1024), *va = vseg + (size_t)blk * (NI * 1024);
             const uint32_t lane_off = (uint32_t)lane * 16u;
@@ -408,7 +410,7 @@ decode_attn_kernel(DecodeParams p) {
                 load_k();
                 __builtin_amdgcn_sched_barrier(0);
                 block_values<BF16, LPR, G, NI>(s, vr, o, mrun, srun);
-                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (RANK > 0) __builtin_amdgcn_sched_barrier(0);
                 load_v();
             }
             block_scores<BF16, LPR, G, NI>(kr, qf, s);
@@ -1138,7 +1140,7 @@ static hipError_t launch_decode_s(DecodeParams p, int nblk, hipStream_t st) {
         return hipGetLastError();
     }
     const int row_bytes = p.D * (BF16 ? 2 : 4);
-    if (units_grouped(p.n_seg, HU, p.nl, p.L, cus, p.N, row_bytes, EV)) {
+    if (units_grouped(p.n_seg, HU, p.nl, p.L, cus, p.N, row_bytes)) {
         p.turn = grouped_turn(p.n_seg);
         p.by_nl = fast_div(p.nl);
         p.by_seg = fast_div(p.n_seg);

@@ -22,7 +22,7 @@ extern "C" int blocks(int HU, int waves, int W) { return pkv::grouped_blocks(HU,
 extern "C" int unit(int block, int wv, int waves, int W, int HU) { const pkv::GroupedUnit x = pkv::grouped_unit(block, wv, waves, W, HU); return x.live ? x.hu : -1 - x.hu; }
 extern "C" int counted(int at, int units, int hu, int HU) { return pkv::counted_units(at, units, hu, HU); }
 extern "C" int segment(int x, int y, int n_seg) { return pkv::grouped_segment(x, y, pkv::grouped_turn(n_seg), pkv::fast_div(n_seg)); }
-extern "C" int grouped(int n_seg, int HU, int nl, int L, int N, int row_bytes, int known) { return pkv::units_grouped(n_seg, HU, nl, L, 256, N, row_bytes, known); }
+extern "C" int grouped(int n_seg, int HU, int nl, int L, int N, int row_bytes) { return pkv::units_grouped(n_seg, HU, nl, L, 256, N, row_bytes); }
 """
 
 
@@ -126,14 +126,12 @@ def test_units_of_a_grouped_launch(lib, HU, W, n_seg):
 
 def test_which_launches_are_grouped(lib):
     """Only where many units are counted in one cache line of lens, and never beyond four units per compute unit."""
-    assert lib.grouped(40, 24, 40, 40, 100, 256, 0) and lib.grouped(32, 32, 1, 1, 200, 256, 0) and lib.grouped(32, 32, 32, 32, 608, 128, 0) and not lib.grouped(32, 32, 32, 32, 609, 128, 0)
-    assert not lib.grouped(1024, 1, 32, 32, 60, 256, 0)              # segments of one unit
-    assert not lib.grouped(32, 32, 4, 32, 60, 256, 0)                # eight sequences, 4 of 32 layers
-    assert not lib.grouped(16, 40, 1, 40, 60, 256, 0)                # a layer a call
-    assert not lib.grouped(128, 8, 32, 32, 60, 256, 0)
-    assert not lib.grouped(64, 16, 32, 32, 60, 256, 0)               # half of the units in a line
+    assert lib.grouped(40, 24, 40, 40, 100, 256) and lib.grouped(32, 32, 1, 1, 200, 256) and lib.grouped(32, 32, 32, 32, 800, 128) and not lib.grouped(32, 32, 32, 32, 801, 128)
+    assert not lib.grouped(1024, 1, 32, 32, 60, 256)              # segments of one unit
+    assert not lib.grouped(32, 32, 4, 32, 60, 256)                # eight sequences, 4 of 32 layers
+    assert not lib.grouped(16, 40, 1, 40, 60, 256)                # a layer a call
+    assert not lib.grouped(128, 8, 32, 32, 60, 256)
+    assert not lib.grouped(64, 16, 32, 32, 60, 256)               # half of the units in a line
     for n_seg in range(1, 34):                                       # a sequence of 32 heads
-        for N in (60, 200, 201, 304, 305):
-            for known in (0, 1):
-                long_ok = N <= 304 and (known or n_seg > 22)
-                assert lib.grouped(n_seg, 32, n_seg, n_seg, N, 256, known) == (12 < n_seg <= 32 and (N <= 200 or long_ok)), (n_seg, N, known)
+        for N in (60, 200, 201, 400, 401):
+            assert lib.grouped(n_seg, 32, n_seg, n_seg, N, 256) == (12 < n_seg <= 32 and (N <= 200 or (N <= 400 and n_seg > 22))), (n_seg, N)
