@@ -161,24 +161,28 @@ __host__ __device__ __forceinline__ int grouped_segment(int x, int y, int turn, 
 // Whether a launch is grouped.  The units of a segment are counted by atomics on its word of lens, and a cache line of these words
 // takes about 8 ns for each: 1024 units of 18 rows in one line 13.4 us, without the count 6.2.  A grouped launch counts less where the
 // capacity leaves few wavefronts to a unit; where it does not (much room for new tokens, which the launch does not know) it has the order of
-// its workgroups alone.  So where more than 1.5 units per compute unit, and most of the launch's, are counted in a line, on keys of up to
-// 50 KB per head, or 100 from 2.75 units per compute unit on.  us per step, one unit per workgroup / grouped, room for 8 tokens and for 256,
-// D 128, 40 % within a factor 3:
+// its workgroups alone.  So on keys of up to 26 KB per head where three quarters of a unit per compute unit are counted in a line, up to 50 KB
+// where one is, at least half of the launch's, and a segment has 16 units, and up to 76 where more than 1.5 and half are and the launch has
+// more than 2, 100 where it has more than 2.75.  us per step, one unit per workgroup / grouped, room for 8 tokens and for 256, D 128, 40 % within a factor 3:
 //   1024 units of 32 segments, N60 13.3 / 7.3 and 13.1 / 10.8, N130 14.2 / 9.3 and 13.5 / 12.4, N200 14.7 / 12.6 and 14.9 / 14.3, N300 17.7 / 16.6 and 17.7 /
 //     16.8, N400 19.8 / 20.2 and 19.9 / 19.7, at 10 % 14.4 / 7.9; 960 of 40, N300 15.4 / 15.1 and 15.6 / 15.0, N400 17.5 / 18.4 and 17.9 / 17.9, at 10 % x0.66; fp32 N130 17.6 /
 //     16.0 and 18.0 / 16.7;
 //   768 of 24, N60 10.8 / 7.1 and 10.3 / 10.5, N200 12.9 / 10.4 and 12.6 / 12.0, N300 14.7 / 12.6 and 14.7 / 14.0; 608 of 19, N60 10.6 / 7.0 and 10.1 /
-//     10.5, but N400 at a factor 30 12.8 / 16.1;
+//     10.5, N300 13.3 / 13.2 and 12.9 / 13.7, at a factor 30 11.4 / 10.3 and 10.7 / 12.1, but N400 of that 12.8 / 16.1;
 //   512 of 16, N60 10.5 / 6.9 and 9.9 / 10.3, N200 11.3 / 9.2 and 10.8 / 10.9, N300 12.3 / 11.4 and 11.5 / 11.9 (factor 30 with room, N200 10.3 / 11.0, N300 10.7 /
 //     11.2); 416 of 13, N60 9.4 / 6.7 and 8.7 / 9.2, N200 9.7 / 8.7 and 9.3 / 9.5;
 //   longer prompts gain too where few rows are kept, and lose where many of unequal lengths are: 864 units of 36 segments, N350 at a factor 30 14.1 / 16.3; of 400 ... 3000 positions 832 of 26
 //     x0.92 ... 1.11 on average, at worst 1.09 ... 1.28, 960 of 40 0.91 ... 1.05 and 1.04 ... 1.10;
-//   other lines: 1024 units, 128 in a line (eight sequences, 4 of 32 layers), N60 7.0 / 7.6, N200 11.7 / 14.4; 256 (128 segments of 8), N60 8.1 / 7.9, N200
-//     12.5 / 13.7; 960 units, 384 (80 segments of 12), N200 11.1 / 12.2; 1024 segments of one unit, N60 6.7 / 7.6.
+//   fewer in a line, on average and at worst of 7 spreads, budgets and rooms: 192 of 192 units, N100 x0.96 and 1.03, N200 1.02, 1.07; 256 of 256 0.90, 1.02 and 0.96, 1.03; 288 of 288 (24
+//     segments of 12), N100 0.93, 1.02 and N200 1.02, 1.12; 384 of 960 (80 of 12) 0.83, 1.02 and 0.95, 1.17; 256 of 1024 (128 of 8), N100 0.93, 1.03, N130 0.97, 1.16; 512 of 1024 (64 of
+//     16), N200 0.87, 1.07; 128 of 1024 (eight sequences, 4 of 32 layers), N60 7.0 / 7.6 us, N200 11.7 / 14.4; 1024 segments of one unit, N60 6.7 / 7.6.
 inline bool units_grouped(long long n_seg, int HU, int nl, int L, long long cus, int N, int row_bytes) {
     const long long units = n_seg * HU, apart = nl == L ? 32 : nl < 32 ? nl : 32, line = (n_seg < apart ? n_seg : apart) * HU;   // units in a line of lens
-    return units <= 4 * cus && 2 * line > 3 * cus && 2 * line > units &&
-           (long long)N * row_bytes <= (4 * units > 11 * cus ? 100 : 50) << 10;
+    const long long keys = (long long)N * row_bytes;
+    if (units > 4 * cus) return false;
+    if (keys <= 26 << 10) return 4 * line >= 3 * cus;
+    if (keys <= 50 << 10) return line >= cus && 2 * line >= units && HU >= 16;
+    return units > 2 * cus && 2 * line > 3 * cus && 2 * line > units && keys <= (4 * units > 11 * cus ? 100 : 76) << 10;
 }
 
 // Length class of a segment: quarter octaves of its capacity below that of the longest one, the last class open.

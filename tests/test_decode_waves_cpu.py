@@ -125,13 +125,16 @@ def test_units_of_a_grouped_launch(lib, HU, W, n_seg):
 
 
 def test_which_launches_are_grouped(lib):
-    """Only where many units are counted in one cache line of lens, and never beyond four units per compute unit."""
+    """Only where many units are counted in one cache line of lens, the more the longer the prompt, and never beyond four units per
+    compute unit."""
     assert lib.grouped(40, 24, 40, 40, 100, 256) and lib.grouped(32, 32, 1, 1, 200, 256) and lib.grouped(32, 32, 32, 32, 800, 128) and not lib.grouped(32, 32, 32, 32, 801, 128)
     assert not lib.grouped(1024, 1, 32, 32, 60, 256)              # segments of one unit
     assert not lib.grouped(32, 32, 4, 32, 60, 256)                # eight sequences, 4 of 32 layers
     assert not lib.grouped(16, 40, 1, 40, 60, 256)                # a layer a call
-    assert not lib.grouped(128, 8, 32, 32, 60, 256)
-    assert not lib.grouped(64, 16, 32, 32, 60, 256)               # half of the units in a line
+    for N in (60, 104, 105, 200):                                    # 256 of 1024 units in a line, 288 of 288
+        assert lib.grouped(128, 8, 32, 32, N, 256) == lib.grouped(24, 12, 24, 24, N, 256) == (N <= 104)
+    assert lib.grouped(64, 16, 32, 32, 200, 256) and not lib.grouped(64, 16, 32, 32, 201, 256)   # half of the units in a line
     for n_seg in range(1, 34):                                       # a sequence of 32 heads
-        for N in (60, 200, 201, 400, 401):
-            assert lib.grouped(n_seg, 32, n_seg, n_seg, N, 256) == (12 < n_seg <= 32 and (N <= 200 or (N <= 400 and n_seg > 22))), (n_seg, N)
+        for N in (60, 104, 105, 200, 201, 304, 305, 400, 401):
+            least = 6 if N <= 104 else 8 if N <= 200 else 17 if N <= 304 else 23 if N <= 400 else 99
+            assert lib.grouped(n_seg, 32, n_seg, n_seg, N, 256) == (least <= n_seg <= 32), (n_seg, N)
