@@ -4,8 +4,9 @@
 //
 //  decode_attn_kernel   a unit is one (sequence, layer, kv head), or a sub-group of G of its query heads.  One to
 //                       eight wavefronts work on a unit (see the launcher) and take its row blocks round-robin.  A
-//                       wavefront issues all K and V loads of a block up front (16 B per lane, whole rows, fully
-//                       coalesced), then does the dot products, a block softmax and the weighted V sum in registers
+//                       wavefront requests the K and V rows of its first block together (16 B per lane, whole rows, fully
+//                       coalesced) and those of the next one as this one's are used up; it does the dot products, a
+//                       block softmax and the weighted V sum in registers
 //                       for every query head of the group, so each cached byte is read from HBM once per group.
 //                       The wavefronts' (max, sum, weighted V) are merged through LDS and the output is
 //                       written directly: no partial results ever go to HBM.
@@ -250,7 +251,7 @@ decode_attn_kernel(DecodeParams p) {
         static_assert(W == 4, "a workgroup holds one, two or four units");
         const RankedUnit x = ranked_unit(blockIdx.x, wv, p.rank, HU, p.n_seg);
         UW = x.UW; hu = x.hu; live = x.live;
-        if (!live && UW != 2) return;                      // no barrier ahead, or the whole workgroup has none
+        if (!live && UW != 2) return;                      // one wavefront each: the barrier below is for those that go on; four: none of the workgroup has a unit
         int i_seg = 0;
         if (live) i_seg = x.first + (p.rank.by_length ? ranked_segment<RANK>(p.caps, x.n, p.nl, p.L, p.l0, x.first, x.rank, lane) : x.rank);
         b = i_seg / p.nl; l = p.l0 + i_seg % p.nl;
@@ -1127,8 +1128,7 @@ int compute_units() {
 //   beyond: one, two or four wavefronts per unit, the longest segments first (see ranked_shape).  The lengths differ by up
 //       to two orders of magnitude, and in index order the launch ends with a few long segments on a chip that is
 //       otherwise empty.
-// Four row loads of K and of V in flight per wavefront; the next block is not requested ahead of the work on this
-// one (that costs 22 registers and gains nothing: the other three wavefronts of the SIMD fill the gap).
+// Four row loads of K and of V in flight per wavefront; the next block's go into the registers of those that are used up.
 template <bool BF16, int LPR, int G, bool EV>
 static hipError_t launch_decode_s(DecodeParams p, int nblk, hipStream_t st) {
     constexpr int NI = 4;

@@ -128,7 +128,7 @@ __device__ __forceinline__ f32x16 mma_tile(const bf16x8 (&stat)[KS], const bf16x
 // column sums of one 128-key stage leave the workgroup once per stage: the wavefronts' values meet in LDS
 // behind the barrier the stage needs anyway and are added in a fixed order (no atomics, bitwise reproducible).
 struct FusedParams {
-    int B, L, H, Hkv, N, D;
+    int N;
     int T;                     // 32-row tiles: ceil(N / 32)
     int npairs;                // ceil(T / 2), at most the wavefronts of a workgroup
     int nheads;                // B*L*H
@@ -940,7 +940,7 @@ hipError_t launch_importance(const pkv_shape& s, const void* q, Strides qs, cons
         if ((e = launch_stream<true>(s, p, st)) != hipSuccess) return e;
     } else {
         FusedParams p;
-        p.B = s.B; p.L = s.L; p.H = s.H; p.Hkv = s.Hkv; p.N = s.N; p.D = s.D;
+        p.N = s.N;
         p.T = (s.N + 31) / 32;
         p.npairs = (p.T + 1) / 2;
         p.nheads = (int)heads;

@@ -1,4 +1,6 @@
-"""csrc/fast_div.hpp, compiled for the host: quotient and remainder by a precomputed multiplier, at the edges of every quotient."""
+"""csrc/fast_div.hpp, compiled for the host: quotient and remainder by a precomputed multiplier, at the edges of the
+quotients up to 400 and of a geometric sample of those beyond.  (That the quotient is at most one short for all of them follows from
+the bound in the header.)"""
 import ctypes as C
 import os
 import subprocess
