@@ -159,7 +159,7 @@ def _median(v):
 def _decode_source_digest():
     import hashlib
     h = hashlib.sha256()
-    for f in ("decode.hip", "decode_rows.hpp", "pkv_common.hpp"):
+    for f in ("decode.hip", "decode_rows.hpp", "fast_div.hpp", "pkv_common.hpp"):
         with open(os.path.join(ROOT, "paper_2412_03409_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
